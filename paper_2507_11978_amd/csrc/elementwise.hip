@@ -4,8 +4,8 @@
 // `tile((BLOCK_SIZE,))`); the application is element-wise, so which program owns which block
 // does not show in the result and the kernels split the vectors their own way: 16-byte vectors
 // (8 elements), four in flight per thread and operand, one contiguous 16 KB chunk per workgroup.  softmax and rms_norm tile a
-// matrix into rows (`tile((1, -1))`): one program per row; a row of up to 8192 elements is read
-// once into the registers of one wavefront, reduced with cross-lane exchanges, and written once.
+// matrix into rows (`tile((1, -1))`): one program per row; a row of up to 32768 elements is read
+// once into the registers of one or four wavefronts, reduced with cross-lane exchanges, and written once.
 // Everything is computed in fp32 and converted once (round to nearest even) to the 16-bit format.
 //
 // All four are bound by HBM traffic: add moves 3 x 2 bytes per element, the others 2 x 2.
@@ -130,38 +130,68 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// OP 0: softmax;  OP 1: rms_norm.  One wavefront per row; the row (cols a multiple of 8, at most
-// 512 * NV, unit column stride) sits in registers as NV 8-element vectors per lane.
-template <int OP, int NV, bool BF16>
+// OP 0: softmax;  OP 1: rms_norm.  Rows with unit column stride, any length up to 512 * NV * WPR, any pitch and alignment:
+// WPR wavefronts per row (1: four rows per workgroup; 4: one), the row held in registers as NV 8-element vectors per lane, so
+// it is read once and written once whatever it needs to know about itself.  Bound by memory: 3001 x 5003 bf16 softmax moves
+// its 60 MB in 11.9 us (5.0 TB/s, a large copy's rate); read three times element by element (row_block_kernel) it took 36 us.
+// Rows of odd length or pitch start on any 2-byte boundary.  The vectors are laid from the row's first 16-byte boundary on,
+// where a load or store touches no cache line twice; the up to seven elements before it and the up to seven behind the last
+// whole vector are one element each for the first lanes.
+template <int OP, int NV, bool BF16, int WPR>
 __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restrict__ x, int64_t sxr, uint16_t *__restrict__ out, int64_t sor,
                                                        int64_t rows, int64_t cols, float eps)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;                                  // (no barrier follows)
-    const int64_t nvec = cols / 8;
+    constexpr int RL = 64 * WPR;                              // lanes per row
+    constexpr int dt = BF16 ? NT_BF16 : NT_F16;
+    __shared__ float red[2][4];
+    const int wave = threadIdx.x >> 6, rl = WPR == 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+    const int64_t row = WPR == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x;
+    if (WPR == 1 && row >= rows) return;                      // (no barrier follows)
     const uint16_t *xr = x + row * sxr;
-    float f[NV][8];
+    uint16_t *orow = out + row * sor;
+    const int n = (int)cols;
+    const int to_boundary = (int)((0 - reinterpret_cast<uintptr_t>(xr)) & 15) >> 1;
+    const int head = to_boundary < n ? to_boundary : n;
+    const int nvec = (n - head) >> 3, rest = (n - head) & 7;
+    const int edge = rl < head ? rl : (rl < head + rest ? nvec * 8 + rl : -1);      // this lane's single element
+    const float pad = OP == 0 ? -INFINITY : 0.f;              // what is not there: no part of the maximum, of a sum
+    const uint16_t *xv = xr + head;
+    float fe = pad, f[NV][8];
+    if (edge >= 0) fe = to_f32(xr[edge], dt);
+    u32x4 raw[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int64_t idx = (int64_t)v * 64 + lane;
-        u32x4 raw{0, 0, 0, 0};
-        if (idx < nvec) __builtin_memcpy(&raw, xr + idx * 8, 16);
-        unpack8<BF16>(raw, f[v]);
-        if (OP == 0 && idx >= nvec) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) f[v][e] = -INFINITY;
-        }
+        const int idx = v * RL + rl;
+        raw[v] = u32x4{0, 0, 0, 0};
+        if (idx < nvec) __builtin_memcpy(&raw[v], xv + idx * 8, 16);
     }
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const bool in = v * RL + rl < nvec;
+        unpack8<BF16>(raw[v], f[v]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[v][e] = in ? f[v][e] : pad;
+    }
+    auto across = [&](float v, bool is_max) {                 // over the row's lanes
+        v = is_max ? wave_max(v) : wave_sum(v);
+        if constexpr (WPR == 4) {
+            float *r = red[is_max ? 1 : 0];
+            if ((rl & 63) == 0) r[wave] = v;
+            __syncthreads();
+            v = is_max ? fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3])) : (r[0] + r[1]) + (r[2] + r[3]);
+        }
+        return v;
+    };
     float scale;
     if constexpr (OP == 0) {
-        float m = -INFINITY;
+        float m = fe;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int e = 0; e < 8; ++e) m = fmaxf(m, f[v][e]);
-        m = wave_max(m);
-        float s = 0.f;
+        m = across(m, true);
+        fe = __expf(fe - m);
+        float s = fe;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -169,26 +199,29 @@ __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restric
                 f[v][e] = __expf(f[v][e] - m);
                 s += f[v][e];
             }
-        scale = 1.0f / wave_sum(s);
+        scale = 1.0f / across(s, false);
     } else {
-        float s = 0.f;
+        float s = fe * fe;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int e = 0; e < 8; ++e) s = __builtin_fmaf(f[v][e], f[v][e], s);
-        scale = 1.0f / sqrtf(wave_sum(s) / (float)cols + eps);
+        scale = 1.0f / sqrtf(across(s, false) / (float)cols + eps);
     }
-    uint16_t *orow = out + row * sor;
+    uint16_t *ov = orow + head;
+    const bool stream = (reinterpret_cast<uintptr_t>(ov) & 15) == 0;      // (wavefront-uniform; the hint on rows that straddle lines costs more than it gives)
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int64_t idx = (int64_t)v * 64 + lane;
+        const int idx = v * RL + rl;
         if (idx < nvec) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) f[v][e] *= scale;
             const u32x4 r = pack8<BF16>(f[v]);
-            __builtin_nontemporal_store(r, reinterpret_cast<u32x4 *>(orow + idx * 8));       // (streamed: softmax 12.4 -> 10.3 us, rms_norm 11.3 -> 8.4 us at 4096 x 4096)
+            if (stream) __builtin_nontemporal_store(r, reinterpret_cast<u32x4 *>(ov + idx * 8));       // (streamed: softmax 12.4 -> 10.3 us, rms_norm 11.3 -> 8.4 us at 4096 x 4096)
+            else __builtin_memcpy(ov + idx * 8, &r, 16);
         }
     }
+    if (edge >= 0) orow[edge] = from_f32(fe * scale, dt);
 }
 
 // Any row length and strides: one workgroup per row, the row is read once per pass.
@@ -256,12 +289,13 @@ nt_status launch_map(int op, const void *x, int64_t sx, const void *y, int64_t s
     return check_launch("map_strided_kernel");
 }
 
-template <int OP, int NV>
-static void launch_row_wave(const uint16_t *x, int64_t sxr, uint16_t *out, int64_t sor, int64_t rows, int64_t cols, float eps, bool bf16, hipStream_t s)
+template <int OP, int NV, int WPR>
+static nt_status launch_row_wave(const uint16_t *x, int64_t sxr, uint16_t *out, int64_t sor, int64_t rows, int64_t cols, float eps, bool bf16, hipStream_t s)
 {
-    dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-    if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
-    else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
+    dim3 grid((unsigned)(WPR == 1 ? (rows + 3) / 4 : rows)), block(256);
+    if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true, WPR>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
+    else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false, WPR>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
+    return check_launch("row_wave_kernel");
 }
 
 template <int OP>
@@ -271,13 +305,23 @@ static nt_status launch_rows_t(const void *x, int64_t sxr, int64_t sxc, void *ou
     const uint16_t *X = (const uint16_t *)x;
     uint16_t *O = (uint16_t *)out;
     const bool bf16 = dtype == NT_BF16;
-    if (sxc == 1 && soc == 1 && cols % 8 == 0 && cols <= 8192 && rows < (1LL << 33)) {
-        if (cols <= 512) launch_row_wave<OP, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        else if (cols <= 1024) launch_row_wave<OP, 2>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        else if (cols <= 2048) launch_row_wave<OP, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        else if (cols <= 4096) launch_row_wave<OP, 8>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        else launch_row_wave<OP, 16>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        return check_launch("row_wave_kernel");
+    // Rows with unit column stride that fit the registers of one or four wavefronts (measured, bf16 softmax, us, one / four per
+    // row): 4096 x 4096 10.2 / 11.0, 3001 x 3001 8.1 / 8.6, 4096 x 1024 3.8 / 5.6 -- against 3001 x 5003 11.6 / 11.9,
+    // 8192 x 8192 49.1 / 45.7, and, with too few rows to occupy the chip, 256 x 4096 4.2 / 3.5, 64 x 8192 5.9 / 3.7.
+    // (row_block_kernel, which such rows of odd length took before: 3001 x 5003 36 us, 16 x 5003 9.3 us)
+    if (sxc == 1 && soc == 1 && cols <= 32768 && rows <= 0x7fffffffLL) {
+        if (cols <= 512) return launch_row_wave<OP, 1, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 1024) return launch_row_wave<OP, 2, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 2048) return launch_row_wave<OP, 4, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 4096 && rows >= 2048) {
+            if (cols <= 3072) return launch_row_wave<OP, 6, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            return launch_row_wave<OP, 8, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        }
+        if (cols <= 4096) return launch_row_wave<OP, 2, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 6144) return launch_row_wave<OP, 3, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 8192) return launch_row_wave<OP, 4, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        if (cols <= 16384) return launch_row_wave<OP, 8, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        return launch_row_wave<OP, 16, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
     }
     if (rows > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "too many rows");
     hipLaunchKernelGGL((row_block_kernel<OP>), dim3((unsigned)rows), dim3(256), 0, s, X, sxr, sxc, O, sor, soc, cols, eps, dtype);

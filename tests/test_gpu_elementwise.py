@@ -102,6 +102,32 @@ def test_softmax_and_rms_norm(dt, rows, cols):
         assert_one_ulp(bits_of(out), oe.rms_norm(x, dt, eps), dt, f"rms_norm {dt} {rows}x{cols} eps={eps}")
 
 
+@pytest.mark.parametrize("rows,cols", [(3, 1), (5, 7), (9, 9), (6, 511), (5, 513), (5, 1025), (5, 2047), (5, 2049), (2048, 2049), (2049, 3073), (3, 4097),
+                                       (3, 6144), (3, 6151), (2, 8191), (2, 8193), (2, 16391), (2, 32768), (1, 32769)])
+def test_rows_of_any_length_and_alignment(rows, cols):
+    """Rows in registers: the elements before a row's first 16-byte boundary and behind its last whole vector, at the edges of
+    the lengths each variant holds; odd pitches (every row starts elsewhere), input and output aligned differently; in place;
+    what lies between the rows stays untouched."""
+    dt, pitch = "bf16", cols + 3
+    x = si.normal_bits((rows, cols), dt, rows + cols, 3.0)
+    ibuf = torch.full((rows, pitch), float("nan"), dtype=TORCH_DT[dt], device="cuda")
+    ibuf[:, 1:1 + cols] = to_gpu(x, dt)
+    for start, row in ((1, pitch), (2, cols + 6)):
+        obuf = torch.full((rows, row), -3.0, dtype=TORCH_DT[dt], device="cuda")
+        out = obuf[:, start:start + cols]
+        nt.softmax(ibuf[:, 1:1 + cols], out)
+        torch.cuda.synchronize()
+        assert_one_ulp(bits_of(out), oe.softmax(x, dt), dt, f"softmax {rows}x{cols}")
+        assert (obuf[:, :start] == -3.0).all() and (obuf[:, start + cols:] == -3.0).all()
+        nt.rms_norm(ibuf[:, 1:1 + cols], out, eps=1e-5)
+        torch.cuda.synchronize()
+        assert_one_ulp(bits_of(out), oe.rms_norm(x, dt, 1e-5), dt, f"rms_norm {rows}x{cols}")
+        assert (obuf[:, :start] == -3.0).all() and (obuf[:, start + cols:] == -3.0).all()
+    nt.rms_norm(ibuf[:, 1:1 + cols], ibuf[:, 1:1 + cols], eps=1e-5)
+    torch.cuda.synchronize()
+    assert torch.equal(ibuf[:, 1:1 + cols], out)
+
+
 def test_row_kernels_padded_pitch_transposed_views_and_extremes():
     dt, rows, cols = "f16", 12, 1024
     x = si.normal_bits((rows, cols), dt, 9, 2.0)
