@@ -153,7 +153,7 @@ nt_status nt_arrange_conv2d(const nt_tensor_desc *dx, const nt_tensor_desc *dw, 
 nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_out);
 
 /* Which kernel the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call launched:
- * 0 operand-map (generic) kernel, 1 staged kernel, 2 direct-to-LDS kernel, 3 convolution kernel (operands staged
+ * 0 operand-map (generic) kernel, or the 64 x 64 x 32 tile named by the caller, 1 staged kernel, 2 direct-to-LDS kernel, 3 convolution kernel (operands staged
  * through registers), 4 convolution kernel (operands streamed straight into LDS), 5 unfolded input written to the
  * workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks the reduction filter tap by filter
  * tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of the filter that it puts in the

@@ -8,8 +8,14 @@ __global__ __launch_bounds__(256) void conv_ws_sum_kernel(const float *ws, int k
                                                           int64_t syn, int64_t syf, int out_dtype)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < slice; i += (int64_t)gridDim.x * 256) {
-        float sum = ws[i];
-        for (int j = 1; j < ksplit; ++j) sum += ws[j * slice + i];
+        float sum = 0.f;                                      // (eight slices' loads in flight, added in slice order)
+        for (int j = 0; j < ksplit; j += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = j + u < ksplit ? ws[(j + u) * slice + i] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += v[u];
+        }
         const int64_t n = i / fpq, r = i - n * fpq, f = r / pq, x = r - f * pq;
         store_out(Y, n * syn + f * syf + x, sum, out_dtype);
     }

@@ -19,8 +19,10 @@ constexpr int kSliceK = 32;      // k extent of one LDS slice
 // workgroup per unit, ring of four = 128 KB).  Smaller tiles leave room for two workgroups
 // per unit (at most 72 KB and 256 registers each), whose epilogues, launches and prologues
 // then overlap the other's multiplications; their ring is three slices (256 x 128: 72 KB) or
-// four (128 x 128: 64 KB).
-constexpr int ring_of(int bm, int bn) { return bm + bn == 384 || bm + bn == 320 ? 3 : 4; }   // (320: the convolution kernel's 256 x 64, 60 KB)
+// four (128 x 128: 64 KB).  The 64 x 64 tile is for products too small to fill the chip, whose time is the latency of their
+// loads: eight slices (64 KB), so that a reduction of up to 256 is requested whole before the first slice is waited for
+// (256 x 256 x 256 on 16 programs: 43.4 us through the operand-map kernel, which waits for every k tile, 3.9 us here).
+constexpr int ring_of(int bm, int bn) { return bm + bn == 128 ? 8 : bm + bn == 384 || bm + bn == 320 ? 3 : 4; }   // (320: the convolution kernel's 256 x 64, 60 KB)
 constexpr int residency_of(int bm, int bn) { return bm + bn == 512 ? 1 : 2; }
 
 // s_waitcnt that waits until at most n vector-memory operations are outstanding and leaves

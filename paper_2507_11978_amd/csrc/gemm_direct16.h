@@ -125,7 +125,13 @@ struct DirectTile16<E, MNCONTIG> {
     uint32_t voff[PER];
     uint32_t rd[T];
 
-    static __device__ __forceinline__ int swizzle(int krow) { return ((krow & 3) << 2) | (((krow >> 3) & 1) << 1); }
+    // E = 64: a row is only half of the 256 bytes the banks cover, so even and odd k rows lie in different halves by themselves
+    // and the four even (odd) rows a half wavefront reads at a time are told apart by bits 1 and 3 of k, over the four chunk pairs
+    static __device__ __forceinline__ int swizzle(int krow)
+    {
+        if constexpr (E == 64) return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2);
+        return ((krow & 3) << 2) | (((krow >> 3) & 1) << 1);
+    }
 
     __device__ __forceinline__ void init(int wave, int lane, int64_t ld, int wave_origin, uint32_t region)
     {
@@ -200,9 +206,9 @@ __device__ __forceinline__ void store_tile16_rows(char *smem, int wave, char *C,
     constexpr int ES = OUT == NT_F32 ? 4 : 2;
     constexpr int PASSES = ES / 2;                        // an fp32 tile takes one pass per half of the columns
     constexpr int PW = WN / PASSES;                       // columns per pass
-    constexpr int RB = WN * 2;                            // bytes per region row: 256 or 128
+    constexpr int RB = WN * 2;                            // bytes per region row: 256, 128 or 64
     constexpr int CPR = RB / 16;                          // 16-byte chunks per row
-    constexpr int RSH = RB == 256 ? 0 : 1;                // log2(rows per 256 bytes of LDS)
+    constexpr int RSH = RB == 256 ? 0 : (RB == 128 ? 1 : 2);      // log2(rows per 256 bytes of LDS)
     constexpr int EPC = 16 / ES;                          // elements per chunk
     constexpr int RPI = 64 / CPR;                         // rows per store instruction
     constexpr int TNP = PW / 16;                          // blocks per pass
@@ -1028,6 +1034,7 @@ static nt_status launch_direct16_t(const FastArgs &a, int alay, int blay, int64_
     nt_status launch_direct16_##T##_bf16(const FastArgs &a, int alay, int blay, int64_t nwg, hipStream_t s); \
     nt_status launch_direct16_edge_##T##_f16(const FastArgs &a, int alay, int blay, int64_t nwg, hipStream_t s); \
     nt_status launch_direct16_edge_##T##_bf16(const FastArgs &a, int alay, int blay, int64_t nwg, hipStream_t s);
+NT_DIRECT16_DECL(64x64)
 NT_DIRECT16_DECL(128x128)
 NT_DIRECT16_DECL(256x128)
 NT_DIRECT16_DECL(128x256)

@@ -41,13 +41,19 @@ static const TileEntry kTiles[] = {{64, 64, 32}, {128, 128, 64}, {256, 128, 64},
 // (time of one 64-wide k tile with the whole unit's matrix rate) plus a fixed `fixed` microseconds of launch, prologue and
 // epilogue, which `resident` co-resident workgroups overlap with each other's multiplications.  The constants are fits to
 // measurements on 8192 x 8192 x K and batched 2048 x 2048 x K problems.
-nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K)
+nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow)
 {
     struct Cand { int bm, bn; double fixed, step; int resident; };
     // (fits to 8192 x 8192 x K, 4096 x 4096 x K and 32 x 2048 x 2048 x K for K = 256 .. 8192 on a chip with every unit busy;
     // the 256 x 256 figures are those of the persistent kernel)
     const Cand cands[] = {{256, 256, 8.5, 1.42, 1}, {128, 256, 7.0, 0.82, 2}, {256, 128, 6.5, 0.915, 2}, {128, 128, 4.5, 0.51, 2}};
     const double kt = (double)((K + 63) / 64);
+    // Products of at most two 64 x 64 tiles per unit leave a wider tile's matrix pipes waiting for its loads: the narrow tile
+    // has four times the programs and an eighth of the reduction in flight per program.  Measured against 128 x 128, us:
+    // 256 tiles 4.5 / 5.8 (K = 256), 7.3 / 10.7 (1024), 11.0 / 18.4 (2048); 512 tiles 5.8 / 6.2, 10.0 / 11.1, 16.9 / 18.6 and
+    // 33.1 / 32.2 (4096); 576 tiles 7.6 / 6.1, 14.4 / 11.2.
+    const int64_t small = batch * ((M + 63) / 64) * ((N + 63) / 64);
+    if (narrow && (small <= 256 || (small <= 512 && kt <= 48))) return nt_tile_cfg{64, 64, 32};
     nt_tile_cfg best{128, 128, 64};
     double best_cost = 0;
     for (const Cand &c : cands) {
@@ -234,8 +240,15 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *ws, int ks
     const ActParams ap = act_params(act);
     const int64_t total = M * N;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        float sum = ws[i];
-        for (int j = 1; j < ksplit; ++j) sum += ws[j * total + i];
+        // (eight slices' loads in flight, added in slice order: one after the other they took 4 us for 8 slices of 16 x 4096)
+        float sum = 0.f;
+        for (int j = 0; j < ksplit; j += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = j + u < ksplit ? ws[(j + u) * total + i] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += v[u];
+        }
         const int64_t m = i / N, n = i - m * N;
         const float x = combine(sum, D ? load_as_f32(D, m * sdm + n * sdn, out_dtype) : 0.f, alpha, beta);
         store_out(C, m * scm + n * scn, act ? activate(x, ap) : x, out_dtype);
@@ -444,18 +457,20 @@ static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nc
 // The same for a GEMM with few output tiles and a long reduction (a skinny product): the split is run as a batched
 // product over equal parts of K, so only a number of parts that divides the k tiles evenly is taken (at least 8 k tiles
 // each).  Two dependent launches and the trip of the partial tiles through memory have their price: the split is taken
-// when an estimate of it (12 us for the launches, 0.37 us per k tile of a program that has its compute unit to
-// itself, the slices written and read at 3 TB/s) beats the estimate of the single launch (7 us + 0.37 us per k tile).
-// Measured: 1024 x 1024 x 1024 11 us unsplit against 19 split, 1024 x 1024 x 4096 31 against 24, 256 x 256 x 8192 55
-// against 15, 512 x 512 x 2048 17 against 13.
-static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N)
+// when an estimate of it (the launches, a program's k tiles with its compute unit to itself, the slices written and read at
+// 3 TB/s) beats the estimate of the single launch.  `small`: the 64 x 64 tile (us: 3.5 + 0.24 per 64-k tile, the split's
+// launches 6), else 128 x 128 (7 + 0.37 and 12).
+// Measured: 1024 x 1024 x 1024 on 128 x 128 11 us unsplit against 19 split; on 64 x 64, unsplit / split: 256 x 256 x 2048 10.6 /
+// 8.0, x 8192 32.9 / 9.8, 512 x 512 x 4096 18.7 / 12.7, 16 x 1024 x 4096 20.0 / 8.0 (on 128 x 128, split: 10.3, 12.1, 13.5, 10.8).
+static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small)
 {
-    if (programs >= 128 || kt < 32) return 1;
+    if (programs >= (small ? 192 : 128) || kt < 32) return 1;
+    const double step = small ? 0.24 : 0.37, once = small ? 3.5 : 7.0, twice = small ? 6.0 : 12.0;
     const int64_t want = std::min<int64_t>((256 + programs / 2) / programs, kt / 8);
     for (int64_t d = want; d >= 2; --d) {
         if (kt % d) continue;
-        const double single = 7.0 + 0.37 * (double)kt;
-        const double split = 12.0 + 0.37 * (double)kt / (double)d + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
+        const double single = once + step * (double)kt;
+        const double split = twice + step * (double)kt / (double)d + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
         return split < single ? (int)d : 1;
     }
     return 1;
@@ -695,7 +710,7 @@ static nt_status route_conv_unfold(const GemmLaunch &g, int *path_out, bool *tak
     u.mc = matrix(h.K, PQ, h.ys[1]);                     // filters x positions
     u.batch = h.N; u.sa_batch = 0; u.sb_batch = PQ; u.sc_batch = h.ys[0];
     u.M = h.K; u.N = PQ; u.K = K;
-    u.tile = pick_gemm_tile(u.batch, u.M, u.N, u.K);
+    u.tile = pick_gemm_tile(u.batch, u.M, u.N, u.K, true);
     u.mt = (u.M + u.tile.bm - 1) / u.tile.bm; u.nt = (u.N + u.tile.bn - 1) / u.tile.bn; u.kt = (u.K + u.tile.bk - 1) / u.tile.bk;
     u.in_dtype = g.in_dtype; u.out_dtype = g.out_dtype; u.stream = g.stream;
     u.alpha = 1.f; u.beta = 0.f; u.act = 0; u.has_d = false;
@@ -710,7 +725,7 @@ static nt_status route_conv_unfold(const GemmLaunch &g, int *path_out, bool *tak
 static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *blay_out)
 {
     const nt_tile_cfg t = g.tile;
-    if (!(plain(g.ma) && plain(g.mb) && plain(g.mc) && (!g.has_d || plain(g.md)) && t.bk == 64 && t.bm >= 128 && t.bn >= 128 && g.kt > 0)) return false;
+    if (!(plain(g.ma) && plain(g.mb) && plain(g.mc) && (!g.has_d || plain(g.md)) && g.kt > 0)) return false;
     FastArgs a{};
     int alay, blay;
     if (g.ma.coff[0] == 1) { alay = KCONTIG; a.lda = g.ma.roff[0]; }
@@ -731,7 +746,7 @@ static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *
     a.scn = g.mc.coff[0];
     a.sa_batch = g.sa_batch; a.sb_batch = g.sb_batch; a.sc_batch = g.sc_batch;
     a.M = g.M; a.N = g.N; a.K = g.K;
-    a.mt = g.mt; a.nt = g.nt; a.kt = g.kt;
+    a.mt = g.mt; a.nt = g.nt; a.kt = (g.K + 63) / 64;
     a.out_dtype = g.out_dtype;
     a.alpha = g.alpha;
     a.beta = g.has_d ? g.beta : 0.f;
@@ -745,6 +760,9 @@ static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *
         a.sdn = g.md.coff[0];
         a.sd_batch = g.sd_batch;
     }
+    // (the 64 x 64 tile is built for the direct kernel only)
+    if (t.bm < 128 && !(a.scn == 1 && (!a.D || a.sdn == 1) && (alay == KCONTIG || g.K * a.lda < (1LL << 30)) && (blay == KCONTIG || g.K * a.ldb < (1LL << 30))))
+        return false;
     *out = a;
     *alay_out = alay;
     *blay_out = blay;
@@ -765,7 +783,7 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     // of a load, counted from the load's own start: with an odd pitch, or an extent that is no multiple of 4 bytes,
     // the word that holds the operand's last element can end 2 bytes past it and is then dropped; the kernel is told
     // (patch) and fetches that one element by itself.  The range never extends past the operand.
-    const bool ragged_mn = (g.M % t.bm) || (g.N % t.bn), ragged_k = (g.K % t.bk) != 0;
+    const bool ragged_mn = (g.M % t.bm) || (g.N % t.bn), ragged_k = (g.K % 64) != 0;
     auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     const bool out_ok = a.scn == 1 && (!a.D || a.sdn == 1);
     const bool aligned = al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0 && a.sa_batch % 8 == 0 && a.sb_batch % 8 == 0;
@@ -776,9 +794,11 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     const bool direct = plain_direct || (out_ok && (alay == KCONTIG || g.K * a.lda < (1LL << 30)) && (blay == KCONTIG || g.K * a.ldb < (1LL << 30)));
     if (direct && !plain_direct)
         a.patch = (words_aligned(a.lda, a.sa_batch, a.a_extent) ? 0 : 1) | (words_aligned(a.ldb, a.sb_batch, a.b_extent) ? 0 : 2);
-    if (path_out) *path_out = direct ? PATH_DIRECT : PATH_FAST;
+    // (a caller who names the 64 x 64 x 32 tile is told path 0 whatever its operands are)
+    const bool named_small = t.bm < 128 && g.user_tile;
+    if (path_out) *path_out = named_small ? PATH_GENERIC : direct ? PATH_DIRECT : PATH_FAST;
     if (g.trace.out) {
-        if (!direct) return fail(NT_ERR_UNSUPPORTED, "this product does not run on the kernels that stream their operands into LDS");
+        if (!direct || named_small) return fail(NT_ERR_UNSUPPORTED, "this product does not run on the kernels that stream their operands into LDS");
         const int64_t rows = g.trace.operand == 0 ? t.bm : t.bn;
         if ((size_t)rows * 32 > g.trace.capacity) return fail(NT_ERR_BUFFER_TOO_SMALL, "trace buffer smaller than the slice");
         if (g.trace.program < 0 || g.trace.program >= nwg) return fail(NT_ERR_INVALID_ARG, "program_id outside the grid");
@@ -792,13 +812,14 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     struct Entry { int bm, bn; Launcher direct[2], edge[2], staged[2]; };
 #define NT_ENTRY(BM, BN, T) {BM, BN, {launch_direct16_##T##_f16, launch_direct16_##T##_bf16}, {launch_direct16_edge_##T##_f16, launch_direct16_edge_##T##_bf16}, \
                              {launch_fast_##T##_f16, launch_fast_##T##_bf16}}
-    static const Entry table[] = {NT_ENTRY(128, 128, 128x128), NT_ENTRY(256, 128, 256x128), NT_ENTRY(128, 256, 128x256), NT_ENTRY(256, 256, 256x256)};
+    static const Entry table[] = {{64, 64, {launch_direct16_64x64_f16, launch_direct16_64x64_bf16}, {launch_direct16_edge_64x64_f16, launch_direct16_edge_64x64_bf16}, {nullptr, nullptr}},
+                                  NT_ENTRY(128, 128, 128x128), NT_ENTRY(256, 128, 256x128), NT_ENTRY(128, 256, 128x256), NT_ENTRY(256, 256, 256x256)};
 #undef NT_ENTRY
     for (const Entry &e : table) {
         if (e.bm != t.bm || e.bn != t.bn) continue;
         const Launcher launch = (direct ? (plain_direct ? e.direct : e.edge) : e.staged)[bf16 ? 1 : 0];
         // k split: `ksplit` equal parts of K as the entries of a batched product into fp32 slices of the workspace
-        const int ksplit = g.batch == 1 && !ragged_k ? gemm_ksplit(g.mt * g.nt, g.kt, g.M, g.N) : 1;
+        const int ksplit = g.batch == 1 && !ragged_k && (t.bm >= 128 || !g.user_tile) ? gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128) : 1;
         WorkspaceLease lease;
         float *ws = nullptr;                                 // (none: too large, or no memory; then no split)
         if (ksplit > 1) {
@@ -810,7 +831,7 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
         t_k_split = ksplit;
         FastArgs part = a;
         const int64_t Kp = g.K / ksplit;
-        part.K = Kp; part.kt = g.kt / ksplit;
+        part.K = Kp; part.kt = a.kt / ksplit;
         part.sa_batch = alay == KCONTIG ? Kp : Kp * a.lda;
         part.sb_batch = blay == KCONTIG ? Kp : Kp * a.ldb;
         // (K and Kp are multiples of 64: a part's words are as aligned as the whole's, and a part is as streamable)
@@ -835,6 +856,14 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     FastArgs a{};
     int alay = KCONTIG, blay = MNCONTIG;
     if (lower_plain(g, &a, &alay, &blay)) return route_matrix(g, a, alay, blay, path_out);
+    // (the library's own 64 x 64 tile is built for the direct kernel only: what that does not take, an addmm input without unit
+    // stride along n say, runs as before on 128 x 128)
+    if (!g.user_tile && g.tile.bm == 64 && !g.conv.valid) {
+        GemmLaunch w = g;
+        w.tile = nt_tile_cfg{128, 128, 64};
+        w.mt = (g.M + 127) / 128; w.nt = (g.N + 127) / 128; w.kt = (g.K + 63) / 64;
+        if (lower_plain(w, &a, &alay, &blay)) return route_matrix(w, a, alay, blay, path_out);
+    }
     if (path_out) *path_out = PATH_GENERIC;
     ConvArgs c{};
     if (!g.has_d && g.alpha == 1.f && g.act == 0 && match_conv(g, &c)) return route_conv_implicit(g, c, path_out);

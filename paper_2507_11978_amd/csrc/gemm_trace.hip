@@ -16,6 +16,7 @@ static nt_status trace_layouts(const FastArgs &a, int alay, int blay, hipStream_
 template <bool EDGE>
 static nt_status trace_tiles(const FastArgs &a, int bm, int bn, int alay, int blay, hipStream_t s)
 {
+    if (bm == 64 && bn == 64) return trace_layouts<64, 64, EDGE>(a, alay, blay, s);
     if (bm == 128 && bn == 128) return trace_layouts<128, 128, EDGE>(a, alay, blay, s);
     if (bm == 256 && bn == 128) return trace_layouts<256, 128, EDGE>(a, alay, blay, s);
     if (bm == 128 && bn == 256) return trace_layouts<128, 256, EDGE>(a, alay, blay, s);

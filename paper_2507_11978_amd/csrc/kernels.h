@@ -62,7 +62,8 @@ bool tile_is_built(nt_tile_cfg cfg);
 // into how many parts the calling thread's last launch_gemm split its reduction (1: no split)
 int last_k_split();
 // the tile the MFMA kernels run a plain (batched) product of this size fastest with, by a cost model fitted to measurements
-nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K);
+// (narrow: the 64 x 64 tile may be taken -- operands and output have the unit strides of the direct kernel)
+nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow);
 // the tile of a dense unit-stride convolution (M positions, N filters, reduction K), by an estimate that includes the k split
 nt_tile_cfg pick_conv_tile(int64_t M, int64_t N, int64_t K);
 nt_status launch_gemm(const GemmLaunch &g, int *path_out);

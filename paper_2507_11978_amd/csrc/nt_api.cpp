@@ -35,7 +35,8 @@ struct ViewPrograms { const nt_meta_op *ops[3]; int32_t n[3]; };
 // other's multiplications.  The constants are fits to measurements on 8192 x 8192 x K and
 // batched 2048 x 2048 x K problems.
 // unit_stride: a convolution with stride 1 (the class the dedicated convolution kernels take)
-nt_tile_cfg pick_tile(int kind, int64_t batch, int64_t M, int64_t N, int64_t K, nt_tile_cfg cfg, bool unit_stride = false)
+// narrow: a product whose operands have a unit stride along one of their axes and whose output has it along n
+nt_tile_cfg pick_tile(int kind, int64_t batch, int64_t M, int64_t N, int64_t K, nt_tile_cfg cfg, bool unit_stride = false, bool narrow = false)
 {
     if (cfg.bm || cfg.bn || cfg.bk) return cfg;
     // The 64 x 64 tile of the operand-map kernel is for small strided convolutions and small caller-arranged views.
@@ -46,7 +47,7 @@ nt_tile_cfg pick_tile(int kind, int64_t batch, int64_t M, int64_t N, int64_t K, 
     const bool tiny = (M <= 64 || N <= 64) && ((kind == KIND_CONV && !unit_stride) || kind == KIND_VIEWS);
     if (tiny) return nt_tile_cfg{64, 64, 32};
     if (kind == KIND_CONV) return nt::pick_conv_tile(M, N, K);     // 256 output positions per program, 256 or 128 filters
-    return nt::pick_gemm_tile(batch, M, N, K);
+    return nt::pick_gemm_tile(batch, M, N, K, narrow);
 }
 
 
@@ -201,7 +202,9 @@ nt_status build_problem(int kind, const nt_tensor_desc *d0, const nt_tensor_desc
         const nt::ConvHint &h = p->vconv.hint;
         p->tile = pick_tile(KIND_CONV, 1, p->M, p->N, p->K, cfg, h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1);
     } else {
-        p->tile = pick_tile(kind, p->batch, p->M, p->N, p->K, cfg, sh == 1 && sw == 1);
+        auto unit_axis = [&](const nt_tensor_desc *d) { return d->stride[o] == 1 || d->stride[o + 1] == 1; };
+        const bool narrow = (kind == KIND_GEMM || kind == KIND_BMM) && d2->stride[o + 1] == 1 && unit_axis(d0) && unit_axis(d1) && p->K >= 8;
+        p->tile = pick_tile(kind, p->batch, p->M, p->N, p->K, cfg, sh == 1 && sw == 1, narrow);
     }
     NT_TRY(nt::arrange_matmul(p->va, p->vb, p->vc, p->tile, &p->mm));
     return NT_OK;

@@ -377,6 +377,34 @@ def test_overhanging_tiles_on_the_direct_kernel(M, N, K, tile, dt, out):
         assert torch.isnan(buf[0]).all() and torch.isnan(buf[M + 1]).all() and torch.isnan(buf[:, N:]).all()
 
 
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (128, 192, 256), (256, 64, 640), (64, 64, 32), (63, 65, 31), (8, 8, 8), (65, 129, 257), (200, 72, 320),
+                                   (130, 70, 513)])
+def test_named_64_tile_on_unit_stride_operands(M, N, K, dt, out):
+    """The 64 x 64 x 32 tile named by the caller: whole tiles and slices, one slice, more slices than the ring holds, everything
+    odd, the smallest operands the loads take; four orientations, a batch, the fused epilogue (bit exact: integer inputs)."""
+    A, B = si.gemm_inputs(M, N, K, dt, seed=83, dist="int")
+    ref = onum.gemm(A, B, dt)
+    want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+    a, b = to_gpu(A, dt), to_gpu(B, dt)
+    at, bt = a.t().contiguous().t(), b.t().contiguous().t()
+    for aa, bb in [(a, b), (a, bt), (at, b), (at, bt)]:
+        buf = torch.full((M + 2, N + 8), float("nan"), dtype=TORCH_DT[out], device="cuda")
+        C = buf[1:M + 1, :N]
+        nt.gemm(aa, bb, C, tile=(64, 64, 32))
+        torch.cuda.synchronize()
+        assert torch.equal(C.cpu(), want)
+        assert torch.isnan(buf[0]).all() and torch.isnan(buf[M + 1]).all() and torch.isnan(buf[:, N:]).all()
+    inp = torch.full((M, N), 3.0, dtype=TORCH_DT[out], device="cuda")
+    C = torch.empty((M, N), dtype=TORCH_DT[out], device="cuda")
+    nt.addmm(inp, a, bt, C, alpha=-1.0, beta=2.0, tile=(64, 64, 32), act="relu")
+    C3 = torch.empty((3, M, N), dtype=TORCH_DT[out], device="cuda")
+    nt.bmm(torch.stack([a, a, a]), b[None].expand(3, K, N), C3, tile=(64, 64, 32))
+    torch.cuda.synchronize()
+    assert torch.equal(C.cpu(), torch.from_numpy(np.maximum(6.0 - ref, 0.0)).to(torch.float32).to(TORCH_DT[out]))
+    assert torch.equal(C3.cpu(), want[None].expand(3, M, N))
+
+
 def test_overhanging_tiles_bmm_and_bias_on_the_direct_kernel():
     dt, Bn, M, N, K = "f16", 3, 300, 392, 128
     A, B = si.gemm_inputs(M, N, K, dt, seed=82, dist="normal", batch=Bn)
