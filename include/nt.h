@@ -153,7 +153,8 @@ nt_status nt_arrange_conv2d(const nt_tensor_desc *dx, const nt_tensor_desc *dw, 
 nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_out);
 
 /* Which kernel the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call launched:
- * 0 operand-map (generic) kernel, or the 64 x 64 x 32 tile named by the caller, 1 staged kernel, 2 direct-to-LDS kernel, 3 convolution kernel (operands staged
+ * 0 operand-map (generic) kernel, or the 64 x 64 x 32 tile named by the caller, 1 staged kernel, 2 direct-to-LDS kernel (or
+ * the kernel for products of at most 32 rows, which splits the reduction inside a program), 3 convolution kernel (operands staged
  * through registers), 4 convolution kernel (operands streamed straight into LDS), 5 unfolded input written to the
  * workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks the reduction filter tap by filter
  * tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of the filter that it puts in the
@@ -356,6 +357,8 @@ nt_status nt_trace_tile(int32_t kind, const nt_tensor_desc *d0, const nt_tensor_
  * (nt_last_kernel_path() 2, 4 or 6 for the same arguments) can be traced: otherwise NT_ERR_UNSUPPORTED.  The ring-unrolled
  * variant of the 256 x 256 kernel and its persistent form (one workgroup walking several programs) have the same per-lane
  * offsets and slice stepping as the kernel traced here.
+ * A product of at most 32 rows may run on a kernel that loads its fragments through registers; what is traced then is the
+ * direct-to-LDS kernel that the same arguments run on when the caller names the tile.
  * Path 6 may run tile rows of two heights (the first ones 256 or 224 positions, the rest 32 fewer; tile row i starts where
  * the tile rows before it end): the rows of values_out past the traced program's height are left untouched.
  * Path 6 sums over the reduction index in another order than the arrangement lists it: its slice s, index kk is channel

@@ -5,6 +5,7 @@
 #include "gemm_conv_tap.h"
 #include "gemm_direct.h"
 #include "gemm_direct16.h"
+#include "gemm_skinny.h"
 
 namespace nt {
 
@@ -770,12 +771,18 @@ static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *
 }
 
 // ---- route 4: plain matrices on the MFMA kernels (with the k split for skinny products)
+// (a product of few rows with the library's own tile runs on a kernel of its own, which splits the reduction inside a program)
 static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int blay, int *path_out)
 {
     const nt_tile_cfg t = g.tile;
     const bool bf16 = g.in_dtype == NT_BF16;
     const int64_t nwg = g.batch * g.mt * g.nt;
     hipStream_t s = (hipStream_t)g.stream;
+    if (g.batch == 1 && !g.user_tile && !g.trace.out && skinny_ok(a, alay, blay)) {
+        if (path_out) *path_out = PATH_DIRECT;
+        t_k_split = skinny_parts(a);
+        return launch_skinny(a, bf16, s);
+    }
     // Operands stored to a C (and added to a D) with unit stride along n stream straight into LDS.  Full tiles of
     // 16-byte aligned operands: plain loads.  Everything else -- tiles that overhang M or N, a ragged K, rows with
     // only the element's 2-byte alignment -- takes the same loads as range-checked buffer accesses (EDGE kernels),

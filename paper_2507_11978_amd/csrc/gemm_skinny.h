@@ -1,0 +1,13 @@
+// Products of few rows on a kernel of their own (gemm_skinny.hip).
+#pragma once
+#include "gemm_fast.h"
+
+namespace nt {
+
+// whether the kernel takes this (unbatched) product, and is the faster one for it
+bool skinny_ok(const FastArgs &a, int alay, int blay);
+// into how many parts it splits the reduction (inside a program)
+int skinny_parts(const FastArgs &a);
+nt_status launch_skinny(const FastArgs &a, bool bf16, hipStream_t s);
+
+}  // namespace nt

@@ -405,6 +405,39 @@ def test_named_64_tile_on_unit_stride_operands(M, N, K, dt, out):
     assert torch.equal(C3.cpu(), want[None].expand(3, M, N))
 
 
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (16, 48, 512), (7, 33, 575), (16, 17, 127), (2, 1001, 4097), (17, 40, 1024), (32, 64, 576), (31, 100, 704),
+                                   (20, 50, 333), (33, 64, 512)])
+def test_products_of_few_rows(M, N, K, dt, out):
+    """At most 32 rows, both operands contiguous along k: one step, fewer steps than wavefronts, a ragged end of K, columns and
+    rows that do not fill a block, odd pitches; an output pitch, the fused epilogue, a column-major output (bit exact: integer
+    inputs); what lies around C stays untouched, and a repeated call gives the same bits."""
+    A, B = si.gemm_inputs(M, N, K, dt, seed=84, dist="int")
+    ref = onum.gemm(A, B, dt)
+    want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+    a, bt = to_gpu(A, dt), to_gpu(B, dt).t().contiguous().t()
+    buf = torch.full((M + 2, N + 8), float("nan"), dtype=TORCH_DT[out], device="cuda")
+    C = buf[1:M + 1, :N]
+    nt.gemm(a, bt, C)
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_DIRECT and nt.last_k_split() == (min(8, K // 64) if M <= 16 or (M <= 32 and K % 8 == 0) else 1)
+    assert torch.equal(C.cpu(), want)
+    assert torch.isnan(buf[0]).all() and torch.isnan(buf[M + 1]).all() and torch.isnan(buf[:, N:]).all()
+    inp = torch.full((N,), 3.0, dtype=TORCH_DT[out], device="cuda")
+    Ct = torch.empty((N, M), dtype=TORCH_DT[out], device="cuda").t()
+    nt.addmm(inp, a, bt, Ct, alpha=-1.0, beta=2.0, act="relu")
+    torch.cuda.synchronize()
+    assert torch.equal(Ct.cpu(), torch.from_numpy(np.maximum(6.0 - ref, 0.0)).to(torch.float32).to(TORCH_DT[out]))
+    An, Bn = si.gemm_inputs(M, N, K, dt, seed=85, dist="normal")
+    a, bt = to_gpu(An, dt), to_gpu(Bn, dt).t().contiguous().t()
+    C1, C2 = torch.empty((M, N), dtype=TORCH_DT[out], device="cuda"), torch.empty((M, N), dtype=TORCH_DT[out], device="cuda")
+    nt.gemm(a, bt, C1)
+    nt.gemm_noalloc(a, bt, C2)
+    torch.cuda.synchronize()
+    assert torch.equal(C1, C2)
+    assert_gates(to_f64(C1), onum.gemm(An, Bn, dt), out, "few rows")
+
+
 def test_overhanging_tiles_bmm_and_bias_on_the_direct_kernel():
     dt, Bn, M, N, K = "f16", 3, 300, 392, 128
     A, B = si.gemm_inputs(M, N, K, dt, seed=82, dist="normal", batch=Bn)
