@@ -314,6 +314,9 @@ static bool match_conv(const GemmLaunch &g, ConvArgs *a)
 // through a WorkspaceLease from before its first launch that touches it until after its last: the lease serialises host
 // threads (a mutex) and streams (an event recorded behind the last consumer, which a call on any other stream makes its
 // stream wait for before its own first launch), so calls that overlap on one device queue up instead of racing.
+// The event carries no system-scope fence: it only orders kernels of one device, and what it orders is the last consumer's reads
+// before the next caller's writes (a consumer's input left the writer's caches at the launch boundary between the two).  The
+// fence cost every call 2 us on the device (the paper's conv task 29.5 -> 27.6 us).
 static constexpr size_t kSplitWsMax = 256u << 20;
 
 class WorkspaceLease {
@@ -333,7 +336,7 @@ public:
             void *p = nullptr;
             hipEvent_t ev = nullptr;
             if (hipMalloc(&p, kSplitWsMax) != hipSuccess) { (void)hipGetLastError(); ok = false; }
-            else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(p); ok = false; }
+            else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(p); ok = false; }
             else { w.p = p; w.done = ev; }
         }
         if (ok && w.used && w.last != stream && hipStreamWaitEvent(stream, w.done, 0) != hipSuccess) { (void)hipGetLastError(); ok = false; }
