@@ -272,9 +272,187 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
     }
 }
 
+// ---- few query rows (a decoding step: one query per head against a cache of keys)
+// Bound by reading K and V once; of the 128 query rows of sdpa_kernel's block all but a few would be padding, and its one
+// workgroup per head walks the keys in turn.  Here one workgroup of 16 wavefronts (4: short sequences, or heads
+// enough to fill the chip) per (head, query) deals the keys out to its
+// wavefronts, 32 at a time: eight lanes hold one key's 64 elements (a load instruction covers 8 keys, 1 KB), four keys per lane
+// group in flight and the next four behind them.  Scores, weights and sums stay in fp32 (a lane group keeps a maximum and a
+// sum of its own: no exchange in the loop but the score's, three adds across eight lanes); the groups' results are brought to a
+// common maximum at the end, first within a wavefront, then through LDS.
+// Measured, bf16, 4 x 48 heads x 2047 keys (100 MB): 33.9 us with sdpa_kernel, 19.1 here (5.3 TB/s, a large copy's rate); 8 heads x 2048 keys 30.2 and 10.7.
+constexpr int kDecodeKeys = 4;                                // keys per lane group and batch
+
+template <bool BF16>
+__device__ __forceinline__ void unpack8_f32(u32x4 v, float (&f)[8])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t w = v[q];
+        if constexpr (BF16) {
+            f[2 * q] = __builtin_bit_cast(float, w << 16);
+            f[2 * q + 1] = __builtin_bit_cast(float, w & 0xffff0000u);
+        } else {
+            f[2 * q] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));
+            f[2 * q + 1] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
+        }
+    }
+}
+
+// sum over the eight lanes of a group (lanes 8 i .. 8 i + 7), in all of them
+__device__ __forceinline__ float sum_of_eight(float v)
+{
+    auto from = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v += from(v, std::integral_constant<int, 0xB1>{});        // lane ^ 1
+    v += from(v, std::integral_constant<int, 0x4E>{});        // lane ^ 2
+    v += from(v, std::integral_constant<int, 0x141>{});       // mirrored within eight: the other four's sum
+    return v;
+}
+
+template <bool BF16, int kDecodeWaves>
+__global__ __launch_bounds__(64 * kDecodeWaves) void sdpa_decode_kernel(const SdpaArgs g)
+{
+    constexpr int BATCH = 8 * kDecodeKeys;                     // keys per wavefront and batch
+    __shared__ float red_o[kDecodeWaves][kHeadDim], red_m[kDecodeWaves], red_l[kDecodeWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sub = lane & 7, slot = lane >> 3;
+    // (all queries of a head on one XCD, see sdpa_kernel; nqb: the queries)
+    const int w = blockIdx.x, nq = g.nqb;
+    int bh = w / nq, qi = w % nq;
+    if (w < (g.BH & ~7) * nq) {
+        const int j = w >> 3;
+        bh = (j / nq) * 8 + (w & 7);
+        qi = j % nq;
+    }
+    const int b = bh / g.H, h = bh % g.H;
+    const uint16_t *Kp = g.K + b * g.k_sb + h * g.k_sh + 8 * sub;
+    const uint16_t *Vp = g.V + b * g.v_sb + h * g.v_sh + 8 * sub;
+    float q[8];
+    {
+        u32x4 raw;
+        __builtin_memcpy(&raw, g.Q + b * g.q_sb + h * g.q_sh + (int64_t)qi * g.q_ss + 8 * sub, 16);
+        unpack8_f32<BF16>(raw, q);
+    }
+    float m = -INFINITY, l = 0.f, o[8];                        // this lane group's maximum (base-2 units), sum and output
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+
+    struct Keys { u32x4 k[kDecodeKeys], v[kDecodeKeys]; };
+    auto fetch = [&](Keys &t, int batch) {
+#pragma unroll
+        for (int u = 0; u < kDecodeKeys; ++u) {
+            const int key = batch * BATCH + u * 8 + slot;
+            const int64_t kc = key < g.Sk ? key : g.Sk - 1;
+            __builtin_memcpy(&t.k[u], Kp + kc * g.k_ss, 16);
+            __builtin_memcpy(&t.v[u], Vp + kc * g.v_ss, 16);
+        }
+    };
+    auto use = [&](const Keys &t, int batch) {
+        float s[kDecodeKeys], top = m;
+#pragma unroll
+        for (int u = 0; u < kDecodeKeys; ++u) {
+            float k[8], dot = 0.f;
+            unpack8_f32<BF16>(t.k[u], k);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dot = __builtin_fmaf(q[e], k[e], dot);
+            dot = sum_of_eight(dot) * g.scale_log2e;
+            s[u] = batch * BATCH + u * 8 + slot < g.Sk ? dot : -INFINITY;
+            top = fmaxf(top, s[u]);
+        }
+        const float ref = top == -INFINITY ? 0.f : top;        // (nothing to weigh yet: weights 0, not 0 / 0)
+        const float alpha = __builtin_amdgcn_exp2f(m - ref);
+        m = top;
+        l *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < kDecodeKeys; ++u) {
+            const float p = __builtin_amdgcn_exp2f(s[u] - ref);
+            float v[8];
+            unpack8_f32<BF16>(t.v[u], v);
+            l += p;
+            // (a key that does not exist repeats the last one with weight 0: an infinity there must not become 0 * inf)
+            const bool live = batch * BATCH + u * 8 + slot < g.Sk;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(p, live ? v[e] : 0.f, o[e]);
+        }
+    };
+    const int batches = (g.Sk + BATCH - 1) / BATCH;
+    Keys t[2];
+    if (wave < batches) fetch(t[0], wave);
+    for (int n = wave; n < batches; n += 2 * kDecodeWaves) {
+        if (n + kDecodeWaves < batches) fetch(t[1], n + kDecodeWaves);
+        use(t[0], n);
+        if (n + 2 * kDecodeWaves < batches) fetch(t[0], n + 2 * kDecodeWaves);
+        if (n + kDecodeWaves < batches) use(t[1], n + kDecodeWaves);
+    }
+    // the wavefront's eight groups to a common maximum, summed
+    float top = m;
+#pragma unroll
+    for (int x = 8; x < 64; x <<= 1) top = fmaxf(top, __shfl_xor(top, x, 64));
+    const float ref = top == -INFINITY ? 0.f : top;
+    const float c = __builtin_amdgcn_exp2f(m - ref);
+    l *= c;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= c;
+#pragma unroll
+    for (int x = 8; x < 64; x <<= 1) {
+        l += __shfl_xor(l, x, 64);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], x, 64);
+    }
+    if (lane < 8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red_o[wave][8 * lane + e] = o[e];
+        if (lane == 0) { red_m[wave] = top; red_l[wave] = l; }
+    }
+    __syncthreads();
+    // ... and the wavefronts': thread d has element d of the output row
+    if (tid < kHeadDim) {
+        float mx = red_m[0];
+#pragma unroll
+        for (int i = 1; i < kDecodeWaves; ++i) mx = fmaxf(mx, red_m[i]);
+        const float r = mx == -INFINITY ? 0.f : mx;
+        float lsum = 0.f, osum = 0.f;
+#pragma unroll
+        for (int i = 0; i < kDecodeWaves; ++i) {
+            const float f = __builtin_amdgcn_exp2f(red_m[i] - r);
+            lsum = __builtin_fmaf(red_l[i], f, lsum);
+            osum = __builtin_fmaf(red_o[i][tid], f, osum);
+        }
+        const float v = osum / lsum;
+        g.O[b * g.o_sb + h * g.o_sh + (int64_t)qi * g.o_ss + tid] = BF16 ? f32_to_bf16_rne(v) : f32_to_f16_rne(v);
+    }
+}
+
+// One workgroup per query pays while they do not queue up for the units with the same keys (bf16, us, sdpa_kernel / this one):
+// 192 heads x 1 query x 2047 keys 33.9 / 19.1, x 2 34.5 / 29.2, x 4 35.4 / 39.3; 8 heads x 16 x 2047 30.6 / 11.0, x 32 30.6 / 12.0.
+static bool few_queries(int64_t heads, int64_t queries)
+{
+    return heads <= 0x3fffffff && (queries == 1 || (queries == 2 && heads <= 256) || (queries <= 32 && heads * queries <= 256));
+}
+
 nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
 {
     if (batch <= 0 || a.H <= 0 || a.Sq <= 0) return NT_OK;
+    if (few_queries(batch * a.H, a.Sq)) {
+        SdpaArgs k = a;
+        k.BH = (int32_t)(batch * a.H);
+        k.nqb = a.Sq;
+        const int64_t programs = batch * a.H * a.Sq;
+        const int waves = programs >= 768 || a.Sk <= 128 ? 4 : 16;
+        const dim3 grid((unsigned)programs), block(64 * waves);
+        if (waves == 4) {
+            if (bf16) hipLaunchKernelGGL((sdpa_decode_kernel<true, 4>), grid, block, 0, (hipStream_t)stream, k);
+            else hipLaunchKernelGGL((sdpa_decode_kernel<false, 4>), grid, block, 0, (hipStream_t)stream, k);
+        } else {
+            if (bf16) hipLaunchKernelGGL((sdpa_decode_kernel<true, 16>), grid, block, 0, (hipStream_t)stream, k);
+            else hipLaunchKernelGGL((sdpa_decode_kernel<false, 16>), grid, block, 0, (hipStream_t)stream, k);
+        }
+        return check_launch("sdpa_decode_kernel");
+    }
     const int64_t bh = batch * a.H, nqb = (a.Sq + kQBlock - 1) / kQBlock;
     if (bh * nqb > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "batch * heads * query blocks exceeds 2^31 - 1");
     SdpaArgs k = a;

@@ -100,3 +100,25 @@ def test_sdpa_scores_rising_along_the_keys(dt):
         qb, kb = si.round_to_bits(q, dt), si.round_to_bits(np.ascontiguousarray(kf), dt)
         vb = si.normal_bits((1, 2, Sk, 64), dt, 71, 1.0)
         assert_gates(run(qb, kb, vb, dt), oat.sdpa(qb, kb, vb, dt), dt, f"sdpa rising scores {per_block} {dt}")
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,Sq,Sk", [(1, 1, 1, 1), (1, 3, 2, 7), (2, 5, 1, 8), (1, 9, 2, 31), (3, 3, 1, 33), (1, 1, 1, 511), (2, 8, 2, 513), (1, 17, 1, 1057),
+                                       (1, 8, 32, 96), (1, 16, 16, 1030), (2, 96, 1, 70)])
+def test_few_queries(dt, B, H, Sq, Sk):
+    """A workgroup per query: fewer keys than lane groups, than wavefronts' batches, ragged last batches, several batches per
+    wavefront, head counts that are and are not multiples of eight; scores that rise along the keys; strided operands."""
+    q, k, v = (si.normal_bits(s, dt, 80 + i, 1.5) for i, s in enumerate([(B, H, Sq, 64), (B, H, Sk, 64), (B, H, Sk, 64)]))
+    ref = oat.sdpa(q, k, v, dt)
+    assert_gates(run(q, k, v, dt), ref, dt, f"sdpa {dt} {B}x{H}x{Sq}x{Sk}")
+    kd = onum.decode(k, dt) * np.linspace(0.1, 6.0, Sk)[None, None, :, None]
+    kb = si.round_to_bits(kd.astype(np.float32), dt)
+    ref = oat.sdpa(q, kb, v, dt, scale=-0.4)
+    qs, ks, vs = (to_gpu(np.ascontiguousarray(t.transpose(0, 2, 1, 3)), dt).permute(0, 2, 1, 3) for t in (q, kb, v))
+    vbuf = torch.full((B, H, Sk + 1, 71), float("nan"), dtype=TORCH_DT[dt], device="cuda")       # rows of odd pitch, NaN behind the keys
+    vbuf[:, :, :Sk, 3:67] = vs
+    obuf = torch.full((B, H, Sq, 66), -7.0, dtype=TORCH_DT[dt], device="cuda")
+    nt.sdpa(qs, ks, vbuf[:, :, :Sk, 3:67], obuf[..., 1:65], scale=-0.4)
+    torch.cuda.synchronize()
+    assert_gates(to_f64(obuf[..., 1:65]), ref, dt, f"sdpa strided {dt} {B}x{H}x{Sq}x{Sk}")
+    assert (obuf[..., 0] == -7.0).all() and (obuf[..., 65] == -7.0).all()
