@@ -155,8 +155,8 @@ nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_o
 /* Which kernel the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call launched:
  * 0 operand-map (generic) kernel, or the 64 x 64 x 32 tile named by the caller, 1 staged kernel, 2 direct-to-LDS kernel (or
  * the kernel for products of at most 32 rows, which splits the reduction inside a program), 3 convolution kernel (operands staged
- * through registers), 4 convolution kernel (operands streamed straight into LDS), 5 unfolded input written to the
- * workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks the reduction filter tap by filter
+ * through registers), 4 convolution kernel (operands streamed straight into LDS), 5 a strided or
+ * dilated convolution through the workspace (a channels-last copy, or the unfolded input, + the matrix kernels), 6 convolution kernel that streams into LDS and walks the reduction filter tap by filter
  * tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of the filter that it puts in the
  * workspace),
  * -1 none (nothing launched yet, an error, or an empty problem).  For tests and diagnostics. */
@@ -305,7 +305,10 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * out-of-image positions (padding) read as zero.  dy must have P = (H + 2*pad_h - R) /
  * stride_h + 1 (integer division), likewise Q; otherwise NT_ERR_SHAPE_MISMATCH.
  * Descriptors have ndim 4 with arbitrary strides.
- * Dense unit-stride calls (contiguous NCHW input, at most one column of padding) never materialise the unfolded input; with
+ * Strided calls with channels in whole blocks of 32 and more than one filter tap, and unit-stride calls with such channels and
+ * few output positions, run on a zero-padded channels-last copy of their input, made in the workspace beside the filter's
+ * tap-major copy (a call captured in a graph that needs no k split keeps to the kernels below).
+ * Other dense unit-stride calls (contiguous NCHW input, at most one column of padding) never materialise the unfolded input; with
  * more than 128 filters and channels in whole blocks of 32 they copy the filter (only) into the workspace in tap-major order,
  * unless it is stored that way already (a channels-last filter: strides (R S C, 1, S C, C)), which is then read as it is.  The
  * other convolutions on the library's own tile go through the library's workspace when what they need fits it:

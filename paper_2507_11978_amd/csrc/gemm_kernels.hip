@@ -1,6 +1,7 @@
 // Dispatch between the kernels, plus the small auxiliary kernels (zero fill, address trace).
 #include <mutex>
 
+#include "gemm_conv_cl.h"
 #include "gemm_conv_direct.h"
 #include "gemm_conv_tap.h"
 #include "gemm_direct.h"
@@ -319,6 +320,14 @@ static bool match_conv(const GemmLaunch &g, ConvArgs *a)
 // fence cost every call 2 us on the device (the paper's conv task 29.5 -> 27.6 us).
 static constexpr size_t kSplitWsMax = 256u << 20;
 
+// whether work on the stream is being captured into a graph
+static bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return st != hipStreamCaptureStatusNone;
+}
+
 class WorkspaceLease {
 public:
     WorkspaceLease() = default;
@@ -332,7 +341,9 @@ public:
         Slot &w = table()[dev];
         w.mu.lock();
         bool ok = true;
-        if (!w.p) {
+        if (!w.p && capturing(stream)) {                      // (an allocation would invalidate the capture)
+            ok = false;
+        } else if (!w.p) {
             void *p = nullptr;
             hipEvent_t ev = nullptr;
             if (hipMalloc(&p, kSplitWsMax) != hipSuccess) { (void)hipGetLastError(); ok = false; }
@@ -627,6 +638,98 @@ static bool conv_is_bare(const GemmLaunch &g)        // a convolution and nothin
     return g.conv.valid && !g.user_tile && !g.no_workspace && !g.ws_given && g.batch == 1 && !g.has_d && g.alpha == 1.f && g.act == 0;
 }
 
+// Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
+// estimate of its product.  A unit runs two programs at a time; a program costs a fixed part and its slices, a split the
+// kernel that adds the parts and their trip through memory.  (Fits, us: 392 programs of 128 x 128 with 36 slices 27.5, 196
+// with 144 44, 144 of 64 x 64 with 72 13.8, 1568 with 36 36.)
+static void conv_cl_plan(int64_t F, int64_t M, int64_t slices, int *tile_out, int *parts_out)
+{
+    double best = 0;
+    for (int tile = 64; tile <= 128; tile += 64)
+        for (int64_t ks = 1; ks <= 8; ++ks) {
+            const int64_t per = (slices + ks - 1) / ks;
+            if (ks > 1 && (per < 4 || (slices + per - 1) / per != ks)) continue;
+            const double load = std::max(1.0, (double)(((F + tile - 1) / tile) * ((M + tile - 1) / tile) * ks) / 256.0);
+            const double rounds = load <= 2.0 ? 1.0 : load / 2.0;
+            double c = tile == 64 ? 4.0 * rounds + (double)per * (load <= 1.0 ? 0.12 : 0.12 * std::max(2.0, load))
+                                  : 6.0 * rounds + (double)per * (load <= 1.0 ? 0.24 : 0.29 * std::max(2.0, load));
+            if (ks > 1) c += 4.0 + (double)ks * (double)F * (double)M * 8.0 / 3.0e6;
+            if (best == 0 || c < best) { best = c; *tile_out = tile; *parts_out = (int)ks; }
+        }
+}
+
+// ---- route 0: on a channels-last copy of the input (gemm_conv_cl.hip), the filter's tap-major copy beside it: convolutions
+// with channels in whole blocks of 32 that are
+//   strided or dilated, with more than one tap (the unfolded input, route 3, is then several times the copy: 62.0 -> 39.2 us
+//   for (32,128,56,56)*(256,128,3,3) stride 2, 100 -> 50 for (16,320,27,27)*(334,320,5,5); with one tap it is no larger, and
+//   route 3's wide tiles win, 30.1 against 34.1 for (32,256,56,56)*(512,256,1,1)), or
+//   of unit stride with few positions (conv_small): the kernels of route 1 compute rows of 8 positions, 12 of 16 for an
+//   output row of 12, and spend more on a program's start than on its few slices: (32,512,7,7)*(512,512,3,3) 48 -> 31 us,
+//   (3,224,13,13)*(256,224,3,3) 21.8 -> 13.6, (8,64,14,14)*(64,64,3,3) 16.7 -> 10.3; with many, the wider tiles of route 1
+//   win, 123 against 170 for (32,256,56,56)*(256,256,3,3).  The reduction is split into as many parts as there.
+static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bool *taken)
+{
+    *taken = false;
+    const ConvHint &h = g.conv;
+    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.ys[3] != 1 || h.ys[2] != h.Q || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
+    const int64_t RS = h.R * h.S, K = h.C * RS, PQ = h.P * h.Q, M = h.N * PQ, F = h.K;
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1;
+    if (M >= (1LL << 30) || F >= (1LL << 22) || K > 32768 || F * K >= (1LL << 30)) return NT_OK;
+    const bool natural = h.ws[3] == 1 && h.ws[2] == h.S && h.ws[1] == RS && h.ws[0] >= K;
+    const bool tap_major = !natural && h.ws[1] == 1 && h.ws[3] == h.C && h.ws[2] == h.S * h.C && h.ws[0] == K && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
+    if (!natural && !tap_major) return NT_OK;
+    int tile = 128, parts = 1;
+    int64_t per = K / 32;
+    if (unit) {
+        const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);          // (positions as route 1 counts them)
+        if (!conv_small(M8, F)) return NT_OK;
+        int32_t kt_per = 0;
+        parts = conv_ksplit(M8, F, (K + 63) / 64, g.tile.bn, &kt_per);
+        per = 2 * (int64_t)kt_per;
+        // (without a split route 1 needs no workspace: a captured call stays independent of it, as its replays take no lease)
+        if (parts == 1 && capturing((hipStream_t)g.stream)) return NT_OK;
+        if (((F + 127) / 128) * ((M + 127) / 128) * parts < 192) tile = 64;
+    } else {
+        if (RS == 1) return NT_OK;
+        conv_cl_plan(F, M, K / 32, &tile, &parts);
+        per = (K / 32 + parts - 1) / parts;
+    }
+    // the copy: the padded image, or (one tap per axis) only the positions that are read
+    const int64_t eh = h.R == 1 ? h.sh : 1, ew = h.S == 1 ? h.sw : 1;
+    const int64_t Hc = h.R == 1 ? h.P : h.H + 2 * h.ph, Wc = h.S == 1 ? h.Q : h.W + 2 * h.pw;
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t copy_bytes = up((size_t)h.N * Hc * Wc * h.C * 2), filter_bytes = natural ? up((size_t)F * K * 2) : 0;
+    const size_t split_bytes = parts > 1 ? (size_t)parts * F * M * 4 : 0;
+    WorkspaceLease lease;
+    char *region = (char *)lease.acquire(copy_bytes + filter_bytes + split_bytes, (hipStream_t)g.stream);
+    if (!region) return NT_OK;
+    *taken = true;
+    hipStream_t s = (hipStream_t)g.stream;
+    ConvClCopy c{};
+    c.x = (const uint16_t *)g.A; c.P = (uint16_t *)region;
+    for (int d = 0; d < 4; ++d) c.xs[d] = h.xs[d];
+    c.N = (int32_t)h.N; c.C = (int32_t)h.C; c.H = (int32_t)h.H; c.W = (int32_t)h.W; c.Hc = (int32_t)Hc; c.Wc = (int32_t)Wc;
+    c.ph = (int32_t)h.ph; c.pw = (int32_t)h.pw; c.eh = (int32_t)eh; c.ew = (int32_t)ew;
+    c.w = natural ? (const uint16_t *)g.B : nullptr;
+    c.Wt = (uint16_t *)(region + copy_bytes);
+    c.ldb = h.ws[0]; c.F = (int32_t)F; c.RS = (int32_t)RS;
+    nt_status st = launch_conv_cl_copy(c, s);
+    if (st != NT_OK) return st;
+    ConvClArgs a{};
+    a.P = c.P; a.Wt = natural ? c.Wt : (const uint16_t *)g.B; a.Y = g.C;
+    a.syn = h.ys[0]; a.syf = h.ys[1];
+    a.F = (int32_t)F; a.M = (int32_t)M; a.C = (int32_t)h.C; a.K = (int32_t)K;
+    a.PQ = (int32_t)PQ; a.Q = (int32_t)h.Q; a.Hc = (int32_t)Hc; a.Wc = (int32_t)Wc;
+    a.S = (int32_t)h.S; a.sp = (int32_t)(h.sh / eh); a.sq = (int32_t)(h.sw / ew); a.dh = (int32_t)h.dh; a.dw = (int32_t)h.dw;
+    a.mt = (int32_t)((F + tile - 1) / tile); a.nt = (int32_t)((M + tile - 1) / tile);
+    a.ksplit = parts; a.per = (int32_t)per;
+    a.ws = (float *)(region + copy_bytes + filter_bytes);
+    a.out_dtype = g.out_dtype;
+    t_k_split = parts;
+    if (path_out) *path_out = !unit ? PATH_CONV_UNFOLD : (F > 128 && RS <= 32 ? PATH_CONV_TAP : PATH_CONV_DIRECT);
+    return launch_conv_cl(a, tile, g.in_dtype == NT_BF16, s);
+}
+
 // ---- route 2: a unit-stride convolution that the implicit kernels do not take as it is (more than one column of padding, a
 // channels-last or otherwise strided input): on a dense zero-padded copy of its input, made once in the workspace (the
 // input's size, not C R S times it), it is a dense convolution without padding.  *taken = false: not this route.
@@ -875,11 +978,13 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
         if (lower_plain(w, &a, &alay, &blay)) return route_matrix(w, a, alay, blay, path_out);
     }
     if (path_out) *path_out = PATH_GENERIC;
+    bool taken = false;
+    nt_status st = route_conv_channels_last(g, path_out, &taken);
+    if (taken || st != NT_OK) return st;
     ConvArgs c{};
     if (!g.has_d && g.alpha == 1.f && g.act == 0 && match_conv(g, &c)) return route_conv_implicit(g, c, path_out);
     if (g.trace.out) return fail(NT_ERR_UNSUPPORTED, "this launch does not run on the kernels that stream their operands into LDS");
-    bool taken = false;
-    nt_status st = route_conv_padded_copy(g, path_out, &taken);
+    st = route_conv_padded_copy(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     st = route_conv_unfold(g, path_out, &taken);
     if (taken || st != NT_OK) return st;

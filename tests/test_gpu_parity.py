@@ -664,6 +664,41 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
             assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
 
 
+@pytest.mark.parametrize("shape,stride,pad", [
+    ((2, 32, 9, 9, 64, 3, 3), (2, 2), (1, 1)),         # one block of 32 channels: 9 slices (odd), 50 positions
+    ((3, 96, 13, 11, 70, 3, 3), (2, 1), (1, 1)),       # 96 channels: the second copy tile holds 32; 27 slices; mixed strides; ragged filters
+    ((5, 64, 14, 14, 130, 3, 3), (3, 3), (2, 2)),      # stride 3, wide padding, 36 positions per image: chunks straddle images
+    ((2, 64, 20, 18, 128, 1, 3), (2, 2), (0, 1)),      # one tap along h: the copy holds the rows that are read
+    ((9, 32, 7, 7, 33, 7, 7), (2, 2), (3, 3)),         # 49 slices, 16 positions per image
+    ((1, 160, 6, 5, 8, 2, 2), (2, 2), (0, 0)),         # 6 positions in all, 8 filters
+    ((32, 64, 30, 30, 256, 3, 3), (2, 2), (1, 1)),     # enough programs for the 128 x 128 tile
+    ((2, 64, 7, 7, 300, 3, 3), (1, 1), (1, 1)),        # unit stride, few positions: odd rows of 7
+    ((3, 32, 5, 6, 40, 1, 1), (1, 1), (0, 0)),         # one slice
+])
+def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
+    """Channels in whole blocks of 32, strided or with few positions: the edges of the copy's tiles, of the product's tiles in
+    filters and positions, odd and single slices, output chunks that end inside an image, splits.  Small integers: exact;
+    NCHW and channels-last inputs and filters; what lies around the output (a channel slice) stays untouched."""
+    N, Cc, H, W, K, R, S = shape
+    for dt, out in (("f16", "f32"), ("bf16", "bf16"), ("f16", "f16")):
+        X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, seed=33, dist="int")
+        ref = onum.conv2d(X, Wt, dt, stride, pad, nthreads=16)
+        want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+        for last in (False, True):
+            x, w = to_gpu(X, dt), to_gpu(Wt, dt)
+            if last:
+                x, w = (t.permute(0, 2, 3, 1).contiguous().permute(0, 3, 1, 2) for t in (x, w))
+                if stride == (1, 1):
+                    w = to_gpu(Wt, dt)
+            big = torch.full((N, K + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
+            Y = big[:, 2:K + 2]
+            nt.conv2d_implicit(x, w, Y, stride, pad)
+            torch.cuda.synchronize()
+            assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if stride == (1, 1) else (nt.PATH_CONV_UNFOLD,))
+            assert torch.equal(Y.cpu(), want), f"conv {shape} {stride} {pad} {dt} {out} channels_last={last}"
+            assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
+
+
 def test_conv2d_dense_integer_exact_and_padding_edges():
     # small integers: exact; a wrong halo element or a missed padding row changes the result
     N, Cc, H, W, K, R, S = 2, 8, 16, 16, 128, 3, 3
