@@ -156,23 +156,22 @@ def make_desc(shape: Sequence[int], strides: Sequence[int] | None = None) -> Ten
     return d
 
 
-_desc_cache: dict = {}
+_ref_cache: dict = {}
 
 
-def _desc_of(t) -> TensorDesc:
-    """Descriptor of a torch tensor (sizes and element strides) or a (shape, strides) pair.  Descriptors of tensors
-    are read-only inputs of the library and are kept by (shape, strides): a call on a layout seen before builds none."""
-    if isinstance(t, TensorDesc):
-        return t
+def _ref(t):
+    """Reference (ctypes) to the descriptor of a torch tensor (sizes and element strides), a (shape, strides) pair, or a
+    TensorDesc.  Descriptors of tensors are read-only inputs of the library and their references are kept by (shape,
+    strides): a call on a layout seen before builds none.  (A reference keeps its descriptor alive by itself.)"""
     if hasattr(t, "data_ptr"):
-        key = (tuple(t.shape), tuple(t.stride()))
-        d = _desc_cache.get(key)
-        if d is None:
-            if len(_desc_cache) > 4096:
-                _desc_cache.clear()
-            d = _desc_cache[key] = make_desc(*key)
-        return d
-    return make_desc(*t)
+        key = (t.shape, t.stride())
+        r = _ref_cache.get(key)
+        if r is None:
+            if len(_ref_cache) > 4096:
+                _ref_cache.clear()
+            r = _ref_cache[key] = C.byref(make_desc(*key))
+        return r
+    return C.byref(t if isinstance(t, TensorDesc) else make_desc(*t))
 
 
 def make_ops(ops) -> tuple:
@@ -214,9 +213,12 @@ def make_ops(ops) -> tuple:
     return arr, len(ops)
 
 
+_LIBRARY_TILE = TileCfg(0, 0, 0)                            # (read-only inputs, passed by value)
+
+
 def _cfg(tile) -> TileCfg:
     if tile is None:
-        return TileCfg(0, 0, 0)
+        return _LIBRARY_TILE
     if isinstance(tile, TileCfg):
         return tile
     return TileCfg(*[int(x) for x in tile])
@@ -259,7 +261,7 @@ def _arrange_problem(fn, descs, extra, tile, operand, program_id, k):
     kt = C.c_int64()
     tshape = (C.c_int64 * 2)()
     cfg = _cfg(tile)
-    ds = [C.byref(_desc_of(d)) for d in descs]
+    ds = [_ref(d) for d in descs]
     if operand is None:
         _check(fn(*ds, *extra, cfg, grid, C.byref(kt), 0, 0, 0, None, None, 0, None))
         return tuple(grid), kt.value
@@ -296,20 +298,31 @@ def tile_supported(tile) -> bool:
 
 
 # ---------------------------------------------------------------------------- kernels
-_dtype_names: dict = {}
+_dtype_codes: dict = {}
 
 
-def _torch_dtype_name(t) -> str:
-    if not _dtype_names:
+def _code(t) -> int:
+    """nt_dtype of a torch tensor's elements."""
+    if not _dtype_codes:
         import torch
-        _dtype_names.update({torch.float16: "f16", torch.bfloat16: "bf16", torch.float32: "f32"})
-    return _dtype_names[t.dtype]
+        _dtype_codes.update({torch.float16: _DTYPES["f16"], torch.bfloat16: _DTYPES["bf16"], torch.float32: _DTYPES["f32"]})
+    return _dtype_codes[t.dtype]
+
+
+_current_raw_stream = None
 
 
 def _stream_ptr(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    """The HIP stream to launch on, as an address: the given torch stream, or the current device's current one."""
+    global _current_raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        import torch
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        # (a Stream object per call costs a microsecond: torch's own raw query, where it has one)
+        _current_raw_stream = (lambda: raw(device())) if raw and device else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _current_raw_stream()
 
 
 def _require_cuda(*ts):
@@ -321,18 +334,18 @@ def _require_cuda(*ts):
 def gemm(A, B, Cout, tile=None, stream=None):
     """Cout[M,N] = A[M,K] @ B[K,N] on the GPU; tensors may be any strided views."""
     _require_cuda(A, B, Cout)
-    _check(load().nt_gemm(A.data_ptr(), C.byref(_desc_of(A)), B.data_ptr(), C.byref(_desc_of(B)),
-                          Cout.data_ptr(), C.byref(_desc_of(Cout)), _DTYPES[_torch_dtype_name(A)],
-                          _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_gemm(A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
+                          Cout.data_ptr(), _ref(Cout), _code(A),
+                          _code(Cout), _cfg(tile), _stream_ptr(stream)))
     return Cout
 
 
 def gemm_noalloc(A, B, Cout, tile=None, stream=None):
     """gemm() through the entry point that allocates no device memory (a k split uses the library's fixed scratch array)."""
     _require_cuda(A, B, Cout)
-    _check(load().nt_gemm_noalloc(A.data_ptr(), C.byref(_desc_of(A)), B.data_ptr(), C.byref(_desc_of(B)),
-                                  Cout.data_ptr(), C.byref(_desc_of(Cout)), _DTYPES[_torch_dtype_name(A)],
-                                  _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_gemm_noalloc(A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
+                                  Cout.data_ptr(), _ref(Cout), _code(A),
+                                  _code(Cout), _cfg(tile), _stream_ptr(stream)))
     return Cout
 
 
@@ -341,7 +354,7 @@ def mfma_probe(data, out, iters=2000, blocks=1024, stream=None):
     _require_cuda(data, out)
     if out.numel() < blocks * 256:
         raise ValueError("out must hold blocks * 256 floats")
-    _check(load().nt_mfma_probe(data.data_ptr(), data.numel(), _DTYPES[_torch_dtype_name(data)], int(iters), int(blocks), out.data_ptr(), _stream_ptr(stream)))
+    _check(load().nt_mfma_probe(data.data_ptr(), data.numel(), _code(data), int(iters), int(blocks), out.data_ptr(), _stream_ptr(stream)))
     return 2.0 * 16 * 16 * 32 * 64 * iters * 4 * blocks
 
 
@@ -378,10 +391,10 @@ def addmm(inp, A, B, Cout, alpha=1.0, beta=1.0, tile=None, stream=None, act=None
                 view = inp.expand(Cout.shape)
             except RuntimeError:
                 view = inp
-        _check(load().nt_addmm_act(view.data_ptr() if view is not None else None, C.byref(_desc_of(view)) if view is not None else None,
-                                   A.data_ptr(), C.byref(_desc_of(A)), B.data_ptr(), C.byref(_desc_of(B)),
-                                   Cout.data_ptr(), C.byref(_desc_of(Cout)), float(alpha), float(beta), ACTIVATIONS[act],
-                                   _DTYPES[_torch_dtype_name(A)], _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+        _check(load().nt_addmm_act(view.data_ptr() if view is not None else None, _ref(view) if view is not None else None,
+                                   A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
+                                   Cout.data_ptr(), _ref(Cout), float(alpha), float(beta), ACTIVATIONS[act],
+                                   _code(A), _code(Cout), _cfg(tile), _stream_ptr(stream)))
         return Cout
     _require_cuda(inp, A, B, Cout)
     if inp.dtype != Cout.dtype:
@@ -390,41 +403,41 @@ def addmm(inp, A, B, Cout, alpha=1.0, beta=1.0, tile=None, stream=None, act=None
         view = inp.expand(Cout.shape)
     except RuntimeError:
         view = inp                                    # not broadcastable: the library reports the mismatch
-    _check(load().nt_addmm(view.data_ptr(), C.byref(_desc_of(view)), A.data_ptr(), C.byref(_desc_of(A)),
-                           B.data_ptr(), C.byref(_desc_of(B)), Cout.data_ptr(), C.byref(_desc_of(Cout)),
-                           float(alpha), float(beta), _DTYPES[_torch_dtype_name(A)],
-                           _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_addmm(view.data_ptr(), _ref(view), A.data_ptr(), _ref(A),
+                           B.data_ptr(), _ref(B), Cout.data_ptr(), _ref(Cout),
+                           float(alpha), float(beta), _code(A),
+                           _code(Cout), _cfg(tile), _stream_ptr(stream)))
     return Cout
 
 
 def add(x, y, out, block_size=0, stream=None):
     """out = x + y over 1-D tensors (16-bit floating point, any stride)."""
     _require_cuda(x, y, out)
-    _check(load().nt_add(x.data_ptr(), C.byref(_desc_of(x)), y.data_ptr(), C.byref(_desc_of(y)), out.data_ptr(),
-                         C.byref(_desc_of(out)), _DTYPES[_torch_dtype_name(x)], int(block_size), _stream_ptr(stream)))
+    _check(load().nt_add(x.data_ptr(), _ref(x), y.data_ptr(), _ref(y), out.data_ptr(),
+                         _ref(out), _code(x), int(block_size), _stream_ptr(stream)))
     return out
 
 
 def silu(x, out, block_size=0, stream=None):
     _require_cuda(x, out)
-    _check(load().nt_silu(x.data_ptr(), C.byref(_desc_of(x)), out.data_ptr(), C.byref(_desc_of(out)),
-                          _DTYPES[_torch_dtype_name(x)], int(block_size), _stream_ptr(stream)))
+    _check(load().nt_silu(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
+                          _code(x), int(block_size), _stream_ptr(stream)))
     return out
 
 
 def softmax(x, out, stream=None):
     """Row-wise softmax of a 2-D tensor."""
     _require_cuda(x, out)
-    _check(load().nt_softmax(x.data_ptr(), C.byref(_desc_of(x)), out.data_ptr(), C.byref(_desc_of(out)),
-                             _DTYPES[_torch_dtype_name(x)], _stream_ptr(stream)))
+    _check(load().nt_softmax(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
+                             _code(x), _stream_ptr(stream)))
     return out
 
 
 def rms_norm(x, out, eps=1e-6, stream=None):
     """Row-wise x / sqrt(mean(x^2) + eps) of a 2-D tensor (no weight)."""
     _require_cuda(x, out)
-    _check(load().nt_rms_norm(x.data_ptr(), C.byref(_desc_of(x)), out.data_ptr(), C.byref(_desc_of(out)),
-                              float(eps), _DTYPES[_torch_dtype_name(x)], _stream_ptr(stream)))
+    _check(load().nt_rms_norm(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
+                              float(eps), _code(x), _stream_ptr(stream)))
     return out
 
 
@@ -435,34 +448,34 @@ def matmul_views(A, ops_a, B, ops_b, Cout, ops_c, tile=None, stream=None):
     oa, na = make_ops(ops_a)
     ob, nb = make_ops(ops_b)
     oc, nc = make_ops(ops_c)
-    _check(load().nt_matmul_views(A.data_ptr(), C.byref(_desc_of(A)), oa, na, B.data_ptr(), C.byref(_desc_of(B)), ob, nb,
-                                  Cout.data_ptr(), C.byref(_desc_of(Cout)), oc, nc, _DTYPES[_torch_dtype_name(A)],
-                                  _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_matmul_views(A.data_ptr(), _ref(A), oa, na, B.data_ptr(), _ref(B), ob, nb,
+                                  Cout.data_ptr(), _ref(Cout), oc, nc, _code(A),
+                                  _code(Cout), _cfg(tile), _stream_ptr(stream)))
     return Cout
 
 
 def sdpa(q, k, v, out, scale=0.0, stream=None):
     """out = softmax(scale * q @ k^T) @ v per (batch, head); tensors [batch, heads, seq, 64]; scale 0 = 1/sqrt(64)."""
     _require_cuda(q, k, v, out)
-    _check(load().nt_sdpa(q.data_ptr(), C.byref(_desc_of(q)), k.data_ptr(), C.byref(_desc_of(k)), v.data_ptr(), C.byref(_desc_of(v)),
-                          out.data_ptr(), C.byref(_desc_of(out)), float(scale), _DTYPES[_torch_dtype_name(q)], _stream_ptr(stream)))
+    _check(load().nt_sdpa(q.data_ptr(), _ref(q), k.data_ptr(), _ref(k), v.data_ptr(), _ref(v),
+                          out.data_ptr(), _ref(out), float(scale), _code(q), _stream_ptr(stream)))
     return out
 
 
 def bmm(A, B, Cout, tile=None, stream=None):
     _require_cuda(A, B, Cout)
-    _check(load().nt_bmm(A.data_ptr(), C.byref(_desc_of(A)), B.data_ptr(), C.byref(_desc_of(B)),
-                         Cout.data_ptr(), C.byref(_desc_of(Cout)), _DTYPES[_torch_dtype_name(A)],
-                         _DTYPES[_torch_dtype_name(Cout)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_bmm(A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
+                         Cout.data_ptr(), _ref(Cout), _code(A),
+                         _code(Cout), _cfg(tile), _stream_ptr(stream)))
     return Cout
 
 
 def conv2d_implicit(x, w, y, stride=(1, 1), pad=(0, 0), tile=None, stream=None):
     _require_cuda(x, w, y)
-    _check(load().nt_conv2d_implicit(x.data_ptr(), C.byref(_desc_of(x)), w.data_ptr(), C.byref(_desc_of(w)),
-                                     y.data_ptr(), C.byref(_desc_of(y)), int(stride[0]), int(stride[1]),
-                                     int(pad[0]), int(pad[1]), _DTYPES[_torch_dtype_name(x)],
-                                     _DTYPES[_torch_dtype_name(y)], _cfg(tile), _stream_ptr(stream)))
+    _check(load().nt_conv2d_implicit(x.data_ptr(), _ref(x), w.data_ptr(), _ref(w),
+                                     y.data_ptr(), _ref(y), int(stride[0]), int(stride[1]),
+                                     int(pad[0]), int(pad[1]), _code(x),
+                                     _code(y), _cfg(tile), _stream_ptr(stream)))
     return y
 
 
@@ -475,9 +488,9 @@ def trace_loader_slice(kind, a, b, c, operand, program_id, slice_index, tile=Non
     kinds = {"gemm": 0, "bmm": 1, "conv2d": 2}
     _require_cuda(a, b, c)
     out = torch.full((256 * 32,), -1, dtype=torch.int16, device="cuda")
-    _check(load().nt_trace_loader_slice(kinds[kind], a.data_ptr(), C.byref(_desc_of(a)), b.data_ptr(), C.byref(_desc_of(b)),
-                                        C.byref(_desc_of(c)), int(stride[0]), int(stride[1]), int(pad[0]), int(pad[1]),
-                                        _DTYPES[_torch_dtype_name(a)], _DTYPES[_torch_dtype_name(c)], _cfg(tile), int(operand),
+    _check(load().nt_trace_loader_slice(kinds[kind], a.data_ptr(), _ref(a), b.data_ptr(), _ref(b),
+                                        _ref(c), int(stride[0]), int(stride[1]), int(pad[0]), int(pad[1]),
+                                        _code(a), _code(c), _cfg(tile), int(operand),
                                         int(program_id), int(slice_index), out.data_ptr(), out.numel(), _stream_ptr(stream)))
     torch.cuda.synchronize()
     return out.cpu().numpy().view(np.uint16).reshape(256, 32)
@@ -493,7 +506,7 @@ def trace_tile(kind, d0, d1, d2, tile, operand, program_id, k, stride=(1, 1), pa
     cap = max(cfg.bm * cfg.bk, cfg.bk * cfg.bn, cfg.bm * cfg.bn)
     off = torch.full((cap,), -7, dtype=torch.int64, device="cuda")
     mask = torch.full((cap,), 9, dtype=torch.uint8, device="cuda")
-    _check(load().nt_trace_tile(kinds[kind], C.byref(_desc_of(d0)), C.byref(_desc_of(d1)), C.byref(_desc_of(d2)),
+    _check(load().nt_trace_tile(kinds[kind], _ref(d0), _ref(d1), _ref(d2),
                                 int(stride[0]), int(stride[1]), int(pad[0]), int(pad[1]), cfg, int(operand),
                                 int(program_id), int(k), off.data_ptr(), mask.data_ptr(), cap, _stream_ptr(stream)))
     torch.cuda.synchronize()

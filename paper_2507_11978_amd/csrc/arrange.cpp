@@ -344,6 +344,24 @@ nt_status Arrangement::lower_matrix_view(OperandMap *map, int64_t *batch_out, in
     const std::vector<int> &lv = levels_[0];
     const int rank = (int)lv.size();
     if (rank != 2 && rank != 3) return fail(NT_ERR_SHAPE_MISMATCH, "matrix view must have rank 2 (or 3 with batch)");
+    if (nodes_.empty()) {
+        // No meta-operation but permutations: every dimension is one of the source's, an axis is one digit that steps by its
+        // stride, nothing can leave the tensor.  What the steps below come to, without their allocations (each plain product
+        // lowers three such views per call: 0.8 us of its host time).
+        const int r = lv[rank - 2], c = lv[rank - 1];
+        OperandMap m{};
+        m.rows = size_[r];
+        m.cols = size_[c];
+        m.nrd = m.ncd = 1;
+        m.rrad[0] = size_[r];
+        m.crad[0] = size_[c];
+        m.roff[0] = src_.stride[r];
+        m.coff[0] = src_.stride[c];
+        *map = m;
+        if (batch_out) *batch_out = rank == 3 ? size_[lv[0]] : 1;
+        if (batch_stride_out) *batch_stride_out = rank == 3 ? src_.stride[lv[0]] : 0;
+        return NT_OK;
+    }
     std::vector<Var> vars;
     std::vector<std::vector<int>> digits(3);      // per axis: variable ids, slowest first
     std::map<int, Lin> lin;                       // dimension id -> linear form

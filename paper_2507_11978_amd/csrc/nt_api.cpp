@@ -156,7 +156,7 @@ void recognise_conv(const nt_tensor_desc *dx, const nt_tensor_desc *dw, const nt
 
 nt_status build_problem(int kind, const nt_tensor_desc *d0, const nt_tensor_desc *d1, const nt_tensor_desc *d2,
                         int32_t sh, int32_t sw, int32_t ph, int32_t pw, nt_tile_cfg cfg, Problem *p,
-                        const ViewPrograms *views = nullptr)
+                        const ViewPrograms *views = nullptr, bool grid_only = false)
 {
     if (!d0 || !d1 || !d2) return fail(NT_ERR_INVALID_ARG, "null tensor descriptor");
     if (cfg.bm < 0 || cfg.bn < 0 || cfg.bk < 0) return fail(NT_ERR_INVALID_ARG, "negative tile size");
@@ -206,6 +206,16 @@ nt_status build_problem(int kind, const nt_tensor_desc *d0, const nt_tensor_desc
         const bool narrow = (kind == KIND_GEMM || kind == KIND_BMM) && d2->stride[o + 1] == 1 && unit_axis(d0) && unit_axis(d1) && p->K >= 8;
         p->tile = pick_tile(kind, p->batch, p->M, p->N, p->K, cfg, sh == 1 && sw == 1, narrow);
     }
+    if (grid_only) {
+        // A launch needs the matmul arrangement's grid only.  The three views agree (checked above) and every tile is positive,
+        // so the arrangement cannot be improper and its outermost shape is Algorithm 1's ceil on each axis; building it -- two
+        // dozen meta-operations on hierarchical tensors -- was half a small product's host time (2.5 us of 5.5).
+        p->mm.batch = p->batch;
+        p->mm.mt = (p->M + p->tile.bm - 1) / p->tile.bm;
+        p->mm.nt = (p->N + p->tile.bn - 1) / p->tile.bn;
+        p->mm.kt = (p->K + p->tile.bk - 1) / p->tile.bk;
+        return NT_OK;
+    }
     NT_TRY(nt::arrange_matmul(p->va, p->vb, p->vc, p->tile, &p->mm));
     return NT_OK;
 }
@@ -246,7 +256,7 @@ nt_status run(int kind, const void *A, const nt_tensor_desc *dA, const void *B, 
     if ((cfg.bm || cfg.bn || cfg.bk) && cfg.bm > 0 && cfg.bn > 0 && cfg.bk > 0 && !nt::tile_is_built(cfg))
         return fail(NT_ERR_UNSUPPORTED, "no kernel built for this tile shape (see nt_tile_supported)");
     Problem p;
-    NT_TRY(build_problem(kind, dA, dB, dC, sh, sw, ph, pw, cfg, &p, views));
+    NT_TRY(build_problem(kind, dA, dB, dC, sh, sw, ph, pw, cfg, &p, views, true));
     if (p.batch == 0 || p.M == 0 || p.N == 0) return NT_OK;
     if (!C || (p.K > 0 && (!A || !B))) return fail(NT_ERR_INVALID_ARG, "null device pointer");
     nt::GemmLaunch g{};

@@ -161,3 +161,38 @@ def test_matmul_views_errors():
         nt.matmul_views(a, [("flatten", 0, 2)], a, [], c, [])                 # rank 1
     with pytest.raises(nt.NtError):
         nt.matmul_views(a, [], torch.zeros((9, 8), dtype=torch.float16, device="cuda"), [], c, [])   # inner sizes differ
+
+
+@pytest.mark.parametrize("batch", [None, 3])
+@pytest.mark.parametrize("order", ["plain", "transposed", "pitched", "strided"])
+def test_views_without_operations_lower_like_views_with_an_idle_one(batch, order):
+    """A tensor that is its own matrix view is lowered without the general steps; flattening one dimension into itself changes
+    nothing and takes them: the same bits, in every layout, batched or not, with a permutation in between."""
+    dt, M, N, K = "f16", 70, 45, 96
+    idle = [("flatten", 0, 1)]
+
+    def layout(rows, cols, seed):
+        shape = (rows, cols) if batch is None else (batch, rows, cols)
+        t = to_gpu(si.normal_bits(shape, dt, seed, 1.0), dt)
+        if order == "transposed":
+            return t.transpose(-1, -2).contiguous().transpose(-1, -2)
+        if order in ("pitched", "strided"):
+            step = 1 if order == "pitched" else 2
+            buf = torch.zeros(shape[:-1] + (cols * step + 3,), dtype=t.dtype, device="cuda")
+            buf[..., :cols * step:step] = t
+            return buf[..., :cols * step:step]
+        return t
+    a, b = layout(M, K, 1), layout(K, N, 2)
+    outs = []
+    for ops in ([], idle):
+        c = torch.full(((M, N) if batch is None else (batch, M, N)), float("nan"), dtype=torch.float32, device="cuda")
+        nt.matmul_views(a, ops, b, ops, c, ops)
+        outs.append(c)
+        at = a.transpose(-1, -2)
+        swap = [("permute", (1, 0) if batch is None else (0, 2, 1))]
+        c = torch.full_like(c, float("nan"))
+        nt.matmul_views(at, swap + ops, b, ops, c, ops)
+        outs.append(c)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, outs[0]) for o in outs)
+    assert np.allclose(to_f64(outs[0]), to_f64(a) @ to_f64(b), rtol=1e-5, atol=1e-4)

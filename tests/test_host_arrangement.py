@@ -145,6 +145,23 @@ def test_conv_arrangement(shape, stride, pad, full):
             _same(nt.arrange_conv2d(*d, stride, pad, tile=tile, operand=1, program_id=pid, k=k), arr.tile_index_set(b, pid, (k,)))
 
 
+@pytest.mark.parametrize("tile", [None, (64, 64, 32), (128, 128, 64), (256, 128, 64), (128, 256, 64), (256, 256, 64)])
+def test_grid_of_a_product_is_the_ceil_of_its_sizes(tile):
+    """What a launch computes instead of building the arrangement: the arranged operands' outermost shape and number of k tiles,
+    for sizes around tile edges, the smallest, one-sided ones and an empty reduction, with and without a batch."""
+    def ceil(a, b):
+        return -(-a // b)
+    for M, N, K in [(1, 1, 1), (64, 128, 32), (65, 127, 33), (256, 1, 4096), (3001, 5003, 1999), (8192, 8, 64), (7, 1000, 0), (129, 257, 63)]:
+        for Bn in (None, 1, 3):
+            d = [(s if Bn is None else (Bn,) + s, None) for s in ((M, K), (K, N), (M, N))]
+            grid, kt = (nt.arrange_gemm if Bn is None else nt.arrange_bmm)(*d, tile=tile)
+            if tile is None:                                     # the library's own tile: one of the built ones
+                assert any(grid == (Bn or 1, ceil(M, bm), ceil(N, bn)) and kt == ceil(K, bk)
+                           for bm, bn, bk in [(64, 64, 32), (128, 128, 64), (256, 128, 64), (128, 256, 64), (256, 256, 64)])
+            else:
+                assert grid == (Bn or 1, ceil(M, tile[0]), ceil(N, tile[1])) and kt == ceil(K, tile[2])
+
+
 # ----------------------------------------------------------------- program order swizzle
 @pytest.mark.parametrize("batch,mt,nt_", [(1, 4, 4), (1, 16, 16), (1, 12, 20), (32, 8, 8), (1, 32, 32), (1, 392, 2),
                                           (1, 1, 1), (1, 7, 3), (2, 9, 1), (1, 47, 79), (19, 5, 3), (8, 1, 1)])
