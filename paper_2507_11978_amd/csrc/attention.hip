@@ -22,11 +22,14 @@
 // same order: V_j sits in LDS as [key][d] and the transposing LDS read (ds_read_b64_tr_b16)
 // delivers, for a lane's d, four consecutive keys at any position.  O^T again has the query on
 // the lane axis, so rescaling by 2^(M - M') is a per-lane scalar.  Q fragments stay in registers.
-// K_j and V_j go global -> registers -> LDS (double buffered), the next block's loads in flight
-// during the current block's arithmetic; 32 KB of LDS and ~160 registers per workgroup let
-// several workgroups share a compute unit, which hides the exponentials of one behind the MFMAs
-// of another.
-#include "gemm_fast.h"
+// K_j and V_j travel straight into LDS (range-checked loads; through registers where strides do not allow it), K two blocks
+// ahead and V one: rings of three and two blocks, 40 KB, and 117 registers let four workgroups share a compute unit, which
+// overlaps the exponentials of one with the MFMAs of another.  (Through registers, one block ahead, two blocks of each, three
+// workgroups: 69.8 us against 63.8 at 4 x 48 heads x 1024 fp16, 90.5 / 81.2 at 4 x 16 x 2048; the next half block's scores
+// computed between this one's exponentials measured no gain.)  What bounds it: the matrix and vector work of co-resident
+// wavefronts overlap only in part -- a loop of just this mix, 16 MFMAs and 96 vector instructions per 64 keys, takes 442 ns
+// per wavefront and SIMD against 252 for the MFMAs alone on constant data -- and the clock falls by a third on real data.
+#include "gemm_direct.h"
 #include <type_traits>
 
 namespace nt {
@@ -67,11 +70,11 @@ __device__ __forceinline__ float add_pair(uint32_t w, float acc)
     else return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w), __builtin_bit_cast(half2v, 0x3c003c00u), acc, false);
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
+template <bool BF16, bool DMA>
+__global__ __launch_bounds__(256, 4) void sdpa_kernel(const SdpaArgs g)
 {
     constexpr uint32_t BLK = kKeyBlock * kHeadDim * 2;                 // bytes of one K or V block in LDS (8 KB)
-    __shared__ __attribute__((aligned(16))) char smem[4 * BLK];        // [K0][K1][V0][V1]
+    __shared__ __attribute__((aligned(16))) char smem[5 * BLK];        // rings of three K and two V blocks: [K0][K1][K2][V0][V1]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
     // Workgroup -> (batch * head, query block).  Consecutive workgroup indices go to different XCDs (index mod 8),
@@ -97,30 +100,40 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) __builtin_memcpy(&qf[ks], Qp + (int64_t)qrow_c * g.q_ss + 16 * ks + 8 * hi, 16);
 
-    // ---- staging of a K / V block: 512 16-byte chunks each, two per thread; rows past Sk read as zero
-    u32x4 kst[2], vst[2];
-    auto fetch = [&](int key0) {
+    // ---- a K or V block into an LDS slot: 64 rows of 128 bytes, two 1 KB loads per wavefront.  Lane l's 16 bytes land at
+    // l * 16, so the swizzle is applied to the chunk it fetches.  Rows past Sk read as zero (the range check).
+    const int nblk = (g.Sk + kKeyBlock - 1) / kKeyBlock;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    const int swave = __builtin_amdgcn_readfirstlane(wave);
+    int ld_row[2], k_ch[2], v_ch[2];                                   // this lane's row and 16-byte chunk of K and of V
+    uint32_t k_off[2], v_off[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = tid + 256 * u, row = c >> 3, ch = c & 7;
-            const int key = key0 + row;
-            u32x4 kk{0, 0, 0, 0}, vv{0, 0, 0, 0};
-            if (key < g.Sk) {
-                __builtin_memcpy(&kk, Kp + (int64_t)key * g.k_ss + ch * 8, 16);
-                __builtin_memcpy(&vv, Vp + (int64_t)key * g.v_ss + ch * 8, 16);
+    for (int u = 0; u < 2; ++u) {
+        ld_row[u] = (wave * 2 + u) * 8 + (lane >> 3);
+        k_ch[u] = (lane & 7) ^ ((ld_row[u] ^ (ld_row[u] >> 3)) & 7);
+        v_ch[u] = (lane & 7) ^ (((ld_row[u] >> 1) & 1) << 2);
+        k_off[u] = ((uint32_t)ld_row[u] * (uint32_t)g.k_ss + (uint32_t)(k_ch[u] * 8)) * 2u;
+        v_off[u] = ((uint32_t)ld_row[u] * (uint32_t)g.v_ss + (uint32_t)(v_ch[u] * 8)) * 2u;
+    }
+    const u32x4 k_rsrc = make_rsrc(Kp, ((int64_t)(g.Sk - 1) * g.k_ss + kHeadDim) * 2), v_rsrc = make_rsrc(Vp, ((int64_t)(g.Sk - 1) * g.v_ss + kHeadDim) * 2);
+    auto request = [&](int kb, uint32_t slot, const uint16_t *p, int64_t ss, const int (&ch)[2], u32x4 rsrc, const uint32_t (&off)[2]) {
+        if constexpr (DMA) {
+            // (blocks past the last: an offset beyond the range, no traffic; the count of outstanding loads stays the same)
+            const uint32_t at = kb < nblk ? (uint32_t)kb * (uint32_t)(kKeyBlock * 2) * (uint32_t)ss : 0x80000000u;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) dma16_buf(rsrc, off[u], at, lds0 + slot + (uint32_t)((swave * 2 + u) * 1024));
+        } else if (kb < nblk) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int key = kb * kKeyBlock + ld_row[u];
+                u32x4 v{0, 0, 0, 0};
+                if (key < g.Sk) __builtin_memcpy(&v, p + (int64_t)key * ss + ch[u] * 8, 16);
+                lds_write16(smem, slot + (uint32_t)((wave * 2 + u) * 1024 + lane * 16), v);
             }
-            kst[u] = kk;
-            vst[u] = vv;
         }
     };
-    auto stash = [&](uint32_t buf) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = tid + 256 * u, row = c >> 3, ch = c & 7;
-            lds_write16(smem, buf * BLK + (uint32_t)(row * 128 + ((ch ^ ((row ^ (row >> 3)) & 7)) << 4)), kst[u]);
-            lds_write16(smem, (2 + buf) * BLK + (uint32_t)(row * 128 + ((ch ^ (((row >> 1) & 1) << 2)) << 4)), vst[u]);
-        }
-    };
+    auto request_k = [&](int kb, uint32_t slot) { request(kb, slot, Kp, g.k_ss, k_ch, k_rsrc, k_off); };
+    auto request_v = [&](int kb, uint32_t slot) { request(kb, 3 * BLK + slot, Vp, g.v_ss, v_ch, v_rsrc, v_off); };
 
     // ---- per-lane LDS read addresses
     // K fragment (A operand, row = key l32 of a 32-key half, chunk 2 ks + hi, swizzled like the write)
@@ -148,15 +161,11 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
     float m_ref = 0.f, l_run = 0.f;                                    // row reference M (base-2 units of the scaled scores), row sum
     bool first = true;
 
-    const int nblk = (g.Sk + kKeyBlock - 1) / kKeyBlock;
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    // one key block; the LDS buffer index is a compile-time constant so that every LDS address is base + immediate
-    auto block = [&](auto cur_c, const int kb) {
-        constexpr uint32_t cur = (uint32_t)decltype(cur_c)::value;
-        if (kb + 1 < nblk) fetch((kb + 1) * kKeyBlock);                // in flight during this block's arithmetic
-
+    request_k(0, 0);
+    request_v(0, 0);
+    request_k(1, BLK);
+    // one key block: K in the slot at LDS offset `slot`, V in the slot at `vslot` behind the K ring
+    auto block = [&](const uint32_t slot, const uint32_t vslot, const int kb) {
         // ---- S^T = K Q^T: st[jb][v] <-> key jb * 32 + 8 (v / 4) + 4 hi + v % 4, query l32
         float16v st[2];
 #pragma unroll
@@ -165,7 +174,7 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
             for (int v = 0; v < 16; ++v) st[jb][v] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const u32x4 kf = lds_read16(smem, k_rd[jb ? (ks ^ 2) : ks] + (cur * BLK + (uint32_t)(jb * 4096)));
+                const u32x4 kf = lds_read16(smem, k_rd[jb ? (ks ^ 2) : ks] + slot + (uint32_t)(jb * 4096));
                 st[jb] = mfma32<BF16>(kf, qf[ks], st[jb]);
             }
         }
@@ -231,7 +240,7 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
                     u32x2 part[2];
 #pragma unroll
                     for (int pt = 0; pt < 2; ++pt) {
-                        const uint32_t addr = v_rd[db] + ((2 + cur) * BLK + (uint32_t)((jb * 32 + 16 * s2 + 8 * pt) * 128));
+                        const uint32_t addr = v_rd[db] + vslot + (3 * BLK + (uint32_t)((jb * 32 + 16 * s2 + 8 * pt) * 128));
                         typedef short4v_a __attribute__((address_space(3))) * lds_s4;
                         const short4v_a t = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(smem + addr));
                         part[pt] = __builtin_bit_cast(u32x2, t);
@@ -239,14 +248,22 @@ __global__ __launch_bounds__(256, 2) void sdpa_kernel(const SdpaArgs g)
                     const u32x2 p0 = part[0], p1 = part[1];
                     ot[db] = mfma32<BF16>(u32x4{p0[0], p0[1], p1[0], p1[1]}, pk[jb][s2], ot[db]);
                 }
-        // ---- next block into the other LDS buffer
-        if (kb + 1 < nblk) stash(cur ^ 1u);
-        __syncthreads();
     };
-    for (int kb = 0; kb < nblk; kb += 2) {
-        block(std::integral_constant<int, 0>{}, kb);
-        if (kb + 1 < nblk) block(std::integral_constant<int, 1>{}, kb + 1);
+    // At the top of block kb this wavefront's part of K and V has landed (the two loads of K's next block may be in flight); the
+    // barrier says that all parts have, and that everybody is done with block kb - 1: its V slot takes V's next block, its K slot
+    // K's next but one.
+    uint32_t slot = 0, ahead = 2 * BLK, vslot = 0;
+    for (int kb = 0; kb < nblk; ++kb) {
+        if constexpr (DMA) NT_WAIT_VMCNT(2);
+        __syncthreads();
+        request_v(kb + 1, vslot ^ BLK);
+        request_k(kb + 2, ahead);
+        block(slot, vslot, kb);
+        ahead = slot;
+        vslot ^= BLK;
+        slot = slot == 2 * BLK ? 0 : slot + BLK;
     }
+    if constexpr (DMA) NT_WAIT_VMCNT(0);                                  // (no load of this workgroup may land in its LDS after it has ended)
 
     // ---- O = O^T / l, stored along d: after the half-wavefronts trade register groups a lane owns
     // d = 32 db + 16 hi .. + 15 of its query row
@@ -459,8 +476,15 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
     k.BH = (int32_t)bh;
     k.nqb = (int32_t)nqb;
     dim3 grid((unsigned)(bh * nqb)), block(256);
-    if (bf16) hipLaunchKernelGGL((sdpa_kernel<true>), grid, block, 0, (hipStream_t)stream, k);
-    else hipLaunchKernelGGL((sdpa_kernel<false>), grid, block, 0, (hipStream_t)stream, k);
+    // (rows that do not overlap, and offsets that fit the range-checked loads: else through registers)
+    auto streams = [&](int64_t ss) { return ss >= kHeadDim && ((int64_t)a.Sk + 2 * kKeyBlock) * ss * 2 < (1LL << 31); };
+    if (streams(a.k_ss) && streams(a.v_ss)) {
+        if (bf16) hipLaunchKernelGGL((sdpa_kernel<true, true>), grid, block, 0, (hipStream_t)stream, k);
+        else hipLaunchKernelGGL((sdpa_kernel<false, true>), grid, block, 0, (hipStream_t)stream, k);
+    } else {
+        if (bf16) hipLaunchKernelGGL((sdpa_kernel<true, false>), grid, block, 0, (hipStream_t)stream, k);
+        else hipLaunchKernelGGL((sdpa_kernel<false, false>), grid, block, 0, (hipStream_t)stream, k);
+    }
     return check_launch("sdpa_kernel");
 }
 

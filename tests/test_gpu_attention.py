@@ -122,3 +122,36 @@ def test_few_queries(dt, B, H, Sq, Sk):
     torch.cuda.synchronize()
     assert_gates(to_f64(obuf[..., 1:65]), ref, dt, f"sdpa strided {dt} {B}x{H}x{Sq}x{Sk}")
     assert (obuf[..., 0] == -7.0).all() and (obuf[..., 65] == -7.0).all()
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("Sk", [1, 63, 64, 65, 128, 129, 192, 321])
+def test_key_blocks_of_every_kind_of_rows(dt, Sk):
+    """One to six key blocks (the rings hold three and two), a last block of one key, of all but one; rows that the range-checked
+    loads take -- dense, pitched, of odd pitch with NaN between and behind them -- and rows they do not (a key repeated for
+    every position): the same result."""
+    B, H, Sq = 1, 3, 130
+    q, k, v = (si.normal_bits((B, H, n, 64), dt, 90 + i, 1.5) for i, n in enumerate([Sq, Sk, Sk]))
+    ref = oat.sdpa(q, k, v, dt)
+    gq, gk, gv = (to_gpu(t, dt) for t in (q, k, v))
+    out = torch.full((B, H, Sq, 64), float("nan"), dtype=TORCH_DT[dt], device="cuda")
+    nt.sdpa(gq, gk, gv, out)
+    torch.cuda.synchronize()
+    assert_gates(to_f64(out), ref, dt, f"sdpa {dt} {Sk} keys")
+    for pitch, at in ((72, 8), (67, 1)):
+        views = []
+        for t in (gk, gv):
+            buf = torch.full((B, H, Sk + 70, pitch), float("nan"), dtype=TORCH_DT[dt], device="cuda")
+            buf[:, :, :Sk, at:at + 64] = t
+            views.append(buf[:, :, :Sk, at:at + 64])
+        o2 = torch.full_like(out, float("nan"))
+        nt.sdpa(gq, views[0], views[1], o2)
+        torch.cuda.synchronize()
+        assert torch.equal(o2, out), pitch
+    one_k, one_v = gk[:, :, :1].expand(B, H, Sk, 64), gv[:, :, :1].expand(B, H, Sk, 64)      # stride 0 along the keys
+    o3 = torch.full_like(out, float("nan"))
+    nt.sdpa(gq, one_k, one_v, o3)
+    o4 = torch.full_like(out, float("nan"))
+    nt.sdpa(gq, one_k.contiguous(), one_v.contiguous(), o4)
+    torch.cuda.synchronize()
+    assert torch.equal(o3, o4)
