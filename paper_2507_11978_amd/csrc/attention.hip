@@ -47,6 +47,7 @@ struct SdpaArgs {
 };
 
 constexpr int kHeadDim = 64, kQBlock = 128, kKeyBlock = 64;
+constexpr uint32_t kSdpaLds = 5 * kKeyBlock * kHeadDim * 2;        // LDS of one group of wavefronts: 40 KB
 
 typedef short short4v_a __attribute__((ext_vector_type(4)));
 
@@ -70,12 +71,15 @@ __device__ __forceinline__ float add_pair(uint32_t w, float acc)
     else return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w), __builtin_bit_cast(half2v, 0x3c003c00u), acc, false);
 }
 
-template <bool BF16, bool DMA>
-__global__ __launch_bounds__(256, 4) void sdpa_kernel(const SdpaArgs g)
+// SPLIT: the key blocks are dealt out to SPLIT groups of four wavefronts (group i: blocks i, i + SPLIT, ...), each with rings, a
+// row reference, sums and an accumulator of its own; group 0 merges them at the end.
+template <bool BF16, bool DMA, int SPLIT>
+__global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
 {
     constexpr uint32_t BLK = kKeyBlock * kHeadDim * 2;                 // bytes of one K or V block in LDS (8 KB)
-    __shared__ __attribute__((aligned(16))) char smem[5 * BLK];        // rings of three K and two V blocks: [K0][K1][K2][V0][V1]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    extern __shared__ __attribute__((aligned(1024))) char all_smem[];  // per group, rings of three K and two V blocks: [K0][K1][K2][V0][V1]
+    const int lane = threadIdx.x & 63, group = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), tid = threadIdx.x & 255, wave = tid >> 6;
+    char *smem = all_smem + group * (kSdpaLds);
     const int l32 = lane & 31, hi = lane >> 5;
     // Workgroup -> (batch * head, query block).  Consecutive workgroup indices go to different XCDs (index mod 8),
     // each with an L2 of its own; the query blocks of one head all read that head's K and V, so every group of
@@ -161,9 +165,9 @@ __global__ __launch_bounds__(256, 4) void sdpa_kernel(const SdpaArgs g)
     float m_ref = 0.f, l_run = 0.f;                                    // row reference M (base-2 units of the scaled scores), row sum
     bool first = true;
 
-    request_k(0, 0);
-    request_v(0, 0);
-    request_k(1, BLK);
+    request_k(group, 0);
+    request_v(group, 0);
+    request_k(group + SPLIT, BLK);
     // one key block: K in the slot at LDS offset `slot`, V in the slot at `vslot` behind the K ring
     auto block = [&](const uint32_t slot, const uint32_t vslot, const int kb) {
         // ---- S^T = K Q^T: st[jb][v] <-> key jb * 32 + 8 (v / 4) + 4 hi + v % 4, query l32
@@ -253,17 +257,47 @@ __global__ __launch_bounds__(256, 4) void sdpa_kernel(const SdpaArgs g)
     // barrier says that all parts have, and that everybody is done with block kb - 1: its V slot takes V's next block, its K slot
     // K's next but one.
     uint32_t slot = 0, ahead = 2 * BLK, vslot = 0;
-    for (int kb = 0; kb < nblk; ++kb) {
+    for (int kb = group; kb - group < nblk; kb += SPLIT) {               // (the same number of passes, and barriers, in every group)
         if constexpr (DMA) NT_WAIT_VMCNT(2);
         __syncthreads();
-        request_v(kb + 1, vslot ^ BLK);
-        request_k(kb + 2, ahead);
-        block(slot, vslot, kb);
+        request_v(kb + SPLIT, vslot ^ BLK);
+        request_k(kb + 2 * SPLIT, ahead);
+        if (SPLIT == 1 || kb < nblk) block(slot, vslot, kb);
         ahead = slot;
         vslot ^= BLK;
         slot = slot == 2 * BLK ? 0 : slot + BLK;
     }
     if constexpr (DMA) NT_WAIT_VMCNT(0);                                  // (no load of this workgroup may land in its LDS after it has ended)
+
+    if constexpr (SPLIT > 1) {
+        // the other groups' (reference, sum, accumulator) through LDS, 34 floats per lane, lane by lane the same (query, d)
+        __syncthreads();                                                  // (everybody's loads have landed, everybody's reads are done)
+        float *ex = reinterpret_cast<float *>(all_smem);
+        if (group > 0) {
+            float *e = ex + (group - 1) * (34 * 256) + tid;
+            e[0] = first ? -INFINITY : m_ref;                             // (a group that had no block: weight 0)
+            e[256] = l_run;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) e[(2 + i) * 256] = ot[i >> 4][i & 15];
+        }
+        __syncthreads();
+        if (group > 0) return;
+        float top = m_ref;
+#pragma unroll
+        for (int i = 0; i < SPLIT - 1; ++i) top = fmaxf(top, ex[i * (34 * 256) + tid]);
+        const float own = __builtin_amdgcn_exp2f(m_ref - top);
+        l_run *= own;
+#pragma unroll
+        for (int v = 0; v < 32; ++v) ot[v >> 4][v & 15] *= own;
+#pragma unroll
+        for (int i = 0; i < SPLIT - 1; ++i) {
+            const float *e = ex + i * (34 * 256) + tid;
+            const float c = __builtin_amdgcn_exp2f(e[0] - top);
+            l_run = __builtin_fmaf(e[256], c, l_run);
+#pragma unroll
+            for (int v = 0; v < 32; ++v) ot[v >> 4][v & 15] = __builtin_fmaf(e[(2 + v) * 256], c, ot[v >> 4][v & 15]);
+        }
+    }
 
     // ---- O = O^T / l, stored along d: after the half-wavefronts trade register groups a lane owns
     // d = 32 db + 16 hi .. + 15 of its query row
@@ -444,6 +478,28 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void sdpa_decode_kernel(const Sd
     }
 }
 
+template <bool BF16, bool DMA, int SPLIT>
+static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream_t s)
+{
+    auto kern = sdpa_kernel<BF16, DMA, SPLIT>;
+    static DeviceOnce configured;
+    if (!configured.done()) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(SPLIT * kSdpaLds));
+        if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
+        configured.set();
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)programs), dim3(256 * SPLIT), SPLIT * kSdpaLds, s, k);
+    return check_launch("sdpa_kernel");
+}
+
+template <bool BF16, bool DMA>
+static nt_status launch_sdpa_split(const SdpaArgs &k, int64_t programs, int split, hipStream_t s)
+{
+    if (split == 4) return launch_sdpa_inst<BF16, DMA, 4>(k, programs, s);
+    if (split == 2) return launch_sdpa_inst<BF16, DMA, 2>(k, programs, s);
+    return launch_sdpa_inst<BF16, DMA, 1>(k, programs, s);
+}
+
 // One workgroup per query pays while they do not queue up for the units with the same keys (bf16, us, sdpa_kernel / this one):
 // 192 heads x 1 query x 2047 keys 33.9 / 19.1, x 2 34.5 / 29.2, x 4 35.4 / 39.3; 8 heads x 16 x 2047 30.6 / 11.0, x 32 30.6 / 12.0.
 static bool few_queries(int64_t heads, int64_t queries)
@@ -475,17 +531,18 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
     SdpaArgs k = a;
     k.BH = (int32_t)bh;
     k.nqb = (int32_t)nqb;
-    dim3 grid((unsigned)(bh * nqb)), block(256);
     // (rows that do not overlap, and offsets that fit the range-checked loads: else through registers)
-    auto streams = [&](int64_t ss) { return ss >= kHeadDim && ((int64_t)a.Sk + 2 * kKeyBlock) * ss * 2 < (1LL << 31); };
-    if (streams(a.k_ss) && streams(a.v_ss)) {
-        if (bf16) hipLaunchKernelGGL((sdpa_kernel<true, true>), grid, block, 0, (hipStream_t)stream, k);
-        else hipLaunchKernelGGL((sdpa_kernel<false, true>), grid, block, 0, (hipStream_t)stream, k);
-    } else {
-        if (bf16) hipLaunchKernelGGL((sdpa_kernel<true, false>), grid, block, 0, (hipStream_t)stream, k);
-        else hipLaunchKernelGGL((sdpa_kernel<false, false>), grid, block, 0, (hipStream_t)stream, k);
-    }
-    return check_launch("sdpa_kernel");
+    const int nblk = (int)(((int64_t)a.Sk + kKeyBlock - 1) / kKeyBlock);
+    auto streams = [&](int64_t ss) { return ss >= kHeadDim && ((int64_t)a.Sk + 10 * kKeyBlock) * ss * 2 < (1LL << 31); };
+    const bool dma = streams(a.k_ss) && streams(a.v_ss);
+    // A unit holds four groups of four wavefronts: launches with fewer programs than that split the keys, where there are enough
+    // blocks to pay for the larger workgroup and the merge.  Measured (us, one group / split): 160 programs x 24 blocks 26.7 /
+    // 19.3, 90 x 32 34.1 / 23.1, 8 x 32 27.0 / 21.0, 144 x 13 15.8 / 14.0, 288 x 32 46.5 (as it was) / 36.3; 256 x 8 11.4 / 12.2.
+    const int64_t programs = bh * nqb;
+    const int split = nblk < 12 ? 1 : programs <= 256 ? 4 : programs <= 512 ? 2 : 1;
+    hipStream_t s = (hipStream_t)stream;
+    if (bf16) return dma ? launch_sdpa_split<true, true>(k, programs, split, s) : launch_sdpa_split<true, false>(k, programs, split, s);
+    return dma ? launch_sdpa_split<false, true>(k, programs, split, s) : launch_sdpa_split<false, false>(k, programs, split, s);
 }
 
 nt_status launch_sdpa_desc(const void *q, const nt_tensor_desc *dq, const void *k, const nt_tensor_desc *dk,

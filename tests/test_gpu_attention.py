@@ -125,9 +125,9 @@ def test_few_queries(dt, B, H, Sq, Sk):
 
 
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
-@pytest.mark.parametrize("Sk", [1, 63, 64, 65, 128, 129, 192, 321])
+@pytest.mark.parametrize("Sk", [1, 63, 64, 65, 128, 129, 192, 321, 705, 768, 833, 1025])
 def test_key_blocks_of_every_kind_of_rows(dt, Sk):
-    """One to six key blocks (the rings hold three and two), a last block of one key, of all but one; rows that the range-checked
+    """One to seventeen key blocks (the rings hold three and two, twelve and more are dealt out to four groups of wavefronts), a last block of one key, of all but one; rows that the range-checked
     loads take -- dense, pitched, of odd pitch with NaN between and behind them -- and rows they do not (a key repeated for
     every position): the same result."""
     B, H, Sq = 1, 3, 130
