@@ -4,18 +4,27 @@
 namespace nt {
 
 // filter [F][C][R * S] (row pitch ldb) -> [F][R * S][C] (row pitch K = C R S): one workgroup per filter, the row read and
-// written with consecutive lanes on consecutive elements, permuted on its way through LDS
+// written 16 bytes per thread (C is a multiple of 32: eight k' belong to one tap), permuted on its way through LDS
+// (256 filters of 2304: 4.4 us, 4.8 with two bytes per thread: the launch and two trips to memory)
 __global__ __launch_bounds__(256) void conv_repack_filter_kernel(const uint16_t *w, int64_t ldb, uint16_t *out, int32_t C, int32_t RS)
 {
-    extern __shared__ uint16_t row[];
+    extern __shared__ __attribute__((aligned(16))) uint16_t row[];
     const int32_t K = C * RS;
     const uint16_t *src = w + (int64_t)blockIdx.x * ldb;
     uint16_t *dst = out + (int64_t)blockIdx.x * K;
-    for (int32_t i = threadIdx.x; i < K; i += 256) row[i] = src[i];
+    for (int32_t i = threadIdx.x * 8; i < K; i += 2048) {
+        u32x4 v;
+        __builtin_memcpy(&v, src + i, 16);
+        *reinterpret_cast<u32x4 *>(row + i) = v;
+    }
     __syncthreads();
-    for (int32_t j = threadIdx.x; j < K; j += 256) {
+    for (int32_t j = threadIdx.x * 8; j < K; j += 2048) {
         const int32_t tap = j / C, c = j - tap * C;
-        dst[j] = row[c * RS + tap];
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = row[(c + i) * RS + tap];
+        const u32x4 v{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+        *reinterpret_cast<u32x4 *>(dst + j) = v;
     }
 }
 

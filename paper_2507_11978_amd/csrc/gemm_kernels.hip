@@ -638,6 +638,38 @@ static bool conv_is_bare(const GemmLaunch &g)        // a convolution and nothin
     return g.conv.valid && !g.user_tile && !g.no_workspace && !g.ws_given && g.batch == 1 && !g.has_d && g.alpha == 1.f && g.act == 0;
 }
 
+// a dense row-major matrix as an operand map
+static OperandMap matrix_map(int64_t rows, int64_t cols, int64_t row_pitch)
+{
+    OperandMap m{};
+    m.rows = rows; m.cols = cols; m.base = 0; m.nrd = 1; m.ncd = 1; m.nchk = 0;
+    m.rrad[0] = rows; m.crad[0] = cols; m.roff[0] = row_pitch; m.coff[0] = 1;
+    return m;
+}
+
+// Y[n] (filters x positions) = W (filters x K) . U[n] (K x positions, row pitch `pitch`, image n at U + n * image) on the matrix kernels
+static GemmLaunch per_image_product(const GemmLaunch &g, const void *U, int64_t K, int64_t pitch, int64_t image)
+{
+    const ConvHint &h = g.conv;
+    const int64_t PQ = h.P * h.Q;
+    GemmLaunch u{};
+    u.A = g.B; u.B = U; u.C = g.C;
+    u.ma = matrix_map(h.K, K, h.ws[0]);
+    u.mb = matrix_map(K, PQ, pitch);
+    u.mc = matrix_map(h.K, PQ, h.ys[1]);
+    u.batch = h.N; u.sa_batch = 0; u.sb_batch = image; u.sc_batch = h.ys[0];
+    u.M = h.K; u.N = PQ; u.K = K;
+    u.tile = pick_gemm_tile(u.batch, u.M, u.N, u.K, true);
+    u.mt = (u.M + u.tile.bm - 1) / u.tile.bm; u.nt = (u.N + u.tile.bn - 1) / u.tile.bn; u.kt = (u.K + u.tile.bk - 1) / u.tile.bk;
+    u.in_dtype = g.in_dtype; u.out_dtype = g.out_dtype; u.stream = g.stream;
+    u.alpha = 1.f; u.beta = 0.f; u.act = 0; u.has_d = false;
+    u.no_workspace = true;                               // (the caller of this holds it, or needs none)
+    return u;
+}
+
+static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *blay_out);
+static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int blay, int *path_out);
+
 // Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
 // estimate of its product.  A unit runs two programs at a time; a program costs a fixed part and its slices, a split the
 // kernel that adds the parts and their trip through memory.  (Fits, us: 392 programs of 128 x 128 with 36 slices 27.5, 196
@@ -686,6 +718,20 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
         int32_t kt_per = 0;
         parts = conv_ksplit(M8, F, (K + 63) / 64, g.tile.bn, &kt_per);
         per = 2 * (int64_t)kt_per;
+        // One tap, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, small tiles:
+        // (2,192,28,28)*(200,192,1,1) 14.2 -> 9.7 us a call, (7,352,7,7)*(384,352,1,1) 19.5 -> 10.0.  (With a split route 1 keeps it:
+        // a copy buys nothing there.)
+        if (RS == 1 && parts > 1) return NT_OK;
+        if (RS == 1 && h.ph == 0 && h.pw == 0 && natural && h.xs[3] == 1 && h.xs[2] == h.W && h.xs[0] >= 0 && PQ >= 8) {
+            const GemmLaunch u = per_image_product(g, g.A, h.C, h.xs[1], h.xs[0]);
+            FastArgs fa{};
+            int alay, blay;
+            if (lower_plain(u, &fa, &alay, &blay)) {
+                *taken = true;
+                if (path_out) *path_out = F > 128 ? PATH_CONV_TAP : PATH_CONV_DIRECT;
+                return route_matrix(u, fa, alay, blay, nullptr);
+            }
+        }
         // (without a split route 1 needs no workspace: a captured call stays independent of it, as its replays take no lease)
         if (parts == 1 && capturing((hipStream_t)g.stream)) return NT_OK;
         if (((F + 127) / 128) * ((M + 127) / 128) * parts < 192) tile = 64;
@@ -804,24 +850,7 @@ static nt_status route_conv_unfold(const GemmLaunch &g, int *path_out, bool *tak
     const int64_t blocks = std::min<int64_t>((Mp / 8 + 255) / 256, 1 << 16);
     hipLaunchKernelGGL(conv_unfold_kernel, dim3((unsigned)blocks, (unsigned)K), dim3(256), 0, s, ua);
     { const nt_status lst = check_launch("conv_unfold_kernel"); if (lst != NT_OK) return lst; }
-    auto matrix = [](int64_t rows, int64_t cols, int64_t row_pitch) {
-        OperandMap m{};
-        m.rows = rows; m.cols = cols; m.base = 0; m.nrd = 1; m.ncd = 1; m.nchk = 0;
-        m.rrad[0] = rows; m.crad[0] = cols; m.roff[0] = row_pitch; m.coff[0] = 1;
-        return m;
-    };
-    GemmLaunch u{};
-    u.A = g.B; u.B = U; u.C = g.C;
-    u.ma = matrix(h.K, K, h.ws[0]);                      // filters x CRS
-    u.mb = matrix(K, PQ, Mp);                            // CRS x the image's positions
-    u.mc = matrix(h.K, PQ, h.ys[1]);                     // filters x positions
-    u.batch = h.N; u.sa_batch = 0; u.sb_batch = PQ; u.sc_batch = h.ys[0];
-    u.M = h.K; u.N = PQ; u.K = K;
-    u.tile = pick_gemm_tile(u.batch, u.M, u.N, u.K, true);
-    u.mt = (u.M + u.tile.bm - 1) / u.tile.bm; u.nt = (u.N + u.tile.bn - 1) / u.tile.bn; u.kt = (u.K + u.tile.bk - 1) / u.tile.bk;
-    u.in_dtype = g.in_dtype; u.out_dtype = g.out_dtype; u.stream = g.stream;
-    u.alpha = 1.f; u.beta = 0.f; u.act = 0; u.has_d = false;
-    u.no_workspace = true;                               // (this route holds the workspace)
+    const GemmLaunch u = per_image_product(g, U, K, Mp, PQ);      // (this route holds the workspace)
     const nt_status st = launch_gemm(u, nullptr);
     if (path_out) *path_out = PATH_CONV_UNFOLD;
     return st;
