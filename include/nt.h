@@ -178,11 +178,12 @@ int32_t nt_tile_supported(nt_tile_cfg cfg);
  * Any strides are accepted; unit-stride operands with 16-byte aligned rows take the
  * fastest path.  M or N of 0: nothing is launched.  K of 0: C is zero-filled.
  * C must not alias A or B.
- * Memory (nt_gemm, nt_addmm, nt_addmm_act): a product with few output tiles and a long reduction (a skinny
- * product such as 16 x 4096 x 4096) has K dealt to several programs per tile; their fp32 partial tiles go
+ * Memory (nt_gemm, nt_addmm, nt_addmm_act): a product with few output tiles and a long reduction (256 x 256 x
+ * 8192, say) has K dealt to several programs per tile; their fp32 partial tiles go
  * through the library's workspace, the same one, under the same rules, as described at nt_conv2d_implicit
  * (one allocation of 256 MB per GPU, made by the first call that needs it, handed from call to call in stream
- * order; partial tiles added in a fixed order).
+ * order; partial tiles added in a fixed order).  At most 16 rows (32 on 16-byte aligned rows) of operands with unit
+ * stride along k need none of it: their reduction is split inside a program.
  */
 nt_status nt_gemm(const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                   void *C, const nt_tensor_desc *dC, nt_dtype in_dtype, nt_dtype out_dtype,
@@ -317,8 +318,8 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * named by the caller, every tile is gathered through the index map.
  * Memory: a dense unit-stride call with few output tiles and a long reduction has its reduction dealt to
  * several programs per tile, whose fp32 partial tiles go through a workspace that the library owns: one device
- * allocation of 256 MB per GPU, made by the first call on that GPU that needs it (that one call allocates, and
- * cannot be captured in a HIP graph), never moved or freed until the process ends.  All calls on a GPU share it,
+ * allocation of 256 MB per GPU, made by the first call on that GPU that needs it (captured in a HIP graph before any
+ * such call, it runs without), never moved or freed until the process ends.  All calls on a GPU share it,
  * one after the other: a call that finds it last used on another stream makes its own stream wait for that use
  * to finish (an event), so overlapping calls queue up for the workspace instead of racing.  What does not fit
  * the workspace, or a failed allocation, runs without it (no split, or through the index map).  The partial tiles

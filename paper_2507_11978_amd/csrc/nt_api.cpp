@@ -39,10 +39,10 @@ struct ViewPrograms { const nt_meta_op *ops[3]; int32_t n[3]; };
 nt_tile_cfg pick_tile(int kind, int64_t batch, int64_t M, int64_t N, int64_t K, nt_tile_cfg cfg, bool unit_stride = false, bool narrow = false)
 {
     if (cfg.bm || cfg.bn || cfg.bk) return cfg;
-    // The 64 x 64 tile of the operand-map kernel is for small strided convolutions and small caller-arranged views.
-    // Plain products, however small or skinny, run better as overhanging 128-wide tiles of the MFMA kernels (measured:
-    // 64 x 64 x 64 in 10.7 us against 18.3, 16 x 4096 x 256 in 11 us against 34, 64 x 64 x 4096 in 13.5 us against 552),
-    // and unit-stride convolutions on the convolution kernels' 256-position tile although most of it may stay empty
+    // The 64 x 64 tile on the operand-map kernel is for small strided convolutions and small caller-arranged views.
+    // Plain products, however small or skinny, run better on the MFMA kernels, with overhanging tiles (measured:
+    // 64 x 64 x 64 in 3.1 us on the device against 18.3, 64 x 64 x 4096 in 7.3 us against 552),
+    // and unit-stride convolutions on theirs although most of a tile may stay empty
     // ((32,64,56,56) * (64,64,3,3): 35 us against 242; (1,64,8,8) * (64,64,3,3): 19 us against 104).
     const bool tiny = (M <= 64 || N <= 64) && ((kind == KIND_CONV && !unit_stride) || kind == KIND_VIEWS);
     if (tiny) return nt_tile_cfg{64, 64, 32};
