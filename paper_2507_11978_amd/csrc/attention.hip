@@ -10,7 +10,7 @@
 // every term carries the same factor 2^-M, which cancels in O / l.  M is raised (and O, l scaled
 // by 2^(M - M')) when a block holds a score more than 15 above it, which the row sum of that block
 // reveals (2^15 is half the largest fp16 number), and it is set to the block's maximum at the first
-// block.  FlashAttention-2 raises M to the exact maximum at every block; keeping a lagging one
+// block that holds a score above -inf.  FlashAttention-2 raises M to the exact maximum at every block; keeping a lagging one
 // removes the maximum search from all but a few blocks.
 //
 // Mapping onto the matrix cores: everything is computed transposed.  A wavefront owns 32 query
@@ -162,8 +162,10 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
     for (int db = 0; db < 2; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) ot[db][v] = 0.f;
-    float m_ref = 0.f, l_run = 0.f;                                    // row reference M (base-2 units of the scaled scores), row sum
-    bool first = true;
+    // Row reference M (base-2 units of the scaled scores; -inf: no score above -inf yet) and row sum.  While a row has no reference,
+    // its blocks are weighed against 0, which gives the weight 0 that scores of -inf have (against -inf it would be -inf + inf).
+    float m_ref = -INFINITY, l_run = 0.f;
+    bool pending = true;                                               // wavefront-uniform: some row has no reference
 
     request_k(group, 0);
     request_v(group, 0);
@@ -211,27 +213,28 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
                     }
         };
         bool accept = false;
-        if (!first) {
+        if (!pending) {
             exponentials(m_ref);
             accept = __all(rs < 32768.f);                                // no weight beyond 2^15: the reference is close enough
         }
-        if (!accept) {                                                   // wavefront-uniform: first block, or a score far above M
+        if (!accept) {                                                   // wavefront-uniform: a row without reference, or a score far above M
             float mx = st[0][0] * g.scale_log2e;
 #pragma unroll
             for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) mx = fmaxf(mx, st[jb][v] * g.scale_log2e);
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));                      // block maximum of the scaled scores
-            const float m_new = first ? mx : fmaxf(m_ref, mx);           // M only rises after the first block
-            const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-            exponentials(m_new);
+            const float m_new = fmaxf(m_ref, mx);                        // M only rises
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m_ref - m_use);
+            exponentials(m_use);
             l_run *= alpha;
 #pragma unroll
             for (int db = 0; db < 2; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) ot[db][v] *= alpha;
             m_ref = m_new;
-            first = false;
+            pending = __any(m_new == -INFINITY);
         }
         l_run += rs;
         // ---- O^T += V^T P^T: k step (jb, s2) lists its 16 keys as jb*32 + 16 s2 + 8 part + 4 hi + 0..3
@@ -275,7 +278,7 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
         float *ex = reinterpret_cast<float *>(all_smem);
         if (group > 0) {
             float *e = ex + (group - 1) * (34 * 256) + tid;
-            e[0] = first ? -INFINITY : m_ref;                             // (a group that had no block: weight 0)
+            e[0] = m_ref;                                                 // (-inf, a group whose keys have no weight: 0 below)
             e[256] = l_run;
 #pragma unroll
             for (int i = 0; i < 32; ++i) e[(2 + i) * 256] = ot[i >> 4][i & 15];

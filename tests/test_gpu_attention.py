@@ -155,3 +155,53 @@ def test_key_blocks_of_every_kind_of_rows(dt, Sk):
     nt.sdpa(gq, one_k.contiguous(), one_v.contiguous(), o4)
     torch.cuda.synchronize()
     assert torch.equal(o3, o4)
+
+
+# how the keys are dealt out follows from the number of (head, query block) programs and of key blocks: one group of wavefronts
+# walks them, four groups share them, two groups do, a workgroup per query
+WALKS = [(2, 3, 130, 640), (1, 3, 130, 1024), (1, 150, 130, 832), (1, 3, 1, 1024)]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,Sq,Sk", WALKS)
+def test_scores_of_minus_infinity(dt, B, H, Sq, Sk):
+    """Keys masked by a score of -inf (an infinite key channel; a lowest value whose product overflows) have weight 0 wherever
+    they lie: whole key blocks of them first, last, all around, in some queries of a wavefront and not in others."""
+    q, k, v = (onum.decode(si.normal_bits((B, H, n, 64), dt, 110 + i, 1.0), dt).astype(np.float32) for i, n in enumerate([Sq, Sk, Sk]))
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    v = si.round_to_bits(v, dt)
+    low = -65504.0 if dt == "f16" else -3.3895314e38
+    for alive in (slice(0, 64), slice(Sk - 64, Sk), slice(Sk - 1, Sk), slice(300, 311), slice(64, 600)):
+        masked = np.ones(Sk, dtype=bool)
+        masked[alive] = False
+        for mask, channel in ((-np.inf, 1.0), (low, 4.0 if dt == "bf16" else 65504.0)):
+            qm, km = q.copy(), k.copy()
+            qm[..., 0] = channel
+            if mask == low:
+                qm[..., ::2, 0] = 0.0                                # every other query sees all keys
+            km[..., masked, 0] = mask
+            qb, kb = si.round_to_bits(qm, dt), si.round_to_bits(km, dt)
+            ref = oat.sdpa(qb, kb, v, dt)
+            assert_gates(run(qb, kb, v, dt), ref, dt, f"sdpa {dt} {B}x{H}x{Sq}x{Sk} alive {alive} mask {mask}")
+    k[..., 0] = -np.inf                                              # no key at all: 0 / 0, as in the definition
+    assert np.isnan(run(si.round_to_bits(q, dt), si.round_to_bits(k, dt), v, dt)).all()
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,Sq,Sk", [(1, 3, 130, 1393), (1, 150, 130, 833), (1, 257, 10, 770)])
+def test_keys_dealt_to_groups_with_references_far_apart(dt, B, H, Sq, Sk):
+    """Scores that rise (scale > 0) or fall (scale < 0) along the keys, slowly and by hundreds of powers of two from end to end:
+    the groups of wavefronts that share the keys end with references far apart, and a group's last block may be missing."""
+    rng = np.random.default_rng(120)
+    w = rng.standard_normal(64).astype(np.float32)
+    w /= np.linalg.norm(w)
+    q = rng.standard_normal((B, H, Sq, 64)).astype(np.float32)
+    q += (2.0 - q @ w)[..., None] * w                                # every query's component along w is 2
+    vb = si.normal_bits((B, H, Sk, 64), dt, 121, 1.0)
+    qb = si.round_to_bits(q, dt)
+    for per_block in (2.0, 30.0):                                    # rise per 64 keys, in base-2 units
+        step = per_block / 64.0 / (2.0 * 0.125 * 1.4427)
+        kf = (np.arange(Sk, dtype=np.float32)[:, None] * step) * w[None, :] + 0.05 * rng.standard_normal((Sk, 64)).astype(np.float32)
+        kb = si.round_to_bits(np.ascontiguousarray(np.broadcast_to(kf, (B, H, Sk, 64))), dt)
+        for scale in (0.125, -0.125):
+            assert_gates(run(qb, kb, vb, dt, scale=scale), oat.sdpa(qb, kb, vb, dt, scale=scale), dt, f"sdpa {dt} {H} heads {per_block} {scale}")
