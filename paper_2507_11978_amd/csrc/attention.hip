@@ -73,9 +73,13 @@ __device__ __forceinline__ float add_pair(uint32_t w, float acc)
 
 // SPLIT: the key blocks are dealt out to SPLIT groups of four wavefronts (group i: blocks i, i + SPLIT, ...), each with rings, a
 // row reference, sums and an accumulator of its own; group 0 merges them at the end.
+// AHEAD: rows that the range-checked loads do not take, one group: K and V through registers, one block ahead (loaded and
+// written to LDS at the top of a block instead, bf16, rows of pitch 63: 4 x 48 heads x 1024 78 us against 68, 8 x 64 heads,
+// 128 x 2048, 66 against 56; 2.1 M packed keys x 8 heads 32.0 ms in four groups, 29.1 so).
 template <bool BF16, bool DMA, int SPLIT>
-__global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
+__global__ __launch_bounds__(256 * SPLIT, DMA || SPLIT > 1 ? 4 : 2) void sdpa_kernel(const SdpaArgs g)
 {
+    constexpr bool AHEAD = !DMA && SPLIT == 1;
     constexpr uint32_t BLK = kKeyBlock * kHeadDim * 2;                 // bytes of one K or V block in LDS (8 KB)
     extern __shared__ __attribute__((aligned(1024))) char all_smem[];  // per group, rings of three K and two V blocks: [K0][K1][K2][V0][V1]
     const int lane = threadIdx.x & 63, group = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), tid = threadIdx.x & 255, wave = tid >> 6;
@@ -167,11 +171,13 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
     float m_ref = -INFINITY, l_run = 0.f;
     bool pending = true;                                               // wavefront-uniform: some row has no reference
 
-    request_k(group, 0);
-    request_v(group, 0);
-    request_k(group + SPLIT, BLK);
+    if constexpr (!AHEAD) {
+        request_k(group, 0);
+        request_v(group, 0);
+        request_k(group + SPLIT, BLK);
+    }
     // one key block: K in the slot at LDS offset `slot`, V in the slot at `vslot` behind the K ring
-    auto block = [&](const uint32_t slot, const uint32_t vslot, const int kb) {
+    auto block = [&](const uint32_t slot, const uint32_t vslot, const int kb) __attribute__((always_inline)) {
         // ---- S^T = K Q^T: st[jb][v] <-> key jb * 32 + 8 (v / 4) + 4 hi + v % 4, query l32
         float16v st[2];
 #pragma unroll
@@ -256,19 +262,56 @@ __global__ __launch_bounds__(256 * SPLIT, 4) void sdpa_kernel(const SdpaArgs g)
                     ot[db] = mfma32<BF16>(u32x4{p0[0], p0[1], p1[0], p1[1]}, pk[jb][s2], ot[db]);
                 }
     };
-    // At the top of block kb this wavefront's part of K and V has landed (the two loads of K's next block may be in flight); the
-    // barrier says that all parts have, and that everybody is done with block kb - 1: its V slot takes V's next block, its K slot
-    // K's next but one.
-    uint32_t slot = 0, ahead = 2 * BLK, vslot = 0;
-    for (int kb = group; kb - group < nblk; kb += SPLIT) {               // (the same number of passes, and barriers, in every group)
-        if constexpr (DMA) NT_WAIT_VMCNT(2);
+    if constexpr (AHEAD) {
+        // the next block's loads are in flight during this one's arithmetic and go to the other of two slots each behind it
+        u32x4 k_st[2], v_st[2];
+        auto fetch = [&](int kb) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int key = kb * kKeyBlock + ld_row[u];
+                k_st[u] = v_st[u] = u32x4{0, 0, 0, 0};
+                if (key < g.Sk) {
+                    __builtin_memcpy(&k_st[u], Kp + (int64_t)key * g.k_ss + k_ch[u] * 8, 16);
+                    __builtin_memcpy(&v_st[u], Vp + (int64_t)key * g.v_ss + v_ch[u] * 8, 16);
+                }
+            }
+        };
+        auto stash = [&](uint32_t at) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                lds_write16(smem, at + (uint32_t)((wave * 2 + u) * 1024 + lane * 16), k_st[u]);
+                lds_write16(smem, 3 * BLK + at + (uint32_t)((wave * 2 + u) * 1024 + lane * 16), v_st[u]);
+            }
+        };
+        auto step = [&](auto cur, int kb) {                               // (a compile-time slot: every LDS address is base + immediate)
+            constexpr uint32_t at = decltype(cur)::value;
+            if (kb + 1 < nblk) fetch(kb + 1);
+            block(at, at, kb);
+            if (kb + 1 < nblk) stash(at ^ BLK);
+            __syncthreads();
+        };
+        fetch(0);
+        stash(0);
         __syncthreads();
-        request_v(kb + SPLIT, vslot ^ BLK);
-        request_k(kb + 2 * SPLIT, ahead);
-        if (SPLIT == 1 || kb < nblk) block(slot, vslot, kb);
-        ahead = slot;
-        vslot ^= BLK;
-        slot = slot == 2 * BLK ? 0 : slot + BLK;
+        for (int kb = 0; kb < nblk; kb += 2) {
+            step(std::integral_constant<uint32_t, 0>{}, kb);
+            if (kb + 1 < nblk) step(std::integral_constant<uint32_t, BLK>{}, kb + 1);
+        }
+    } else {
+        // At the top of block kb this wavefront's part of K and V has landed (the two loads of K's next block may be in flight); the
+        // barrier says that all parts have, and that everybody is done with block kb - 1: its V slot takes V's next block, its K
+        // slot K's next but one.
+        uint32_t slot = 0, ahead = 2 * BLK, vslot = 0;
+        for (int kb = group; kb - group < nblk; kb += SPLIT) {               // (the same number of passes, and barriers, in every group)
+            if constexpr (DMA) NT_WAIT_VMCNT(2);
+            __syncthreads();
+            request_v(kb + SPLIT, vslot ^ BLK);
+            request_k(kb + 2 * SPLIT, ahead);
+            if (SPLIT == 1 || kb < nblk) block(slot, vslot, kb);
+            ahead = slot;
+            vslot ^= BLK;
+            slot = slot == 2 * BLK ? 0 : slot + BLK;
+        }
     }
     if constexpr (DMA) NT_WAIT_VMCNT(0);                                  // (no load of this workgroup may land in its LDS after it has ended)
 
@@ -499,7 +542,8 @@ template <bool BF16, bool DMA>
 static nt_status launch_sdpa_split(const SdpaArgs &k, int64_t programs, int split, hipStream_t s)
 {
     if (split == 4) return launch_sdpa_inst<BF16, DMA, 4>(k, programs, s);
-    if (split == 2) return launch_sdpa_inst<BF16, DMA, 2>(k, programs, s);
+    if constexpr (DMA)
+        if (split == 2) return launch_sdpa_inst<BF16, true, 2>(k, programs, s);
     return launch_sdpa_inst<BF16, DMA, 1>(k, programs, s);
 }
 
@@ -538,11 +582,14 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
     const int nblk = (int)(((int64_t)a.Sk + kKeyBlock - 1) / kKeyBlock);
     auto streams = [&](int64_t ss) { return ss >= kHeadDim && ((int64_t)a.Sk + 10 * kKeyBlock) * ss * 2 < (1LL << 31); };
     const bool dma = streams(a.k_ss) && streams(a.v_ss);
+    const bool far = a.k_ss >= kHeadDim && a.v_ss >= kHeadDim && !dma;     // (keys spread over 2 GB and more: every load a long way off)
     // A unit holds four groups of four wavefronts: launches with fewer programs than that split the keys, where there are enough
     // blocks to pay for the larger workgroup and the merge.  Measured (us, one group / split): 160 programs x 24 blocks 26.7 /
     // 19.3, 90 x 32 34.1 / 23.1, 8 x 32 27.0 / 21.0, 144 x 13 15.8 / 14.0, 288 x 32 46.5 (as it was) / 36.3; 256 x 8 11.4 / 12.2.
     const int64_t programs = bh * nqb;
-    const int split = nblk < 12 ? 1 : programs <= 256 ? 4 : programs <= 512 ? 2 : 1;
+    // Through registers, where a group's loads are not ahead of its arithmetic, four groups pay while units stay empty (32
+    // programs x 64 blocks 57 / 44, 160 x 24 24.2 / 22.0, 256 x 32 32 / 35), two do not (512 x 32 51 / 56).
+    const int split = nblk < 12 || far ? 1 : programs <= (dma ? 256 : 160) ? 4 : programs <= 512 && dma ? 2 : 1;
     hipStream_t s = (hipStream_t)stream;
     if (bf16) return dma ? launch_sdpa_split<true, true>(k, programs, split, s) : launch_sdpa_split<true, false>(k, programs, split, s);
     return dma ? launch_sdpa_split<false, true>(k, programs, split, s) : launch_sdpa_split<false, false>(k, programs, split, s);

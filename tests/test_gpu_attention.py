@@ -188,6 +188,27 @@ def test_scores_of_minus_infinity(dt, B, H, Sq, Sk):
 
 
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("Sk", [1, 64, 65, 129, 705])
+@pytest.mark.parametrize("H", [3, 150])
+def test_rows_that_overlap(dt, H, Sk):
+    """Keys and values whose rows overlap (pitch 63, 40, 0: not for the range-checked loads): the same bits as from a copy of
+    theirs, one block, blocks ahead of each other, a last block of one key; and with enough keys for groups."""
+    Sq = 130
+    gq = to_gpu(si.normal_bits((1, H, Sq, 64), dt, 130, 1.0), dt)
+    for n in (Sk, Sk + 700):
+        for pitch in (63, 40, 0):
+            k, v = (to_gpu(si.normal_bits((H * n * pitch + 64,), dt, 131 + i, 1.0), dt).as_strided((1, H, n, 64), (0, n * pitch, pitch, 1)) for i in range(2))
+            got, ref = torch.full_like(gq, float("nan")), torch.full_like(gq, float("nan"))
+            nt.sdpa(gq, k, v, got)
+            nt.sdpa(gq, k.contiguous(), v.contiguous(), ref)
+            torch.cuda.synchronize()
+            assert_gates(to_f64(ref), oat.sdpa(*(t.contiguous().cpu().view(torch.int16).numpy().view(np.uint16) for t in (gq, k, v)), dt), dt, f"sdpa {n}")
+            if H == 3 or n < 705:
+                assert torch.equal(got, ref), (n, pitch)             # (300 programs: groups for the copy, none for these rows)
+            assert_gates(to_f64(got), to_f64(ref), dt, f"sdpa rows of pitch {pitch}, {n} keys")
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
 @pytest.mark.parametrize("B,H,Sq,Sk", [(1, 3, 130, 1393), (1, 150, 130, 833), (1, 257, 10, 770)])
 def test_keys_dealt_to_groups_with_references_far_apart(dt, B, H, Sq, Sk):
     """Scores that rise (scale > 0) or fall (scale < 0) along the keys, slowly and by hundreds of powers of two from end to end:
