@@ -289,12 +289,20 @@ nt_status launch_map(int op, const void *x, int64_t sx, const void *y, int64_t s
     return check_launch("map_strided_kernel");
 }
 
+// A launch has fewer than 2^32 work-items along a dimension (of more, the runtime starts the remainder modulo 2^32 and reports no
+// error): 2^24 - 1 workgroups of 256.  More rows than those hold go out in several launches.
+constexpr int64_t kMaxWorkgroups = (1 << 24) - 1;
+
 template <int OP, int NV, int WPR>
 static nt_status launch_row_wave(const uint16_t *x, int64_t sxr, uint16_t *out, int64_t sor, int64_t rows, int64_t cols, float eps, bool bf16, hipStream_t s)
 {
-    dim3 grid((unsigned)(WPR == 1 ? (rows + 3) / 4 : rows)), block(256);
-    if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true, WPR>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
-    else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false, WPR>), grid, block, 0, s, x, sxr, out, sor, rows, cols, eps);
+    constexpr int64_t most = (WPR == 1 ? 4 : 1) * kMaxWorkgroups;
+    for (int64_t r0 = 0; r0 < rows; r0 += most) {
+        const int64_t n = std::min(rows - r0, most);
+        dim3 grid((unsigned)(WPR == 1 ? (n + 3) / 4 : n)), block(256);
+        if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true, WPR>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
+        else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false, WPR>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
+    }
     return check_launch("row_wave_kernel");
 }
 
@@ -309,7 +317,7 @@ static nt_status launch_rows_t(const void *x, int64_t sxr, int64_t sxc, void *ou
     // row): 4096 x 4096 10.2 / 11.0, 3001 x 3001 8.1 / 8.6, 4096 x 1024 3.8 / 5.6 -- against 3001 x 5003 11.6 / 11.9,
     // 8192 x 8192 49.1 / 45.7, and, with too few rows to occupy the chip, 256 x 4096 4.2 / 3.5, 64 x 8192 5.9 / 3.7.
     // (row_block_kernel, which such rows of odd length took before: 3001 x 5003 36 us, 16 x 5003 9.3 us)
-    if (sxc == 1 && soc == 1 && cols <= 32768 && rows <= 0x7fffffffLL) {
+    if (sxc == 1 && soc == 1 && cols <= 32768 && (rows <= 0x7fffffffLL || (cols % 8 == 0 && cols <= 8192 && rows < (1LL << 33)))) {
         if (cols <= 512) return launch_row_wave<OP, 1, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
         if (cols <= 1024) return launch_row_wave<OP, 2, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
         if (cols <= 2048) return launch_row_wave<OP, 4, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
@@ -324,7 +332,8 @@ static nt_status launch_rows_t(const void *x, int64_t sxr, int64_t sxc, void *ou
         return launch_row_wave<OP, 16, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
     }
     if (rows > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "too many rows");
-    hipLaunchKernelGGL((row_block_kernel<OP>), dim3((unsigned)rows), dim3(256), 0, s, X, sxr, sxc, O, sor, soc, cols, eps, dtype);
+    for (int64_t r0 = 0; r0 < rows; r0 += kMaxWorkgroups)
+        hipLaunchKernelGGL((row_block_kernel<OP>), dim3((unsigned)std::min(rows - r0, kMaxWorkgroups)), dim3(256), 0, s, X + r0 * sxr, sxr, sxc, O + r0 * sor, sor, soc, cols, eps, dtype);
     return check_launch("row_block_kernel");
 }
 

@@ -176,3 +176,17 @@ def test_prepared_call_is_the_same_call():
     nt.add(x, y, a)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("rows,cols,step", [(2**24 + 3, 4104, 1), (2**26 + 5, 8, 1), (2**31 + 5, 8, 1), (2**24 + 3, 5, 2)])
+def test_more_rows_than_one_launch_holds(rows, cols, step):
+    """Every row of more than 2^24 workgroups' worth is computed (one row per workgroup, four, one of strided columns).  One input
+    row for all; the output rows overlap but for their first element, so an element that stays behind is a row left out."""
+    x = torch.zeros((1, cols * step), dtype=torch.float16, device="cuda").expand(rows, cols * step)[:, ::step]
+    buf = torch.full((rows - 1 + (cols - 1) * step + 1,), -1.0, dtype=torch.float16, device="cuda")
+    out = buf.as_strided((rows, cols), (1, step))
+    nt.softmax(x, out)
+    torch.cuda.synchronize()
+    want = torch.tensor(1.0 / cols, dtype=torch.float16, device="cuda")
+    assert all((part == want).all() for part in (buf[:1000], buf[rows // 2:rows // 2 + 1000], buf[rows - 1000:rows], out[rows - 1]))
+    assert all((out[r] == want).all() for r in (2**24 - 2, 2**24 - 1, 2**24, min(2**26, rows - 1)))
