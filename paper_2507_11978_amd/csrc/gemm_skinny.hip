@@ -159,7 +159,8 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_skinny_kernel(const Fa
 // outweigh the saved launch (64 x 1024 x 8192 17.9 / 10.5; 33 x 5000 x 2047, odd pitches, 17.6 / 12.4).
 bool skinny_ok(const FastArgs &a, int alay, int blay)
 {
-    if (alay != KCONTIG || blay != KCONTIG || a.M > 32 || a.K < kSkinnyStep || a.N > (1 << 30)) return false;
+    // (k in 32 bits; fewer than 2^32 work-items in the launch, of more the runtime starts the remainder only)
+    if (alay != KCONTIG || blay != KCONTIG || a.M > 32 || a.K < kSkinnyStep || a.K > (1 << 30) || a.N > (1 << 26)) return false;
     auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     return a.M <= 16 || (al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0);
 }

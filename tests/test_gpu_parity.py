@@ -438,6 +438,27 @@ def test_products_of_few_rows(M, N, K, dt, out):
     assert_gates(to_f64(C1), onum.gemm(An, Bn, dt), out, "few rows")
 
 
+def test_products_of_few_rows_with_a_very_long_axis():
+    """More columns than 2^32 work-items serve, a reduction beyond 32 bits (the operands' rows overlap: they need little memory)."""
+    N, K = 2**27 + 21, 64
+    buf = torch.randint(-2, 3, (2 * N + K,), device="cuda", dtype=torch.int8).to(torch.float16)
+    a = torch.zeros((1, K), dtype=torch.float16, device="cuda")
+    a[0, 3], a[0, 60] = 1.0, -2.0
+    C = torch.full((1, N), float("nan"), dtype=torch.float16, device="cuda")
+    nt.gemm(a, buf.as_strided((K, N), (1, 2)), C)                        # column n of B: buf[2 n : 2 n + 64]
+    torch.cuda.synchronize()
+    assert torch.equal(C[0], buf[3:3 + 2 * N:2] - 2 * buf[60:60 + 2 * N:2])
+    del buf, C
+    K = 2**31 + 64
+    a, b = torch.zeros((K,), dtype=torch.float16, device="cuda"), torch.zeros((K,), dtype=torch.float16, device="cuda")
+    for i, v in ((5, 1.0), (2**20 + 1, 2.0), (2**30 + 7, 4.0), (2**31 - 1, 8.0), (2**31, 16.0), (K - 1, 32.0)):
+        a[i], b[i] = v, 1.0
+    C = torch.full((1, 1), float("nan"), dtype=torch.float32, device="cuda")
+    nt.gemm(a.as_strided((1, K), (8, 1)), b.as_strided((K, 1), (1, 8)), C)
+    torch.cuda.synchronize()
+    assert C.item() == 63.0
+
+
 def test_overhanging_tiles_bmm_and_bias_on_the_direct_kernel():
     dt, Bn, M, N, K = "f16", 3, 300, 392, 128
     A, B = si.gemm_inputs(M, N, K, dt, seed=82, dist="normal", batch=Bn)
