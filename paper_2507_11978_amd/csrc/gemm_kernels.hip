@@ -477,16 +477,20 @@ static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nc
 // launches 6), else 128 x 128 (7 + 0.37 and 12).
 // Measured: 1024 x 1024 x 1024 on 128 x 128 11 us unsplit against 19 split; on 64 x 64, unsplit / split: 256 x 256 x 2048 10.6 /
 // 8.0, x 8192 32.9 / 9.8, 512 x 512 x 4096 18.7 / 12.7, 16 x 1024 x 4096 20.0 / 8.0 (on 128 x 128, split: 10.3, 12.1, 13.5, 10.8).
-static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small)
+// *cost_out: the estimate of the way taken.
+static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out)
 {
-    if (programs >= (small ? 192 : 128) || kt < 32) return 1;
     const double step = small ? 0.24 : 0.37, once = small ? 3.5 : 7.0, twice = small ? 6.0 : 12.0;
+    const double single = once + step * (double)kt;
+    *cost_out = single;
+    if (programs >= (small ? 192 : 128) || kt < 32) return 1;
     const int64_t want = std::min<int64_t>((256 + programs / 2) / programs, kt / 8);
     for (int64_t d = want; d >= 2; --d) {
         if (kt % d) continue;
-        const double single = once + step * (double)kt;
         const double split = twice + step * (double)kt / (double)d + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
-        return split < single ? (int)d : 1;
+        if (split >= single) return 1;
+        *cost_out = split;
+        return (int)d;
     }
     return 1;
 }
@@ -913,11 +917,17 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     const bool bf16 = g.in_dtype == NT_BF16;
     const int64_t nwg = g.batch * g.mt * g.nt;
     hipStream_t s = (hipStream_t)g.stream;
-    if (g.batch == 1 && !g.user_tile && !g.trace.out && skinny_ok(a, alay, blay)) {
+    const bool ragged_mn = (g.M % t.bm) || (g.N % t.bn), ragged_k = (g.K % 64) != 0;
+    // k split: `ksplit` equal parts of K as the entries of a batched product into fp32 slices of the workspace
+    double split_cost = 0;
+    const int ksplit = g.batch == 1 && !ragged_k && (t.bm >= 128 || !g.user_tile) ? gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost) : 1;
+    const bool skinny = g.batch == 1 && !g.user_tile && !g.trace.out && skinny_ok(a, alay, blay);
+    auto run_skinny = [&]() {
         if (path_out) *path_out = PATH_DIRECT;
         t_k_split = skinny_parts(a);
         return launch_skinny(a, bf16, s);
-    }
+    };
+    if (skinny && (ksplit == 1 || skinny_cost(a) <= split_cost)) return run_skinny();
     // Operands stored to a C (and added to a D) with unit stride along n stream straight into LDS.  Full tiles of
     // 16-byte aligned operands: plain loads.  Everything else -- tiles that overhang M or N, a ragged K, rows with
     // only the element's 2-byte alignment -- takes the same loads as range-checked buffer accesses (EDGE kernels),
@@ -925,7 +935,6 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     // of a load, counted from the load's own start: with an odd pitch, or an extent that is no multiple of 4 bytes,
     // the word that holds the operand's last element can end 2 bytes past it and is then dropped; the kernel is told
     // (patch) and fetches that one element by itself.  The range never extends past the operand.
-    const bool ragged_mn = (g.M % t.bm) || (g.N % t.bn), ragged_k = (g.K % 64) != 0;
     auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     const bool out_ok = a.scn == 1 && (!a.D || a.sdn == 1);
     const bool aligned = al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0 && a.sa_batch % 8 == 0 && a.sb_batch % 8 == 0;
@@ -960,8 +969,6 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     for (const Entry &e : table) {
         if (e.bm != t.bm || e.bn != t.bn) continue;
         const Launcher launch = (direct ? (plain_direct ? e.direct : e.edge) : e.staged)[bf16 ? 1 : 0];
-        // k split: `ksplit` equal parts of K as the entries of a batched product into fp32 slices of the workspace
-        const int ksplit = g.batch == 1 && !ragged_k && (t.bm >= 128 || !g.user_tile) ? gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128) : 1;
         WorkspaceLease lease;
         float *ws = nullptr;                                 // (none: too large, or no memory; then no split)
         if (ksplit > 1) {
@@ -969,7 +976,7 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
             ws = split_region(g, (size_t)ksplit * g.M * g.N * 4, lease, &st);
             if (st != NT_OK) return st;
         }
-        if (!ws) return launch(a, alay, blay, nwg, s);
+        if (!ws) return skinny ? run_skinny() : launch(a, alay, blay, nwg, s);
         t_k_split = ksplit;
         FastArgs part = a;
         const int64_t Kp = g.K / ksplit;

@@ -165,6 +165,16 @@ bool skinny_ok(const FastArgs &a, int alay, int blay)
     return a.M <= 16 || (al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0);
 }
 
+// A program's wavefronts walk an eighth of the reduction each, however few programs there are: with few columns and a long
+// reduction a k split of tiles, which deals it out to the whole chip, is ahead.  Measured (us, this kernel / split; 0.28 a step of
+// a wavefront with one block of rows, 0.45 with two): 16 x 64 x 8192 7.2 / 8.8, x 16384 11.8 / 9.6, x 65536 39 / 15;
+// 16 x 1024 x 8192 7.5 / 9.8, x 16384 13.3 / 11.2; 16 x 2048 x 16384 14.1 / 15.9; 32 x 64 x 8192 9.7 / 9.0, x 4096 6.1 / 8.5.
+double skinny_cost(const FastArgs &a)
+{
+    const double steps = (double)((a.K / kSkinnyStep + kSkinnyWaves - 1) / kSkinnyWaves);
+    return 2.5 + steps * (a.M <= 16 ? 0.28 : 0.45);
+}
+
 int skinny_parts(const FastArgs &a) { return (int)std::min<int64_t>(kSkinnyWaves, a.K / kSkinnyStep); }
 
 nt_status launch_skinny(const FastArgs &a, bool bf16, hipStream_t s)

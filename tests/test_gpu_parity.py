@@ -438,6 +438,22 @@ def test_products_of_few_rows(M, N, K, dt, out):
     assert_gates(to_f64(C1), onum.gemm(An, Bn, dt), out, "few rows")
 
 
+@pytest.mark.parametrize("M,N,K,tiles", [(16, 16, 65536, True), (1, 64, 16384, True), (7, 1000, 16384, True), (32, 256, 16384, True),
+                                         (16, 64, 4096, False), (16, 2048, 8192, False), (32, 4096, 4096, False), (16, 16, 65535, False)])
+def test_few_columns_and_a_long_reduction_are_dealt_to_the_whole_chip(M, N, K, tiles):
+    """Few rows and few columns leave the chip to a handful of programs: a long reduction is split over tiles instead of over a
+    program's wavefronts (where K allows it), in the entry point that allocates nothing too.  Small integers: exact."""
+    A, B = si.gemm_inputs(M, N, K, "bf16", seed=86, dist="int")
+    want = torch.from_numpy(onum.gemm(A, B, "bf16")).to(torch.float32)
+    a, bt = to_gpu(A, "bf16"), to_gpu(B, "bf16").t().contiguous().t()
+    for fn in (nt.gemm, nt.gemm_noalloc):
+        C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        fn(a, bt, C)
+        torch.cuda.synchronize()
+        assert (nt.last_k_split() > 8) == tiles
+        assert torch.equal(C.cpu(), want)
+
+
 def test_products_of_few_rows_with_a_very_long_axis():
     """More columns than 2^32 work-items serve, a reduction beyond 32 bits (the operands' rows overlap: they need little memory)."""
     N, K = 2**27 + 21, 64
