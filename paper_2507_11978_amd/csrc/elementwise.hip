@@ -10,6 +10,7 @@
 //
 // All four are bound by HBM traffic: add moves 3 x 2 bytes per element, the others 2 x 2.
 #include "gemm_device.h"
+#include <type_traits>
 
 namespace nt {
 
@@ -137,7 +138,10 @@ __device__ __forceinline__ float wave_sum(float v)
 // Rows of odd length or pitch start on any 2-byte boundary.  The vectors are laid from the row's first 16-byte boundary on,
 // where a load or store touches no cache line twice; the up to seven elements before it and the up to seven behind the last
 // whole vector are one element each for the first lanes.
-template <int OP, int NV, bool BF16, int WPR>
+// EDGES: rows that are not whole vectors.  Those that are have their vectors laid from the row's start, wherever it lies: there the
+// edges' arithmetic is what a short row costs (rms_norm 100000 x 128 bf16 21.1 us with it, 18.8 without; pitch 65, 64 columns, 24.0
+// and 19.3), and the single elements a long one (20000 x 4096, pitch 4097, 52.7 and 47.7).
+template <int OP, int NV, bool BF16, int WPR, bool EDGES>
 __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restrict__ x, int64_t sxr, uint16_t *__restrict__ out, int64_t sor,
                                                        int64_t rows, int64_t cols, float eps)
 {
@@ -150,14 +154,18 @@ __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restric
     const uint16_t *xr = x + row * sxr;
     uint16_t *orow = out + row * sor;
     const int n = (int)cols;
-    const int to_boundary = (int)((0 - reinterpret_cast<uintptr_t>(xr)) & 15) >> 1;
-    const int head = to_boundary < n ? to_boundary : n;
-    const int nvec = (n - head) >> 3, rest = (n - head) & 7;
-    const int edge = rl < head ? rl : (rl < head + rest ? nvec * 8 + rl : -1);      // this lane's single element
+    int head = 0, rest = 0;
+    if constexpr (EDGES) {
+        const int to_boundary = (int)((0 - reinterpret_cast<uintptr_t>(xr)) & 15) >> 1;
+        head = to_boundary < n ? to_boundary : n;
+        rest = (n - head) & 7;
+    }
+    const int nvec = (n - head) >> 3;
+    const int edge = !EDGES ? -1 : rl < head ? rl : (rl < head + rest ? nvec * 8 + rl : -1);      // this lane's single element
     const float pad = OP == 0 ? -INFINITY : 0.f;              // what is not there: no part of the maximum, of a sum
     const uint16_t *xv = xr + head;
     float fe = pad, f[NV][8];
-    if (edge >= 0) fe = to_f32(xr[edge], dt);
+    if (EDGES && edge >= 0) fe = to_f32(xr[edge], dt);
     u32x4 raw[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -170,7 +178,7 @@ __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restric
         const bool in = v * RL + rl < nvec;
         unpack8<BF16>(raw[v], f[v]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[v][e] = in ? f[v][e] : pad;
+        for (int e = 0; e < 8; ++e) f[v][e] = OP == 1 || in ? f[v][e] : pad;         // (zeros stay zeros)
     }
     auto across = [&](float v, bool is_max) {                 // over the row's lanes
         v = is_max ? wave_max(v) : wave_sum(v);
@@ -190,8 +198,8 @@ __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restric
 #pragma unroll
             for (int e = 0; e < 8; ++e) m = fmaxf(m, f[v][e]);
         m = across(m, true);
-        fe = __expf(fe - m);
-        float s = fe;
+        if constexpr (EDGES) fe = __expf(fe - m);
+        float s = EDGES ? fe : 0.f;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -221,7 +229,7 @@ __global__ __launch_bounds__(256) void row_wave_kernel(const uint16_t *__restric
             else __builtin_memcpy(ov + idx * 8, &r, 16);
         }
     }
-    if (edge >= 0) orow[edge] = from_f32(fe * scale, dt);
+    if (EDGES && edge >= 0) orow[edge] = from_f32(fe * scale, dt);
 }
 
 // Any row length and strides: one workgroup per row, the row is read once per pass.
@@ -293,15 +301,15 @@ nt_status launch_map(int op, const void *x, int64_t sx, const void *y, int64_t s
 // error): 2^24 - 1 workgroups of 256.  More rows than those hold go out in several launches.
 constexpr int64_t kMaxWorkgroups = (1 << 24) - 1;
 
-template <int OP, int NV, int WPR>
+template <int OP, int NV, int WPR, bool EDGES>
 static nt_status launch_row_wave(const uint16_t *x, int64_t sxr, uint16_t *out, int64_t sor, int64_t rows, int64_t cols, float eps, bool bf16, hipStream_t s)
 {
     constexpr int64_t most = (WPR == 1 ? 4 : 1) * kMaxWorkgroups;
     for (int64_t r0 = 0; r0 < rows; r0 += most) {
         const int64_t n = std::min(rows - r0, most);
         dim3 grid((unsigned)(WPR == 1 ? (n + 3) / 4 : n)), block(256);
-        if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true, WPR>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
-        else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false, WPR>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
+        if (bf16) hipLaunchKernelGGL((row_wave_kernel<OP, NV, true, WPR, EDGES>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
+        else hipLaunchKernelGGL((row_wave_kernel<OP, NV, false, WPR, EDGES>), grid, block, 0, s, x + r0 * sxr, sxr, out + r0 * sor, sor, n, cols, eps);
     }
     return check_launch("row_wave_kernel");
 }
@@ -318,18 +326,22 @@ static nt_status launch_rows_t(const void *x, int64_t sxr, int64_t sxc, void *ou
     // 8192 x 8192 49.1 / 45.7, and, with too few rows to occupy the chip, 256 x 4096 4.2 / 3.5, 64 x 8192 5.9 / 3.7.
     // (row_block_kernel, which such rows of odd length took before: 3001 x 5003 36 us, 16 x 5003 9.3 us)
     if (sxc == 1 && soc == 1 && cols <= 32768 && (rows <= 0x7fffffffLL || (cols % 8 == 0 && cols <= 8192 && rows < (1LL << 33)))) {
-        if (cols <= 512) return launch_row_wave<OP, 1, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 1024) return launch_row_wave<OP, 2, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 2048) return launch_row_wave<OP, 4, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 4096 && rows >= 2048) {
-            if (cols <= 3072) return launch_row_wave<OP, 6, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-            return launch_row_wave<OP, 8, 1>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        }
-        if (cols <= 4096) return launch_row_wave<OP, 2, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 6144) return launch_row_wave<OP, 3, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 8192) return launch_row_wave<OP, 4, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        if (cols <= 16384) return launch_row_wave<OP, 8, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
-        return launch_row_wave<OP, 16, 4>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        auto by_length = [&](auto edges) {
+            constexpr bool E = decltype(edges)::value;
+            if (cols <= 512) return launch_row_wave<OP, 1, 1, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 1024) return launch_row_wave<OP, 2, 1, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 2048) return launch_row_wave<OP, 4, 1, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 4096 && rows >= 2048) {
+                if (cols <= 3072) return launch_row_wave<OP, 6, 1, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+                return launch_row_wave<OP, 8, 1, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            }
+            if (cols <= 4096) return launch_row_wave<OP, 2, 4, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 6144) return launch_row_wave<OP, 3, 4, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 8192) return launch_row_wave<OP, 4, 4, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            if (cols <= 16384) return launch_row_wave<OP, 8, 4, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+            return launch_row_wave<OP, 16, 4, E>(X, sxr, O, sor, rows, cols, eps, bf16, s);
+        };
+        return cols % 8 ? by_length(std::true_type{}) : by_length(std::false_type{});
     }
     if (rows > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "too many rows");
     for (int64_t r0 = 0; r0 < rows; r0 += kMaxWorkgroups)

@@ -103,7 +103,9 @@ def test_softmax_and_rms_norm(dt, rows, cols):
 
 
 @pytest.mark.parametrize("rows,cols", [(3, 1), (5, 7), (9, 9), (6, 511), (5, 513), (5, 1025), (5, 2047), (5, 2049), (2048, 2049), (2049, 3073), (3, 4097),
-                                       (3, 6144), (3, 6151), (2, 8191), (2, 8193), (2, 16391), (2, 32768), (1, 32769)])
+                                       (3, 6144), (3, 6151), (2, 8191), (2, 8193), (2, 16391), (2, 32768), (1, 32769),
+                                       # whole vectors, wherever their rows start
+                                       (5, 8), (5, 512), (5, 1024), (5, 2048), (2048, 3072), (2049, 4096), (5, 4096), (3, 8192), (2, 16384)])
 def test_rows_of_any_length_and_alignment(rows, cols):
     """Rows in registers: the elements before a row's first 16-byte boundary and behind its last whole vector, at the edges of
     the lengths each variant holds; odd pitches (every row starts elsewhere), input and output aligned differently; in place;
