@@ -11,9 +11,9 @@
  *   - Plain C types only.  "device" pointers are HIP device addresses (for example
  *     torch.Tensor.data_ptr()); "host" pointers are ordinary process memory.
  *   - Strides are in ELEMENTS, not bytes, and may describe any non-overlapping view.
- *   - The caller owns every buffer it passes.  The library keeps one thing between calls: a workspace of 256 MB
+ *   - The caller owns every buffer it passes.  The library keeps one thing between calls: a workspace of 352 MB
  *     per GPU, allocated by the first call on that GPU that needs one (see "Memory" at nt_gemm and
- *     nt_conv2d_implicit) and kept, never moved, until the process ends.  Calls that need it while another call's
+ *     nt_conv2d_implicit) and kept, never moved, until the process ends.  Calls that need the same part of it while another call's
  *     work on it is still queued -- from other host threads or on other streams of the same GPU -- wait their turn:
  *     the later call's stream waits (on the device, through an event) for the earlier call's last kernel that
  *     touches the workspace.  Results never depend on what other calls do.
@@ -181,7 +181,7 @@ int32_t nt_tile_supported(nt_tile_cfg cfg);
  * Memory (nt_gemm, nt_addmm, nt_addmm_act): a product with few output tiles and a long reduction (256 x 256 x
  * 8192, say) has K dealt to several programs per tile; their fp32 partial tiles go
  * through the library's workspace, the same one, under the same rules, as described at nt_conv2d_implicit
- * (one allocation of 256 MB per GPU, made by the first call that needs it, handed from call to call in stream
+ * (one allocation per GPU, made by the first call that needs it, handed from call to call in stream
  * order; partial tiles added in a fixed order).  At most 16 rows (32 on 16-byte aligned rows) of operands with unit
  * stride along k need none of it unless few columns meet a very long reduction (16 x 64 x 16384): their reduction is
  * split inside a program.
@@ -309,7 +309,8 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * Descriptors have ndim 4 with arbitrary strides.
  * Strided calls with channels in whole blocks of 32 and more than one filter tap, and unit-stride calls with such channels and
  * few output positions, run on a zero-padded channels-last copy of their input, made in the workspace beside the filter's
- * tap-major copy (a call captured in a graph that needs no k split keeps to the kernels below).
+ * tap-major copy (unit-stride calls that need no k split keep to the kernels below with at most 128 filters, and where they
+ * are captured in a graph).
  * Other dense unit-stride calls (contiguous NCHW input, at most one column of padding) never materialise the unfolded input; with
  * more than 128 filters and channels in whole blocks of 32 they copy the filter (only) into the workspace in tap-major order,
  * unless it is stored that way already (a channels-last filter: strides (R S C, 1, S C, C)), which is then read as it is.  The
@@ -319,10 +320,11 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * named by the caller, every tile is gathered through the index map.
  * Memory: a dense unit-stride call with few output tiles and a long reduction has its reduction dealt to
  * several programs per tile, whose fp32 partial tiles go through a workspace that the library owns: one device
- * allocation of 256 MB per GPU, made by the first call on that GPU that needs it (captured in a HIP graph before any
- * such call, it runs without), never moved or freed until the process ends.  All calls on a GPU share it,
- * one after the other: a call that finds it last used on another stream makes its own stream wait for that use
- * to finish (an event), so overlapping calls queue up for the workspace instead of racing.  What does not fit
+ * allocation of 352 MB per GPU, made by the first call on that GPU that needs it (captured in a HIP graph before any
+ * such call, it runs without), never moved or freed until the process ends.  It is 256 MB and three times 32 MB for calls
+ * that need no more than that.  Calls on a GPU that use the same part of it do so one after the other: a call that finds it
+ * last used on another stream makes its own stream wait for that use to finish (an event), so overlapping calls queue up
+ * instead of racing; up to three streams of small calls have a part each.  What does not fit
  * the workspace, or a failed allocation, runs without it (no split, or through the index map).  The partial tiles
  * are added in a fixed order: a call repeated on the same data gives the same bits.
  */

@@ -309,16 +309,20 @@ static bool match_conv(const GemmLaunch &g, ConvArgs *a)
     return true;
 }
 
-// Workspace of the k splits (convolution, skinny GEMM), of the zero-padded copy and of the unfolded input of a convolution:
-// one allocation of kSplitWsMax bytes per device, made by the first call on that device that needs it and kept until the
-// process ends (never freed or moved, so work in flight never loses it).  Every call on a device shares it.  A call holds it
-// through a WorkspaceLease from before its first launch that touches it until after its last: the lease serialises host
-// threads (a mutex) and streams (an event recorded behind the last consumer, which a call on any other stream makes its
-// stream wait for before its own first launch), so calls that overlap on one device queue up instead of racing.
+// Workspace of the k splits (convolution, skinny GEMM) and of the copies and the unfolded input of a convolution: one allocation
+// per device, made by the first call on that device that needs it and kept until the process ends (never freed or moved, so work
+// in flight never loses it).  It is cut into lanes, one of kSplitWsMax bytes and kSmallLanes of kSmallLane bytes for what fits
+// those, so that calls on a few streams overlap as calls without workspace do.  A call holds a lane through a WorkspaceLease from
+// before its first launch that touches it until after its last: the lease serialises host threads (a mutex) and streams (an event
+// recorded behind the last consumer, which a call on any other stream makes its stream wait for before its own first launch), so
+// calls that meet on one lane queue up instead of racing.  A stream keeps to the small lane it has used before, a new one takes
+// the lane that has not been taken for the longest time.  (Two streams of (2,64,56,56)*(64,64,3,3) from two threads, us a call: 30
+// on one lane, 14; alternating (4,256,14,14)*(256,256,3,3) 32 and 19.)
 // The event carries no system-scope fence: it only orders kernels of one device, and what it orders is the last consumer's reads
 // before the next caller's writes (a consumer's input left the writer's caches at the launch boundary between the two).  The
 // fence cost every call 2 us on the device (the paper's conv task 29.5 -> 27.6 us).
-static constexpr size_t kSplitWsMax = 256u << 20;
+static constexpr size_t kSplitWsMax = 256u << 20, kSmallLane = 32u << 20;
+static constexpr int kSmallLanes = 3;
 
 // whether work on the stream is being captured into a graph
 static bool capturing(hipStream_t stream)
@@ -337,42 +341,78 @@ public:
     void *acquire(size_t bytes, hipStream_t stream)
     {
         int dev = 0;
-        if (slot_ || bytes > kSplitWsMax || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-        Slot &w = table()[dev];
-        w.mu.lock();
-        bool ok = true;
-        if (!w.p && capturing(stream)) {                      // (an allocation would invalidate the capture)
-            ok = false;
-        } else if (!w.p) {
-            void *p = nullptr;
-            hipEvent_t ev = nullptr;
-            if (hipMalloc(&p, kSplitWsMax) != hipSuccess) { (void)hipGetLastError(); ok = false; }
-            else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(p); ok = false; }
-            else { w.p = p; w.done = ev; }
+        if (lane_ || bytes > kSplitWsMax || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+        Device &d = table()[dev];
+        if (!ready(d, stream)) return nullptr;
+        Lane *w = bytes <= kSmallLane ? small_lane(d, stream) : &d.lane[0];
+        w->mu.lock();
+        if (w->used && w->last != stream && hipStreamWaitEvent(stream, w->done, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            w->mu.unlock();
+            return nullptr;
         }
-        if (ok && w.used && w.last != stream && hipStreamWaitEvent(stream, w.done, 0) != hipSuccess) { (void)hipGetLastError(); ok = false; }
-        if (!ok) { w.mu.unlock(); return nullptr; }
-        slot_ = &w;
+        lane_ = w;
         stream_ = stream;
-        return w.p;
+        return w->p;
     }
     ~WorkspaceLease()
     {
-        if (!slot_) return;
-        if (hipEventRecord(slot_->done, stream_) == hipSuccess) { slot_->last = stream_; slot_->used = true; }
+        if (!lane_) return;
+        if (hipEventRecord(lane_->done, stream_) == hipSuccess) { lane_->last = stream_; lane_->used = true; }
         else {
             // without the marker a later call on another stream could not wait for this one's work: wait for it here
             (void)hipGetLastError();
             (void)hipStreamSynchronize(stream_);
-            slot_->used = false;
+            lane_->used = false;
         }
-        slot_->mu.unlock();
+        lane_->mu.unlock();
     }
 
 private:
-    struct Slot { void *p = nullptr; hipEvent_t done = nullptr; hipStream_t last = nullptr; bool used = false; std::mutex mu; };
-    static Slot *table() { static Slot t[64]; return t; }
-    Slot *slot_ = nullptr;
+    // (owner and stamp -- who was given the lane last, and when -- under the device's mutex, the rest under the lane's)
+    struct Lane { void *p = nullptr; hipEvent_t done = nullptr; hipStream_t last = nullptr, owner = nullptr; bool used = false; uint64_t stamp = 0; std::mutex mu; };
+    struct Device { Lane lane[1 + kSmallLanes]; void *p = nullptr; uint64_t clock = 0; std::mutex mu; };
+    static Device *table() { static Device t[64]; return t; }
+
+    // the device's allocation, made if need be
+    static bool ready(Device &d, hipStream_t stream)
+    {
+        std::lock_guard<std::mutex> lock(d.mu);
+        if (d.p) return true;
+        if (capturing(stream)) return false;                  // (an allocation would invalidate the capture)
+        void *p = nullptr;
+        hipEvent_t ev[1 + kSmallLanes] = {};
+        bool ok = hipMalloc(&p, kSplitWsMax + kSmallLanes * kSmallLane) == hipSuccess;
+        for (hipEvent_t &e : ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            for (hipEvent_t e : ev)
+                if (e) (void)hipEventDestroy(e);
+            if (p) (void)hipFree(p);
+            return false;
+        }
+        for (int i = 0; i <= kSmallLanes; ++i) {
+            d.lane[i].p = (char *)p + (i ? kSplitWsMax + (size_t)(i - 1) * kSmallLane : 0);
+            d.lane[i].done = ev[i];
+        }
+        d.p = p;
+        return true;
+    }
+    // the small lane of this stream
+    static Lane *small_lane(Device &d, hipStream_t stream)
+    {
+        std::lock_guard<std::mutex> lock(d.mu);
+        Lane *w = &d.lane[1];
+        for (int i = 1; i <= kSmallLanes; ++i) {
+            Lane &l = d.lane[i];
+            if (l.stamp && l.owner == stream) { w = &l; break; }
+            if (l.stamp < w->stamp) w = &l;
+        }
+        w->owner = stream;
+        w->stamp = ++d.clock;
+        return w;
+    }
+    Lane *lane_ = nullptr;
     hipStream_t stream_ = nullptr;
 };
 
@@ -736,8 +776,11 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
                 return route_matrix(u, fa, alay, blay, nullptr);
             }
         }
-        // (without a split route 1 needs no workspace: a captured call stays independent of it, as its replays take no lease)
-        if (parts == 1 && capturing((hipStream_t)g.stream)) return NT_OK;
+        // Without a split route 1 needs no workspace.  Up to 128 filters it is no slower by enough to give that up ((1,32,56,56) *
+        // (32,32,3,3) 12.2 / 11.5 us, (2,32,64,64) * (128,32,3,3) 15.7 / 12.8, but 6.5 / 9.8 and 9.4 / 16 on two streams; (8,32,28,28) *
+        // (256,32,3,3) 19.4 / 12.5, 10.5 / 10.5); a captured call stays independent of it, as its replays take no lease.
+        ConvArgs probe{};
+        if (parts == 1 && ((F <= 128 && match_conv(g, &probe)) || capturing((hipStream_t)g.stream))) return NT_OK;
         if (((F + 127) / 128) * ((M + 127) / 128) * parts < 192) tile = 64;
     } else {
         if (RS == 1) return NT_OK;

@@ -1,6 +1,8 @@
 """GPU parity of the calls that go through the library's workspace when they overlap on one device, and of operands
 whose last element a range-checked 16-byte load cannot fetch (odd pitches and extents, an operand that ends exactly at
 the end of a page)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -73,6 +75,43 @@ def test_two_streams_padded_copy_and_unfolded_routes():
     for r in range(rounds):
         assert np.array_equal(to_f64(ya[r]), ref_a), f"round {r}: padded copy"
         assert np.array_equal(to_f64(yb[r]), ref_b), f"round {r}: unfolded input"
+
+
+def test_more_streams_than_parts_of_the_workspace():
+    """Five streams, two threads: calls small enough for the workspace's small parts (a k split, a channels-last copy, a skinny
+    product) meet on them and with calls that need the large one; every result is the exact one of its own problem."""
+    dt, rounds = "f16", 5
+    streams = [torch.cuda.Stream() for _ in range(5)]
+    jobs = []
+    for i in range(4):
+        N, Cc, hw, K, stride = [(4, 256, 14, 256, 1), (2, 64, 30, 96, 2), (3, 128, 9, 70, 1), (1, 32, 57, 40, 2)][i]
+        X, Wt = si.conv_inputs(N, Cc, hw, hw, K, 3, 3, dt, seed=60 + i, dist="int")
+        ref = onum.conv2d(X, Wt, dt, (stride, stride), (1, 1), nthreads=16)
+        x, w = to_gpu(X, dt), to_gpu(Wt, dt)
+        jobs.append((ref, lambda y, s, x=x, w=w, st=stride: nt.conv2d_implicit(x, w, y, (st, st), (1, 1), stream=s)))
+    A, B = si.gemm_inputs(48, 640, 4096, dt, seed=65, dist="int")
+    a, b = to_gpu(A, dt), to_gpu(B, dt)
+    jobs.append((onum.gemm(A, B, dt), lambda y, s: nt.gemm(a, b, y, stream=s)))
+    X, Wt = si.conv_inputs(16, 64, 112, 112, 32, 3, 3, dt, seed=66, dist="int")                      # a copy of 26 MB: with the filter's, and
+    big_x, big_w = to_gpu(np.concatenate([X, X]), dt), to_gpu(Wt, dt)                                 # twice the images, more than a small part
+    big_ref = onum.conv2d(X, Wt, dt, (2, 2), (1, 1), nthreads=16)
+    jobs.append((np.concatenate([big_ref, big_ref]), lambda y, s: nt.conv2d_implicit(big_x, big_w, y, (2, 2), (1, 1), stream=s)))
+    outs = [[torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda") for ref, _ in jobs] for _ in range(2 * rounds)]
+    torch.cuda.synchronize()
+
+    def work(first):
+        for r in range(first, 2 * rounds, 2):
+            for j, (_, run) in enumerate(jobs):
+                run(outs[r][j], streams[(r + j) % 5])
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for r in range(2 * rounds):
+        for j, (ref, _) in enumerate(jobs):
+            assert np.array_equal(to_f64(outs[r][j]), ref), (r, j)
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
