@@ -714,6 +714,16 @@ static GemmLaunch per_image_product(const GemmLaunch &g, const void *U, int64_t 
 static bool lower_plain(const GemmLaunch &g, FastArgs *out, int *alay_out, int *blay_out);
 static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int blay, int *path_out);
 
+// what route 3 takes (if the workspace is to be had)
+static bool conv_unfold_ok(const GemmLaunch &g)
+{
+    const ConvHint &h = g.conv;
+    const int64_t K = h.C * h.R * h.S, Mp = (h.N * h.P * h.Q + 7) / 8 * 8;
+    return conv_is_bare(g) && h.ys[3] == 1 && h.ys[2] == h.Q && h.ws[3] == 1 && h.ws[2] == h.S && h.ws[1] == h.R * h.S && h.ws[0] >= K &&
+           h.ws[0] < (1 << 22) && h.N * h.C * h.H * h.W > 0 && (h.N - 1) * h.xs[0] + (h.H - 1) * h.xs[2] + (h.W - 1) * h.xs[3] < (1LL << 31) &&
+           h.xs[0] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 && h.P * h.Q >= 8 && K >= 8 && K <= 65535 && Mp < (1 << 22) && (size_t)K * Mp * 2 <= kSplitWsMax;
+}
+
 // Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
 // estimate of its product.  A unit runs two programs at a time; a program costs a fixed part and its slices, a split the
 // kernel that adds the parts and their trip through memory.  (Fits, us: 392 programs of 128 x 128 with 36 slices 27.5, 196
@@ -790,6 +800,10 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
     // the copy: the padded image, or (one tap per axis) only the positions that are read
     const int64_t eh = h.R == 1 ? h.sh : 1, ew = h.S == 1 ? h.sw : 1;
     const int64_t Hc = h.R == 1 ? h.P : h.H + 2 * h.ph, Wc = h.S == 1 ? h.Q : h.W + 2 * h.pw;
+    // (strides far beyond the filter read a fraction of a large image: the unfolded input is then the smaller copy by far.
+    // (32,64,112,112) * (128,64,2,2), 51 MB, stride 8: 23.4 against 18.4; stride 4 25.7 / 25.2; (8,256,56,56) * (512,256,2,2), 13 MB,
+    // stride 8: 15.7 / 22.9)
+    if (!unit && h.N * Hc * Wc >= (16 << 20) / h.C && h.N * Hc * Wc >= 8 * RS * M && conv_unfold_ok(g)) return NT_OK;
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t copy_bytes = up((size_t)h.N * Hc * Wc * h.C * 2), filter_bytes = natural ? up((size_t)F * K * 2) : 0;
     const size_t split_bytes = parts > 1 ? (size_t)parts * F * M * 4 : 0;
@@ -876,12 +890,8 @@ static nt_status route_conv_unfold(const GemmLaunch &g, int *path_out, bool *tak
 {
     *taken = false;
     const ConvHint &h = g.conv;
-    if (!(conv_is_bare(g) && h.ys[3] == 1 && h.ys[2] == h.Q && h.ws[3] == 1 && h.ws[2] == h.S && h.ws[1] == h.R * h.S && h.ws[0] >= h.C * h.R * h.S &&
-          h.ws[0] < (1 << 22) && h.N * h.C * h.H * h.W > 0 && (h.N - 1) * h.xs[0] + (h.H - 1) * h.xs[2] + (h.W - 1) * h.xs[3] < (1LL << 31) &&
-          h.xs[0] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 && h.P * h.Q >= 8 && h.C * h.R * h.S >= 8 && h.C * h.R * h.S <= 65535))
-        return NT_OK;
+    if (!conv_unfold_ok(g)) return NT_OK;
     const int64_t K = h.C * h.R * h.S, PQ = h.P * h.Q, M = h.N * PQ, Mp = (M + 7) / 8 * 8;
-    if (Mp >= (1 << 22)) return NT_OK;
     WorkspaceLease lease;
     uint16_t *U = (uint16_t *)lease.acquire((size_t)K * Mp * 2, (hipStream_t)g.stream);
     if (!U) return NT_OK;

@@ -736,6 +736,18 @@ def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
             assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
 
 
+@pytest.mark.parametrize("K,R,stride", [(16, 2, 8), (16, 2, 4), (8, 3, 16)])
+def test_conv2d_strides_far_beyond_the_filter(K, R, stride):
+    """A large image of which few positions are read: copied whole or unfolded, the same exact integers."""
+    N, Cc, H, W = 6, 64, 210, 212
+    X, Wt = si.conv_inputs(N, Cc, H, W, K, R, R, "f16", seed=34, dist="int")
+    ref = onum.conv2d(X, Wt, "f16", (stride, stride), (0, 0), nthreads=16)
+    Y = torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda")
+    nt.conv2d_implicit(to_gpu(X, "f16"), to_gpu(Wt, "f16"), Y, (stride, stride), (0, 0))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_f64(Y), ref)
+
+
 def test_conv2d_dense_integer_exact_and_padding_edges():
     # small integers: exact; a wrong halo element or a missed padding row changes the result
     N, Cc, H, W, K, R, S = 2, 8, 16, 16, 128, 3, 3
