@@ -320,11 +320,14 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * named by the caller, every tile is gathered through the index map.
  * Memory: a dense unit-stride call with few output tiles and a long reduction has its reduction dealt to
  * several programs per tile, whose fp32 partial tiles go through a workspace that the library owns: one device
- * allocation of 352 MB per GPU, made by the first call on that GPU that needs it (captured in a HIP graph before any
- * such call, it runs without), never moved or freed until the process ends.  It is 256 MB and three times 32 MB for calls
+ * allocation of 352 MB per GPU, made by the first call on that GPU that needs it, never moved or freed until the process
+ * ends.  It is 256 MB and three times 32 MB for calls
  * that need no more than that.  Calls on a GPU that use the same part of it do so one after the other: a call that finds it
  * last used on another stream makes its own stream wait for that use to finish (an event), so overlapping calls queue up
- * instead of racing; up to three streams of small calls have a part each.  What does not fit
+ * instead of racing; up to three streams of small calls have a part each.  Calls captured into a HIP graph use an
+ * allocation of their own instead (256 MB, made by the first of them that needs it, in its capture if need be): replays may
+ * overlap calls that are not captured, on any stream; replays of graphs that hold such calls must not overlap each other
+ * (within one graph such calls follow one another).  What does not fit
  * the workspace, or a failed allocation, runs without it (no split, or through the index map).  The partial tiles
  * are added in a fixed order: a call repeated on the same data gives the same bits.
  */

@@ -318,18 +318,22 @@ static bool match_conv(const GemmLaunch &g, ConvArgs *a)
 // calls that meet on one lane queue up instead of racing.  A stream keeps to the small lane it has used before, a new one takes
 // the lane that has not been taken for the longest time.  (Two streams of (2,64,56,56)*(64,64,3,3) from two threads, us a call: 30
 // on one lane, 14; alternating (4,256,14,14)*(256,256,3,3) 32 and 19.)
+// Calls captured into a graph never touch those lanes or their events: a replay takes no lease, so nothing would order it against
+// the calls around it.  They share an allocation of their own (kSplitWsMax bytes, made by the first that needs it); within a
+// capture the event between two streams becomes an edge of the graph, and replays that overlap each other are the caller's to avoid.
 // The event carries no system-scope fence: it only orders kernels of one device, and what it orders is the last consumer's reads
 // before the next caller's writes (a consumer's input left the writer's caches at the launch boundary between the two).  The
 // fence cost every call 2 us on the device (the paper's conv task 29.5 -> 27.6 us).
 static constexpr size_t kSplitWsMax = 256u << 20, kSmallLane = 32u << 20;
 static constexpr int kSmallLanes = 3;
 
-// whether work on the stream is being captured into a graph
-static bool capturing(hipStream_t stream)
+// the capture (a number above 0) that work on the stream goes into, 0: none
+static unsigned long long capture_of(hipStream_t stream)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return true; }
-    return st != hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(stream, &st, &id) != hipSuccess) { (void)hipGetLastError(); return ~0ull; }
+    return st == hipStreamCaptureStatusNone ? 0 : id;
 }
 
 class WorkspaceLease {
@@ -343,43 +347,56 @@ public:
         int dev = 0;
         if (lane_ || bytes > kSplitWsMax || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
         Device &d = table()[dev];
-        if (!ready(d, stream)) return nullptr;
-        Lane *w = bytes <= kSmallLane ? small_lane(d, stream) : &d.lane[0];
+        const unsigned long long capture = capture_of(stream);
+        if (capture == ~0ull) return nullptr;
+        if (!(capture ? ready_for_captures(d) : ready(d))) return nullptr;
+        Lane *w = capture ? &d.captures : bytes <= kSmallLane ? small_lane(d, stream) : &d.lane[0];
         w->mu.lock();
-        if (w->used && w->last != stream && hipStreamWaitEvent(stream, w->done, 0) != hipSuccess) {
+        // (an event recorded in another capture says nothing about this one)
+        if (w->used && w->last != stream && w->capture == capture && (!w->marked || hipStreamWaitEvent(stream, w->done, 0) != hipSuccess)) {
             (void)hipGetLastError();
             w->mu.unlock();
             return nullptr;
         }
         lane_ = w;
         stream_ = stream;
+        w->capture = capture;
         return w->p;
     }
     ~WorkspaceLease()
     {
         if (!lane_) return;
-        if (hipEventRecord(lane_->done, stream_) == hipSuccess) { lane_->last = stream_; lane_->used = true; }
-        else {
-            // without the marker a later call on another stream could not wait for this one's work: wait for it here
+        lane_->last = stream_;
+        lane_->used = lane_->marked = hipEventRecord(lane_->done, stream_) == hipSuccess;
+        if (!lane_->marked) {
+            // without the marker a later call on another stream could not wait for this one's work: wait for it here (in a capture,
+            // where there is nothing to wait for yet, such a call runs without the workspace)
             (void)hipGetLastError();
-            (void)hipStreamSynchronize(stream_);
-            lane_->used = false;
+            if (lane_->capture) lane_->used = true;
+            else (void)hipStreamSynchronize(stream_);
         }
         lane_->mu.unlock();
     }
 
 private:
     // (owner and stamp -- who was given the lane last, and when -- under the device's mutex, the rest under the lane's)
-    struct Lane { void *p = nullptr; hipEvent_t done = nullptr; hipStream_t last = nullptr, owner = nullptr; bool used = false; uint64_t stamp = 0; std::mutex mu; };
-    struct Device { Lane lane[1 + kSmallLanes]; void *p = nullptr; uint64_t clock = 0; std::mutex mu; };
+    struct Lane {
+        void *p = nullptr;
+        hipEvent_t done = nullptr;
+        hipStream_t last = nullptr, owner = nullptr;
+        bool used = false, marked = false;
+        uint64_t stamp = 0;
+        unsigned long long capture = 0;
+        std::mutex mu;
+    };
+    struct Device { Lane lane[1 + kSmallLanes], captures; void *p = nullptr; uint64_t clock = 0; std::mutex mu; };
     static Device *table() { static Device t[64]; return t; }
 
     // the device's allocation, made if need be
-    static bool ready(Device &d, hipStream_t stream)
+    static bool ready(Device &d)
     {
         std::lock_guard<std::mutex> lock(d.mu);
         if (d.p) return true;
-        if (capturing(stream)) return false;                  // (an allocation would invalidate the capture)
         void *p = nullptr;
         hipEvent_t ev[1 + kSmallLanes] = {};
         bool ok = hipMalloc(&p, kSplitWsMax + kSmallLanes * kSmallLane) == hipSuccess;
@@ -397,6 +414,22 @@ private:
         }
         d.p = p;
         return true;
+    }
+    // ... and the captured calls', which a thread in relaxed mode may make during a capture
+    static bool ready_for_captures(Device &d)
+    {
+        std::lock_guard<std::mutex> lock(d.mu);
+        if (d.captures.p) return true;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return false; }
+        void *p = nullptr;
+        bool ok = hipMalloc(&p, kSplitWsMax) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(&d.captures.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+        if (!ok) (void)hipGetLastError();
+        if (!ok && p) (void)hipFree(p);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (ok) d.captures.p = p;
+        return ok;
     }
     // the small lane of this stream
     static Lane *small_lane(Device &d, hipStream_t stream)
@@ -790,7 +823,7 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
         // (32,32,3,3) 12.2 / 11.5 us, (2,32,64,64) * (128,32,3,3) 15.7 / 12.8, but 6.5 / 9.8 and 9.4 / 16 on two streams; (8,32,28,28) *
         // (256,32,3,3) 19.4 / 12.5, 10.5 / 10.5); a captured call stays independent of it, as its replays take no lease.
         ConvArgs probe{};
-        if (parts == 1 && ((F <= 128 && match_conv(g, &probe)) || capturing((hipStream_t)g.stream))) return NT_OK;
+        if (parts == 1 && ((F <= 128 && match_conv(g, &probe)) || capture_of((hipStream_t)g.stream) != 0)) return NT_OK;
         if (((F + 127) / 128) * ((M + 127) / 128) * parts < 192) tile = 64;
     } else {
         if (RS == 1) return NT_OK;

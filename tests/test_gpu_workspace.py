@@ -114,6 +114,51 @@ def test_more_streams_than_parts_of_the_workspace():
             assert np.array_equal(to_f64(outs[r][j]), ref), (r, j)
 
 
+@pytest.mark.parametrize("warm", [False, True])
+def test_calls_captured_into_a_graph(warm):
+    """Strided and unit-stride convolutions and a split product captured on two streams of one capture, with and without calls
+    on another stream before: replayed several times while the same calls run on that other stream, every result exact."""
+    dt = "f16"
+    jobs = []
+    for i, (N, Cc, hw, K, stride) in enumerate([(2, 64, 30, 96, 2), (4, 256, 14, 256, 1), (8, 32, 28, 256, 1), (2, 48, 21, 40, 2)]):
+        X, Wt = si.conv_inputs(N, Cc, hw, hw, K, 3, 3, dt, seed=70 + i, dist="int")
+        ref = onum.conv2d(X, Wt, dt, (stride, stride), (1, 1), nthreads=16)
+        jobs.append((ref, to_gpu(X, dt), lambda x, y, s, w=to_gpu(Wt, dt), st=stride: nt.conv2d_implicit(x, w, y, (st, st), (1, 1), stream=s)))
+    A, B = si.gemm_inputs(48, 640, 4096, dt, seed=75, dist="int")
+    jobs.append((onum.gemm(A, B, dt), to_gpu(A, dt), lambda x, y, s, b=to_gpu(B, dt): nt.gemm(x, b, y, stream=s)))
+    eager, main, side = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+
+    def outputs():
+        return [torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda") for ref, _, _ in jobs]
+    loose = outputs()
+    if warm:
+        for (_, x, run), y in zip(jobs, loose):
+            run(x, y, eager)
+    torch.cuda.synchronize()
+    captured, inputs = outputs(), [x.clone() for _, x, _ in jobs]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=main):
+        side.wait_stream(main)
+        for j, ((_, _, run), x, y) in enumerate(zip(jobs, inputs, captured)):
+            run(x, y, (main, side)[j % 2])
+        main.wait_stream(side)
+    for r in range(6):
+        sign = 1.0 if r % 2 == 0 else -1.0                               # (other inputs each time: nothing left from the last replay)
+        for (_, x, _), inp, y in zip(jobs, inputs, captured):
+            torch.mul(x, sign, out=inp)
+            y.fill_(float("nan"))
+        for y in loose:
+            y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(main):
+            graph.replay()
+        for (_, x, run), y in zip(jobs, loose):
+            run(x, y, eager)
+        torch.cuda.synchronize()
+        for (ref, _, _), y, z in zip(jobs, captured, loose):
+            assert np.array_equal(to_f64(y), sign * ref) and np.array_equal(to_f64(z), ref), r
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("M,N,K", [(257, 259, 131), (300, 129, 97), (129, 131, 33), (255, 255, 31)])
 def test_operand_that_ends_at_the_end_of_a_page(M, N, K, ta, tb):
