@@ -153,12 +153,12 @@ nt_status nt_arrange_conv2d(const nt_tensor_desc *dx, const nt_tensor_desc *dw, 
 nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_out);
 
 /* Which kernel the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call launched:
- * 0 operand-map (generic) kernel, or the 64 x 64 x 32 tile named by the caller, 1 staged kernel, 2 direct-to-LDS kernel (or
- * the kernel for products of at most 32 rows, which splits the reduction inside a program), 3 convolution kernel (operands staged
- * through registers), 4 convolution kernel (operands streamed straight into LDS), 5 a strided or
- * dilated convolution through the workspace (a channels-last copy, or the unfolded input, + the matrix kernels), 6 convolution kernel that streams into LDS and walks the reduction filter tap by filter
- * tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of the filter that it puts in the
- * workspace),
+ * 0 operand-map (generic) kernel, 1 staged kernel, 2 direct-to-LDS kernel (or the kernel for products of at most 32 rows,
+ * which splits the reduction inside a program; a 1 x 1 convolution that runs as a product per image reports the product's
+ * kernel), 3 convolution kernel (operands staged through registers), 4 convolution kernel (operands streamed straight into
+ * LDS), 5 unfolded input written to the workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks
+ * the reduction filter tap by filter tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of
+ * the filter that it puts in the workspace), 7 convolution on a channels-last copy of its input in the workspace,
  * -1 none (nothing launched yet, an error, or an empty problem).  For tests and diagnostics. */
 int32_t nt_last_kernel_path(void);
 

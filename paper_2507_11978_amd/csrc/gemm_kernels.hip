@@ -815,8 +815,7 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
             int alay, blay;
             if (lower_plain(u, &fa, &alay, &blay)) {
                 *taken = true;
-                if (path_out) *path_out = F > 128 ? PATH_CONV_TAP : PATH_CONV_DIRECT;
-                return route_matrix(u, fa, alay, blay, nullptr);
+                return route_matrix(u, fa, alay, blay, path_out);
             }
         }
         // Without a split route 1 needs no workspace.  Up to 128 filters it is no slower by enough to give that up ((1,32,56,56) *
@@ -866,7 +865,7 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
     a.ws = (float *)(region + copy_bytes + filter_bytes);
     a.out_dtype = g.out_dtype;
     t_k_split = parts;
-    if (path_out) *path_out = !unit ? PATH_CONV_UNFOLD : (F > 128 && RS <= 32 ? PATH_CONV_TAP : PATH_CONV_DIRECT);
+    if (path_out) *path_out = PATH_CONV_CL;
     return launch_conv_cl(a, tile, g.in_dtype == NT_BF16, s);
 }
 
@@ -1031,11 +1030,9 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     const bool direct = plain_direct || (out_ok && (alay == KCONTIG || g.K * a.lda < (1LL << 30)) && (blay == KCONTIG || g.K * a.ldb < (1LL << 30)));
     if (direct && !plain_direct)
         a.patch = (words_aligned(a.lda, a.sa_batch, a.a_extent) ? 0 : 1) | (words_aligned(a.ldb, a.sb_batch, a.b_extent) ? 0 : 2);
-    // (a caller who names the 64 x 64 x 32 tile is told path 0 whatever its operands are)
-    const bool named_small = t.bm < 128 && g.user_tile;
-    if (path_out) *path_out = named_small ? PATH_GENERIC : direct ? PATH_DIRECT : PATH_FAST;
+    if (path_out) *path_out = direct ? PATH_DIRECT : PATH_FAST;
     if (g.trace.out) {
-        if (!direct || named_small) return fail(NT_ERR_UNSUPPORTED, "this product does not run on the kernels that stream their operands into LDS");
+        if (!direct) return fail(NT_ERR_UNSUPPORTED, "this product does not run on the kernels that stream their operands into LDS");
         const int64_t rows = g.trace.operand == 0 ? t.bm : t.bn;
         if ((size_t)rows * 32 > g.trace.capacity) return fail(NT_ERR_BUFFER_TOO_SMALL, "trace buffer smaller than the slice");
         if (g.trace.program < 0 || g.trace.program >= nwg) return fail(NT_ERR_INVALID_ARG, "program_id outside the grid");

@@ -156,22 +156,24 @@ def test_conv_tile_and_split_chosen_together(shape, want_split):
 
 
 def test_full_size_conv_of_the_papers_kernel_list():
-    """(4, 512, 14, 14) * (512, 512, 3, 3) in the launch configuration bench.py times (k split over 18 programs per
-    output tile): every output against the oracle, and a second call gives the same bits."""
+    """(4, 512, 14, 14) * (512, 512, 3, 3) in the launch configuration bench.py times (on the channels-last copy, its reduction
+    split) and on the implicit kernel (the tile named; 18 programs per output tile): every output against the oracle, and a
+    second call gives the same bits."""
     cfg = si.CONFIGS["c6_f16_conv_paper"]
     N, Cc, H, W, K, R, S = (cfg[k] for k in ("N", "C", "H", "W", "K", "R", "S"))
     dt = cfg["dtype"]
     X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, cfg["seed"])
     ref = onum.conv2d(X, Wt, dt, (1, 1), (0, 0), nthreads=THREADS)
     x, w = to_gpu(X, dt), to_gpu(Wt, dt)
-    Y = torch.full(ref.shape, float("nan"), dtype=torch.float16, device="cuda")
-    Y2 = torch.full(ref.shape, float("nan"), dtype=torch.float16, device="cuda")
-    nt.conv2d_implicit(x, w, Y, (1, 1), (0, 0))
-    nt.conv2d_implicit(x, w, Y2, (1, 1), (0, 0))
-    torch.cuda.synchronize()
-    assert nt.last_kernel_path() in (nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) and nt.last_k_split() == 18
-    assert torch.equal(Y, Y2)
-    check_samples(to_f64(Y).ravel(), ref.ravel(), "f16")
+    for tile, path in ((None, nt.PATH_CONV_CL), ((256, 128, 64), nt.PATH_CONV_DIRECT)):
+        Y = torch.full(ref.shape, float("nan"), dtype=torch.float16, device="cuda")
+        Y2 = torch.full(ref.shape, float("nan"), dtype=torch.float16, device="cuda")
+        nt.conv2d_implicit(x, w, Y, (1, 1), (0, 0), tile=tile)
+        nt.conv2d_implicit(x, w, Y2, (1, 1), (0, 0), tile=tile)
+        torch.cuda.synchronize()
+        assert nt.last_kernel_path() == path and (nt.last_k_split() == 18 if tile else nt.last_k_split() > 1)
+        assert torch.equal(Y, Y2)
+        check_samples(to_f64(Y).ravel(), ref.ravel(), "f16")
 
 
 @pytest.mark.parametrize("name", ["f1_f16_addmm", "f1_f16_bias_gelu"])

@@ -73,7 +73,7 @@ def check_product(M, N, K, dt, tile, ta, tb, lda_pad=0, ldb_pad=0, batch=None):
     for pid in sorted({0, n_prog - 1, n_prog // 2}):
         i, j = (pid % (mt * ntl)) // ntl, pid % ntl
         for sl in sorted({0, n_slices - 1, n_slices // 2}):
-            k_tile, half = sl // 2, sl % 2
+            k_tile, half = sl * 32 // BK, sl * 32 % BK // 32
             for operand, view in ((0, a_arr), (1, b_arr)):
                 got = loader_offsets(kind, sha, sa, shb, sb, shc, dt, operand, pid, sl, tile=tile, want_path=nt.PATH_DIRECT)
                 o_off, o_mask, shp = arr.tile_index_set(view, pid, (k_tile,))
@@ -95,13 +95,13 @@ def check_product(M, N, K, dt, tile, ta, tb, lda_pad=0, ldb_pad=0, batch=None):
                 assert (msk[inside][:, ~k_past] == 1).all()
 
 
-@pytest.mark.parametrize("tile", [(128, 128, 64), (256, 128, 64), (128, 256, 64), (256, 256, 64)])
+@pytest.mark.parametrize("tile", [(64, 64, 32), (128, 128, 64), (256, 128, 64), (128, 256, 64), (256, 256, 64)])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 def test_full_tiles(tile, ta, tb):
     check_product(512, 768, 192, "f16", tile, ta, tb)
 
 
-@pytest.mark.parametrize("tile", [(128, 128, 64), (256, 256, 64), (128, 256, 64)])
+@pytest.mark.parametrize("tile", [(64, 64, 32), (128, 128, 64), (256, 256, 64), (128, 256, 64)])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 def test_ragged_tiles_and_odd_pitches(tile, ta, tb):
     check_product(301, 203, 151, "bf16", tile, ta, tb)             # odd pitches, every extent ragged
@@ -203,9 +203,9 @@ def test_convolution(Nn, C, H, W, F, R, S, pad, layout):
 
 def test_refusals():
     dt = "f16"
-    a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((64, 64), (64, 64), (64, 64)))
-    with pytest.raises(nt.NtError) as e:                     # a tile that the operand-map kernel runs
-        nt.trace_loader_slice("gemm", a, b, c, 0, 0, 0, tile=(64, 64, 32))
+    a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((64, 128), (64, 64), (64, 64)))
+    with pytest.raises(nt.NtError) as e:                     # rows with a step between their elements: the operand-map kernel
+        nt.trace_loader_slice("gemm", a[:, ::2], b, c, 0, 0, 0, tile=(64, 64, 32))
     assert e.value.name == "NT_ERR_UNSUPPORTED"
     a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((256, 64), (64, 256), (256, 256)))
     for bad in ((0, 4, 0), (0, 0, 2), (2, 0, 0)):

@@ -213,10 +213,14 @@ def test_addmm_fused_activation(M, N, K, tile, out, path, act):
     A = si.round_to_bits(onum.decode(A, dt).astype(np.float32) * 12.0, dt)         # spread the results over the activations' bends
     bias = torch.from_numpy(np.random.default_rng(52).standard_normal((N,)).astype(np.float32)).to(TORCH_DT[out]).cuda()
     ref = onum.addmm_act(to_f64(bias), A, B, dt, act, alpha=0.5, beta=2.0)
-    # (ragged, odd-pitched problems stream directly as well; a column-major output takes the staged kernel)
+    # (ragged, odd-pitched problems stream directly as well; a column-major output takes the staged kernel, rows with a step
+    # between their elements the operand-map kernel)
     C = torch.full((N, M), float("nan"), dtype=TORCH_DT[out], device="cuda").t() if path == "staged" else \
         torch.full((M, N), float("nan"), dtype=TORCH_DT[out], device="cuda")
-    nt.addmm(bias, to_gpu(A, dt), to_gpu(B, dt), C, alpha=0.5, beta=2.0, tile=tile, act=act)
+    a = to_gpu(A, dt)
+    if path == "generic":
+        a = torch.stack([a, a], dim=2).reshape(M, 2 * K)[:, ::2]
+    nt.addmm(bias, a, to_gpu(B, dt), C, alpha=0.5, beta=2.0, tile=tile, act=act)
     torch.cuda.synchronize()
     assert nt.last_kernel_path() == {"direct": nt.PATH_DIRECT, "staged": nt.PATH_STAGED, "generic": nt.PATH_GENERIC}[path]
     if out == "f32":
@@ -294,6 +298,12 @@ def test_bmm_small(tile):
     nt.bmm(to_gpu(A, dt), to_gpu(B, dt), C, tile=tile)
     torch.cuda.synchronize()
     assert_gates(to_f64(C), ref, "f16", f"bmm {tile}")
+    a = to_gpu(A, dt)
+    C.fill_(float("nan"))
+    nt.bmm(torch.stack([a, a], dim=3).reshape(Bn, M, 2 * K)[:, :, ::2], to_gpu(B, dt), C, tile=tile)      # a step along k: the operand-map kernel
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_GENERIC
+    assert_gates(to_f64(C), ref, "f16", f"bmm {tile}, operand map")
 
 
 def test_bmm_strided_batch_views():
@@ -335,7 +345,8 @@ def test_conv2d_small(shape, stride, pad, tile):
     ((1, 8, 8, 18, 128, 3, 3), (1, 0), (256, 128, 64)),       # padding along h only
     ((2, 64, 8, 8, 128, 1, 1), (0, 0), (256, 128, 64)),       # 1x1 filter
     ((2, 4, 9, 8, 256, 5, 3), (2, 1), (256, 256, 64)),        # 5x3 filter
-    ((5, 64, 24, 16, 256, 3, 3), (1, 1), None),               # library default tile
+    ((5, 64, 24, 16, 256, 3, 3), (1, 1), None),               # library default tile: few positions, on the channels-last copy
+    ((12, 64, 32, 32, 256, 3, 3), (1, 1), None),              # ... enough of them for this kernel
 ])
 def test_conv2d_dense_unit_stride(shape, pad, tile, dt, out):
     """Shapes the dedicated implicit-GEMM kernel takes: contiguous NCHW, stride 1 (here with Q % 8 == 0)."""
@@ -346,8 +357,11 @@ def test_conv2d_dense_unit_stride(shape, pad, tile, dt, out):
     Y = torch.full(ref.shape, float("nan"), dtype=TORCH_DT[out], device="cuda")
     nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad, tile=tile)
     torch.cuda.synchronize()
-    # whole 32-k slices (C * R * S a multiple of 32) stream straight into LDS, other reductions are staged through registers
-    assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if (Cc * R * S) % 32 == 0 else (nt.PATH_CONV,))
+    if shape[0] == 5:
+        assert nt.last_kernel_path() == (nt.PATH_CONV_CL if tile is None else nt.PATH_CONV_TAP)
+    else:
+        # whole 32-k slices (C * R * S a multiple of 32) stream straight into LDS, other reductions are staged through registers
+        assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if (Cc * R * S) % 32 == 0 else (nt.PATH_CONV,))
     assert_gates(to_f64(Y), ref, out, f"conv dense {shape} {pad} {tile}")
 
 
@@ -540,7 +554,7 @@ def test_skinny_addmm_split_along_k_applies_the_epilogue_once():
 def test_kernel_paths_are_the_intended_ones():
     """Operands with unit stride along an axis stream directly into LDS (aligned full tiles with plain loads, ragged or
     unaligned problems with range-checked ones), an output without unit stride along n takes the staged kernel, other
-    strides and tiny tiles the operand-map kernel; strided and widely padded convolutions unfold their input into the
+    strides the operand-map kernel; strided and widely padded convolutions unfold their input into the
     workspace unless the caller names a tile."""
     def path_of(M, N, K, tile=None, view=None):
         A, B = si.gemm_inputs(M, N, K, "f16", seed=1, dist="int")
@@ -564,7 +578,9 @@ def test_kernel_paths_are_the_intended_ones():
     assert path_of(501, 515, 201) == nt.PATH_DIRECT          # everything odd
     assert path_of(512, 512, 256, view="strided_c") == nt.PATH_STAGED      # C without unit stride along n
     assert path_of(512, 512, 256, view="strided_a") == nt.PATH_GENERIC
-    assert path_of(256, 256, 64, tile=(64, 64, 32)) == nt.PATH_GENERIC
+    assert path_of(256, 256, 64, tile=(64, 64, 32)) == nt.PATH_DIRECT
+    assert path_of(256, 256, 64, tile=(64, 64, 32), view="strided_a") == nt.PATH_GENERIC
+    assert path_of(256, 256, 64, tile=(64, 64, 32), view="strided_c") == nt.PATH_GENERIC    # (no staged kernel of that tile)
     X, Wt = si.conv_inputs(2, 8, 16, 16, 128, 3, 3, "f16", seed=3)
     # (unit stride with two columns of padding: the convolution kernel on a zero-padded copy of the input)
     for stride, pad, want in [((1, 1), (1, 1), nt.PATH_CONV), ((2, 2), (1, 1), nt.PATH_CONV_UNFOLD), ((1, 1), (2, 2), nt.PATH_CONV)]:
@@ -611,15 +627,17 @@ def test_conv2d_dense_rows_that_are_no_multiple_of_eight(shape, pad):
     for dt, out in (("f16", "f32"), ("bf16", "bf16")):
         X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, seed=23, dist="int")
         ref = onum.conv2d(X, Wt, dt, (1, 1), pad)
-        buf = torch.full((ref.size + 64,), float("nan"), dtype=TORCH_DT[out], device="cuda")
-        Y = buf[32:32 + ref.size].view(ref.shape)
-        nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad)
-        torch.cuda.synchronize()
-        assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if (Cc * R * S) % 32 == 0 else (nt.PATH_CONV,))
         # the sums are integers below 2^24: exact in fp32, then rounded once (to nearest even) to the output format
         want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
-        assert torch.equal(Y.cpu(), want), f"conv {shape} {pad} {dt} {out}"
-        assert torch.isnan(buf[:32]).all() and torch.isnan(buf[32 + ref.size:]).all()
+        for tile in ((256, 128, 64), None):                  # (named: on this kernel; the library's own choice may be another)
+            buf = torch.full((ref.size + 64,), float("nan"), dtype=TORCH_DT[out], device="cuda")
+            Y = buf[32:32 + ref.size].view(ref.shape)
+            nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad, tile=tile)
+            torch.cuda.synchronize()
+            if tile:
+                assert nt.last_kernel_path() == (nt.PATH_CONV_DIRECT if (Cc * R * S) % 32 == 0 else nt.PATH_CONV)
+            assert torch.equal(Y.cpu(), want), f"conv {shape} {pad} {dt} {out} {tile}"
+            assert torch.isnan(buf[:32]).all() and torch.isnan(buf[32 + ref.size:]).all()
 
 
 @pytest.mark.parametrize("shape,pad", [
@@ -638,16 +656,22 @@ def test_conv2d_dense_split_along_k(shape, pad):
     for dt, out in (("f16", "f32"), ("bf16", "bf16"), ("f16", "f16")):
         X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, seed=29, dist="int")
         ref = onum.conv2d(X, Wt, dt, (1, 1), pad)
-        big = torch.full((N, K + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
-        Y = big[:, 2:K + 2]
-        nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad)
-        torch.cuda.synchronize()
-        assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if (Cc * R * S) % 32 == 0 else (nt.PATH_CONV,))
-        assert nt.last_k_split() > 1
         # the sums are integers below 2^24: exact in fp32, then rounded once (to nearest even) to the output format
         want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
-        assert torch.equal(Y.cpu(), want), f"conv split {shape} {pad} {dt} {out}"
-        assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
+        for tile in ((256, 128, 64), (256, 256, 64), None):  # (named: on these kernels; the library's own choice: on the channels-last copy)
+            big = torch.full((N, K + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
+            Y = big[:, 2:K + 2]
+            nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad, tile=tile)
+            torch.cuda.synchronize()
+            if (Cc * R * S) % 32:
+                assert nt.last_kernel_path() == nt.PATH_CONV
+            elif tile:
+                assert nt.last_kernel_path() == (nt.PATH_CONV_TAP if tile[1] == 256 and K > 128 else nt.PATH_CONV_DIRECT)
+            elif R * S > 1:
+                assert nt.last_kernel_path() == nt.PATH_CONV_CL
+            assert nt.last_k_split() > 1
+            assert torch.equal(Y.cpu(), want), f"conv split {shape} {pad} {dt} {out} {tile}"
+            assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
 
 
 def test_conv2d_dense_split_along_k_is_reproducible():
@@ -667,19 +691,22 @@ def test_conv2d_dense_split_along_k_is_reproducible():
 
 @pytest.mark.parametrize("shape,stride,pad", [
     ((4, 32, 28, 28, 64, 3, 3), (2, 2), (1, 1)),       # the strided 3 x 3 of a residual stage
+    ((4, 16, 28, 28, 64, 3, 3), (2, 2), (1, 1)),       # the same with channels that are no whole block of 32
     ((2, 64, 14, 14, 128, 1, 1), (2, 2), (0, 0)),      # strided 1 x 1 (downsample)
     ((2, 3, 32, 32, 64, 7, 7), (2, 2), (3, 3)),        # a stem: wide padding, few channels (C R S = 147)
     ((3, 16, 12, 12, 40, 5, 5), (1, 1), (2, 2)),       # 5 x 5, padding 2
     ((2, 32, 9, 11, 72, 7, 7), (1, 1), (3, 3)),        # 7 x 7, padding 3; C R S = 1568 (whole 32-k slices)
+    ((2, 16, 9, 11, 72, 4, 6), (1, 1), (1, 2)),        # whole 32-k slices of half blocks of channels
     ((2, 8, 6, 5, 16, 3, 3), (1, 1), (0, 2)),          # padding along w only; planes of 6 x 9 = 54 elements (groups of 8 cross planes)
     ((1, 8, 3, 3, 8, 1, 1), (1, 1), (0, 0)),           # 9 positions, nothing padded (only the channels-last view takes the copy)
     ((2, 8, 9, 7, 24, 3, 2), (2, 1), (2, 1)),          # mixed strides, 49 > P Q = 35 positions per image, ragged everything
     ((1, 8, 5, 5, 16, 3, 3), (2, 2), (1, 1)),          # 9 positions per image
 ])
 def test_conv2d_through_the_workspace(shape, stride, pad):
-    """Convolutions the implicit kernels do not take as they are.  Strided ones: the unfolded input is written once into
-    the workspace and the product runs per image on the matrix kernels.  Unit-stride ones (wide padding, channels-last
-    input): a dense zero-padded copy of the input is made and the implicit kernels run on it without padding.  Small
+    """Convolutions the implicit kernels do not take as they are.  Channels in whole blocks of 32 and more than one tap: on the
+    channels-last copy.  Other strided ones: the unfolded input is written once into the workspace and the product runs per
+    image on the matrix kernels.  Other unit-stride ones (wide padding, channels-last input): a dense zero-padded copy of the
+    input is made and the implicit kernels run on it without padding.  Small
     integers: exact; NCHW and channels-last views; what lies around the output (a channel slice of a larger tensor)
     stays untouched."""
     N, Cc, H, W, K, R, S = shape
@@ -693,8 +720,10 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
             Y = big[:, 2:K + 2]
             nt.conv2d_implicit(x, to_gpu(Wt, dt), Y, stride, pad)
             torch.cuda.synchronize()
-            if stride == (1, 1):
-                assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if (Cc * R * S) % 32 == 0 else (nt.PATH_CONV,))
+            if Cc % 32 == 0 and R * S > 1:
+                assert nt.last_kernel_path() == nt.PATH_CONV_CL
+            elif stride == (1, 1):
+                assert nt.last_kernel_path() == (nt.PATH_CONV_DIRECT if (Cc * R * S) % 32 == 0 else nt.PATH_CONV)
             else:
                 assert nt.last_kernel_path() == nt.PATH_CONV_UNFOLD
             assert torch.equal(Y.cpu(), want), f"conv {shape} {stride} {pad} {dt} {out} channels_last={channels_last}"
@@ -731,7 +760,8 @@ def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
             Y = big[:, 2:K + 2]
             nt.conv2d_implicit(x, w, Y, stride, pad)
             torch.cuda.synchronize()
-            assert nt.last_kernel_path() in ((nt.PATH_CONV_DIRECT, nt.PATH_CONV_TAP) if stride == (1, 1) else (nt.PATH_CONV_UNFOLD,))
+            # (one tap over dense images: the input is the matrix already)
+            assert nt.last_kernel_path() == (nt.PATH_DIRECT if R * S == 1 and not last else nt.PATH_CONV_CL)
             assert torch.equal(Y.cpu(), want), f"conv {shape} {stride} {pad} {dt} {out} channels_last={last}"
             assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
 

@@ -46,6 +46,7 @@ def test_convolution_written_as_an_arrangement_by_the_caller(shape, stride, pad,
     ((32, 128, 20, 24, 256, 3, 3), (1, 1), (1, 1), "tap"),         # ... and the one that walks the reduction tap by tap
     ((2, 16, 21, 21, 64, 3, 3), (2, 2), (1, 1), "unfold"),        # strided: the unfolded input + the matrix kernels
     ((2, 8, 20, 20, 32, 5, 5), (1, 1), (2, 2), "padded"),         # two columns of padding: the zero-padded copy
+    ((2, 64, 21, 19, 70, 3, 3), (2, 2), (1, 1), "last"),          # channels in whole blocks of 32: the channels-last copy
 ])
 def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride, pad, want):
     """Views that address their tensors exactly like the Section 4.3 arrangement are recognised from their lowered index maps
@@ -62,7 +63,7 @@ def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride
     nt.matmul_views(x, px, w, pw, Y, py)
     torch.cuda.synchronize()
     path = nt.last_kernel_path()
-    assert path == {"direct": nt.PATH_CONV_DIRECT, "tap": nt.PATH_CONV_TAP, "unfold": nt.PATH_CONV_UNFOLD, "padded": nt.PATH_CONV}[want]
+    assert path == {"direct": nt.PATH_CONV_DIRECT, "tap": nt.PATH_CONV_TAP, "unfold": nt.PATH_CONV_UNFOLD, "padded": nt.PATH_CONV, "last": nt.PATH_CONV_CL}[want]
     assert np.array_equal(to_f64(Y), ref)
     Y2 = torch.full((N, K, P, Q), float("nan"), dtype=torch.float32, device="cuda")
     nt.conv2d_implicit(x, w, Y2, stride, pad)
@@ -74,7 +75,7 @@ def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride
                                                        ((2, 32, 16, 16, 96, 3, 3), (1, 1), (0, 0), (3, 2))])
 def test_dilated_convolution_views(shape, stride, pad, dilation):
     """The tile operation's dilation, through the public interface: against the oracle's view product and, for its element
-    offsets, the oracle's enumerator (the unfolded input + the matrix kernels run it)."""
+    offsets, the oracle's enumerator (the unfolded input + the matrix kernels run it, or the channels-last copy's)."""
     dt = "bf16"
     N, Cc, H, W, K, R, S = shape
     X, Wt = si.small_int_bits((N, Cc, H, W), dt, 16), si.small_int_bits((K, Cc, R, S), dt, 17)
@@ -82,7 +83,7 @@ def test_dilated_convolution_views(shape, stride, pad, dilation):
     Q = (W + 2 * pad[1] - (S - 1) * dilation[1] - 1) // stride[1] + 1
     px, pw, py = arr.conv2d_operand_programs(R, S, Cc, stride, pad, P, Q, H, W, dilation)
     ref = oracle_views(X, px, Wt, pw, (N, K, P, Q), py, dt)
-    for tile, want in ((None, nt.PATH_CONV_UNFOLD), ((64, 64, 32), nt.PATH_GENERIC)):
+    for tile, want in ((None, nt.PATH_CONV_CL if Cc % 32 == 0 else nt.PATH_CONV_UNFOLD), ((64, 64, 32), nt.PATH_GENERIC)):
         Y = torch.full((N, K, P, Q), float("nan"), dtype=torch.float32, device="cuda")
         nt.matmul_views(to_gpu(X, dt), px, to_gpu(Wt, dt), pw, Y, py, tile=tile)
         torch.cuda.synchronize()
@@ -91,14 +92,17 @@ def test_dilated_convolution_views(shape, stride, pad, dilation):
 
 
 @pytest.mark.parametrize("G,Cg,Kg,hw,stride,pad,dilation,want", [
-    (2, 32, 64, 24, (1, 1), (1, 1), (1, 1), "direct"),      # two groups, each on the convolution kernel
+    (2, 32, 64, 24, (1, 1), (1, 1), (1, 1), "last"),        # two groups (images of theirs are not dense), each on the channels-last copy
+    (2, 16, 64, 24, (1, 1), (1, 1), (1, 1), "padded"),      # ... each on the zero-padded copy
+    (2, 8, 64, 24, (1, 1), (2, 1), (1, 1), "direct"),       # ... with whole 32-k slices
     (4, 8, 8, 15, (2, 2), (1, 1), (1, 1), "unfold"),        # strided groups
+    (3, 32, 40, 15, (2, 2), (1, 1), (1, 1), "last"),        # ... of whole blocks of 32 channels
     (16, 1, 1, 12, (1, 1), (1, 1), (1, 1), None),            # depthwise: reduction of 9
     (3, 4, 6, 11, (1, 2), (2, 0), (2, 1), None),            # dilated groups
 ])
 def test_grouped_convolution_as_a_batched_view(G, Cg, Kg, hw, stride, pad, dilation, want):
     dt = "f16"
-    N, H, W, R, S = 2, hw, hw + 1, 3, 3
+    N, H, W, R, S = 2, hw, hw + 1, 3, 4 if want == "direct" else 3
     X, Wt = si.small_int_bits((N, G * Cg, H, W), dt, 26), si.small_int_bits((G * Kg, Cg, R, S), dt, 27)
     P = (H + 2 * pad[0] - (R - 1) * dilation[0] - 1) // stride[0] + 1
     Q = (W + 2 * pad[1] - (S - 1) * dilation[1] - 1) // stride[1] + 1
@@ -108,7 +112,7 @@ def test_grouped_convolution_as_a_batched_view(G, Cg, Kg, hw, stride, pad, dilat
     nt.matmul_views(to_gpu(X, dt), px, to_gpu(Wt, dt), pw, Y, py)
     torch.cuda.synchronize()
     if want:
-        assert nt.last_kernel_path() == {"direct": nt.PATH_CONV_DIRECT, "unfold": nt.PATH_CONV_UNFOLD}[want]
+        assert nt.last_kernel_path() == {"direct": nt.PATH_CONV_DIRECT, "unfold": nt.PATH_CONV_UNFOLD, "padded": nt.PATH_CONV, "last": nt.PATH_CONV_CL}[want]
     assert np.array_equal(to_f64(Y), ref)
     # the same views on the operand-map kernel (a tile named by the caller): one batched launch
     Y.fill_(float("nan"))

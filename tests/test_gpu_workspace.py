@@ -54,27 +54,29 @@ def test_two_streams_share_the_workspace_without_racing():
         assert np.array_equal(to_f64(yd[r]), ref_d), f"round {r}: product on stream 1"
 
 
-def test_two_streams_padded_copy_and_unfolded_routes():
-    """The same for the convolutions whose zero-padded copy or unfolded input lives in the workspace."""
-    dt = "f16"
-    Xa, Wa = si.conv_inputs(4, 32, 20, 20, 64, 5, 5, dt, seed=51, dist="int")       # padding 2: padded copy
-    Xb, Wb = si.conv_inputs(4, 32, 21, 21, 64, 3, 3, dt, seed=52, dist="int")       # stride 2: unfolded input
-    ref_a = onum.conv2d(Xa, Wa, dt, (1, 1), (2, 2), nthreads=16)
-    ref_b = onum.conv2d(Xb, Wb, dt, (2, 2), (1, 1), nthreads=16)
-    xa, wa, xb, wb = to_gpu(Xa, dt), to_gpu(Wa, dt), to_gpu(Xb, dt), to_gpu(Wb, dt)
-    rounds = 6
-    ya = [torch.full(ref_a.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(rounds)]
-    yb = [torch.full(ref_b.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(rounds)]
-    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+def test_two_streams_padded_copy_unfolded_and_channels_last_routes():
+    """The same for the convolutions whose zero-padded copy, unfolded input or channels-last copy lives in the workspace: all
+    three take turns on both streams."""
+    dt, rounds = "f16", 6
+    cases = []
+    for seed, shape, stride, pad, path in [(51, (4, 16, 20, 20, 64, 5, 5), (1, 1), (2, 2), nt.PATH_CONV), (52, (4, 24, 21, 21, 64, 3, 3), (2, 2), (1, 1), nt.PATH_CONV_UNFOLD),
+                                           (53, (4, 32, 21, 21, 64, 3, 3), (2, 2), (1, 1), nt.PATH_CONV_CL), (54, (4, 32, 20, 20, 64, 5, 5), (1, 1), (2, 2), nt.PATH_CONV_CL)]:
+        X, Wt = si.conv_inputs(*shape, dt, seed=seed, dist="int")
+        ref = onum.conv2d(X, Wt, dt, stride, pad, nthreads=16)
+        ys = [torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(2 * rounds)]
+        cases.append((to_gpu(X, dt), to_gpu(Wt, dt), stride, pad, path, ref, ys))
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
     for r in range(rounds):
-        nt.conv2d_implicit(xa, wa, ya[r], (1, 1), (2, 2), stream=s1)
-        nt.conv2d_implicit(xb, wb, yb[r], (2, 2), (1, 1), stream=s2)
-        assert nt.last_kernel_path() == nt.PATH_CONV_UNFOLD
+        for i in range(len(cases)):
+            for s in range(2):                                            # stream 0 at case i, stream 1 at the one after it
+                x, w, stride, pad, path, _, ys = cases[(i + s) % len(cases)]
+                nt.conv2d_implicit(x, w, ys[2 * r + s], stride, pad, stream=streams[s])
+                assert nt.last_kernel_path() == path
     torch.cuda.synchronize()
-    for r in range(rounds):
-        assert np.array_equal(to_f64(ya[r]), ref_a), f"round {r}: padded copy"
-        assert np.array_equal(to_f64(yb[r]), ref_b), f"round {r}: unfolded input"
+    for _, _, stride, pad, path, ref, ys in cases:
+        for r, y in enumerate(ys):
+            assert np.array_equal(to_f64(y), ref), (r, path, stride)
 
 
 def test_more_streams_than_parts_of_the_workspace():
