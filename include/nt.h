@@ -364,14 +364,17 @@ nt_status nt_trace_tile(int32_t kind, const nt_tensor_desc *d0, const nt_tensor_
  * source element the loader put there, and zero where it fed a zero: compare with nt_arrange_* / the arrangement.
  * A, B: device pointers, read.  dC: the output's descriptor (shape only; nothing is stored).  values_out: DEVICE array of
  * `capacity` entries, at least 32 * (tile rows of the operand).  Only launches that stream their operands straight into LDS
- * (nt_last_kernel_path() 2, 4 or 6 for the same arguments) can be traced: otherwise NT_ERR_UNSUPPORTED.  The ring-unrolled
+ * (nt_last_kernel_path() 2, 4, 6 or 7 for the same arguments) can be traced: otherwise NT_ERR_UNSUPPORTED.  The ring-unrolled
  * variant of the 256 x 256 kernel and its persistent form (one workgroup walking several programs) have the same per-lane
  * offsets and slice stepping as the kernel traced here.
  * A product of at most 32 rows may run on a kernel that loads its fragments through registers; what is traced then is the
  * direct-to-LDS kernel that the same arguments run on when the caller names the tile.
  * Path 6 may run tile rows of two heights (the first ones 256 or 224 positions, the rest 32 fewer; tile row i starts where
  * the tile rows before it end): the rows of values_out past the traced program's height are left untouched.
- * Path 6 sums over the reduction index in another order than the arrangement lists it: its slice s, index kk is channel
+ * Path 7 has tiles of 64 or of 128 positions and as many filters; rows past the tile are left untouched.  A 1 x 1 convolution
+ * that runs as a product per image (path 2) has programs image * mt * nt + i * nt + j for tile i of filters and j of the
+ * image's positions; operand A is still the input.
+ * Paths 6 and 7 sum over the reduction index in another order than the arrangement lists it: their slice s, index kk is channel
  * c = 32 (s % (C / 32)) + kk of filter tap t = s / (C / 32), i.e. the arrangement's k = c * R * S + t.
  */
 nt_status nt_trace_loader_slice(int32_t kind, const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,

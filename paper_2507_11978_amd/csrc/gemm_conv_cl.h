@@ -20,6 +20,9 @@ struct ConvClArgs {
     int32_t ksplit, per;           // parts of the reduction, 32-k slices per part (ksplit 1: all of them)
     float *ws;                     // ksplit > 1: the parts, fp32, [part][f][m]
     int out_dtype;
+    uint16_t *trace_out;           // loader trace (gemm_direct16.h): program i * mt + j for tile i of positions and j of filters
+    int64_t trace_program;
+    int32_t trace_slice, trace_operand;
 };
 
 // What the copies are made from.  Copy position (hc, wc) is input position (hc * eh - ph, wc * ew - pw).
@@ -37,5 +40,7 @@ struct ConvClCopy {
 nt_status launch_conv_cl_copy(const ConvClCopy &c, hipStream_t s);
 // tile: 64 (x 64) or 128 (x 128)
 nt_status launch_conv_cl(const ConvClArgs &a, int tile, bool bf16, hipStream_t s);
+// the loader trace of the same kernel: one workgroup
+nt_status launch_conv_cl_trace(const ConvClArgs &a, int tile, hipStream_t s);
 
 }  // namespace nt

@@ -73,7 +73,8 @@ __global__ __launch_bounds__(256) void conv_cl_copy_kernel(const ConvClCopy g, i
 }
 
 // One program: BT filters x BT positions (and, with a k split, one part of the reduction).  The loop is gemm_direct16_kernel's.
-template <int BT, bool BF16>
+// TRACE: see gemm_direct16_kernel.
+template <int BT, bool BF16, bool TRACE = false>
 __global__ __launch_bounds__(kThreads, 2) void gemm_conv_cl_kernel(const ConvClArgs g)
 {
     constexpr int TM = BT / 32, TN = BT / 32, kRing = ring_of(BT, BT);
@@ -84,13 +85,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_conv_cl_kernel(const ConvClA
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const uint32_t mt = (uint32_t)g.mt, nt_ = (uint32_t)g.nt, grid = mt * nt_;
-    const uint32_t part = blockIdx.x / grid;
-    const uint32_t pid = program_of_workgroup_t<uint32_t>(blockIdx.x - part * grid, mt, nt_);
+    const uint32_t part = TRACE ? 0u : blockIdx.x / grid;
+    const uint32_t pid = TRACE ? (uint32_t)(g.trace_program % mt * nt_ + g.trace_program / mt) : program_of_workgroup_t<uint32_t>(blockIdx.x - part * grid, mt, nt_);
     const uint32_t ti = pid / nt_;
     const int32_t row0 = __builtin_amdgcn_readfirstlane((int)ti) * BT, col0 = __builtin_amdgcn_readfirstlane((int)(pid - ti * nt_)) * BT;
 
     const int32_t all = g.K / kSliceK;
-    const int32_t first = __builtin_amdgcn_readfirstlane((int)part) * g.per;
+    const int32_t first = TRACE ? g.trace_slice : __builtin_amdgcn_readfirstlane((int)part) * g.per;
     const int32_t n_slices = first + g.per < all ? g.per : all - first;
 
     Tile ta, tb;
@@ -149,6 +150,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_conv_cl_kernel(const ConvClA
         if (d < Tile::PER) ta.issue_one(d, pa, lds0 + ring * T_BYTES, wave);
         else tb.issue_one(d - Tile::PER, pb, lds0 + B_BASE + ring * T_BYTES, wave);
     };
+    if constexpr (TRACE) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d) dma(d, 0);
+        NT_WAIT_VMCNT(0);
+        __syncthreads();
+        for (int e = tid; e < BT * kSliceK; e += kThreads)
+            g.trace_out[e] = *reinterpret_cast<const uint16_t *>(smem + (g.trace_operand == 0 ? B_BASE : 0u) + Tile::place(e / kSliceK, e % kSliceK));
+        return;
+    }
     auto trip = [&](auto set_c, uint32_t rring, uint32_t dring) {
         constexpr int set = decltype(set_c)::value;
         constexpr int RS = NM * 3 / 4;
@@ -306,19 +316,24 @@ nt_status launch_conv_cl_copy(const ConvClCopy &c, hipStream_t s)
     return check_launch("conv_cl_copy_kernel");
 }
 
-template <int BT, bool BF16>
+template <int BT, bool BF16, bool TRACE = false>
 static nt_status launch_conv_cl_t(const ConvClArgs &a, hipStream_t s)
 {
     constexpr size_t smem = (size_t)ring_of(BT, BT) * 2 * BT * kSliceK * sizeof(uint16_t);
-    auto kern = gemm_conv_cl_kernel<BT, BF16>;
+    auto kern = gemm_conv_cl_kernel<BT, BF16, TRACE>;
     static DeviceOnce configured;
     if (!configured.done()) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
         configured.set();
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.mt * a.nt * a.ksplit)), dim3(kThreads), smem, s, a);
+    hipLaunchKernelGGL(kern, dim3(TRACE ? 1u : (unsigned)(a.mt * a.nt * a.ksplit)), dim3(kThreads), smem, s, a);
     return check_launch("gemm_conv_cl_kernel");
+}
+
+nt_status launch_conv_cl_trace(const ConvClArgs &a, int tile, hipStream_t s)
+{
+    return tile == 64 ? launch_conv_cl_t<64, false, true>(a, s) : launch_conv_cl_t<128, false, true>(a, s);
 }
 
 nt_status launch_conv_cl(const ConvClArgs &a, int tile, bool bf16, hipStream_t s)

@@ -790,7 +790,7 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
 {
     *taken = false;
     const ConvHint &h = g.conv;
-    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.ys[3] != 1 || h.ys[2] != h.Q || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
+    if (!conv_is_bare(g) || h.C % 32 != 0 || h.ys[3] != 1 || h.ys[2] != h.Q || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
     const int64_t RS = h.R * h.S, K = h.C * RS, PQ = h.P * h.Q, M = h.N * PQ, F = h.K;
     const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1;
     if (M >= (1LL << 30) || F >= (1LL << 22) || K > 32768 || F * K >= (1LL << 30)) return NT_OK;
@@ -810,7 +810,9 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
         // a copy buys nothing there.)
         if (RS == 1 && parts > 1) return NT_OK;
         if (RS == 1 && h.ph == 0 && h.pw == 0 && natural && h.xs[3] == 1 && h.xs[2] == h.W && h.xs[0] >= 0 && PQ >= 8) {
-            const GemmLaunch u = per_image_product(g, g.A, h.C, h.xs[1], h.xs[0]);
+            GemmLaunch u = per_image_product(g, g.A, h.C, h.xs[1], h.xs[0]);
+            u.trace = g.trace;
+            u.trace.operand = 1 - g.trace.operand;           // (the product's A is the filter)
             FastArgs fa{};
             int alay, blay;
             if (lower_plain(u, &fa, &alay, &blay)) {
@@ -864,8 +866,15 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
     a.ksplit = parts; a.per = (int32_t)per;
     a.ws = (float *)(region + copy_bytes + filter_bytes);
     a.out_dtype = g.out_dtype;
-    t_k_split = parts;
     if (path_out) *path_out = PATH_CONV_CL;
+    if (g.trace.out) {
+        if ((size_t)tile * 32 > g.trace.capacity) return fail(NT_ERR_BUFFER_TOO_SMALL, "trace buffer smaller than the slice");
+        if (g.trace.program < 0 || g.trace.program >= (int64_t)a.mt * a.nt) return fail(NT_ERR_INVALID_ARG, "program_id outside the grid");
+        if (g.trace.slice < 0 || g.trace.slice >= K / 32) return fail(NT_ERR_INVALID_ARG, "slice outside the reduction");
+        a.trace_out = g.trace.out; a.trace_program = g.trace.program; a.trace_slice = g.trace.slice; a.trace_operand = g.trace.operand;
+        return launch_conv_cl_trace(a, tile, s);
+    }
+    t_k_split = parts;
     return launch_conv_cl(a, tile, g.in_dtype == NT_BF16, s);
 }
 

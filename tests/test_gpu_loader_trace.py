@@ -201,6 +201,71 @@ def test_convolution(Nn, C, H, W, F, R, S, pad, layout):
                 assert np.array_equal(got[r], B_ref[ks, f]), ((Nn, C, H, W, F, R, S, pad), "w", pid, sl, r)
 
 
+@pytest.mark.parametrize("Nn,C,H,W,F,R,S,stride,pad,layout", [
+    (3, 64, 14, 14, 256, 3, 3, (1, 1), (1, 1), "kcrs"),       # unit stride, few positions; padding on every side
+    (2, 96, 13, 11, 70, 3, 3, (2, 1), (1, 1), "kcrs"),        # mixed strides, channels in one and a half tiles of the copy, ragged filters
+    (2, 64, 12, 13, 130, 3, 2, (2, 2), (0, 1), "krsc"),       # a channels-last filter, read as it is
+    (2, 64, 20, 18, 128, 1, 3, (2, 2), (0, 1), "kcrs"),       # one tap along h: the copy holds the rows that are read
+    (32, 64, 40, 40, 256, 3, 3, (2, 2), (1, 1), "kcrs"),      # the 128 x 128 tile
+    (2, 96, 9, 8, 72, 1, 1, (1, 1), (0, 0), "kcrs"),          # one tap over dense images: a product per image
+])
+def test_convolution_on_the_channels_last_copy(Nn, C, H, W, F, R, S, stride, pad, layout):
+    """The library's own choice for channels in whole blocks of 32: tiles of 64 or 128 positions and filters, the reduction tap by
+    tap, what the copy put in place of the padding."""
+    dt = "f16"
+    P, Q = (H + 2 * pad[0] - R) // stride[0] + 1, (W + 2 * pad[1] - S) // stride[1] + 1
+    K, M, cb = C * R * S, Nn * P * Q, C // 32
+    shx, shw, shy = (Nn, C, H, W), (F, C, R, S), (Nn, F, P, Q)
+    sx, sw = contiguous(shx), contiguous(shw) if layout == "kcrs" else (R * S * C, 1, S * C, C)
+    a_arr, b_arr, _ = arr.conv2d_arrangement(arr.Tensor(shx), arr.Tensor(shw, sw), arr.Tensor(shy), 64, 64, 64, stride, pad)
+    mto, nto, kto = -(-M // 64), -(-F // 64), -(-K // 64)
+
+    def trace(operand, pid, sl):
+        return loader_offsets("conv2d", shx, sx, shw, sw, shy, dt, operand, pid, sl, stride=stride, pad=pad,
+                              want_path=nt.PATH_DIRECT if R * S == 1 else nt.PATH_CONV_CL)
+    BT = int((trace(0, 0, 0)[:, 0] != -2).sum())
+    assert BT == (128 if Nn == 32 else 64)
+    PQ = P * Q
+    if R * S == 1:                                            # program (image, tile of filters, tile of its positions)
+        ft, pt = -(-F // BT), -(-PQ // BT)
+        tiles = [(b, i, j) for b in range(Nn) for i in range(ft) for j in range(pt)]
+    else:                                                     # program (tile of positions, tile of filters)
+        ft, pt = -(-F // BT), -(-M // BT)
+        tiles = [(0, j, i) for i in range(pt) for j in range(ft)]
+    with pytest.raises(nt.NtError):
+        trace(0, len(tiles), 0)
+    with pytest.raises(nt.NtError):
+        trace(0, 0, K // 32)
+    wcols = whole_matrix(b_arr, mto, nto, kto, lambda t: t, False)[:K, :]
+    for pid in sorted({0, len(tiles) // 2, len(tiles) - 1}):
+        b, i, j = tiles[pid]
+        for sl in sorted({0, 1, K // 64, K // 32 - 1}):
+            ks = (32 * (sl % cb) + np.arange(32)) * (R * S) + sl // cb
+            got_x, got_w = trace(0, pid, sl), trace(1, pid, sl)
+            assert (got_x[BT:] == -2).all() and (got_w[BT:] == -2).all()
+            for r in range(BT):
+                if i * BT + r < F:
+                    assert np.array_equal(got_w[r], wcols[ks, i * BT + r]), ("w", pid, sl, r)
+                m = j * BT + r
+                if m < (PQ if R * S == 1 else M):
+                    m += b * PQ
+                    n, p, q = m // PQ, m % PQ // Q, m % Q
+                    h, w = p * stride[0] - pad[0], q * stride[1] - pad[1]
+                    t = sl // cb
+                    hh, ww = h + t // S, w + t % S
+                    c = 32 * (sl % cb) + np.arange(32)
+                    want = ((n * C + c) * H + hh) * W + ww if 0 <= hh < H and 0 <= ww < W else np.full(32, -1)
+                    assert np.array_equal(got_x[r], want), ("x", pid, sl, r)
+    # (the positions' closed form above is the arrangement's: one tile of it, element by element)
+    off, _, shp = arr.tile_index_set(a_arr, 0, (0,))
+    off = off.reshape(shp)
+    for r in range(min(64, M)):
+        n, p, q = r // PQ, r % PQ // Q, r % Q
+        for k in range(min(64, K)):
+            c, hh, ww = k // (R * S), p * stride[0] - pad[0] + k % (R * S) // S, q * stride[1] - pad[1] + k % S
+            assert off[r, k] == (((n * C + c) * H + hh) * W + ww if 0 <= hh < H and 0 <= ww < W else -1)
+
+
 def test_refusals():
     dt = "f16"
     a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((64, 128), (64, 64), (64, 64)))

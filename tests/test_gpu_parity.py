@@ -737,7 +737,8 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
     ((2, 64, 20, 18, 128, 1, 3), (2, 2), (0, 1)),      # one tap along h: the copy holds the rows that are read
     ((9, 32, 7, 7, 33, 7, 7), (2, 2), (3, 3)),         # 49 slices, 16 positions per image
     ((1, 160, 6, 5, 8, 2, 2), (2, 2), (0, 0)),         # 6 positions in all, 8 filters
-    ((32, 64, 30, 30, 256, 3, 3), (2, 2), (1, 1)),     # enough programs for the 128 x 128 tile
+    ((32, 64, 30, 30, 256, 3, 3), (2, 2), (1, 1)),     # many programs of 64 x 64
+    ((32, 64, 40, 40, 256, 3, 3), (2, 2), (1, 1)),     # enough positions for the 128 x 128 tile
     ((2, 64, 7, 7, 300, 3, 3), (1, 1), (1, 1)),        # unit stride, few positions: odd rows of 7
     ((3, 32, 5, 6, 40, 1, 1), (1, 1), (0, 0)),         # one slice
 ])
