@@ -557,6 +557,18 @@ static bool few_queries(int64_t heads, int64_t queries)
 nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
 {
     if (batch <= 0 || a.H <= 0 || a.Sq <= 0) return NT_OK;
+    const int64_t per_entry = a.H * (((int64_t)a.Sq + kQBlock - 1) / kQBlock);
+    if (batch * per_entry > kMaxWorkgroups && batch > 1 && per_entry <= kMaxWorkgroups) {
+        // more programs than one launch holds (few queries: as many, one workgroup per head): in several
+        const int64_t most = kMaxWorkgroups / per_entry;
+        for (int64_t b0 = 0; b0 < batch; b0 += most) {
+            SdpaArgs part = a;
+            part.Q += b0 * a.q_sb; part.K += b0 * a.k_sb; part.V += b0 * a.v_sb; part.O += b0 * a.o_sb;
+            const nt_status st = launch_sdpa(part, std::min(most, batch - b0), bf16, stream);
+            if (st != NT_OK) return st;
+        }
+        return NT_OK;
+    }
     if (few_queries(batch * a.H, a.Sq)) {
         SdpaArgs k = a;
         k.BH = (int32_t)(batch * a.H);
@@ -574,7 +586,7 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
         return check_launch("sdpa_decode_kernel");
     }
     const int64_t bh = batch * a.H, nqb = (a.Sq + kQBlock - 1) / kQBlock;
-    if (bh * nqb > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "batch * heads * query blocks exceeds 2^31 - 1");
+    if (bh * nqb > kMaxWorkgroups) return fail(NT_ERR_UNSUPPORTED, "heads * query blocks exceeds 2^24 - 1");
     SdpaArgs k = a;
     k.BH = (int32_t)bh;
     k.nqb = (int32_t)nqb;

@@ -297,10 +297,7 @@ nt_status launch_map(int op, const void *x, int64_t sx, const void *y, int64_t s
     return check_launch("map_strided_kernel");
 }
 
-// A launch has fewer than 2^32 work-items along a dimension (of more, the runtime starts the remainder modulo 2^32 and reports no
-// error): 2^24 - 1 workgroups of 256.  More rows than those hold go out in several launches.
-constexpr int64_t kMaxWorkgroups = (1 << 24) - 1;
-
+// (more rows than the workgroups of one launch hold go out in several)
 template <int OP, int NV, int WPR, bool EDGES>
 static nt_status launch_row_wave(const uint16_t *x, int64_t sxr, uint16_t *out, int64_t sor, int64_t rows, int64_t cols, float eps, bool bf16, hipStream_t s)
 {

@@ -1094,6 +1094,23 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
 {
     if (!g.no_workspace || g.ws_strict) t_k_split = 1;
     if (g.batch * g.mt * g.nt > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "grid too large");
+    if (g.batch * g.mt * g.nt > kMaxWorkgroups && !g.trace.out) {
+        // more programs than one launch holds: a batch goes out in several
+        const int64_t most = kMaxWorkgroups / (g.mt * g.nt);
+        if (g.batch == 1 || most < 1) return fail(NT_ERR_UNSUPPORTED, "grid too large");
+        const int64_t esz = g.out_dtype == NT_F32 ? 4 : 2;
+        for (int64_t b0 = 0; b0 < g.batch; b0 += most) {
+            GemmLaunch part = g;
+            part.batch = std::min(most, g.batch - b0);
+            part.A = (const char *)g.A + b0 * g.sa_batch * 2;
+            part.B = (const char *)g.B + b0 * g.sb_batch * 2;
+            part.C = (char *)g.C + b0 * g.sc_batch * esz;
+            if (g.has_d) part.D = (const char *)g.D + b0 * g.sd_batch * esz;
+            const nt_status st = launch_gemm(part, path_out);
+            if (st != NT_OK) return st;
+        }
+        return NT_OK;
+    }
     FastArgs a{};
     int alay = KCONTIG, blay = MNCONTIG;
     if (lower_plain(g, &a, &alay, &blay)) return route_matrix(g, a, alay, blay, path_out);

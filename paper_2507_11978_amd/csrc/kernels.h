@@ -19,6 +19,10 @@ struct ConvHint {
     int64_t xs[4], ws[4], ys[4];
 };
 
+// Workgroups of 256 threads that one launch holds: it has fewer than 2^32 work-items along a dimension (of more, the runtime starts
+// the remainder modulo 2^32 and reports no error).
+constexpr int64_t kMaxWorkgroups = (1 << 24) - 1;
+
 // Request for a loader trace instead of a product (nt_trace_loader_slice); out == nullptr: none.
 struct LoaderTrace {
     uint16_t *out;

@@ -226,3 +226,24 @@ def test_keys_dealt_to_groups_with_references_far_apart(dt, B, H, Sq, Sk):
         kb = si.round_to_bits(np.ascontiguousarray(np.broadcast_to(kf, (B, H, Sk, 64))), dt)
         for scale in (0.125, -0.125):
             assert_gates(run(qb, kb, vb, dt, scale=scale), oat.sdpa(qb, kb, vb, dt, scale=scale), dt, f"sdpa {dt} {H} heads {per_block} {scale}")
+
+
+@pytest.mark.parametrize("Sq", [1, 3])
+def test_more_heads_than_one_launch_holds(Sq):
+    """2^24 + 32768 heads: with one key every query's result is its head's value row."""
+    B, H = 513, 32768
+    vc = (torch.arange(H, device="cuda") % 251).to(torch.bfloat16).reshape(1, H, 1, 1).expand(1, H, 1, 64).contiguous().expand(B, H, 1, 64)
+    one = torch.zeros((1, 1, 1, 64), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty((B, H, Sq, 64), dtype=torch.bfloat16, device="cuda").fill_(float("nan"))
+    nt.sdpa(one.expand(B, H, Sq, 64), one.expand(B, H, 1, 64), vc, out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(out[b], vc[b].expand(H, Sq, 64)) for b in (0, 1, 510, 511, 512))
+
+
+def test_few_queries_weigh_in_fp32():
+    """One query per head: scores, weights and sums stay in fp32, so all but a few results are the fp64 result rounded once."""
+    B, H, Sk = 2, 24, 2047
+    q, k, v = (si.normal_bits((B, H, n, 64), "bf16", 140 + i, 1.0) for i, n in enumerate([1, Sk, Sk]))
+    want = torch.from_numpy(oat.sdpa(q, k, v, "bf16")).to(torch.bfloat16)
+    got = torch.from_numpy(run(q, k, v, "bf16")).to(torch.bfloat16)
+    assert (got != want).float().mean() < 0.01                       # (a result within fp32 error of the middle between two)

@@ -468,6 +468,18 @@ def test_few_columns_and_a_long_reduction_are_dealt_to_the_whole_chip(M, N, K, t
         assert torch.equal(C.cpu(), want)
 
 
+@pytest.mark.parametrize("step", [1, 2])
+def test_batches_of_more_programs_than_one_launch_holds(step):
+    """2^24 + 4 batch entries of one program each, on the matrix kernel and (a step along k) on the operand-map kernel."""
+    Bn, K = 2**24 + 4, 8
+    a = torch.ones((1, 1, K * step), dtype=torch.float16, device="cuda")[..., ::step].expand(Bn, 1, K)
+    b = torch.randint(-3, 4, (Bn + K,), device="cuda", dtype=torch.int8).to(torch.float16)
+    C = torch.full((Bn, 1, 1), float("nan"), dtype=torch.float16, device="cuda")
+    nt.bmm(a, b.as_strided((Bn, K, 1), (1, 1, 1)), C)                     # entry i: b[i] + ... + b[i + 7]
+    torch.cuda.synchronize()
+    assert torch.equal(C.view(-1), b.unfold(0, K, 1)[:Bn].sum(dim=1, dtype=torch.float32).to(torch.float16))
+
+
 def test_products_of_few_rows_with_a_very_long_axis():
     """More columns than 2^32 work-items serve, a reduction beyond 32 bits (the operands' rows overlap: they need little memory)."""
     N, K = 2**27 + 21, 64
