@@ -285,7 +285,9 @@ nt_status nt_matmul_views(const void *A, const nt_tensor_desc *dA, const nt_meta
  * (no mask, no dropout), computed with the FlashAttention-2 scheme the paper's sdpa kernels use (Section 5.1):
  * Q and O tiled into blocks of query rows (one program per batch, head and block), K and V into blocks of keys
  * that every program visits in turn with a running maximum and sum; scores and sums in fp32, the probabilities
- * rounded to the 16-bit format before they multiply V.  All four tensors are device pointers to 16-bit elements
+ * rounded to the 16-bit format before they multiply V (a single query per head, and up to 32 where heads x queries <= 256,
+ * keeps them in fp32: one program per query, the keys dealt out to its wavefronts).  A key whose score is -inf has weight 0; a
+ * query all of whose scores are -inf gives NaN.  All four tensors are device pointers to 16-bit elements
  * of `dtype` (NT_F16 or NT_BF16) with descriptors [batch, heads, seq, 64]: any strides along the first three axes,
  * unit stride along the last; other head sizes: NT_ERR_UNSUPPORTED.  K and V share their sequence length (>= 1),
  * Q and O theirs.  scale = 0 stands for 1 / sqrt(64).  O must not alias an input.

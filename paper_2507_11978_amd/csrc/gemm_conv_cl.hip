@@ -7,8 +7,9 @@
 // GEMM kernel, every load 16-byte aligned, no padding test, no fix-up, and positions of several images in one tile.
 // The price is one pass over the input (read once, written once, in the workspace) instead of the unfolded input's R S.
 //
-// Measured, (32,128,56,56) * (256,128,3,3) stride 2 fp16: copy 13.8 us (51 MB moved), product 27.5 us (14.8 GFLOP on 392
-// programs, bound by two co-resident programs' loads), 39.0 us a call; through the unfolded input 38 + 24 us, 63.8 a call.
+// Measured, (32,128,56,56) * (256,128,3,3) stride 2 fp16: copy 13.2 us (51 MB moved), product 26.1 us (14.8 GFLOP on 392
+// programs, bound by two co-resident programs' loads; kernel trace, one launch at a time), 39.1 us a call back to back; through the
+// unfolded input 38 + 24 us, 63.9 a call.
 #include "gemm_conv_cl.h"
 
 #include "gemm_direct16.h"

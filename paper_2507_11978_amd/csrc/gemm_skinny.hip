@@ -10,9 +10,9 @@
 // A step is 64 k.  A 16-byte load instruction that fetches matrix fragments directly (16 rows, 32 k) touches 16 cache lines
 // and uses half of each; here it fetches 8 rows of 64 k, whole lines, and the wavefront turns the step's 16 x 64 blocks round
 // in an LDS region of its own (chunk c of row r at chunk c ^ (r % 8); LDS operations of one wavefront complete in order, so
-// no barrier).  Measured at 16 x 4096 x 4096 fp16, device time: 8.1 us (4.2 TB/s), 10.0 us with fragments fetched directly,
-// 10.9 us as two launches (a k split of 64 x 64 tiles and the kernel that adds the parts); 16 x 8192 x 8192 26.6 us (5.0
-// TB/s, a large copy's rate) against 32.5.  Two batches of U steps are in flight per wavefront; U = 4 measured no better.
+// no barrier).  Measured at 16 x 4096 x 4096 fp16: 7.6 us a call over rotating weights (4.4 TB/s); in graph replays, gaps between
+// the nodes included, 8.1 us, 10.0 with fragments fetched directly, 10.9 as two launches (a k split of 64 x 64 tiles and the
+// kernel that adds the parts); 16 x 8192 x 8192 26.6 us (5.0 TB/s, a large copy's rate) against 32.5.  Two batches of U steps are in flight per wavefront; U = 4 measured no better.
 #include "gemm_skinny.h"
 
 namespace nt {

@@ -157,6 +157,28 @@ def test_key_blocks_of_every_kind_of_rows(dt, Sk):
     assert torch.equal(o3, o4)
 
 
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("Sk", [65, 321, 833])
+def test_keys_spread_over_more_than_two_gigabytes(dt, Sk):
+    """A pitch at which a head's keys reach past the range-checked loads' offsets: through registers, one group whatever the number
+    of blocks; the same as from a copy of theirs (13 blocks of the copy are dealt out to groups)."""
+    H, Sq, pitch = 3, 130, (1 << 30) // (Sk + 640) + 7                 # elements
+    q, k, v = (to_gpu(si.normal_bits((1, H, n, 64), dt, 150 + i, 1.0), dt) for i, n in enumerate([Sq, Sk, Sk]))
+    buf = torch.zeros(((Sk - 1) * pitch + 2 * H * 64,), dtype=TORCH_DT[dt], device="cuda")
+    far = [buf[i * H * 64:].as_strided((1, H, Sk, 64), (0, 64, pitch, 1)) for i in range(2)]
+    for dst, src in zip(far, (k, v)):
+        dst.copy_(src)
+    got, near, ref = (torch.full_like(q, float("nan")) for _ in range(3))
+    nt.sdpa(q, far[0], far[1], got)
+    nt.sdpa(q, far[0], v, near)
+    nt.sdpa(q, k, v, ref)
+    torch.cuda.synchronize()
+    assert torch.equal(got, near)
+    if Sk < 705:
+        assert torch.equal(got, ref)
+    assert_gates(to_f64(got), to_f64(ref), dt, f"sdpa keys of pitch {pitch}")
+
+
 # how the keys are dealt out follows from the number of (head, query block) programs and of key blocks: one group of wavefronts
 # walks them, four groups share them, two groups do, a workgroup per query
 WALKS = [(2, 3, 130, 640), (1, 3, 130, 1024), (1, 150, 130, 832), (1, 3, 1, 1024)]
