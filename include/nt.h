@@ -183,8 +183,8 @@ int32_t nt_tile_supported(nt_tile_cfg cfg);
  * through the library's workspace, the same one, under the same rules, as described at nt_conv2d_implicit
  * (one allocation per GPU, made by the first call that needs it, handed from call to call in stream
  * order; partial tiles added in a fixed order).  At most 16 rows (32 on 16-byte aligned rows) of operands with unit
- * stride along k need none of it unless few columns meet a very long reduction (16 x 64 x 16384): their reduction is
- * split inside a program.
+ * stride along k need none of it unless few columns meet a very long reduction (16 x 64 x 16384) or very many columns a
+ * short one: their reduction is split inside a program.
  */
 nt_status nt_gemm(const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                   void *C, const nt_tensor_desc *dC, nt_dtype in_dtype, nt_dtype out_dtype,

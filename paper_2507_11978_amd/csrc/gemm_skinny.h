@@ -4,7 +4,7 @@
 
 namespace nt {
 
-// whether the kernel takes this (unbatched) product, and is a faster one for it than the 64 x 64 tile unsplit
+// whether the kernel takes this (unbatched) product, and is a faster one for it than tiles without a k split
 bool skinny_ok(const FastArgs &a, int alay, int blay);
 // estimate of its time (us), to be weighed against a k split of tiles
 double skinny_cost(const FastArgs &a);

@@ -154,25 +154,34 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_skinny_kernel(const Fa
     }
 }
 
-// One block of rows: whatever the alignment (7 x 2001 x 1333 5.8 us against 8.4 on 64 x 64 tiles; 16 x 1024 x 1024 3.2 / 6.9).
-// Two: 16-byte aligned rows only, 32 x 4096 x 4096 8.7 / 11.4 us; with more rows the reads of A, which every program repeats,
-// outweigh the saved launch (64 x 1024 x 8192 17.9 / 10.5; 33 x 5000 x 2047, odd pitches, 17.6 / 12.4).
+// Where this kernel is ahead of the tiles (us over rotating weights, fp16, this kernel / tiles).  One block of rows, 16-byte
+// aligned: up to 12288 columns always (16 x 12288 x 128 4.0 / 3.9, x 4096 20.8 / 23.6); with more, each of whose programs costs a
+// workgroup's start, from K = 1024 on (16 x 65536 x 128 11.9 / 7.4, x 512 22 / 17, x 1024 30 / 30, x 4096 101 / 128; 16 x 16384 x
+// 1024 8.9 / 8.6), at most 65536 of them above 8 rows (16 x 128256 x 4096 197 / 187, 1 row 164 / 183).  Unaligned rows, whose loads
+// cost four times as much: up to 4096 columns (16 x 4000 x 2001 7.4 / 10.7), 8192 with K >= 1000 (16 x 8000 x 511 6.6 / 5.4, x 1001
+// 6.7 / 7.3, 16 x 16384 x 2001 24.6 / 17.1), and not the shortest reductions (x 127 4.4 / 3.9).  Two blocks: aligned, up to
+// 8192 columns (32 x 8192 x 4096 18.3 / 21.6, 32 x 16384 x 4096 33.9 / 31.7, 32 x 65536 x 512 26 / 18); with more rows the reads of
+// A, which every program repeats, outweigh the saved launch (64 x 1024 x 8192 17.9 / 10.5).
 bool skinny_ok(const FastArgs &a, int alay, int blay)
 {
     // (k in 32 bits; fewer than 2^32 work-items in the launch, of more the runtime starts the remainder only)
     if (alay != KCONTIG || blay != KCONTIG || a.M > 32 || a.K < kSkinnyStep || a.K > (1 << 30) || a.N > (1 << 26)) return false;
     auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    return a.M <= 16 || (al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0);
+    const bool aligned = al16(a.A) && al16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0;
+    if (a.M > 16) return aligned && a.N <= 8192;
+    if (!aligned) return a.K >= 256 && (a.N <= 4096 || (a.N <= 8192 && a.K >= 1000));
+    return a.N <= 12288 || (a.K >= 1024 && (a.M <= 8 || a.N <= 65536));
 }
 
 // A program's wavefronts walk an eighth of the reduction each, however few programs there are: with few columns and a long
 // reduction a k split of tiles, which deals it out to the whole chip, is ahead.  Measured (us, this kernel / split; 0.28 a step of
-// a wavefront with one block of rows, 0.45 with two): 16 x 64 x 8192 7.2 / 8.8, x 16384 11.8 / 9.6, x 65536 39 / 15;
-// 16 x 1024 x 8192 7.5 / 9.8, x 16384 13.3 / 11.2; 16 x 2048 x 16384 14.1 / 15.9; 32 x 64 x 8192 9.7 / 9.0, x 4096 6.1 / 8.5.
+// a wavefront with one block of rows, 0.45 to 0.6 with two): 16 x 64 x 8192 7.2 / 8.8, x 16384 11.8 / 9.6, x 65536 39 / 15;
+// 16 x 1024 x 8192 7.5 / 9.8, x 16384 13.3 / 11.2; 16 x 2048 x 16384 14.1 / 15.9; 32 x 64 x 8192 9.7 / 9.0, x 4096 6.1 / 8.5;
+// 32 x 2048 x 8192 over rotating weights 16.3 / 13.6.
 double skinny_cost(const FastArgs &a)
 {
     const double steps = (double)((a.K / kSkinnyStep + kSkinnyWaves - 1) / kSkinnyWaves);
-    return 2.5 + steps * (a.M <= 16 ? 0.28 : 0.45);
+    return 2.5 + steps * (a.M <= 16 ? 0.28 : 0.56);
 }
 
 int skinny_parts(const FastArgs &a) { return (int)std::min<int64_t>(kSkinnyWaves, a.K / kSkinnyStep); }

@@ -468,6 +468,18 @@ def test_few_columns_and_a_long_reduction_are_dealt_to_the_whole_chip(M, N, K, t
         assert torch.equal(C.cpu(), want)
 
 
+@pytest.mark.parametrize("M,N,K,split", [(8, 12288, 128, 2), (8, 12289, 128, 1), (8, 20000, 1023, 1), (8, 20000, 1024, 8), (8, 65537, 1024, 8), (9, 65537, 1024, 1),
+                                         (16, 4096, 257, 4), (16, 4097, 257, 1), (16, 5000, 1001, 8), (3, 300, 255, 1), (17, 8192, 192, 3), (17, 8193, 192, 1)])
+def test_few_rows_and_many_columns(M, N, K, split):
+    """Both sides of each line between the kernel for few rows (which splits the reduction inside a program) and the tiles."""
+    A, B = si.gemm_inputs(M, N, K, "f16", seed=87, dist="int")
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    nt.gemm(to_gpu(A, "f16"), to_gpu(B, "f16").t().contiguous().t(), C)
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_DIRECT and nt.last_k_split() == split
+    assert torch.equal(C, (torch.from_numpy(onum.decode(A, "f16")).cuda() @ torch.from_numpy(onum.decode(B, "f16")).cuda()).float())
+
+
 @pytest.mark.parametrize("step", [1, 2])
 def test_batches_of_more_programs_than_one_launch_holds(step):
     """2^24 + 4 batch entries of one program each, on the matrix kernel and (a step along k) on the operand-map kernel."""
