@@ -43,6 +43,9 @@ static const TileEntry kTiles[] = {{64, 64, 32}, {128, 128, 64}, {256, 128, 64},
 // (time of one 64-wide k tile with the whole unit's matrix rate) plus a fixed `fixed` microseconds of launch, prologue and
 // epilogue, which `resident` co-resident workgroups overlap with each other's multiplications.  The constants are fits to
 // measurements on 8192 x 8192 x K and batched 2048 x 2048 x K problems.
+static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out);
+static bool beyond_l2(int64_t M, int64_t N, int64_t kt) { return (M + N) * kt * 64 * 2 > (32 << 20); }
+
 nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow)
 {
     struct Cand { int bm, bn; double fixed, step; int resident; };
@@ -55,7 +58,18 @@ nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool 
     // 256 tiles 4.5 / 5.8 (K = 256), 7.3 / 10.7 (1024), 11.0 / 18.4 (2048); 512 tiles 5.8 / 6.2, 10.0 / 11.1, 16.9 / 18.6 and
     // 33.1 / 32.2 (4096); 576 tiles 7.6 / 6.1, 14.4 / 11.2.
     const int64_t small = batch * ((M + 63) / 64) * ((N + 63) / 64);
-    if (narrow && (small <= 256 || (small <= 512 && kt <= 48))) return nt_tile_cfg{64, 64, 32};
+    // Not where a strip of a tile or two (M or N up to 128) fills more than a round of them (operands from memory, 128 x 128 / this:
+    // 64 x 19712 x 960 14.2 / 18.5, 64 x 31936 x 704 12.9 / 14.9; unaligned rows 77 x 14309 x 2717 56 / 40), and not where the wider
+    // tile's k split is estimated to be ahead of this one's (448 x 1280 x 7168 27.6 / 35.7, 192 x 5376 x 7488 43 / 58).
+    const bool strip = (M <= 128 || N <= 128) && K % 8 == 0;
+    bool take = narrow && (small <= 256 || (small <= 512 && kt <= (strip ? 8 : 48)));
+    if (take && batch == 1 && K % 64 == 0) {
+        double cost = 0, wide = 0;
+        gemm_ksplit(small, K / 64, M, N, true, &cost);
+        // (its estimate is 2 us on the safe side where the operands stay in the L2s: 320 x 1152 x 4928 23 for 18.7)
+        if (gemm_ksplit(((M + 127) / 128) * ((N + 127) / 128), K / 64, M, N, false, &wide) > 1 && wide - (beyond_l2(M, N, K / 64) ? 0 : 2) < cost) take = false;
+    }
+    if (take) return nt_tile_cfg{64, 64, 32};
     nt_tile_cfg best{128, 128, 64};
     double best_cost = 0;
     for (const Cand &c : cands) {
@@ -553,11 +567,13 @@ static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nc
 // *cost_out: the estimate of the way taken.
 static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out)
 {
-    const double step = small ? 0.24 : 0.37, once = small ? 3.5 : 7.0, twice = small ? 6.0 : 12.0;
+    // (operands beyond the L2s come from memory: 72 x 7136 x 3712 0.32 per k tile, 704 x 1408 x 8640 0.33, 192 x 5376 x 7488 0.46)
+    const double step = small ? (beyond_l2(M, N, kt) ? 0.36 : 0.24) : 0.37, once = small ? 3.5 : 7.0, twice = small ? 6.0 : 12.0;
     const double single = once + step * (double)kt;
     *cost_out = single;
     if (programs >= (small ? 192 : 128) || kt < 32) return 1;
-    const int64_t want = std::min<int64_t>((256 + programs / 2) / programs, kt / 8);
+    // (about a program per unit; of the 64 x 64 tile's no more than that: a few units with two of them set the pace)
+    const int64_t want = std::min<int64_t>(small ? 256 / programs : (256 + programs / 2) / programs, kt / 8);
     for (int64_t d = want; d >= 2; --d) {
         if (kt % d) continue;
         const double split = twice + step * (double)kt / (double)d + (double)d * (double)M * (double)N * 8.0 / 3.0e6;

@@ -162,6 +162,15 @@ def test_grid_of_a_product_is_the_ceil_of_its_sizes(tile):
                 assert grid == (Bn or 1, ceil(M, tile[0]), ceil(N, tile[1])) and kt == ceil(K, tile[2])
 
 
+@pytest.mark.parametrize("M,N,K,tile", [(256, 256, 8192, (64, 64)), (1024, 1024, 3072, (64, 64)), (1024, 2048, 3136, (128, 128)), (64, 19712, 512, (64, 64)),
+                                        (64, 19712, 960, (128, 128)), (64, 19713, 963, (64, 64)), (129, 10000, 960, (64, 64)), (448, 1280, 7168, (128, 128)),
+                                        (72, 7136, 3712, (64, 64)), (192, 2048, 7680, (128, 128)), (1024, 1088, 640, (64, 64)), (2048, 2048, 64, (128, 128))])
+def test_default_tile_of_small_products(M, N, K, tile):
+    """Which products the library's own tile is 64 x 64 for, on both sides of its lines (measured beside the rule)."""
+    grid, _ = nt.arrange_gemm(((M, K), None), ((K, N), None), ((M, N), None))
+    assert grid == (1, -(-M // tile[0]), -(-N // tile[1]))
+
+
 # ----------------------------------------------------------------- program order swizzle
 @pytest.mark.parametrize("batch,mt,nt_", [(1, 4, 4), (1, 16, 16), (1, 12, 20), (32, 8, 8), (1, 32, 32), (1, 392, 2),
                                           (1, 1, 1), (1, 7, 3), (2, 9, 1), (1, 47, 79), (19, 5, 3), (8, 1, 1)])
