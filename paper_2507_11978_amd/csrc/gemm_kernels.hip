@@ -3,6 +3,7 @@
 
 #include "gemm_conv_cl.h"
 #include "gemm_conv_direct.h"
+#include "gemm_conv_patch.h"
 #include "gemm_conv_tap.h"
 #include "gemm_direct.h"
 #include "gemm_direct16.h"
@@ -773,6 +774,51 @@ static bool conv_unfold_ok(const GemmLaunch &g)
            h.xs[0] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 && h.P * h.Q >= 8 && K >= 8 && K <= 65535 && Mp < (1 << 22) && (size_t)K * Mp * 2 <= kSplitWsMax;
 }
 
+static bool same_conv(const ConvHint &a, const ConvHint &b)
+{
+    auto same = [](const int64_t (&x)[4], const int64_t (&y)[4]) { return x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3]; };
+    return a.N == b.N && a.C == b.C && a.H == b.H && a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.P == b.P && a.Q == b.Q && a.sh == b.sh && a.sw == b.sw &&
+           a.ph == b.ph && a.pw == b.pw && a.dh == b.dh && a.dw == b.dw && same(a.xs, b.xs) && same(a.ws, b.ws) && same(a.ys, b.ys);
+}
+
+// ---- route 0a: dense planes and filters, channels in whole blocks of 32, 9 or 25 taps: one launch, straight from the caller's
+// tensors (gemm_conv_patch.hip), where that is estimated to be faster than copying the input or the filter first.  Of unit stride
+// only what does not run on tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one
+// block gives a program's wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters.
+static nt_status route_conv_patch(const GemmLaunch &g, int *path_out, bool *taken)
+{
+    *taken = false;
+    const ConvHint &h = g.conv;
+    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
+    const int64_t RS = h.R * h.S, K = h.C * RS, M = h.N * h.P * h.Q, HW = h.H * h.W;
+    if (RS != 9 && RS != 25) return NT_OK;
+    if (h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
+    if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K || h.ws[0] % 8 != 0 || (reinterpret_cast<uintptr_t>(g.B) & 15) != 0) return NT_OK;
+    // (32-bit byte offsets; divisions through fp32 reciprocals, exact below 2^21)
+    const int64_t lim = 1 << 20;
+    if (HW < 4 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || M >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
+        (h.N - 1) * h.xs[0] + (h.C - 1) * h.xs[1] + HW >= (1LL << 30)) return NT_OK;
+    if (h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1 && (h.C < 64 || (h.K > 128 && !conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K)))) return NT_OK;
+    // (the estimate of some dozen tiles costs the host more than the rest of the call: the last few answers are kept, by value)
+    struct Known { ConvHint h{}; ConvPatchArgs a{}; ConvPatchPlan plan{}; bool set = false, take = false; };
+    static thread_local Known known[8];
+    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 8];
+    if (!k.set || !same_conv(k.h, h)) {
+        k.a = ConvPatchArgs{};
+        k.take = conv_patch_plan(h, &k.a, &k.plan);
+        k.h = h;
+        k.set = true;
+    }
+    if (!k.take) return NT_OK;
+    ConvPatchArgs a = k.a;
+    a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
+    a.out_dtype = g.out_dtype;
+    *taken = true;
+    if (path_out) *path_out = PATH_CONV_CL;
+    t_k_split = k.plan.waves;
+    return launch_conv_patch(a, k.plan, g.in_dtype == NT_BF16, (hipStream_t)g.stream);
+}
+
 // Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
 // estimate of its product.  A unit runs two programs at a time; a program costs a fixed part and its slices, a split the
 // kernel that adds the parts and their trip through memory.  (Fits, us: 392 programs of 128 x 128 with 36 slices 27.5, 196
@@ -1140,7 +1186,9 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     }
     if (path_out) *path_out = PATH_GENERIC;
     bool taken = false;
-    nt_status st = route_conv_channels_last(g, path_out, &taken);
+    nt_status st = route_conv_patch(g, path_out, &taken);
+    if (taken || st != NT_OK) return st;
+    st = route_conv_channels_last(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     ConvArgs c{};
     if (!g.has_d && g.alpha == 1.f && g.act == 0 && match_conv(g, &c)) return route_conv_implicit(g, c, path_out);

@@ -1,0 +1,75 @@
+"""Convolutions that run in one launch straight from the caller's tensors (gemm_conv_patch.hip): 9 or 25 taps, dense planes,
+channels in whole blocks of 32, few positions or filters.  Small integers: every sum is exact, so the result must be the
+oracle's bit for bit whatever the tile, the number of wavefronts that share the reduction and the patch's geometry."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_11978_amd as nt
+import synthetic_inputs as si
+from oracle import numeric as onum
+from gpu_util import TORCH_DT, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def inside(t, lead):
+    """the tensor in the middle of a larger buffer of NaNs, `lead` elements from its start"""
+    buf = torch.full((t.numel() + lead + 64,), float("nan"), dtype=t.dtype, device=t.device)
+    v = buf[lead:lead + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("shape,stride,pad", [
+    # one shape for each kernel that is built (filters x positions per tile)
+    ((1, 64, 6, 6, 40, 3, 3), (2, 2), (1, 1)),         # 16 x 32
+    ((7, 128, 25, 25, 100, 3, 3), (2, 2), (1, 1)),     # 16 x 48
+    ((13, 96, 28, 28, 40, 3, 3), (1, 1), (1, 1)),      # 16 x 96
+    ((10, 128, 21, 21, 100, 3, 3), (2, 2), (1, 1)),    # 32 x 32
+    ((12, 64, 25, 25, 72, 3, 3), (1, 1), (1, 1)),      # 32 x 48
+    ((13, 64, 21, 21, 130, 3, 3), (1, 1), (1, 1)),     # 32 x 64
+    ((11, 96, 28, 28, 300, 3, 3), (2, 2), (1, 1)),     # 32 x 96
+    ((3, 96, 21, 21, 300, 3, 3), (1, 1), (1, 1)),      # 64 x 32
+    ((1, 64, 6, 6, 40, 5, 5), (2, 2), (2, 2)),         # 25 taps: 16 x 32
+    ((7, 64, 21, 21, 40, 5, 5), (1, 1), (2, 2)),       # 16 x 64
+    ((7, 96, 28, 28, 40, 5, 5), (1, 1), (2, 2)),       # 16 x 96
+    # edges of the patch
+    ((4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # no padding, rows of 12: a tile's rows end at other places than the input's
+    ((9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # 25 positions per image, odd planes: several images in a tile, 2-byte aligned runs
+    ((40, 64, 2, 2, 17, 3, 3), (1, 1), (1, 1)),        # images of one run
+    ((1, 64, 1, 4, 8, 3, 3), (1, 1), (1, 1)),          # four positions in all, rows of padding on both sides
+    ((2, 288, 3, 50, 20, 3, 3), (1, 1), (1, 1)),       # nine blocks of channels (uneven shares), rows longer than a tile
+    ((3, 64, 10, 9, 24, 9, 1), (1, 1), (4, 0)),        # nine taps in a column
+    ((3, 64, 9, 13, 24, 1, 9), (2, 1), (0, 4)),        # ... in a row, mixed strides
+    ((3, 160, 11, 7, 30, 3, 3), (3, 3), (2, 2)),       # stride as long as the filter, wide padding
+    ((5, 64, 9, 8, 40, 3, 3), (4, 5), (0, 0)),         # rows and columns between the positions that no tap reads
+    ((2, 64, 4, 6, 40, 5, 5), (1, 1), (4, 4)),         # more padding than image under some taps
+])
+def test_conv_patch(shape, stride, pad):
+    N, C, H, W, F, R, S = shape
+    for dt, out, lead in (("f16", "f32", 32), ("bf16", "bf16", 33), ("f16", "f16", 47)):
+        X, Wt = si.conv_inputs(N, C, H, W, F, R, S, dt, seed=91, dist="int")
+        ref = onum.conv2d(X, Wt, dt, stride, pad, nthreads=16)
+        want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+        x, w = inside(to_gpu(X, dt), lead), inside(to_gpu(Wt, dt), 32)            # (rows of the filter stay 16-byte aligned)
+        big = torch.full((N, F + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
+        Y = big[:, 2:F + 2]
+        nt.conv2d_implicit(x, w, Y, stride, pad)
+        torch.cuda.synchronize()
+        assert nt.last_kernel_path() == nt.PATH_CONV_CL and nt.last_k_split() >= 1
+        assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
+        assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
+
+
+def test_conv_patch_of_a_channel_slice():
+    """Images and channels further apart than their sizes, filters longer than the channels they are used with."""
+    dt, N, C, H, W, F = "f16", 3, 96, 12, 11, 48
+    X, Wt = si.conv_inputs(N, C + 64, H, W, F, 3, 3, dt, seed=92, dist="int")
+    Xs, Ws = np.ascontiguousarray(X[:, 32:32 + C]), np.ascontiguousarray(Wt[:, 32:32 + C])
+    ref = onum.conv2d(Xs, Ws, dt, (1, 1), (1, 1), nthreads=16)
+    Y = torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda")
+    nt.conv2d_implicit(to_gpu(X, dt)[:, 32:32 + C], to_gpu(Wt, dt)[:, 32:32 + C], Y, (1, 1), (1, 1))
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_CONV_CL
+    assert np.array_equal(Y.double().cpu().numpy(), ref)
