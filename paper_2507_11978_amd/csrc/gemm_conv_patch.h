@@ -34,8 +34,8 @@ struct ConvPatchArgs {
 };
 
 struct ConvPatchPlan { int tile, waves; };     // wavefronts per program: the parts of the reduction
-// geometry and tile for a convolution; false: not built for it, or the routes through a copy are estimated to be faster
-bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *p);
+// geometry, tile and estimated time (us) for a convolution; false: not built for it
+bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *p, double *cost);
 nt_status launch_conv_patch(const ConvPatchArgs &a, const ConvPatchPlan &p, bool bf16, hipStream_t s);
 
 }  // namespace nt

@@ -296,34 +296,24 @@ static bool patch_sizes(const ConvHint &h, const PatchTile &t, PatchSizes *z)
 // unit's LDS and registers hold; a program costs a fixed part, its blocks of channels -- each the latency of a wavefront's own
 // work, or the unit's throughput for all that are resident, whichever is longer -- and the sum of its wavefronts' parts.
 // A fit to 3907 launches of 179 drawn convolutions (64 to 512 channels and filters, images of 7 to 56, both strides, 3 x 3 and
-// 5 x 5; spread 8.6 %); the tile it names is 2.4 % behind the best one in the mean.
+// 5 x 5; spread 8.4 %); the tile it names is 2.0 % behind the best one in the mean.
 static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t programs, int64_t waves)
 {
+    // (LDS is dealt out in pieces of 1280 bytes: five programs of 32 KB do not fit)
     const double slots = t.maxw == 8 ? 8 : 4, units = 256;
-    const double resident = std::max(1.0, std::min((double)((160 << 10) / (z.region * waves)), std::floor(slots / (double)waves)));
+    const double resident = std::max(1.0, std::min((double)(128 / ((z.region * waves + 1279) / 1280)), std::floor(slots / (double)waves)));
     const double mine = programs > units ? std::min(resident, (double)programs / units) : 1.0;
     double rounds = std::max(1.0, (double)programs / (units * resident));
     rounds = rounds < 4 ? std::ceil(rounds) : rounds + 0.3;
     const double runs = (double)((z.runs + 15) / 16), mm = t.taps * t.mf * t.np, reads = t.taps * (t.mf + t.np);
-    const double latency = 0.141 + 0.0188 * mm + 0.112 * runs, unit = (0.0353 + 0.00613 * reads) * mine * (double)waves;
-    return 2.33 + rounds * (1.29 + 0.575e-3 * (double)z.plane + (double)((z.blocks + waves - 1) / waves) * std::max(latency, unit) + 0.0323 * (double)((waves - 1) * t.mf * t.np));
+    const double latency = 0.139 + 0.0188 * mm + 0.112 * runs, unit = (0.0337 + 0.00615 * reads) * mine * (double)waves;
+    return 2.33 + rounds * (1.30 + 0.572e-3 * (double)z.plane + (double)((z.blocks + waves - 1) / waves) * std::max(latency, unit) + 0.0324 * (double)((waves - 1) * t.mf * t.np));
 }
 
-// Estimated time of the routes that copy the input or the filter first (copy, product, sum of a split's parts; fits to the same
-// convolutions: unit stride within 19 %, strided 11 %), in the same unit; what a call costs the host speaks for one launch too.
-static double copied_cost(const ConvHint &h)
-{
-    const double gflop = 2e-9 * (double)(h.N * h.P * h.Q) * (double)(h.K * h.C * h.R * h.S);
-    const double k = 1e-3 * (double)(h.C * h.R * h.S), filter = 4e-6 * (double)(h.K * h.C * h.R * h.S);
-    const double input = 4e-6 * (double)(h.N * h.C) * (double)((h.H + 2 * h.ph) * (h.W + 2 * h.pw));
-    if (h.sh == 1 && h.sw == 1) return 9.0 + 2.4 * std::min(gflop, 8.0) + 0.8 * std::max(gflop - 8.0, 0.0) + std::min(input, 10.0) + 0.28 * k + 0.73 * filter;
-    return 9.3 + 1.05 * gflop + 0.43 * input + 0.31 * k + 0.77 * filter;
-}
-
-bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best)
+bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best, double *cost_out)
 {
     const int64_t M = h.N * h.P * h.Q;
-    double best_cost = copied_cost(h);
+    double best_cost = 0;
     int i = -1;
     PatchSizes z{};
     best->waves = 0;
@@ -339,10 +329,11 @@ bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best)
             if (waves == last) continue;
             last = waves;
             const double cost = patch_cost(t, c, programs, waves);
-            if (cost < best_cost) { best_cost = cost; best->tile = i; best->waves = (int)waves; z = c; }
+            if (best->waves == 0 || cost < best_cost) { best_cost = cost; best->tile = i; best->waves = (int)waves; z = c; }
         }
     }
     if (best->waves == 0) return false;
+    *cost_out = best_cost;
     const PatchTile &t = kPatchTiles[best->tile];
     const int64_t PT = 16 * t.np, FT = 16 * t.mf, PQ = h.P * h.Q;
     a->xs1 = h.xs[1]; a->syn = h.ys[0]; a->syf = h.ys[1];

@@ -1,0 +1,8 @@
+// Instantiation: 192 and 160 positions x 256 filters per program, both input formats.
+#include "gemm_conv_plane_kernel.h"
+
+namespace nt {
+template nt_status launch_conv_plane_t<6, 5, 8, 2, 9>(const ConvPlaneArgs &a, bool bf16, hipStream_t s);
+template nt_status launch_conv_plane_t<6, 5, 8, 2, 0>(const ConvPlaneArgs &a, bool bf16, hipStream_t s);
+template nt_status launch_conv_plane_t<6, 5, 8, 3, 0>(const ConvPlaneArgs &a, bool bf16, hipStream_t s);
+}

@@ -4,6 +4,7 @@
 #include "gemm_conv_cl.h"
 #include "gemm_conv_direct.h"
 #include "gemm_conv_patch.h"
+#include "gemm_conv_plane.h"
 #include "gemm_conv_tap.h"
 #include "gemm_direct.h"
 #include "gemm_direct16.h"
@@ -781,42 +782,90 @@ static bool same_conv(const ConvHint &a, const ConvHint &b)
            a.ph == b.ph && a.pw == b.pw && a.dh == b.dh && a.dw == b.dw && same(a.xs, b.xs) && same(a.ws, b.ws) && same(a.ys, b.ys);
 }
 
-// ---- route 0a: dense planes and filters, channels in whole blocks of 32, 9 or 25 taps: one launch, straight from the caller's
-// tensors (gemm_conv_patch.hip), where that is estimated to be faster than copying the input or the filter first.  Of unit stride
-// only what does not run on tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one
-// block gives a program's wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters.
-static nt_status route_conv_patch(const GemmLaunch &g, int *path_out, bool *taken)
+// Estimated time (us) of a convolution on the routes that copy its input or fetch the unfolded one: unit stride with many
+// positions by conv_cost (0.9 of it: (32,512,14,14)*(512,512,3,3) 72 for 66, (32,256,56,56)*(256,256,3,3) 143 for 124,
+// (7,448,56,56)*(114,448,3,3) 63 for 58); the others are fits to 179 drawn convolutions (unit stride within 19 %, strided 11 %).
+static double conv_copied_cost(const ConvHint &h)
+{
+    const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1;
+    if (unit && !conv_small(M8, h.K)) {
+        int32_t per = 0;
+        double narrow = 0, wide = 0;
+        const int64_t kt = (h.C * h.R * h.S + 63) / 64;
+        conv_ksplit(M8, h.K, kt, 128, &per, &narrow);
+        if (h.K <= 128) return 0.9 * narrow;
+        conv_ksplit(M8, h.K, kt, 256, &per, &wide);
+        return 0.9 * std::min(narrow, wide);
+    }
+    const double gflop = 2e-9 * (double)(h.N * h.P * h.Q) * (double)(h.K * h.C * h.R * h.S);
+    const double k = 1e-3 * (double)(h.C * h.R * h.S), filter = 4e-6 * (double)(h.K * h.C * h.R * h.S);
+    const double input = 4e-6 * (double)(h.N * h.C) * (double)((h.H + 2 * h.ph) * (h.W + 2 * h.pw));
+    if (unit) return 9.0 + 2.4 * std::min(gflop, 8.0) + 0.8 * std::max(gflop - 8.0, 0.0) + std::min(input, 10.0) + 0.28 * k + 0.73 * filter;
+    return 9.3 + 1.05 * gflop + 0.43 * input + 0.31 * k + 0.77 * filter;
+}
+
+// ---- route 0a: dense planes, channels in whole blocks of 32, the input rows under a tile resident in LDS, where one of the two
+// kernels that do this is estimated to be ahead of the routes below:
+//   gemm_conv_patch.hip, 9 or 25 taps: one launch straight from the caller's tensors.  Of unit stride only what does not run on
+//     tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one block gives a program's
+//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters;
+//   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
+//     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
+//     workspace otherwise: those keep to the patch or the channels-last copy.
+static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
     const ConvHint &h = g.conv;
     if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
-    const int64_t RS = h.R * h.S, K = h.C * RS, M = h.N * h.P * h.Q, HW = h.H * h.W;
-    if (RS != 9 && RS != 25) return NT_OK;
-    if (h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
-    if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K || h.ws[0] % 8 != 0 || (reinterpret_cast<uintptr_t>(g.B) & 15) != 0) return NT_OK;
+    const int64_t RS = h.R * h.S, K = h.C * RS, HW = h.H * h.W, lim = 1 << 20;
+    if (RS < 6 || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
+    if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K) return NT_OK;
     // (32-bit byte offsets; divisions through fp32 reciprocals, exact below 2^21)
-    const int64_t lim = 1 << 20;
-    if (HW < 4 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || M >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
+    if (HW < 8 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || h.N * (h.P * h.Q + 8) >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
         (h.N - 1) * h.xs[0] + (h.C - 1) * h.xs[1] + HW >= (1LL << 30)) return NT_OK;
-    if (h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1 && (h.C < 64 || (h.K > 128 && !conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K)))) return NT_OK;
-    // (the estimate of some dozen tiles costs the host more than the rest of the call: the last few answers are kept, by value)
-    struct Known { ConvHint h{}; ConvPatchArgs a{}; ConvPatchPlan plan{}; bool set = false, take = false; };
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1, small = conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K);
+    const bool patch_ok = (RS == 9 || RS == 25) && h.ws[0] % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0 && !(unit && (h.C < 64 || (h.K > 128 && !small)));
+    const bool plane_ok = K <= 32768 && !(unit && small);
+    // (the estimates cost the host more than the rest of the call: the last few answers are kept, by value)
+    enum { NEITHER, PATCH, PLANE };
+    struct Known { ConvHint h{}; ConvPatchArgs patch{}; ConvPatchPlan patch_plan{}; ConvPlaneArgs plane{}; ConvPlanePlan plane_plan{}; bool set = false, patch_ok = false; int kind = NEITHER; };
     static thread_local Known known[8];
     Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 8];
-    if (!k.set || !same_conv(k.h, h)) {
-        k.a = ConvPatchArgs{};
-        k.take = conv_patch_plan(h, &k.a, &k.plan);
+    if (!k.set || k.patch_ok != patch_ok || !same_conv(k.h, h)) {
+        k = Known{};
         k.h = h;
+        k.patch_ok = patch_ok;
+        double cost = conv_copied_cost(h), c = 0;
+        if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.kind = PATCH; cost = c; }
+        if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) k.kind = PLANE;
         k.set = true;
     }
-    if (!k.take) return NT_OK;
-    ConvPatchArgs a = k.a;
-    a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
-    a.out_dtype = g.out_dtype;
-    *taken = true;
-    if (path_out) *path_out = PATH_CONV_CL;
-    t_k_split = k.plan.waves;
-    return launch_conv_patch(a, k.plan, g.in_dtype == NT_BF16, (hipStream_t)g.stream);
+    hipStream_t s = (hipStream_t)g.stream;
+    const bool bf16 = g.in_dtype == NT_BF16;
+    if (k.kind == PATCH) {
+        ConvPatchArgs a = k.patch;
+        a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
+        a.out_dtype = g.out_dtype;
+        *taken = true;
+        if (path_out) *path_out = PATH_CONV_CL;
+        t_k_split = k.patch_plan.waves;
+        return launch_conv_patch(a, k.patch_plan, bf16, s);
+    }
+    if (k.kind == PLANE) {
+        WorkspaceLease lease;
+        uint16_t *copy = (uint16_t *)lease.acquire((size_t)h.K * K * 2, s);
+        if (!copy) return NT_OK;
+        *taken = true;
+        const nt_status st = launch_conv_plane_filter((const uint16_t *)g.B, h.ws[0], copy, (int32_t)h.K, (int32_t)h.C, (int32_t)RS, s);
+        if (st != NT_OK) return st;
+        ConvPlaneArgs a = k.plane;
+        a.x = (const uint16_t *)g.A; a.w = copy; a.ldb = (uint32_t)K;
+        a.c.Y = g.C; a.c.out_dtype = g.out_dtype;
+        if (path_out) *path_out = unit ? PATH_CONV_TAP : PATH_CONV_CL;
+        return launch_conv_plane(a, k.plane_plan, bf16, s);
+    }
+    return NT_OK;
 }
 
 // Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
@@ -1186,7 +1235,7 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     }
     if (path_out) *path_out = PATH_GENERIC;
     bool taken = false;
-    nt_status st = route_conv_patch(g, path_out, &taken);
+    nt_status st = route_conv_resident(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     st = route_conv_channels_last(g, path_out, &taken);
     if (taken || st != NT_OK) return st;

@@ -1,0 +1,89 @@
+"""Convolutions of many positions whose input rows stay in LDS (gemm_conv_plane.hip): six taps or more, dense planes, channels in
+whole blocks of 32.  Small integers: every sum is exact, so the result must be the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_11978_amd as nt
+import synthetic_inputs as si
+from oracle import numeric as onum
+from gpu_util import TORCH_DT, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def inside(t, lead):
+    """the tensor in the middle of a larger buffer of NaNs, `lead` elements from its start"""
+    buf = torch.full((t.numel() + lead + 64,), float("nan"), dtype=t.dtype, device=t.device)
+    v = buf[lead:lead + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("shape,stride,pad", [
+    # one shape for each kernel that is built: 9 taps, 256 filters per program ...
+    ((19, 64, 57, 57, 130, 3, 3), (1, 1), (1, 1)),     # tiles of 256 positions (and 224); planes of odd size: 2-byte aligned runs
+    ((18, 64, 48, 48, 130, 3, 3), (1, 1), (1, 1)),     # 224
+    ((21, 64, 40, 40, 130, 3, 3), (1, 1), (1, 1)),     # 192
+    ((18, 64, 40, 40, 130, 3, 3), (1, 1), (1, 1)),     # 160
+    ((9, 64, 48, 48, 130, 3, 3), (1, 1), (1, 1)),      # 128
+    ((30, 32, 56, 56, 160, 3, 3), (2, 2), (1, 1)),     # 128, one set of planes; one block of channels
+    # ... 128 filters
+    ((8, 64, 56, 56, 130, 3, 3), (1, 1), (1, 1)),
+    ((18, 64, 48, 48, 72, 3, 3), (1, 1), (1, 1)),
+    ((21, 32, 28, 28, 130, 3, 3), (1, 1), (1, 1)),
+    ((31, 32, 20, 20, 130, 3, 3), (1, 1), (1, 1)),
+    ((26, 32, 20, 20, 72, 3, 3), (1, 1), (1, 1)),
+    ((32, 32, 56, 56, 72, 3, 3), (2, 2), (1, 1)),
+    # other numbers of taps
+    ((21, 32, 40, 40, 130, 5, 5), (1, 1), (2, 2)),
+    ((15, 32, 33, 33, 130, 5, 5), (1, 1), (2, 2)),
+    ((19, 32, 57, 57, 130, 5, 5), (1, 1), (2, 2)),
+    ((11, 32, 56, 56, 130, 5, 5), (1, 1), (2, 2)),
+    ((6, 64, 56, 56, 130, 5, 5), (1, 1), (2, 2)),
+    ((30, 32, 33, 33, 72, 5, 5), (1, 1), (2, 2)),
+    ((34, 32, 17, 17, 72, 5, 5), (1, 1), (2, 2)),
+    ((11, 32, 56, 56, 72, 5, 5), (1, 1), (2, 2)),
+    # odd numbers of blocks of channels, taps in two rows of three, strides and padding of their own, rows of odd length
+    ((9, 96, 48, 48, 130, 3, 3), (1, 1), (0, 2)),
+    ((16, 96, 41, 37, 130, 2, 3), (1, 1), (1, 0)),
+    ((40, 160, 33, 47, 130, 3, 3), (2, 1), (1, 1)),
+    ((150, 64, 9, 9, 136, 3, 3), (1, 1), (1, 1)),      # several images in a tile
+])
+def test_conv_plane(shape, stride, pad):
+    N, C, H, W, F, R, S = shape
+    for dt, out, lead in (("f16", "f16", 33), ("bf16", "f32", 32)):
+        X, Wt = si.conv_inputs(N, C, H, W, F, R, S, dt, seed=93, dist="int")
+        ref = onum.conv2d(X, Wt, dt, stride, pad, nthreads=16)
+        want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+        x, w = inside(to_gpu(X, dt), lead), inside(to_gpu(Wt, dt), 32)
+        big = torch.full((N, F + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
+        Y = big[:, 2:F + 2]
+        nt.conv2d_implicit(x, w, Y, stride, pad)
+        torch.cuda.synchronize()
+        assert nt.last_kernel_path() == (nt.PATH_CONV_TAP if stride == (1, 1) else nt.PATH_CONV_CL) and nt.last_k_split() == 1
+        assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
+        assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
+
+
+@pytest.mark.parametrize("shape,stride", [((9, 64, 48, 48, 130, 3, 3), 1), ((30, 32, 56, 56, 160, 3, 3), 2), ((4, 96, 14, 14, 64, 3, 3), 1)])
+def test_conv_resident_keeps_an_infinity_to_its_window(shape, stride):
+    """An infinity and a NaN in the input reach the outputs whose windows hold them and no other."""
+    N, C, H, W, F, R, S = shape
+    dt = "f16"
+    X, Wt = si.conv_inputs(N, C, H, W, F, R, S, dt, seed=94, dist="int")
+    x, w = to_gpu(X, dt), to_gpu(Wt, dt)
+    ref = torch.from_numpy(onum.conv2d(X, Wt, dt, (stride, stride), (1, 1), nthreads=16))
+    touched = torch.zeros(ref.shape, dtype=torch.bool)
+    for n, c, h, ww, v in ((0, 5, 0, 0, float("inf")), (N - 1, C - 1, H - 1, W - 1, float("nan")), (N // 2, 31, H // 2, 7, float("-inf"))):
+        x[n, c, h, ww] = v
+        for p in range(ref.shape[2]):
+            for q in range(ref.shape[3]):
+                if 0 <= h - (p * stride - 1) < R and 0 <= ww - (q * stride - 1) < S:
+                    touched[n, :, p, q] = True
+    Y = torch.zeros(ref.shape, dtype=torch.float32, device="cuda")
+    nt.conv2d_implicit(x, w, Y, (stride, stride), (1, 1))
+    torch.cuda.synchronize()
+    y = Y.cpu().double()
+    assert torch.equal(y[~touched], ref[~touched])
+    assert not torch.isfinite(y[touched]).any()
