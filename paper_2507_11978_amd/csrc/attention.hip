@@ -1,7 +1,7 @@
 // Scaled dot-product attention, forward (Section 5.1: the paper's sdpa kernels implement the
 // FlashAttention-2 algorithm): O = softmax(scale * Q K^T) V per (batch, head), head size 64.
 //
-// Arrangement: Q and O are tiled into blocks of 128 query rows, one program per (batch, head,
+// Arrangement: Q and O are tiled into blocks of 128 query rows (32 or 64 in launches that leave units empty), one program per (batch, head,
 // block); K and V are tiled into blocks of 64 keys, all of which every program visits in turn.
 // Application (per program): a row reference M (close to the running row maximum), row sum l,
 // accumulator O; per key block
@@ -76,13 +76,16 @@ __device__ __forceinline__ float add_pair(uint32_t w, float acc)
 // AHEAD: rows that the range-checked loads do not take, one group: K and V through registers, one block ahead (loaded and
 // written to LDS at the top of a block instead, bf16, rows of pitch 63: 4 x 48 heads x 1024 78 us against 68, 8 x 64 heads,
 // 128 x 2048, 66 against 56; 2.1 M packed keys x 8 heads 32.0 ms in four groups, 29.1 so).
-template <bool BF16, bool DMA, int SPLIT>
-__global__ __launch_bounds__(256 * SPLIT, DMA || SPLIT > 1 ? 4 : 2) void sdpa_kernel(const SdpaArgs g)
+// NW: wavefronts per group, 32 queries each (4; 1 or 2 where 128 queries a workgroup leave units empty).
+template <bool BF16, bool DMA, int SPLIT, int NW>
+__global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 : 2) void sdpa_kernel(const SdpaArgs g)
 {
     constexpr bool AHEAD = !DMA && SPLIT == 1;
+    static_assert(NW == 4 || !AHEAD, "one group ahead of its arithmetic: four wavefronts");
+    constexpr int QB = 32 * NW, PER = 8 / NW;                          // queries; 1 KB loads per wavefront and block
     constexpr uint32_t BLK = kKeyBlock * kHeadDim * 2;                 // bytes of one K or V block in LDS (8 KB)
     extern __shared__ __attribute__((aligned(1024))) char all_smem[];  // per group, rings of three K and two V blocks: [K0][K1][K2][V0][V1]
-    const int lane = threadIdx.x & 63, group = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), tid = threadIdx.x & 255, wave = tid >> 6;
+    const int lane = threadIdx.x & 63, group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NW)), tid = threadIdx.x % (64 * NW), wave = tid >> 6;
     char *smem = all_smem + group * (kSdpaLds);
     const int l32 = lane & 31, hi = lane >> 5;
     // Workgroup -> (batch * head, query block).  Consecutive workgroup indices go to different XCDs (index mod 8),
@@ -102,41 +105,41 @@ __global__ __launch_bounds__(256 * SPLIT, DMA || SPLIT > 1 ? 4 : 2) void sdpa_ke
     uint16_t *Op = g.O + b * g.o_sb + h * g.o_sh;
 
     // ---- Q fragments (B operand of S^T = K Q^T: column = query l32, 8 consecutive d per k step)
-    const int qrow = qblk * kQBlock + wave * 32 + l32;
+    const int qrow = qblk * QB + wave * 32 + l32;
     const int qrow_c = qrow < g.Sq ? qrow : g.Sq - 1;
     u32x4 qf[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) __builtin_memcpy(&qf[ks], Qp + (int64_t)qrow_c * g.q_ss + 16 * ks + 8 * hi, 16);
 
-    // ---- a K or V block into an LDS slot: 64 rows of 128 bytes, two 1 KB loads per wavefront.  Lane l's 16 bytes land at
+    // ---- a K or V block into an LDS slot: 64 rows of 128 bytes, PER 1 KB loads per wavefront.  Lane l's 16 bytes land at
     // l * 16, so the swizzle is applied to the chunk it fetches.  Rows past Sk read as zero (the range check).
     const int nblk = (g.Sk + kKeyBlock - 1) / kKeyBlock;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     const int swave = __builtin_amdgcn_readfirstlane(wave);
-    int ld_row[2], k_ch[2], v_ch[2];                                   // this lane's row and 16-byte chunk of K and of V
-    uint32_t k_off[2], v_off[2];
+    int ld_row[PER], k_ch[PER], v_ch[PER];                                   // this lane's row and 16-byte chunk of K and of V
+    uint32_t k_off[PER], v_off[PER];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        ld_row[u] = (wave * 2 + u) * 8 + (lane >> 3);
+    for (int u = 0; u < PER; ++u) {
+        ld_row[u] = (wave * PER + u) * 8 + (lane >> 3);
         k_ch[u] = (lane & 7) ^ ((ld_row[u] ^ (ld_row[u] >> 3)) & 7);
         v_ch[u] = (lane & 7) ^ (((ld_row[u] >> 1) & 1) << 2);
         k_off[u] = ((uint32_t)ld_row[u] * (uint32_t)g.k_ss + (uint32_t)(k_ch[u] * 8)) * 2u;
         v_off[u] = ((uint32_t)ld_row[u] * (uint32_t)g.v_ss + (uint32_t)(v_ch[u] * 8)) * 2u;
     }
     const u32x4 k_rsrc = make_rsrc(Kp, ((int64_t)(g.Sk - 1) * g.k_ss + kHeadDim) * 2), v_rsrc = make_rsrc(Vp, ((int64_t)(g.Sk - 1) * g.v_ss + kHeadDim) * 2);
-    auto request = [&](int kb, uint32_t slot, const uint16_t *p, int64_t ss, const int (&ch)[2], u32x4 rsrc, const uint32_t (&off)[2]) {
+    auto request = [&](int kb, uint32_t slot, const uint16_t *p, int64_t ss, const int (&ch)[PER], u32x4 rsrc, const uint32_t (&off)[PER]) {
         if constexpr (DMA) {
             // (blocks past the last: an offset beyond the range, no traffic; the count of outstanding loads stays the same)
             const uint32_t at = kb < nblk ? (uint32_t)kb * (uint32_t)(kKeyBlock * 2) * (uint32_t)ss : 0x80000000u;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) dma16_buf(rsrc, off[u], at, lds0 + slot + (uint32_t)((swave * 2 + u) * 1024));
+            for (int u = 0; u < PER; ++u) dma16_buf(rsrc, off[u], at, lds0 + slot + (uint32_t)((swave * PER + u) * 1024));
         } else if (kb < nblk) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
+            for (int u = 0; u < PER; ++u) {
                 const int key = kb * kKeyBlock + ld_row[u];
                 u32x4 v{0, 0, 0, 0};
                 if (key < g.Sk) __builtin_memcpy(&v, p + (int64_t)key * ss + ch[u] * 8, 16);
-                lds_write16(smem, slot + (uint32_t)((wave * 2 + u) * 1024 + lane * 16), v);
+                lds_write16(smem, slot + (uint32_t)((wave * PER + u) * 1024 + lane * 16), v);
             }
         }
     };
@@ -298,12 +301,12 @@ __global__ __launch_bounds__(256 * SPLIT, DMA || SPLIT > 1 ? 4 : 2) void sdpa_ke
             if (kb + 1 < nblk) step(std::integral_constant<uint32_t, BLK>{}, kb + 1);
         }
     } else {
-        // At the top of block kb this wavefront's part of K and V has landed (the two loads of K's next block may be in flight); the
+        // At the top of block kb this wavefront's part of K and V has landed (the loads of K's next block may be in flight); the
         // barrier says that all parts have, and that everybody is done with block kb - 1: its V slot takes V's next block, its K
         // slot K's next but one.
         uint32_t slot = 0, ahead = 2 * BLK, vslot = 0;
         for (int kb = group; kb - group < nblk; kb += SPLIT) {               // (the same number of passes, and barriers, in every group)
-            if constexpr (DMA) NT_WAIT_VMCNT(2);
+            if constexpr (DMA) NT_WAIT_VMCNT(PER);
             __syncthreads();
             request_v(kb + SPLIT, vslot ^ BLK);
             request_k(kb + 2 * SPLIT, ahead);
@@ -320,28 +323,28 @@ __global__ __launch_bounds__(256 * SPLIT, DMA || SPLIT > 1 ? 4 : 2) void sdpa_ke
         __syncthreads();                                                  // (everybody's loads have landed, everybody's reads are done)
         float *ex = reinterpret_cast<float *>(all_smem);
         if (group > 0) {
-            float *e = ex + (group - 1) * (34 * 256) + tid;
+            float *e = ex + (group - 1) * (34 * 64 * NW) + tid;
             e[0] = m_ref;                                                 // (-inf, a group whose keys have no weight: 0 below)
-            e[256] = l_run;
+            e[64 * NW] = l_run;
 #pragma unroll
-            for (int i = 0; i < 32; ++i) e[(2 + i) * 256] = ot[i >> 4][i & 15];
+            for (int i = 0; i < 32; ++i) e[(2 + i) * 64 * NW] = ot[i >> 4][i & 15];
         }
         __syncthreads();
         if (group > 0) return;
         float top = m_ref;
 #pragma unroll
-        for (int i = 0; i < SPLIT - 1; ++i) top = fmaxf(top, ex[i * (34 * 256) + tid]);
+        for (int i = 0; i < SPLIT - 1; ++i) top = fmaxf(top, ex[i * (34 * 64 * NW) + tid]);
         const float own = __builtin_amdgcn_exp2f(m_ref - top);
         l_run *= own;
 #pragma unroll
         for (int v = 0; v < 32; ++v) ot[v >> 4][v & 15] *= own;
 #pragma unroll
         for (int i = 0; i < SPLIT - 1; ++i) {
-            const float *e = ex + i * (34 * 256) + tid;
+            const float *e = ex + i * (34 * 64 * NW) + tid;
             const float c = __builtin_amdgcn_exp2f(e[0] - top);
-            l_run = __builtin_fmaf(e[256], c, l_run);
+            l_run = __builtin_fmaf(e[64 * NW], c, l_run);
 #pragma unroll
-            for (int v = 0; v < 32; ++v) ot[v >> 4][v & 15] = __builtin_fmaf(e[(2 + v) * 256], c, ot[v >> 4][v & 15]);
+            for (int v = 0; v < 32; ++v) ot[v >> 4][v & 15] = __builtin_fmaf(e[(2 + v) * 64 * NW], c, ot[v >> 4][v & 15]);
         }
     }
 
@@ -524,27 +527,36 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void sdpa_decode_kernel(const Sd
     }
 }
 
-template <bool BF16, bool DMA, int SPLIT>
+template <bool BF16, bool DMA, int SPLIT, int NW>
 static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream_t s)
 {
-    auto kern = sdpa_kernel<BF16, DMA, SPLIT>;
+    auto kern = sdpa_kernel<BF16, DMA, SPLIT, NW>;
     static DeviceOnce configured;
     if (!configured.done()) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(SPLIT * kSdpaLds));
         if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
         configured.set();
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)programs), dim3(256 * SPLIT), SPLIT * kSdpaLds, s, k);
+    hipLaunchKernelGGL(kern, dim3((unsigned)programs), dim3(64 * NW * SPLIT), SPLIT * kSdpaLds, s, k);
     return check_launch("sdpa_kernel");
 }
 
-template <bool BF16, bool DMA>
-static nt_status launch_sdpa_split(const SdpaArgs &k, int64_t programs, int split, hipStream_t s)
+template <bool BF16, bool DMA, int NW>
+static nt_status launch_sdpa_groups(const SdpaArgs &k, int64_t programs, int split, hipStream_t s)
 {
-    if (split == 4) return launch_sdpa_inst<BF16, DMA, 4>(k, programs, s);
-    if constexpr (DMA)
-        if (split == 2) return launch_sdpa_inst<BF16, true, 2>(k, programs, s);
-    return launch_sdpa_inst<BF16, DMA, 1>(k, programs, s);
+    if (split == 4) return launch_sdpa_inst<BF16, DMA, 4, NW>(k, programs, s);
+    if constexpr (DMA || NW < 4)
+        if (split == 2) return launch_sdpa_inst<BF16, DMA, 2, NW>(k, programs, s);
+    if constexpr (DMA || NW == 4) return launch_sdpa_inst<BF16, DMA, 1, NW>(k, programs, s);
+    return fail(NT_ERR_UNSUPPORTED, "no attention kernel for this split");
+}
+
+template <bool BF16, bool DMA>
+static nt_status launch_sdpa_split(const SdpaArgs &k, int64_t programs, int split, int nw, hipStream_t s)
+{
+    if (nw == 1) return launch_sdpa_groups<BF16, DMA, 1>(k, programs, split, s);
+    if (nw == 2) return launch_sdpa_groups<BF16, DMA, 2>(k, programs, split, s);
+    return launch_sdpa_groups<BF16, DMA, 4>(k, programs, split, s);
 }
 
 // One workgroup per query pays while they do not queue up for the units with the same keys (bf16, us, sdpa_kernel / this one):
@@ -585,11 +597,10 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
         }
         return check_launch("sdpa_decode_kernel");
     }
-    const int64_t bh = batch * a.H, nqb = (a.Sq + kQBlock - 1) / kQBlock;
-    if (bh * nqb > kMaxWorkgroups) return fail(NT_ERR_UNSUPPORTED, "heads * query blocks exceeds 2^24 - 1");
+    const int64_t bh = batch * a.H;
+    if (batch * per_entry > kMaxWorkgroups) return fail(NT_ERR_UNSUPPORTED, "heads * query blocks exceeds 2^24 - 1");
     SdpaArgs k = a;
     k.BH = (int32_t)bh;
-    k.nqb = (int32_t)nqb;
     // (rows that do not overlap, and offsets that fit the range-checked loads: else through registers)
     const int nblk = (int)(((int64_t)a.Sk + kKeyBlock - 1) / kKeyBlock);
     auto streams = [&](int64_t ss) { return ss >= kHeadDim && ((int64_t)a.Sk + 10 * kKeyBlock) * ss * 2 < (1LL << 31); };
@@ -597,14 +608,36 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
     const bool far = a.k_ss >= kHeadDim && a.v_ss >= kHeadDim && !dma;     // (keys spread over 2 GB and more: every load a long way off)
     // A unit holds four groups of four wavefronts: launches with fewer programs than that split the keys, where there are enough
     // blocks to pay for the larger workgroup and the merge.  Measured (us, one group / split): 160 programs x 24 blocks 26.7 /
-    // 19.3, 90 x 32 34.1 / 23.1, 8 x 32 27.0 / 21.0, 144 x 13 15.8 / 14.0, 288 x 32 46.5 (as it was) / 36.3; 256 x 8 11.4 / 12.2.
-    const int64_t programs = bh * nqb;
-    // Through registers, where a group's loads are not ahead of its arithmetic, four groups pay while units stay empty (32
-    // programs x 64 blocks 57 / 44, 160 x 24 24.2 / 22.0, 256 x 32 32 / 35), two do not (512 x 32 51 / 56).
-    const int split = nblk < 12 || far ? 1 : programs <= (dma ? 256 : 160) ? 4 : programs <= 512 && dma ? 2 : 1;
+    // 19.3, 90 x 32 34.1 / 23.1, 8 x 32 27.0 / 21.0, 144 x 13 15.8 / 14.0, 288 x 32 46.5 (as it was) / 36.3, 228 x 11 15.0 / 13.5,
+    // 208 x 7 11.2 / 10.6; 256 x 8 11.4 / 12.2 in four groups, 330 x 7 14.1 / 15.3.
+    // Launches that leave units without a program take narrower blocks of queries, as long as one round of the units holds them:
+    // the keys are read more often, but sixteen wavefronts on one unit and none on the next cost more.  128 queries / best (us, in
+    // graph replays): 64 queries, four groups, 2 x 10 heads, 611 x 1102 16.8 / 13.2, two groups, 13 heads, 824 x 248 6.9 / 5.9;
+    // 32 queries, four groups, 2 x 8 heads, 384 x 1216 15.7 / 10.0, 10 x 2 heads, 152 x 512 9.2 / 6.5, two groups, 37 heads, 175 x
+    // 384 8.1 / 6.5.  Beyond a round they lose: 26 heads, 896 x 984 on 364 blocks of 64 21.8 for 16.1.  Four groups of 32 from seven
+    // blocks of keys on (6: 6.3 in two / 6.6, 8: 8.1 / 7.2), of 64 from twelve (9: 8.5 / 8.8, 15: 11.1 / 10.4).
+    auto blocks_of = [&](int64_t queries) { return bh * (((int64_t)a.Sq + queries - 1) / queries); };
+    const int64_t programs = blocks_of(kQBlock);
+    int split = 1, nw = 4;
+    if (far && nblk >= 12) {                                             // (a few blocks: dealt out like anybody's, the same bits)
+    } else if (blocks_of(32) <= 256) {
+        split = nblk >= 7 ? 4 : nblk >= 2 ? 2 : 1;
+        nw = dma || split > 1 ? 1 : 4;
+    } else if (blocks_of(64) <= 256) {
+        split = nblk >= 12 ? 4 : nblk >= 2 ? 2 : 1;
+        nw = dma || split > 1 ? 2 : 4;
+    } else if (dma) {
+        split = programs <= 256 ? (nblk >= 12 ? 4 : nblk >= 7 ? 2 : 1) : programs <= 512 && nblk >= 12 ? 2 : 1;
+    } else {
+        // Through registers, where a group's loads are not ahead of its arithmetic, four groups pay while units stay empty (32
+        // programs x 64 blocks 57 / 44, 160 x 24 24.2 / 22.0, 256 x 32 32 / 35), two do not (512 x 32 51 / 56).
+        split = nblk >= 12 && programs <= 160 ? 4 : 1;
+    }
+    k.nqb = (int32_t)(((int64_t)a.Sq + 32 * nw - 1) / (32 * nw));
     hipStream_t s = (hipStream_t)stream;
-    if (bf16) return dma ? launch_sdpa_split<true, true>(k, programs, split, s) : launch_sdpa_split<true, false>(k, programs, split, s);
-    return dma ? launch_sdpa_split<false, true>(k, programs, split, s) : launch_sdpa_split<false, false>(k, programs, split, s);
+    const int64_t grid = bh * k.nqb;
+    if (bf16) return dma ? launch_sdpa_split<true, true>(k, grid, split, nw, s) : launch_sdpa_split<true, false>(k, grid, split, nw, s);
+    return dma ? launch_sdpa_split<false, true>(k, grid, split, nw, s) : launch_sdpa_split<false, false>(k, grid, split, nw, s);
 }
 
 nt_status launch_sdpa_desc(const void *q, const nt_tensor_desc *dq, const void *k, const nt_tensor_desc *dk,

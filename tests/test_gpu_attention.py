@@ -269,3 +269,26 @@ def test_few_queries_weigh_in_fp32():
     want = torch.from_numpy(oat.sdpa(q, k, v, "bf16")).to(torch.bfloat16)
     got = torch.from_numpy(run(q, k, v, "bf16")).to(torch.bfloat16)
     assert (got != want).float().mean() < 0.01                       # (a result within fp32 error of the middle between two)
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,Sq,Sk", [
+    # launches that leave units empty: blocks of 32 queries in one, two and four groups of one wavefront ...
+    (1, 7, 33, 64), (2, 3, 97, 65), (1, 5, 160, 384), (1, 9, 64, 385), (2, 4, 129, 449), (1, 64, 128, 511), (1, 2, 1000, 1025),
+    # ... of 64 in as many groups of two, up to a full round of the units ...
+    (1, 65, 97, 33), (2, 16, 300, 70), (1, 64, 256, 700), (1, 51, 320, 705), (4, 16, 200, 769),
+    # ... of 128: two groups from seven blocks of keys on, four from twelve
+    (1, 129, 129, 400), (1, 128, 200, 449), (1, 128, 140, 705)])
+def test_blocks_of_queries_of_every_width(dt, B, H, Sq, Sk):
+    q, k, v = (si.normal_bits((B, H, n, 64), dt, 150 + i, 1.0) for i, n in enumerate([Sq, Sk, Sk]))
+    ref = oat.sdpa(q, k, v, dt)
+    assert_gates(run(q, k, v, dt), ref, dt, f"sdpa {dt} {B}x{H}x{Sq}x{Sk}")
+    # rows of K and V that overlap go through registers: the same walk, the same bits as from a copy
+    if Sq * H < 3000:
+        gq = to_gpu(q, dt)
+        gk, gv = (to_gpu(si.normal_bits((B * H * Sk * 60 + 64,), dt, 155 + i, 1.0), dt).as_strided((B, H, Sk, 64), (H * Sk * 60, Sk * 60, 60, 1)) for i in range(2))
+        got, want = torch.full_like(gq, float("nan")), torch.full_like(gq, float("nan"))
+        nt.sdpa(gq, gk, gv, got)
+        nt.sdpa(gq, gk.contiguous(), gv.contiguous(), want)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
