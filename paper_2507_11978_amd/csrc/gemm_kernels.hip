@@ -830,8 +830,8 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     // (the estimates cost the host more than the rest of the call: the last few answers are kept, by value)
     enum { NEITHER, PATCH, PLANE };
     struct Known { ConvHint h{}; ConvPatchArgs patch{}; ConvPatchPlan patch_plan{}; ConvPlaneArgs plane{}; ConvPlanePlan plane_plan{}; bool set = false, patch_ok = false; int kind = NEITHER; };
-    static thread_local Known known[8];
-    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 8];
+    static thread_local Known known[64];
+    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 61];
     if (!k.set || k.patch_ok != patch_ok || !same_conv(k.h, h)) {
         k = Known{};
         k.h = h;

@@ -70,3 +70,25 @@ def test_random_products(case):
     nt.gemm(a, b, C)
     torch.cuda.synchronize()
     assert torch.equal(C.cpu(), want), f"path {nt.last_kernel_path()}, k split {nt.last_k_split()}"
+
+
+def test_convolutions_that_differ_in_one_parameter():
+    """Calls in turn whose sizes agree in all but one of strides in memory, filter, stride, padding and tile (the grid and operand
+    maps of a call are kept by all of these): each its own result, again and again, and errors stay errors in between."""
+    N, C, H, W, F = 2, 32, 9, 9, 16
+    X, Wt = si.conv_inputs(N, C, H, W, F, 3, 3, "f16", seed=170, dist="int")
+    x, w = to_gpu(X, "f16"), to_gpu(Wt, "f16")
+    nhwc = x.permute(0, 2, 3, 1).contiguous().permute(0, 3, 1, 2)
+    krsc = w.permute(0, 2, 3, 1).contiguous().permute(0, 3, 1, 2)
+    calls = [(x, w, (1, 1), (1, 1), None), (nhwc, w, (1, 1), (1, 1), None), (x, krsc, (1, 1), (1, 1), None), (x, w, (1, 1), (1, 1), (64, 64, 32)),
+             (x, w, (2, 2), (1, 1), None), (x, w, (1, 2), (1, 1), None), (x, w, (2, 1), (1, 1), None), (x, w, (1, 1), (0, 1), None), (x, w, (1, 1), (1, 0), None),
+             (x[:1], w, (1, 1), (1, 1), None), (x, w[:8], (1, 1), (1, 1), None)]
+    want = [onum.conv2d(X[:a.shape[0]], Wt[:b.shape[0]], "f16", st, pad) for a, b, st, pad, _ in calls]
+    for _ in range(3):
+        for (a, b, st, pad, tile), ref in zip(calls, want):
+            y = torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda")
+            nt.conv2d_implicit(a, b, y, st, pad, tile=tile)
+            torch.cuda.synchronize()
+            assert np.array_equal(y.double().cpu().numpy(), ref), (a.stride(), b.stride(), st, pad, tile)
+            with pytest.raises(Exception):
+                nt.conv2d_implicit(a, b, y[:, :, 1:], st, pad, tile=tile)
