@@ -401,6 +401,13 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     constexpr uint32_t A_BYTES = TileA::BYTES, B_BYTES = TileB::BYTES, B_BASE = kRing * A_BYTES;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
+    // (every argument that the way to the first load needs, asked for at once: left to the compiler they came in three trips, one
+    // behind the other, 0.2 us of a program that may last 4)
+    if constexpr (EDGE)
+        asm volatile("" : : "s"(gridDim.x), "s"(g.A), "s"(g.B), "s"(g.lda), "s"(g.ldb), "s"(g.sa_batch), "s"(g.sb_batch), "s"(g.mt), "s"(g.nt), "s"(g.alpha), "s"(g.beta), "s"(g.act),
+                     "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.a_extent), "s"(g.b_extent), "s"(g.patch), "s"(g.k_parts), "s"(g.k_short), "s"(g.a_short), "s"(g.b_short));
+    else
+        asm volatile("" : : "s"(gridDim.x), "s"(g.A), "s"(g.B), "s"(g.lda), "s"(g.ldb), "s"(g.sa_batch), "s"(g.sb_batch), "s"(g.mt), "s"(g.nt), "s"(g.kt), "s"(g.alpha), "s"(g.beta), "s"(g.act));
     int64_t bi, ti, tj;
     if constexpr (TRACE) {
         bi = g.trace_program / (g.mt * g.nt);
@@ -413,13 +420,16 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int64_t row0 = ti * BM, col0 = tj * BN;
+    int64_t K = g.K, a_extent = g.a_extent, b_extent = g.b_extent;
+    if constexpr (EDGE)
+        if (bi + 1 == g.k_parts) { K = g.k_short; a_extent = g.a_short; b_extent = g.b_short; }      // (uniform)
 
     const char *gA = reinterpret_cast<const char *>(g.A + bi * g.sa_batch + (ALAY == KCONTIG ? row0 * g.lda : row0));
     const char *gB = reinterpret_cast<const char *>(g.B + bi * g.sb_batch + (BLAY == KCONTIG ? col0 * g.ldb : col0));
     const int64_t a_step = (ALAY == KCONTIG ? (int64_t)kSliceK : (int64_t)kSliceK * g.lda) * 2;
     const int64_t b_step = (BLAY == KCONTIG ? (int64_t)kSliceK : (int64_t)kSliceK * g.ldb) * 2;
     // (EDGE: K need not be a whole number of slices; the tail of the last one is zeroed in LDS, see zero_tail)
-    const int64_t n_slices = EDGE ? (g.K + kSliceK - 1) / kSliceK : g.kt * (kBK / kSliceK);
+    const int64_t n_slices = EDGE ? (K + kSliceK - 1) / kSliceK : g.kt * (kBK / kSliceK);
 
     TileA ta;
     TileB tb;
@@ -449,8 +459,8 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     constexpr int NM = TM * TN, ND = TileA::PER + TileB::PER;
     u32x4 rsrc_a{0, 0, 0, 0}, rsrc_b{0, 0, 0, 0};
     if constexpr (EDGE) {
-        rsrc_a = make_rsrc(gA, g.a_extent - (gA - reinterpret_cast<const char *>(g.A + bi * g.sa_batch)));
-        rsrc_b = make_rsrc(gB, g.b_extent - (gB - reinterpret_cast<const char *>(g.B + bi * g.sb_batch)));
+        rsrc_a = make_rsrc(gA, a_extent - (gA - reinterpret_cast<const char *>(g.A + bi * g.sa_batch)));
+        rsrc_b = make_rsrc(gB, b_extent - (gB - reinterpret_cast<const char *>(g.B + bi * g.sb_batch)));
     }
     auto dma = [&](int d, const char *pa, const char *pb, uint32_t ring) {
         if constexpr (!EDGE) {
@@ -487,7 +497,7 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     // the last slice has landed (g.patch: bit 0 = A, bit 1 = B; set by the host for such operands only).
     int patch_a = -1, patch_b = -1;
     if constexpr (EDGE) {
-        const int kk = (int)(g.K - 1 - last * kSliceK);
+        const int kk = (int)(K - 1 - last * kSliceK);
         const int64_t ra = g.M - 1 - row0, rb = g.N - 1 - col0;
         if ((g.patch & 1) && ra < BM && TileA::owner((int)ra, kk) == wave) patch_a = (int)TileA::place((int)ra, kk);
         if ((g.patch & 2) && rb < BN && TileB::owner((int)rb, kk) == wave) patch_b = (int)TileB::place((int)rb, kk);
@@ -497,18 +507,18 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     auto settle = [&](int64_t s, uint32_t pos) {
         if constexpr (EDGE) {
             if (s != last) return;
-            if ((s + 1) * kSliceK > g.K) {
-                const int keep = (int)(g.K - s * kSliceK);
+            if ((s + 1) * kSliceK > K) {
+                const int keep = (int)(K - s * kSliceK);
                 ta.zero_tail(smem, pos * A_BYTES, wave, lane, keep);
                 tb.zero_tail(smem, B_BASE + pos * B_BYTES, wave, lane, keep);
             }
             if (g.patch && lane == 0) {
                 if (patch_a >= 0)
                     *reinterpret_cast<uint16_t *>(smem + pos * A_BYTES + patch_a) =
-                        *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.A + bi * g.sa_batch) + g.a_extent - 2);
+                        *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.A + bi * g.sa_batch) + a_extent - 2);
                 if (patch_b >= 0)
                     *reinterpret_cast<uint16_t *>(smem + B_BASE + pos * B_BYTES + patch_b) =
-                        *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.B + bi * g.sb_batch) + g.b_extent - 2);
+                        *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.B + bi * g.sb_batch) + b_extent - 2);
             }
         }
     };
@@ -604,13 +614,16 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16u
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int64_t row0 = ti * BM, col0 = tj * BN;
+    int64_t K = g.K, a_extent = g.a_extent, b_extent = g.b_extent;
+    if constexpr (EDGE)
+        if (bi + 1 == g.k_parts) { K = g.k_short; a_extent = g.a_short; b_extent = g.b_short; }      // (uniform)
 
     const char *pa = reinterpret_cast<const char *>(g.A + bi * g.sa_batch + (ALAY == KCONTIG ? row0 * g.lda : row0));
     const char *pb = reinterpret_cast<const char *>(g.B + bi * g.sb_batch + (BLAY == KCONTIG ? col0 * g.ldb : col0));
     const int64_t a_step = (ALAY == KCONTIG ? (int64_t)kSliceK : (int64_t)kSliceK * g.lda) * 2;
     const int64_t b_step = (BLAY == KCONTIG ? (int64_t)kSliceK : (int64_t)kSliceK * g.ldb) * 2;
     // (full tiles: a multiple of 4, at least 4, checked by the host)
-    const int64_t n_slices = EDGE ? (g.K + kSliceK - 1) / kSliceK : g.kt * (kBK / kSliceK);
+    const int64_t n_slices = EDGE ? (K + kSliceK - 1) / kSliceK : g.kt * (kBK / kSliceK);
     const int32_t last = (int32_t)n_slices - 1;
 
     TileA ta;
@@ -647,9 +660,9 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16u
     int32_t rq = 0;
     int patch_a = -1, patch_b = -1;
     if constexpr (EDGE) {
-        rsrc_a = make_rsrc(pa, g.a_extent - (pa - reinterpret_cast<const char *>(g.A + bi * g.sa_batch)));
-        rsrc_b = make_rsrc(pb, g.b_extent - (pb - reinterpret_cast<const char *>(g.B + bi * g.sb_batch)));
-        const int kk = (int)(g.K - 1 - (int64_t)last * kSliceK);
+        rsrc_a = make_rsrc(pa, a_extent - (pa - reinterpret_cast<const char *>(g.A + bi * g.sa_batch)));
+        rsrc_b = make_rsrc(pb, b_extent - (pb - reinterpret_cast<const char *>(g.B + bi * g.sb_batch)));
+        const int kk = (int)(K - 1 - (int64_t)last * kSliceK);
         const int64_t ra = g.M - 1 - row0, rb = g.N - 1 - col0;
         if ((g.patch & 1) && ra < BM && TileA::owner((int)ra, kk) == wave) patch_a = (int)TileA::place((int)ra, kk);
         if ((g.patch & 2) && rb < BN && TileB::owner((int)rb, kk) == wave) patch_b = (int)TileB::place((int)rb, kk);
@@ -661,18 +674,18 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16u
     };
     // what the last slice needs once this wavefront's part of it has landed at ring position `pos`
     auto settle_last = [&](uint32_t pos) {
-        if ((int64_t)(last + 1) * kSliceK > g.K) {
-            const int keep = (int)(g.K - (int64_t)last * kSliceK);
+        if ((int64_t)(last + 1) * kSliceK > K) {
+            const int keep = (int)(K - (int64_t)last * kSliceK);
             ta.zero_tail(smem, pos * A_BYTES, wave, lane, keep);
             tb.zero_tail(smem, B_BASE + pos * B_BYTES, wave, lane, keep);
         }
         if (g.patch && lane == 0) {
             if (patch_a >= 0)
                 *reinterpret_cast<uint16_t *>(smem + pos * A_BYTES + patch_a) =
-                    *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.A + bi * g.sa_batch) + g.a_extent - 2);
+                    *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.A + bi * g.sa_batch) + a_extent - 2);
             if (patch_b >= 0)
                 *reinterpret_cast<uint16_t *>(smem + B_BASE + pos * B_BYTES + patch_b) =
-                    *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.B + bi * g.sb_batch) + g.b_extent - 2);
+                    *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(g.B + bi * g.sb_batch) + b_extent - 2);
         }
     };
 

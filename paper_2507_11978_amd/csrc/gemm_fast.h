@@ -45,6 +45,9 @@ struct FastArgs {
     // direct kernel, range-checked flavour: bit 0 / 1 = the word of a load that holds A's / B's very last element can end
     // past the operand (odd pitch or extent) and is dropped by the range check; the kernel then puts that element in place itself
     int32_t patch;
+    // direct kernel, range-checked flavour, parts of a reduction that is no whole number of them: the last of the k_parts batch
+    // entries (0: entries alike) is k_short long, with bounds of its own
+    int64_t k_parts, k_short, a_short, b_short;
     // persistent kernel: the launch's number of programs (each workgroup walks programs w, w + grid, w + 2 grid, ...)
     int64_t nprog;
     // ... and the start-up stagger: workgroup w starts ((w / 8) % 4) * stagger hundredths of a microsecond late (0: none)

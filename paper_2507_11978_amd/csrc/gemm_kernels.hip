@@ -45,7 +45,7 @@ static const TileEntry kTiles[] = {{64, 64, 32}, {128, 128, 64}, {256, 128, 64},
 // (time of one 64-wide k tile with the whole unit's matrix rate) plus a fixed `fixed` microseconds of launch, prologue and
 // epilogue, which `resident` co-resident workgroups overlap with each other's multiplications.  The constants are fits to
 // measurements on 8192 x 8192 x K and batched 2048 x 2048 x K problems.
-static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out);
+static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out, bool uneven = false);
 static bool beyond_l2(int64_t M, int64_t N, int64_t kt) { return (M + N) * kt * 64 * 2 > (32 << 20); }
 
 nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow)
@@ -559,7 +559,8 @@ nt_tile_cfg pick_conv_tile(int64_t M, int64_t N, int64_t K)
 static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nchk == 0; }
 
 // The same for a GEMM with few output tiles and a long reduction (a skinny product): the split is run as a batched
-// product over equal parts of K, so only a number of parts that divides the k tiles evenly is taken (at least 8 k tiles
+// product over parts of K: equal ones, so that only a number of parts that divides the k tiles evenly is taken, or (`uneven`, the
+// range-checked kernels) the last one shorter, and the cheapest number of parts is (at least 8 k tiles
 // each).  Two dependent launches and the trip of the partial tiles through memory have their price: the split is taken
 // when an estimate of it (the launches, a program's k tiles with its compute unit to itself, the slices written and read at
 // 3 TB/s) beats the estimate of the single launch.  `small`: the 64 x 64 tile (us: 3.5 + 0.24 per 64-k tile, the split's
@@ -567,7 +568,7 @@ static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nc
 // Measured: 1024 x 1024 x 1024 on 128 x 128 11 us unsplit against 19 split; on 64 x 64, unsplit / split: 256 x 256 x 2048 10.6 /
 // 8.0, x 8192 32.9 / 9.8, 512 x 512 x 4096 18.7 / 12.7, 16 x 1024 x 4096 20.0 / 8.0 (on 128 x 128, split: 10.3, 12.1, 13.5, 10.8).
 // *cost_out: the estimate of the way taken.
-static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out)
+static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool small, double *cost_out, bool uneven)
 {
     // (operands beyond the L2s come from memory: 72 x 7136 x 3712 0.32 per k tile, 704 x 1408 x 8640 0.33, 192 x 5376 x 7488 0.46)
     const double step = small ? (beyond_l2(M, N, kt) ? 0.36 : 0.24) : 0.37, once = small ? 3.5 : 7.0, twice = small ? 6.0 : 12.0;
@@ -576,6 +577,16 @@ static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool 
     if (programs >= (small ? 192 : 128) || kt < 32) return 1;
     // (about a program per unit; of the 64 x 64 tile's no more than that: a few units with two of them set the pace)
     const int64_t want = std::min<int64_t>(small ? 256 / programs : (256 + programs / 2) / programs, kt / 8);
+    if (uneven) {
+        int best = 1;
+        for (int64_t d = 2; d <= want; ++d) {
+            const int64_t per = (kt + d - 1) / d;
+            if ((kt + per - 1) / per != d) continue;
+            const double split = twice + step * (double)per + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
+            if (split < *cost_out) { *cost_out = split; best = (int)d; }
+        }
+        return best;
+    }
     for (int64_t d = want; d >= 2; --d) {
         if (kt % d) continue;
         const double split = twice + step * (double)kt / (double)d + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
@@ -1123,16 +1134,12 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     const int64_t nwg = g.batch * g.mt * g.nt;
     hipStream_t s = (hipStream_t)g.stream;
     const bool ragged_mn = (g.M % t.bm) || (g.N % t.bn), ragged_k = (g.K % 64) != 0;
-    // k split: `ksplit` equal parts of K as the entries of a batched product into fp32 slices of the workspace
-    double split_cost = 0;
-    const int ksplit = g.batch == 1 && !ragged_k && (t.bm >= 128 || !g.user_tile) ? gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost) : 1;
     const bool skinny = g.batch == 1 && !g.user_tile && !g.trace.out && skinny_ok(a, alay, blay);
     auto run_skinny = [&]() {
         if (path_out) *path_out = PATH_DIRECT;
         t_k_split = skinny_parts(a);
         return launch_skinny(a, bf16, s);
     };
-    if (skinny && (ksplit == 1 || skinny_cost(a) <= split_cost)) return run_skinny();
     // Operands stored to a C (and added to a D) with unit stride along n stream straight into LDS.  Full tiles of
     // 16-byte aligned operands: plain loads.  Everything else -- tiles that overhang M or N, a ragged K, rows with
     // only the element's 2-byte alignment -- takes the same loads as range-checked buffer accesses (EDGE kernels),
@@ -1148,6 +1155,20 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
         return extent % 4 == 0 && ld % 2 == 0 && s_batch % 2 == 0;
     };
     const bool direct = plain_direct || (out_ok && (alay == KCONTIG || g.K * a.lda < (1LL << 30)) && (blay == KCONTIG || g.K * a.ldb < (1LL << 30)));
+    // k split: `ksplit` parts of K as the entries of a batched product into fp32 slices of the workspace.  Equal parts of whole k tiles;
+    // K no multiple of 64 (range-checked loads): whole k tiles but for a shorter last part.  One launch / so (us over rotating
+    // operands, in graph replays): weights stored [K, N] 10 x 3008 x 5408 25.2 / 11.8, 31 x 3094 x 3768 19.2 / 11.2, 1 x 7779 x 7368
+    // 40.6 / 30.0; [N, K] 47 x 3176 x 4264 21.5 / 12.1, 25 x 1888 x 2083 11.3 / 8.8; square ones 446 x 448 x 6712 37.1 / 15.3,
+    // 448 x 234 x 2021 14.9 / 10.1.  Not those that the kernel for few rows takes, which needs no second launch.
+    double split_cost = 0;
+    int ksplit = 1;
+    if (g.batch == 1 && (t.bm >= 128 || !g.user_tile)) {
+        if (!ragged_k) ksplit = gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost);
+        else if (direct && !skinny && !g.trace.out) ksplit = gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost, true);
+        // (an entry point that brings its own scratch memory refuses what does not fit: not for the sake of a shorter last part)
+        if (ragged_k && g.ws_strict && (size_t)ksplit * g.M * g.N * 4 > g.ws_given_bytes) ksplit = 1;
+    }
+    if (skinny && (ksplit == 1 || skinny_cost(a) <= split_cost)) return run_skinny();
     if (direct && !plain_direct)
         a.patch = (words_aligned(a.lda, a.sa_batch, a.a_extent) ? 0 : 1) | (words_aligned(a.ldb, a.sb_batch, a.b_extent) ? 0 : 2);
     if (path_out) *path_out = direct ? PATH_DIRECT : PATH_FAST;
@@ -1182,13 +1203,16 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
         if (!ws) return skinny ? run_skinny() : launch(a, alay, blay, nwg, s);
         t_k_split = ksplit;
         FastArgs part = a;
-        const int64_t Kp = g.K / ksplit;
-        part.K = Kp; part.kt = a.kt / ksplit;
+        const int64_t per = (a.kt + ksplit - 1) / ksplit, Kp = per * 64, last = g.K - (ksplit - 1) * Kp;
+        part.K = Kp; part.kt = per;
         part.sa_batch = alay == KCONTIG ? Kp : Kp * a.lda;
         part.sb_batch = blay == KCONTIG ? Kp : Kp * a.ldb;
-        // (K and Kp are multiples of 64: a part's words are as aligned as the whole's, and a part is as streamable)
-        part.a_extent = (alay == KCONTIG ? (g.M - 1) * a.lda + Kp : (Kp - 1) * a.lda + g.M) * 2;
-        part.b_extent = (blay == KCONTIG ? (g.N - 1) * a.ldb + Kp : (Kp - 1) * a.ldb + g.N) * 2;
+        // (Kp is a multiple of 64: a part's words are as aligned as the whole's, and a part is as streamable)
+        auto a_bytes = [&](int64_t K) { return (alay == KCONTIG ? (g.M - 1) * a.lda + K : (K - 1) * a.lda + g.M) * 2; };
+        auto b_bytes = [&](int64_t K) { return (blay == KCONTIG ? (g.N - 1) * a.ldb + K : (K - 1) * a.ldb + g.N) * 2; };
+        part.a_extent = a_bytes(Kp);
+        part.b_extent = b_bytes(Kp);
+        if (last != Kp) { part.k_parts = ksplit; part.k_short = last; part.a_short = a_bytes(last); part.b_short = b_bytes(last); }
         part.C = ws; part.scm = g.N; part.scn = 1; part.sc_batch = g.M * g.N; part.out_dtype = NT_F32;
         part.D = nullptr; part.alpha = 1.f; part.beta = 0.f; part.act = 0;
         const nt_status st = launch(part, alay, blay, nwg * ksplit, s);

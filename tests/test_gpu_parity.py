@@ -550,6 +550,47 @@ def test_skinny_products_split_along_k(M, N, K, dt, out):
         assert torch.isnan(buf[0]).all() and torch.isnan(buf[M + 1]).all() and torch.isnan(buf[:, N:]).all()
 
 
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("M,N,K", [
+    (16, 1024, 4097), (20, 1000, 4095), (33, 520, 3075), (64, 296, 2049),      # last parts of one, of all but one, of a few elements
+    (100, 129, 9001), (48, 3008, 5408), (200, 264, 2530), (1, 264, 2111), (257, 130, 20003)])
+def test_split_along_k_with_a_shorter_last_part(M, N, K, dt, out):
+    """K no multiple of 64: the parts are whole k tiles but for the last one, which ends where the operands end (odd pitches,
+    odd extents, overhanging tiles; elements behind the operands are NaN).  Exact integers, every orientation, a fused epilogue."""
+    A, B = si.gemm_inputs(M, N, K, dt, seed=95, dist="int")
+    ref = onum.gemm(A, B, dt)
+    want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
+
+    def inside(t):
+        buf = torch.full((t.numel() + 66,), float("nan"), dtype=t.dtype, device="cuda")
+        v = buf[33:33 + t.numel()].view(t.shape)
+        v.copy_(t)
+        return v
+
+    a, b = to_gpu(A, dt), to_gpu(B, dt)
+    at, bt = inside(a.t().contiguous()).t(), inside(b.t().contiguous()).t()
+    a, b = inside(a), inside(b)
+    split = 1
+    for aa, bb in [(a, b), (a, bt), (at, b), (at, bt)]:
+        buf = torch.full((M + 2, N + 8), float("nan"), dtype=TORCH_DT[out], device="cuda")
+        C = buf[1:M + 1, :N]
+        nt.gemm(aa, bb, C)
+        torch.cuda.synchronize()
+        assert nt.last_kernel_path() == nt.PATH_DIRECT
+        split = max(split, nt.last_k_split())
+        assert torch.equal(C.cpu(), want)
+        assert torch.isnan(buf[0]).all() and torch.isnan(buf[M + 1]).all() and torch.isnan(buf[:, N:]).all()
+        C2 = torch.empty((M, N), dtype=TORCH_DT[out], device="cuda")
+        nt.gemm_noalloc(aa, bb, C2)
+        inp = torch.full((N,), 3.0, dtype=TORCH_DT[out], device="cuda")
+        C3 = torch.empty((M, N), dtype=TORCH_DT[out], device="cuda")
+        nt.addmm(inp, aa, bb, C3, alpha=-1.0, beta=2.0, act="relu")
+        torch.cuda.synchronize()
+        assert torch.equal(C2.cpu(), want)
+        assert torch.equal(C3.cpu(), torch.from_numpy(np.maximum(6.0 - ref, 0.0)).to(torch.float32).to(TORCH_DT[out]))
+    assert split > 1
+
+
 def test_k_split_is_left_alone_where_it_does_not_pay():
     for M, N, K in [(1024, 1024, 1024), (4096, 4096, 4096), (512, 2048, 1024)]:
         A, B = si.gemm_inputs(M, N, K, "f16", seed=94, dist="int")
