@@ -77,14 +77,16 @@ nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool 
     for (const Cand &c : cands) {
         const int64_t programs = batch * ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         const int64_t p = (programs + 255) / 256;
-        // (problems that are not whole aligned tiles run with one workgroup per unit for every tile but the smallest)
+        // (the range-checked kernels for overhanging tiles and ragged or unaligned operands fit two workgroups per unit like the others:
+        // with one assumed for them, 27 x 1344 x 1800 x 656 ran on 256 x 256 in 181 us for 142 on 128 x 256, 30 x 856 x 1472 x 320
+        // 61.8 / 51.7, 31 x 304 x 704 x 64 14.1 / 10.4, 14 x 1640 x 960 x 299 31.9 / 27.9)
         const bool full = M % c.bm == 0 && N % c.bn == 0 && K % 64 == 0;
-        const int resident = full || (c.bm == 128 && c.bn == 128) ? c.resident : 1;
         // (the persistent kernel staggers short programs: a program's fixed part then overlaps other units' multiplications)
         const bool staggered = c.bm == 256 && c.bn == 256 && full && programs >= 512 && kt <= 16;
         const double cost = staggered ? 4.0 + (double)p * (6.0 + kt * c.step)
-                                      : (double)((p + resident - 1) / resident) * c.fixed + (double)p * kt * c.step;
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = nt_tile_cfg{c.bm, c.bn, 64}; }
+                                      : (double)((p + c.resident - 1) / c.resident) * c.fixed + (double)p * kt * c.step;
+        // (among overhanging tiles 128 x 128 on a tie: 27 x 1184 x 448 x 114 19.0 us, on 256 x 128 19.8)
+        if (best_cost == 0 || cost < best_cost * (c.bm + c.bn == 256 && !full ? 1.02 : 1.0)) { best_cost = cost; best = nt_tile_cfg{c.bm, c.bn, 64}; }
     }
     return best;
 }
