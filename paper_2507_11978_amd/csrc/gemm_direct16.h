@@ -401,13 +401,11 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     constexpr uint32_t A_BYTES = TileA::BYTES, B_BYTES = TileB::BYTES, B_BASE = kRing * A_BYTES;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-    // (every argument that the way to the first load needs, asked for at once: left to the compiler they came in three trips, one
-    // behind the other, 0.2 us of a program that may last 4)
+    // (EDGE: every argument that the way to the first load needs, asked for at once: left to the compiler they came in three trips,
+    // one behind the other, 0.2 us of a program that may last 4.  The full tiles' few arguments it asks for well by itself)
     if constexpr (EDGE)
         asm volatile("" : : "s"(gridDim.x), "s"(g.A), "s"(g.B), "s"(g.lda), "s"(g.ldb), "s"(g.sa_batch), "s"(g.sb_batch), "s"(g.mt), "s"(g.nt), "s"(g.alpha), "s"(g.beta), "s"(g.act),
                      "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.a_extent), "s"(g.b_extent), "s"(g.patch), "s"(g.k_parts), "s"(g.k_short), "s"(g.a_short), "s"(g.b_short));
-    else
-        asm volatile("" : : "s"(gridDim.x), "s"(g.A), "s"(g.B), "s"(g.lda), "s"(g.ldb), "s"(g.sa_batch), "s"(g.sb_batch), "s"(g.mt), "s"(g.nt), "s"(g.kt), "s"(g.alpha), "s"(g.beta), "s"(g.act));
     int64_t bi, ti, tj;
     if constexpr (TRACE) {
         bi = g.trace_program / (g.mt * g.nt);

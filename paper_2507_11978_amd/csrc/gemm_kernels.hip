@@ -83,10 +83,11 @@ nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool 
         const bool full = M % c.bm == 0 && N % c.bn == 0 && K % 64 == 0;
         // (the persistent kernel staggers short programs: a program's fixed part then overlaps other units' multiplications)
         const bool staggered = c.bm == 256 && c.bn == 256 && full && programs >= 512 && kt <= 16;
-        const double cost = staggered ? 4.0 + (double)p * (6.0 + kt * c.step)
-                                      : (double)((p + c.resident - 1) / c.resident) * c.fixed + (double)p * kt * c.step;
-        // (among overhanging tiles 128 x 128 on a tie: 27 x 1184 x 448 x 114 19.0 us, on 256 x 128 19.8)
-        if (best_cost == 0 || cost < best_cost * (c.bm + c.bn == 256 && !full ? 1.02 : 1.0)) { best_cost = cost; best = nt_tile_cfg{c.bm, c.bn, 64}; }
+        double cost = staggered ? 4.0 + (double)p * (6.0 + kt * c.step)
+                                : (double)((p + c.resident - 1) / c.resident) * c.fixed + (double)p * kt * c.step;
+        // (an overhanging 256 x 128 not on a tie with 128 x 128: 27 x 1184 x 448 x 114 19.8 us for 19.0)
+        if (c.bm == 256 && c.bn == 128 && !full) cost *= 1.02;
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = nt_tile_cfg{c.bm, c.bn, 64}; }
     }
     return best;
 }
