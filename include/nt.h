@@ -309,10 +309,14 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * out-of-image positions (padding) read as zero.  dy must have P = (H + 2*pad_h - R) /
  * stride_h + 1 (integer division), likewise Q; otherwise NT_ERR_SHAPE_MISMATCH.
  * Descriptors have ndim 4 with arbitrary strides.
+ * Calls with dense planes, channels in whole blocks of 32 and at least six filter taps keep the input rows under an output tile in LDS
+ * where that is estimated to be ahead of the ways below: with few positions or filters and 9 or 25 taps straight from the
+ * caller's tensors, without workspace; with many positions the filter is copied (only) into the workspace -- where the call is captured
+ * in a graph, only if the ways below would go through the workspace too.
  * Strided calls with channels in whole blocks of 32 and more than one filter tap, and unit-stride calls with such channels and
  * few output positions, run on a zero-padded channels-last copy of their input, made in the workspace beside the filter's
  * tap-major copy (unit-stride calls that need no k split keep to the kernels below with at most 128 filters, and where they
- * are captured in a graph).
+ * are captured in a graph, if the first paragraph's do not take them).
  * Other dense unit-stride calls (contiguous NCHW input, at most one column of padding) never materialise the unfolded input; with
  * more than 128 filters and channels in whole blocks of 32 they copy the filter (only) into the workspace in tap-major order,
  * unless it is stored that way already (a channels-last filter: strides (R S C, 1, S C, C)), which is then read as it is.  The

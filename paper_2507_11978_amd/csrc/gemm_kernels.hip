@@ -819,69 +819,6 @@ static double conv_copied_cost(const ConvHint &h)
     return 9.3 + 1.05 * gflop + 0.43 * input + 0.31 * k + 0.77 * filter;
 }
 
-// ---- route 0a: dense planes, channels in whole blocks of 32, the input rows under a tile resident in LDS, where one of the two
-// kernels that do this is estimated to be ahead of the routes below:
-//   gemm_conv_patch.hip, 9 or 25 taps: one launch straight from the caller's tensors.  Of unit stride only what does not run on
-//     tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one block gives a program's
-//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters;
-//   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
-//     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
-//     workspace otherwise: those keep to the patch or the channels-last copy.
-static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
-{
-    *taken = false;
-    const ConvHint &h = g.conv;
-    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
-    const int64_t RS = h.R * h.S, K = h.C * RS, HW = h.H * h.W, lim = 1 << 20;
-    if (RS < 6 || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
-    if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K) return NT_OK;
-    // (32-bit byte offsets; divisions through fp32 reciprocals, exact below 2^21)
-    if (HW < 8 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || h.N * (h.P * h.Q + 8) >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
-        (h.N - 1) * h.xs[0] + (h.C - 1) * h.xs[1] + HW >= (1LL << 30)) return NT_OK;
-    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1, small = conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K);
-    const bool patch_ok = (RS == 9 || RS == 25) && h.ws[0] % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0 && !(unit && (h.C < 64 || (h.K > 128 && !small)));
-    const bool plane_ok = K <= 32768 && !(unit && small);
-    // (the estimates cost the host more than the rest of the call: the last few answers are kept, by value)
-    enum { NEITHER, PATCH, PLANE };
-    struct Known { ConvHint h{}; ConvPatchArgs patch{}; ConvPatchPlan patch_plan{}; ConvPlaneArgs plane{}; ConvPlanePlan plane_plan{}; bool set = false, patch_ok = false; int kind = NEITHER; };
-    static thread_local Known known[64];
-    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 61];
-    if (!k.set || k.patch_ok != patch_ok || !same_conv(k.h, h)) {
-        k = Known{};
-        k.h = h;
-        k.patch_ok = patch_ok;
-        double cost = conv_copied_cost(h), c = 0;
-        if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.kind = PATCH; cost = c; }
-        if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) k.kind = PLANE;
-        k.set = true;
-    }
-    hipStream_t s = (hipStream_t)g.stream;
-    const bool bf16 = g.in_dtype == NT_BF16;
-    if (k.kind == PATCH) {
-        ConvPatchArgs a = k.patch;
-        a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
-        a.out_dtype = g.out_dtype;
-        *taken = true;
-        if (path_out) *path_out = PATH_CONV_CL;
-        t_k_split = k.patch_plan.waves;
-        return launch_conv_patch(a, k.patch_plan, bf16, s);
-    }
-    if (k.kind == PLANE) {
-        WorkspaceLease lease;
-        uint16_t *copy = (uint16_t *)lease.acquire((size_t)h.K * K * 2, s);
-        if (!copy) return NT_OK;
-        *taken = true;
-        const nt_status st = launch_conv_plane_filter((const uint16_t *)g.B, h.ws[0], copy, (int32_t)h.K, (int32_t)h.C, (int32_t)RS, s);
-        if (st != NT_OK) return st;
-        ConvPlaneArgs a = k.plane;
-        a.x = (const uint16_t *)g.A; a.w = copy; a.ldb = (uint32_t)K;
-        a.c.Y = g.C; a.c.out_dtype = g.out_dtype;
-        if (path_out) *path_out = unit ? PATH_CONV_TAP : PATH_CONV_CL;
-        return launch_conv_plane(a, k.plane_plan, bf16, s);
-    }
-    return NT_OK;
-}
-
 // Tile and number of parts of a channels-last convolution (F filters x M positions, `slices` 32-k slices): the cheapest by an
 // estimate of its product.  A unit runs two programs at a time; a program costs a fixed part and its slices, a split the
 // kernel that adds the parts and their trip through memory.  (Fits, us: 392 programs of 128 x 128 with 36 slices 27.5, 196
@@ -900,6 +837,21 @@ static void conv_cl_plan(int64_t F, int64_t M, int64_t slices, int *tile_out, in
             if (ks > 1) c += 4.0 + (double)ks * (double)F * (double)M * 8.0 / 3.0e6;
             if (best == 0 || c < best) { best = c; *tile_out = tile; *parts_out = (int)ks; }
         }
+}
+
+// What that route asks the workspace for: the copy (the padded image, or, one tap per axis, only the positions that are read), the
+// filter's tap-major copy, the parts' sums.
+struct ConvClSizes { int64_t eh, ew, Hc, Wc; size_t copy, filter, split; };
+static ConvClSizes conv_cl_sizes(const ConvHint &h, bool natural, int parts)
+{
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    ConvClSizes z;
+    z.eh = h.R == 1 ? h.sh : 1; z.ew = h.S == 1 ? h.sw : 1;
+    z.Hc = h.R == 1 ? h.P : h.H + 2 * h.ph; z.Wc = h.S == 1 ? h.Q : h.W + 2 * h.pw;
+    z.copy = up((size_t)h.N * z.Hc * z.Wc * h.C * 2);
+    z.filter = natural ? up((size_t)h.K * h.C * h.R * h.S * 2) : 0;
+    z.split = parts > 1 ? (size_t)parts * h.K * h.N * h.P * h.Q * 4 : 0;
+    return z;
 }
 
 // ---- route 0: on a channels-last copy of the input (gemm_conv_cl.hip), the filter's tap-major copy beside it: convolutions
@@ -956,16 +908,13 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
         conv_cl_plan(F, M, K / 32, &tile, &parts);
         per = (K / 32 + parts - 1) / parts;
     }
-    // the copy: the padded image, or (one tap per axis) only the positions that are read
-    const int64_t eh = h.R == 1 ? h.sh : 1, ew = h.S == 1 ? h.sw : 1;
-    const int64_t Hc = h.R == 1 ? h.P : h.H + 2 * h.ph, Wc = h.S == 1 ? h.Q : h.W + 2 * h.pw;
+    const ConvClSizes z = conv_cl_sizes(h, natural, parts);
+    const int64_t eh = z.eh, ew = z.ew, Hc = z.Hc, Wc = z.Wc;
     // (strides far beyond the filter read a fraction of a large image: the unfolded input is then the smaller copy by far.
     // (32,64,112,112) * (128,64,2,2), 51 MB, stride 8: 23.4 against 18.4; stride 4 25.7 / 25.2; (8,256,56,56) * (512,256,2,2), 13 MB,
     // stride 8: 15.7 / 22.9)
     if (!unit && h.N * Hc * Wc >= (16 << 20) / h.C && h.N * Hc * Wc >= 8 * RS * M && conv_unfold_ok(g)) return NT_OK;
-    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t copy_bytes = up((size_t)h.N * Hc * Wc * h.C * 2), filter_bytes = natural ? up((size_t)F * K * 2) : 0;
-    const size_t split_bytes = parts > 1 ? (size_t)parts * F * M * 4 : 0;
+    const size_t copy_bytes = z.copy, filter_bytes = z.filter, split_bytes = z.split;
     WorkspaceLease lease;
     char *region = (char *)lease.acquire(copy_bytes + filter_bytes + split_bytes, (hipStream_t)g.stream);
     if (!region) return NT_OK;
@@ -1006,21 +955,31 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
 // ---- route 2: a unit-stride convolution that the implicit kernels do not take as it is (more than one column of padding, a
 // channels-last or otherwise strided input): on a dense zero-padded copy of its input, made once in the workspace (the
 // input's size, not C R S times it), it is a dense convolution without padding.  *taken = false: not this route.
+// the convolution on the copy, and the copy's bytes; false: not this route's
+static bool conv_on_padded_copy(const GemmLaunch &g, GemmLaunch *g2, ConvArgs *probe, size_t *bytes)
+{
+    const ConvHint &h = g.conv;
+    if (!(conv_is_bare(g) && h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1 && h.ph >= 0 && h.pw >= 0 && h.xs[0] >= 0 && h.xs[1] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 &&
+          (h.H - 1) * h.xs[2] + (h.W - 1) * h.xs[3] < (1LL << 31)))
+        return false;
+    const int64_t Hp = h.H + 2 * h.ph, Wp = h.W + 2 * h.pw, total = h.N * h.C * Hp * Wp;
+    *g2 = g;
+    g2->conv.H = Hp; g2->conv.W = Wp; g2->conv.ph = 0; g2->conv.pw = 0;
+    g2->conv.xs[3] = 1; g2->conv.xs[2] = Wp; g2->conv.xs[1] = Hp * Wp; g2->conv.xs[0] = h.C * Hp * Wp;
+    g2->no_workspace = true;                             // (this route holds the workspace)
+    *bytes = ((size_t)((total + 7) / 8 * 8) * 2 + 255) / 256 * 256;
+    return Hp * Wp >= 8 && total < (1LL << 31) && match_conv(*g2, probe);
+}
+
 static nt_status route_conv_padded_copy(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
     const ConvHint &h = g.conv;
-    if (!(conv_is_bare(g) && h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1 && h.ph >= 0 && h.pw >= 0 && h.xs[0] >= 0 && h.xs[1] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 &&
-          (h.H - 1) * h.xs[2] + (h.W - 1) * h.xs[3] < (1LL << 31)))
-        return NT_OK;
-    const int64_t Hp = h.H + 2 * h.ph, Wp = h.W + 2 * h.pw, total = h.N * h.C * Hp * Wp;
-    GemmLaunch g2 = g;
-    g2.conv.H = Hp; g2.conv.W = Wp; g2.conv.ph = 0; g2.conv.pw = 0;
-    g2.conv.xs[3] = 1; g2.conv.xs[2] = Wp; g2.conv.xs[1] = Hp * Wp; g2.conv.xs[0] = h.C * Hp * Wp;
-    g2.no_workspace = true;                              // (this route holds the workspace)
+    GemmLaunch g2;
     ConvArgs probe{};
-    const size_t bytes = ((size_t)((total + 7) / 8 * 8) * 2 + 255) / 256 * 256;
-    if (!(Hp * Wp >= 8 && total < (1LL << 31) && match_conv(g2, &probe))) return NT_OK;
+    size_t bytes = 0;
+    if (!conv_on_padded_copy(g, &g2, &probe, &bytes)) return NT_OK;
+    const int64_t Hp = g2.conv.H, Wp = g2.conv.W, total = h.N * h.C * Hp * Wp;
     // the copy and, behind it, what the convolution on it will ask for (the filter's tap-major copy, the k split's slices)
     size_t split_bytes = conv_scratch_need(g2, probe);
     if (bytes + split_bytes > kSplitWsMax) split_bytes = 0;
@@ -1077,6 +1036,107 @@ static nt_status route_conv_unfold(const GemmLaunch &g, int *path_out, bool *tak
     const nt_status st = launch_gemm(u, nullptr);
     if (path_out) *path_out = PATH_CONV_UNFOLD;
     return st;
+}
+
+// Whether the routes below run this convolution -- natural filter, dense planes, channels in whole blocks of 32, not few positions of
+// unit stride (what conv_plane_kernel is asked about) -- through the workspace.
+static bool conv_below_uses_workspace(const GemmLaunch &g)
+{
+    const ConvHint &h = g.conv;
+    GemmLaunch g2;
+    ConvArgs c{};
+    size_t repack = 0, bytes = 0;
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1;
+    if (unit) {
+        if (match_conv(g, &c)) {                         // route 1: the filter's copy, given up first, and the split's slices
+            const bool tap = conv_tap_ok(g, c, &repack);
+            const size_t both = conv_scratch_need(g, c), split = both - (tap ? repack : 0);
+            return both > 0 && (both <= kSplitWsMax || (split > 0 && split <= kSplitWsMax));
+        }
+        if (conv_on_padded_copy(g, &g2, &c, &bytes) && bytes <= kSplitWsMax) return true;
+    } else {
+        int tile = 128, parts = 1;
+        conv_cl_plan(h.K, h.N * h.P * h.Q, h.C * h.R * h.S / 32, &tile, &parts);
+        const ConvClSizes z = conv_cl_sizes(h, true, parts);
+        if (z.copy + z.filter + z.split <= kSplitWsMax) return true;
+    }
+    return conv_unfold_ok(g);
+}
+
+// ---- route 0a: dense planes, channels in whole blocks of 32, the input rows under a tile resident in LDS, where one of the two
+// kernels that do this is estimated to be ahead of the routes below:
+//   gemm_conv_patch.hip, 9 or 25 taps: one launch straight from the caller's tensors.  Of unit stride only what does not run on
+//     tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one block gives a program's
+//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters;
+//   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
+//     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
+//     workspace otherwise: those keep to the patch or the channels-last copy.
+static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
+{
+    *taken = false;
+    const ConvHint &h = g.conv;
+    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
+    const int64_t RS = h.R * h.S, K = h.C * RS, HW = h.H * h.W, lim = 1 << 20;
+    if (RS < 6 || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
+    if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K) return NT_OK;
+    // (32-bit byte offsets; divisions through fp32 reciprocals, exact below 2^21)
+    if (HW < 8 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || h.N * (h.P * h.Q + 8) >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
+        (h.N - 1) * h.xs[0] + (h.C - 1) * h.xs[1] + HW >= (1LL << 30)) return NT_OK;
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1, small = conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K);
+    const bool aligned = h.ws[0] % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
+    const bool patch_ok = (RS == 9 || RS == 25) && aligned && !(unit && (h.C < 64 || (h.K > 128 && !small)));
+    const bool plane_ok = K <= 32768 && !(unit && small);
+    // (the estimates cost the host more than the rest of the call: the last few answers are kept, by value)
+    struct Known {
+        ConvHint h{};
+        nt_tile_cfg tile{};
+        ConvPatchArgs patch{};
+        ConvPatchPlan patch_plan{};
+        ConvPlaneArgs plane{};
+        ConvPlanePlan plane_plan{};
+        bool set = false, aligned = false, patch_ahead = false, plane_ahead = false, plane_alone = false;
+    };
+    static thread_local Known known[64];
+    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 61];
+    if (!k.set || k.aligned != aligned || k.tile.bm != g.tile.bm || k.tile.bn != g.tile.bn || k.tile.bk != g.tile.bk || !same_conv(k.h, h)) {
+        k = Known{};
+        k.h = h;
+        k.tile = g.tile;
+        k.aligned = aligned;
+        double cost = conv_copied_cost(h), c = 0;
+        if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.patch_ahead = true; cost = c; }
+        if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) {
+            k.plane_ahead = true;
+            k.plane_alone = !conv_below_uses_workspace(g);
+        }
+        k.set = true;
+    }
+    hipStream_t s = (hipStream_t)g.stream;
+    const bool bf16 = g.in_dtype == NT_BF16;
+    // (a captured call that needs no workspace otherwise stays independent of it, as its replays take no lease)
+    if (k.plane_ahead && !(k.plane_alone && capture_of(s) != 0)) {
+        WorkspaceLease lease;
+        if (uint16_t *copy = (uint16_t *)lease.acquire((size_t)h.K * K * 2, s)) {
+            *taken = true;
+            const nt_status st = launch_conv_plane_filter((const uint16_t *)g.B, h.ws[0], copy, (int32_t)h.K, (int32_t)h.C, (int32_t)RS, s);
+            if (st != NT_OK) return st;
+            ConvPlaneArgs a = k.plane;
+            a.x = (const uint16_t *)g.A; a.w = copy; a.ldb = (uint32_t)K;
+            a.c.Y = g.C; a.c.out_dtype = g.out_dtype;
+            if (path_out) *path_out = unit ? PATH_CONV_TAP : PATH_CONV_CL;
+            return launch_conv_plane(a, k.plane_plan, bf16, s);
+        }
+    }
+    if (k.patch_ahead) {
+        ConvPatchArgs a = k.patch;
+        a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
+        a.out_dtype = g.out_dtype;
+        *taken = true;
+        if (path_out) *path_out = PATH_CONV_CL;
+        t_k_split = k.patch_plan.waves;
+        return launch_conv_patch(a, k.patch_plan, bf16, s);
+    }
+    return NT_OK;
 }
 
 // Plain operands, each with unit stride along one of its axes, on a tile the MFMA kernels are built for: the arguments

@@ -161,6 +161,45 @@ def test_calls_captured_into_a_graph(warm):
             assert np.array_equal(to_f64(y), sign * ref) and np.array_equal(to_f64(z), ref), r
 
 
+def replay_two_at_once(run, problems, path_ok):
+    """Each problem (operands, expected exact result) captured eight times over into a graph of its own; the graphs replayed at once
+    on two streams, six rounds, every output compared."""
+    graphs = []
+    for args, want in problems:
+        outs = [torch.full(want.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(8)]
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            for y in outs:
+                run(*args, y, stream)
+                assert path_ok(), nt.last_kernel_path()
+        graphs.append((stream, graph, outs, want))
+    for r in range(6):
+        for _, _, outs, _ in graphs:
+            for y in outs:
+                y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for stream, graph, _, _ in graphs:
+            with torch.cuda.stream(stream):
+                graph.replay()
+        torch.cuda.synchronize()
+        for _, _, outs, want in graphs:
+            for y in outs:
+                assert np.array_equal(to_f64(y), want), r
+
+
+@pytest.mark.parametrize("shape", [(18, 64, 48, 48, 72, 3, 3), (26, 32, 20, 20, 72, 3, 3), (16, 64, 56, 56, 72, 3, 2)])
+def test_overlapping_replays_of_convolutions_that_need_no_workspace(shape):
+    """Unit stride, at most 128 filters, many positions: an eager call may copy its filter into the workspace, a captured one must
+    not, since nothing orders the replays of two graphs: two with filters of their own, replayed at once."""
+    dt, pad = "f16", (1, 1)
+    problems = []
+    for seed in (80, 81):
+        X, Wt = si.conv_inputs(*shape, dt, seed=seed, dist="int")
+        problems.append(((to_gpu(X, dt), to_gpu(Wt, dt)), onum.conv2d(X, Wt, dt, (1, 1), pad, nthreads=16)))
+    replay_two_at_once(lambda x, w, y, s: nt.conv2d_implicit(x, w, y, (1, 1), pad, stream=s), problems, lambda: nt.last_kernel_path() != nt.PATH_CONV_TAP)
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("M,N,K", [(257, 259, 131), (300, 129, 97), (129, 131, 33), (255, 255, 31)])
 def test_operand_that_ends_at_the_end_of_a_page(M, N, K, ta, tb):
