@@ -184,7 +184,8 @@ int32_t nt_tile_supported(nt_tile_cfg cfg);
  * (one allocation per GPU, made by the first call that needs it, handed from call to call in stream
  * order; partial tiles added in a fixed order).  At most 16 rows (32 on 16-byte aligned rows) of operands with unit
  * stride along k need none of it unless few columns meet a very long reduction (16 x 64 x 16384) or very many columns a
- * short one: their reduction is split inside a program.
+ * short one: their reduction is split inside a program.  A call captured into a HIP graph whose K is no multiple of 64 is not split:
+ * its replays are independent of the workspace.
  */
 nt_status nt_gemm(const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                   void *C, const nt_tensor_desc *dC, nt_dtype in_dtype, nt_dtype out_dtype,
@@ -198,7 +199,8 @@ nt_status nt_gemm(const void *A, const nt_tensor_desc *dA, const void *B, const 
  * more (parts x M x N x 4 bytes) is refused with NT_ERR_UNSUPPORTED and a message that names both sizes; nothing is
  * launched then.  Every call on a GPU shares that GPU's array and nothing orders them: calls that overlap on one
  * GPU (different streams or host threads, both splitting) race on it -- keep them on one stream.  The array needs no
- * clearing between calls: every part writes its whole slice before the sum reads it. */
+ * clearing between calls: every part writes its whole slice before the sum reads it.  (K no multiple of 64: as nt_gemm, not split while
+ * the stream is captured.) */
 #define NT_NOALLOC_SCRATCH_BYTES (32u << 20)
 nt_status nt_gemm_noalloc(const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                           void *C, const nt_tensor_desc *dC, nt_dtype in_dtype, nt_dtype out_dtype,

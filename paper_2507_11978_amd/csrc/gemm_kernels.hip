@@ -1228,6 +1228,9 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     if (g.batch == 1 && (t.bm >= 128 || !g.user_tile)) {
         if (!ragged_k) ksplit = gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost);
         else if (direct && !skinny && !g.trace.out) ksplit = gemm_ksplit(g.mt * g.nt, a.kt, g.M, g.N, t.bm < 128, &split_cost, true);
+        // (the range-checked kernels never needed scratch memory before they were split: captured calls, whose replays take no lease
+        // and which nothing orders against each other, stay without it)
+        if (ragged_k && ksplit > 1 && capture_of(s) != 0) ksplit = 1;
         // (an entry point that brings its own scratch memory refuses what does not fit: not for the sake of a shorter last part)
         if (ragged_k && g.ws_strict && (size_t)ksplit * g.M * g.N * 4 > g.ws_given_bytes) ksplit = 1;
     }

@@ -200,6 +200,22 @@ def test_overlapping_replays_of_convolutions_that_need_no_workspace(shape):
     replay_two_at_once(lambda x, w, y, s: nt.conv2d_implicit(x, w, y, (1, 1), pad, stream=s), problems, lambda: nt.last_kernel_path() != nt.PATH_CONV_TAP)
 
 
+@pytest.mark.parametrize("product", [nt.gemm, nt.gemm_noalloc])
+def test_overlapping_replays_of_products_with_a_ragged_k(product):
+    """K no multiple of 64: split through scratch memory in an eager call, which captured ones -- two graphs replayed at once -- must
+    leave alone."""
+    dt, problems = "bf16", []
+    for seed in (82, 83):
+        A, B = si.gemm_inputs(48, 1500, 5408, dt, seed=seed, dist="int")
+        problems.append(((to_gpu(A, dt), to_gpu(B, dt)), onum.gemm(A, B, dt)))
+    (a, b), want = problems[0]
+    y = torch.full(want.shape, float("nan"), dtype=torch.float32, device="cuda")
+    product(a, b, y)
+    torch.cuda.synchronize()
+    assert nt.last_k_split() > 1 and np.array_equal(to_f64(y), want)
+    replay_two_at_once(lambda a, b, y, s: product(a, b, y, stream=s), problems, lambda: nt.last_k_split() == 1)
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("M,N,K", [(257, 259, 131), (300, 129, 97), (129, 131, 33), (255, 255, 31)])
 def test_operand_that_ends_at_the_end_of_a_page(M, N, K, ta, tb):
