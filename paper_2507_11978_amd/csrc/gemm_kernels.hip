@@ -564,9 +564,10 @@ static bool plain(const OperandMap &m) { return m.nrd == 1 && m.ncd == 1 && m.nc
 // The same for a GEMM with few output tiles and a long reduction (a skinny product): the split is run as a batched
 // product over parts of K: equal ones, so that only a number of parts that divides the k tiles evenly is taken, or (`uneven`, the
 // range-checked kernels) the last one shorter, and the cheapest number of parts is (at least 8 k tiles
-// each).  Two dependent launches and the trip of the partial tiles through memory have their price: the split is taken
-// when an estimate of it (the launches, a program's k tiles with its compute unit to itself, the slices written and read at
-// 3 TB/s) beats the estimate of the single launch.  `small`: the 64 x 64 tile (us: 3.5 + 0.24 per 64-k tile, the split's
+// each).  The uneven ones not beyond what the entry point with its own scratch memory holds: it then sums in the same order as the
+// one with the workspace, and refuses none.  Two dependent launches and the trip of the partial tiles through memory have their
+// price: the split is taken when an estimate of it (the launches, a program's k tiles with its compute unit to itself, the slices
+// written and read at 3 TB/s) beats the estimate of the single launch.  `small`: the 64 x 64 tile (us: 3.5 + 0.24 per 64-k tile, the split's
 // launches 6), else 128 x 128 (7 + 0.37 and 12).
 // Measured: 1024 x 1024 x 1024 on 128 x 128 11 us unsplit against 19 split; on 64 x 64, unsplit / split: 256 x 256 x 2048 10.6 /
 // 8.0, x 8192 32.9 / 9.8, 512 x 512 x 4096 18.7 / 12.7, 16 x 1024 x 4096 20.0 / 8.0 (on 128 x 128, split: 10.3, 12.1, 13.5, 10.8).
@@ -584,7 +585,7 @@ static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool 
         int best = 1;
         for (int64_t d = 2; d <= want; ++d) {
             const int64_t per = (kt + d - 1) / d;
-            if ((kt + per - 1) / per != d) continue;
+            if ((kt + per - 1) / per != d || d * M * N * 4 > (int64_t)NT_NOALLOC_SCRATCH_BYTES) continue;
             const double split = twice + step * (double)per + (double)d * (double)M * (double)N * 8.0 / 3.0e6;
             if (split < *cost_out) { *cost_out = split; best = (int)d; }
         }
@@ -1231,8 +1232,6 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
         // (the range-checked kernels never needed scratch memory before they were split: captured calls, whose replays take no lease
         // and which nothing orders against each other, stay without it)
         if (ragged_k && ksplit > 1 && capture_of(s) != 0) ksplit = 1;
-        // (an entry point that brings its own scratch memory refuses what does not fit: not for the sake of a shorter last part)
-        if (ragged_k && g.ws_strict && (size_t)ksplit * g.M * g.N * 4 > g.ws_given_bytes) ksplit = 1;
     }
     if (skinny && (ksplit == 1 || skinny_cost(a) <= split_cost)) return run_skinny();
     if (direct && !plain_direct)

@@ -60,3 +60,20 @@ def test_gemm_noalloc_refuses_a_split_beyond_its_scratch():
     assert e.value.status == 3 and "scratch" in str(e.value)
     torch.cuda.synchronize()
     assert torch.isnan(C).all()                                     # nothing was launched
+
+
+@pytest.mark.parametrize("M,N,K,tile,parts", [
+    (2560, 2560, 20001, (256, 256, 64), 1),                         # two parts would be 50 MiB
+    (2048, 2048, 20001, (256, 256, 64), 2),                         # two fill the scratch array (three would pay more)
+    (1024, 1040, 9000, None, None), (300, 520, 12345, None, None)])
+def test_gemm_noalloc_of_a_ragged_k_sums_in_the_order_of_gemm(M, N, K, tile, parts):
+    """K no multiple of 64: neither entry point splits into more than the scratch array holds, so the fp32 sums agree bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a, b = (torch.randn(s, generator=g, device="cuda", dtype=torch.float32).to(torch.bfloat16) for s in ((M, K), (K, N)))
+    C0, C1 = (torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    nt.gemm(a, b, C0, tile=tile)
+    split = nt.last_k_split()
+    nt.gemm_noalloc(a, b, C1, tile=tile)
+    torch.cuda.synchronize()
+    assert nt.last_k_split() == split and (parts is None or split == parts)
+    assert torch.equal(C0, C1) and torch.isfinite(C0).all()
