@@ -152,17 +152,31 @@ nt_status nt_arrange_conv2d(const nt_tensor_desc *dx, const nt_tensor_desc *dw, 
  */
 nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_out);
 
-/* Which kernel the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call launched:
+/* Which way the calling thread's last nt_gemm / nt_addmm / nt_addmm_act / nt_bmm / nt_conv2d_implicit call went:
  * 0 operand-map (generic) kernel, 1 staged kernel, 2 direct-to-LDS kernel (or the kernel for products of at most 32 rows,
  * which splits the reduction inside a program; a 1 x 1 convolution that runs as a product per image reports the product's
  * kernel), 3 convolution kernel (operands staged through registers), 4 convolution kernel (operands streamed straight into
  * LDS), 5 unfolded input written to the workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks
  * the reduction filter tap by filter tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of
- * the filter that it puts in the workspace), 7 convolution on a channels-last copy of its input in the workspace,
+ * the filter that it puts in the workspace), 7 convolution on a channels-last copy of its input in the workspace, or, for both 6
+ * (many positions, unit stride) and 7 (any other), a kernel that keeps the input rows in LDS (nt_last_conv_plan tells them apart),
  * -1 none (nothing launched yet, an error, or an empty problem).  For tests and diagnostics. */
 int32_t nt_last_kernel_path(void);
 
-/* Into how many parts the reduction of that call was split (see "Memory" at nt_gemm and nt_conv2d_implicit); 1: not split.
+/* How the calling thread's last nt_conv2d_implicit / nt_matmul_views call (its last group) ran on a kernel that keeps the input rows
+ * under an output tile in LDS, chosen by estimates of their times; kernel 0 and zeros if it ran otherwise.  For tests and diagnostics. */
+typedef struct {
+    int32_t kernel;          /* 1: the one for few positions, straight from the caller's tensors; 2: the one for many, on a copy of the filter */
+    int32_t positions[2];    /* output positions per program: the first tiles', the others' (kernel 1: one height, twice) */
+    int32_t filters;         /* filters per program */
+    int32_t tiles[2];        /* tiles of positions of either height */
+    int32_t wavefronts;      /* per program (kernel 1: the parts of the reduction) */
+    int32_t runs;            /* pieces of input rows that a lane moves per block of channels, at most */
+} nt_conv_plan;
+nt_status nt_last_conv_plan(nt_conv_plan *out);
+
+/* Into how many parts the reduction of that call was split -- over programs (see "Memory" at nt_gemm and nt_conv2d_implicit), or over the
+ * wavefronts of a program (products of few rows; convolutions of few positions straight from the caller's tensors); 1: not split.
  * For tests and diagnostics. */
 int32_t nt_last_k_split(void);
 

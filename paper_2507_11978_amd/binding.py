@@ -37,6 +37,12 @@ class TileCfg(C.Structure):
     _fields_ = [("bm", C.c_int32), ("bn", C.c_int32), ("bk", C.c_int32)]
 
 
+class ConvPlan(C.Structure):
+    """How a convolution ran on a kernel that keeps its input rows in LDS (see nt_conv_plan; kernel 0: it did not)."""
+    _fields_ = [("kernel", C.c_int32), ("positions", C.c_int32 * 2), ("filters", C.c_int32), ("tiles", C.c_int32 * 2), ("wavefronts", C.c_int32),
+                ("runs", C.c_int32)]
+
+
 _lib = None
 
 
@@ -125,6 +131,8 @@ def load():
         getattr(L, name).restype = i32
     L.nt_last_kernel_path.restype = i32
     L.nt_last_k_split.restype = i32
+    L.nt_last_conv_plan.argtypes = [C.POINTER(ConvPlan)]
+    L.nt_last_conv_plan.restype = i32
     L.nt_last_error.restype = C.c_char_p
     L.nt_version.restype = C.c_char_p
     _lib = L
@@ -369,6 +377,16 @@ def last_kernel_path() -> int:
 def last_k_split() -> int:
     """Into how many parts the reduction of this thread's last product / convolution call was split (1: not split)."""
     return int(load().nt_last_k_split())
+
+
+CONV_FEW_POSITIONS, CONV_MANY_POSITIONS = 1, 2
+
+
+def last_conv_plan() -> ConvPlan:
+    """How this thread's last conv2d_implicit / matmul_views call ran on a kernel with resident input rows (kernel 0: it did not)."""
+    plan = ConvPlan()
+    _check(load().nt_last_conv_plan(C.byref(plan)))
+    return plan
 
 
 ACTIVATIONS = {None: 0, "none": 0, "relu": 1, "silu": 2, "gelu_tanh": 3}

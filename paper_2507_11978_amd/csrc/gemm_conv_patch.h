@@ -36,6 +36,7 @@ struct ConvPatchArgs {
 struct ConvPatchPlan { int tile, waves; };     // wavefronts per program: the parts of the reduction
 // geometry, tile and estimated time (us) for a convolution; false: not built for it
 bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *p, double *cost);
+nt_conv_plan conv_patch_describe(const ConvPatchArgs &a, const ConvPatchPlan &p);
 nt_status launch_conv_patch(const ConvPatchArgs &a, const ConvPatchPlan &p, bool bf16, hipStream_t s);
 
 }  // namespace nt

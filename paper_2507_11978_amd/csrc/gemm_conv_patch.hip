@@ -354,6 +354,12 @@ bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best, d
     return true;
 }
 
+nt_conv_plan conv_patch_describe(const ConvPatchArgs &a, const ConvPatchPlan &p)
+{
+    const PatchTile &t = kPatchTiles[p.tile];
+    return nt_conv_plan{1, {16 * t.np, 16 * t.np}, 16 * t.mf, {a.pt, 0}, p.waves, t.umax};
+}
+
 template <int RS, int MF, int NP, int UMAX, int MAXW, bool BF16>
 static nt_status launch_conv_patch_t(const ConvPatchArgs &a, int waves, hipStream_t s)
 {

@@ -27,6 +27,7 @@ struct ConvPlaneArgs {
 struct ConvPlanePlan { int tile; int64_t mt_a, mt; };      // tile heights, tiles of the first height, of both
 // geometry, tile and estimated time (us); false: its input rows do not fit
 bool conv_plane_plan(const ConvHint &h, ConvPlaneArgs *a, ConvPlanePlan *p, double *cost);
+nt_conv_plan conv_plane_describe(const ConvPlanePlan &p);
 nt_status launch_conv_plane(const ConvPlaneArgs &a, const ConvPlanePlan &p, bool bf16, hipStream_t s);
 // filter [F][C][RS] (row pitch ldb) -> [F][C / 32][RS][32]
 nt_status launch_conv_plane_filter(const uint16_t *w, int64_t ldb, uint16_t *out, int32_t F, int32_t C, int32_t RS, hipStream_t s);

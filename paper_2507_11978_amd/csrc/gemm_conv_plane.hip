@@ -51,6 +51,11 @@ struct PlaneTile { int tma, tmb, tn, u, taps; nt_status (*launch)(const ConvPlan
 static const PlaneTile kPlaneTiles[] = {NT_PLANE_TILES(NT_PLANE_ENTRY)};
 #undef NT_PLANE_ENTRY
 
+nt_conv_plan conv_plane_describe(const ConvPlanePlan &p)
+{
+    const PlaneTile &t = kPlaneTiles[p.tile];
+    return nt_conv_plan{2, {32 * t.tma, 32 * t.tmb}, 32 * t.tn, {(int32_t)p.mt_a, (int32_t)(p.mt - p.mt_a)}, kThreads / 64, t.u};
+}
 nt_status launch_conv_plane(const ConvPlaneArgs &a, const ConvPlanePlan &p, bool bf16, hipStream_t s) { return kPlaneTiles[p.tile].launch(a, bf16, s); }
 
 // Tile heights and widths by an estimate (us): the filter's copy, then rounds of one program per unit.  A program costs a fixed

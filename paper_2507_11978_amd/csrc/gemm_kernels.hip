@@ -603,6 +603,8 @@ static int gemm_ksplit(int64_t programs, int64_t kt, int64_t M, int64_t N, bool 
 
 static thread_local int t_k_split = 1;
 int last_k_split() { return t_k_split; }
+static thread_local nt_conv_plan t_conv_plan;
+const nt_conv_plan &last_conv_plan() { return t_conv_plan; }
 
 // Where a k split's fp32 partial tiles go: the region the caller of this launch has set aside (a route that already holds
 // the workspace, or an entry point that brings its own scratch memory), else the library's workspace through `lease`.
@@ -1125,6 +1127,7 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
             a.x = (const uint16_t *)g.A; a.w = copy; a.ldb = (uint32_t)K;
             a.c.Y = g.C; a.c.out_dtype = g.out_dtype;
             if (path_out) *path_out = unit ? PATH_CONV_TAP : PATH_CONV_CL;
+            t_conv_plan = conv_plane_describe(k.plane_plan);
             return launch_conv_plane(a, k.plane_plan, bf16, s);
         }
     }
@@ -1135,6 +1138,7 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
         *taken = true;
         if (path_out) *path_out = PATH_CONV_CL;
         t_k_split = k.patch_plan.waves;
+        t_conv_plan = conv_patch_describe(k.patch, k.patch_plan);
         return launch_conv_patch(a, k.patch_plan, bf16, s);
     }
     return NT_OK;
@@ -1293,6 +1297,7 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
 nt_status launch_gemm(const GemmLaunch &g, int *path_out)
 {
     if (!g.no_workspace || g.ws_strict) t_k_split = 1;
+    t_conv_plan = nt_conv_plan{};
     if (g.batch * g.mt * g.nt > 0x7fffffffLL) return fail(NT_ERR_UNSUPPORTED, "grid too large");
     if (g.batch * g.mt * g.nt > kMaxWorkgroups && !g.trace.out) {
         // more programs than one launch holds: a batch goes out in several

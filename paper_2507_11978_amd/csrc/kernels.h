@@ -59,12 +59,15 @@ struct GemmLaunch {
     LoaderTrace trace;
 };
 
-// Which code path a launch would take (reported for tests and the benchmark).
+// Which code path a launch would take (reported for tests and the benchmark).  The two kernels with resident input rows go by
+// PATH_CONV_TAP (many positions, unit stride) or PATH_CONV_CL, the routes that took such calls before; last_conv_plan() tells.
 enum KernelPath { PATH_GENERIC = 0, PATH_FAST = 1, PATH_DIRECT = 2, PATH_CONV = 3, PATH_CONV_DIRECT = 4, PATH_CONV_UNFOLD = 5, PATH_CONV_TAP = 6, PATH_CONV_CL = 7 };
 
 bool tile_is_built(nt_tile_cfg cfg);
 // into how many parts the calling thread's last launch_gemm split its reduction (1: no split)
 int last_k_split();
+// how it ran on the convolution kernels that keep the input rows in LDS (kernel 0: it did not)
+const nt_conv_plan &last_conv_plan();
 // the tile the MFMA kernels run a plain (batched) product of this size fastest with, by a cost model fitted to measurements
 // (narrow: the 64 x 64 tile may be taken -- operands and output have the unit strides of the direct kernel)
 nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow);

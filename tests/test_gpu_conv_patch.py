@@ -37,8 +37,8 @@ def inside(t, lead):
     # edges of the patch
     ((4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # no padding, rows of 12: a tile's rows end at other places than the input's
     ((9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # 25 positions per image, odd planes: several images in a tile, 2-byte aligned runs
-    ((40, 64, 2, 2, 17, 3, 3), (1, 1), (1, 1)),        # images of one run
-    ((1, 64, 1, 4, 8, 3, 3), (1, 1), (1, 1)),          # four positions in all, rows of padding on both sides
+    ((40, 64, 2, 4, 17, 3, 3), (1, 1), (1, 1)),        # images of two runs
+    ((1, 64, 1, 8, 8, 3, 3), (1, 1), (1, 1)),          # eight positions in all, rows of padding on both sides
     ((2, 288, 3, 50, 20, 3, 3), (1, 1), (1, 1)),       # nine blocks of channels (uneven shares), rows longer than a tile
     ((3, 64, 10, 9, 24, 9, 1), (1, 1), (4, 0)),        # nine taps in a column
     ((3, 64, 9, 13, 24, 1, 9), (2, 1), (0, 4)),        # ... in a row, mixed strides
@@ -57,7 +57,8 @@ def test_conv_patch(shape, stride, pad):
         Y = big[:, 2:F + 2]
         nt.conv2d_implicit(x, w, Y, stride, pad)
         torch.cuda.synchronize()
-        assert nt.last_kernel_path() == nt.PATH_CONV_CL and nt.last_k_split() >= 1
+        plan = nt.last_conv_plan()
+        assert plan.kernel == nt.CONV_FEW_POSITIONS and nt.last_kernel_path() == nt.PATH_CONV_CL and nt.last_k_split() == plan.wavefronts
         assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
         assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
 
@@ -71,5 +72,5 @@ def test_conv_patch_of_a_channel_slice():
     Y = torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda")
     nt.conv2d_implicit(to_gpu(X, dt)[:, 32:32 + C], to_gpu(Wt, dt)[:, 32:32 + C], Y, (1, 1), (1, 1))
     torch.cuda.synchronize()
-    assert nt.last_kernel_path() == nt.PATH_CONV_CL
+    assert nt.last_conv_plan().kernel == nt.CONV_FEW_POSITIONS
     assert np.array_equal(Y.double().cpu().numpy(), ref)

@@ -47,7 +47,7 @@ def inside(t, lead):
     # odd numbers of blocks of channels, taps in two rows of three, strides and padding of their own, rows of odd length
     ((9, 96, 48, 48, 130, 3, 3), (1, 1), (0, 2)),
     ((16, 96, 41, 37, 130, 2, 3), (1, 1), (1, 0)),
-    ((40, 160, 33, 47, 130, 3, 3), (2, 1), (1, 1)),
+    ((20, 96, 47, 47, 200, 3, 3), (2, 1), (1, 1)),
     ((150, 64, 9, 9, 136, 3, 3), (1, 1), (1, 1)),      # several images in a tile
 ])
 def test_conv_plane(shape, stride, pad):
@@ -61,6 +61,7 @@ def test_conv_plane(shape, stride, pad):
         Y = big[:, 2:F + 2]
         nt.conv2d_implicit(x, w, Y, stride, pad)
         torch.cuda.synchronize()
+        assert nt.last_conv_plan().kernel == nt.CONV_MANY_POSITIONS
         assert nt.last_kernel_path() == (nt.PATH_CONV_TAP if stride == (1, 1) else nt.PATH_CONV_CL) and nt.last_k_split() == 1
         assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
         assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
@@ -84,6 +85,34 @@ def test_conv_resident_keeps_an_infinity_to_its_window(shape, stride):
     Y = torch.zeros(ref.shape, dtype=torch.float32, device="cuda")
     nt.conv2d_implicit(x, w, Y, (stride, stride), (1, 1))
     torch.cuda.synchronize()
+    assert nt.last_conv_plan().kernel == (nt.CONV_FEW_POSITIONS if H == 14 else nt.CONV_MANY_POSITIONS)
     y = Y.cpu().double()
     assert torch.equal(y[~touched], ref[~touched])
     assert not torch.isfinite(y[touched]).any()
+
+
+def test_the_diagnostic_tells_the_kernels_of_a_path_apart():
+    """Paths 6 and 7 stand for two kernels each; what ran otherwise, failed or was no convolution leaves nothing behind."""
+    def run(shape, stride, tile=None, last=False):
+        N, C, H, W, F, R, S = shape
+        x, w = torch.zeros((N, C, H, W), dtype=torch.float16, device="cuda"), torch.zeros((F, C, R, S), dtype=torch.float16, device="cuda")
+        if last:
+            x = x.contiguous(memory_format=torch.channels_last)
+        y = torch.empty((N, F, (H + 2 - R) // stride + 1, (W + 2 - S) // stride + 1), dtype=torch.float16, device="cuda")
+        nt.conv2d_implicit(x, w, y, (stride, stride), (1, 1), tile=tile)
+        torch.cuda.synchronize()
+        p = nt.last_conv_plan()
+        return nt.last_kernel_path(), p.kernel, p.filters, tuple(p.positions), tuple(p.tiles), p.wavefronts, p.runs
+    nothing = (0, 0, (0, 0), (0, 0), 0, 0)
+    assert run((2, 64, 14, 14, 64, 3, 3), 1)[:2] == (nt.PATH_CONV_CL, nt.CONV_FEW_POSITIONS)
+    assert run((2, 64, 14, 14, 64, 3, 3), 1, last=True) == (nt.PATH_CONV_CL,) + nothing
+    assert run((9, 64, 48, 48, 130, 3, 3), 1) == (nt.PATH_CONV_TAP, nt.CONV_MANY_POSITIONS, 256, (128, 96), (0, 216), 4, 2)
+    assert run((9, 64, 48, 48, 130, 3, 3), 1, tile=(256, 256, 64)) == (nt.PATH_CONV_TAP,) + nothing
+    assert run((30, 32, 56, 56, 160, 3, 3), 2)[:2] == (nt.PATH_CONV_CL, nt.CONV_MANY_POSITIONS)
+    a = torch.zeros((64, 64), dtype=torch.float16, device="cuda")
+    nt.gemm(a, a, torch.empty_like(a))
+    assert nt.last_conv_plan().kernel == 0
+    run((2, 64, 14, 14, 64, 3, 3), 1)
+    with pytest.raises(nt.NtError):
+        nt.gemm(a, a[:32], torch.empty_like(a))
+    assert nt.last_conv_plan().kernel == 0
