@@ -376,7 +376,8 @@ nt_status nt_trace_tile(int32_t kind, const nt_tensor_desc *d0, const nt_tensor_
  * kernels do not go through the operand map that nt_trace_tile runs: each lane derives its own addresses (swizzled LDS slots,
  * range-checked loads, for the convolution the unfolded input generated on the fly with its padding fix-ups).  This call
  * launches ONE workgroup of the very kernel that nt_gemm / nt_bmm / nt_conv2d_implicit would launch for the same arguments
- * (kind: 0 / 1 / 2 as in nt_trace_tile; no k split), as program `program_id` (b * mt * nt + i * nt + j).  The workgroup
+ * (kind: 0 / 1 / 2 as in nt_trace_tile; no k split; for a convolution that runs on one of the kernels that keep the input rows in LDS,
+ * kind NT_TRACE_CONV_RESIDENT traces that kernel and kind 2 the one that the call would run on without them), as program `program_id` (b * mt * nt + i * nt + j).  The workgroup
  * requests that program's 32-k slice `slice` (slice s covers k 32 s .. 32 s + 31; a k tile of 64 is two slices) with the
  * kernel's own loads, waits, applies what the kernel applies to a slice once it has landed (zeroing the k past K, the
  * padding elements of the convolution's runs), and copies the slice out of LDS:
@@ -386,7 +387,7 @@ nt_status nt_trace_tile(int32_t kind, const nt_tensor_desc *d0, const nt_tensor_
  * source element the loader put there, and zero where it fed a zero: compare with nt_arrange_* / the arrangement.
  * A, B: device pointers, read.  dC: the output's descriptor (shape only; nothing is stored).  values_out: DEVICE array of
  * `capacity` entries, at least 32 * (tile rows of the operand).  Only launches that stream their operands straight into LDS
- * (nt_last_kernel_path() 2, 4, 6 or 7 for the same arguments) can be traced: otherwise NT_ERR_UNSUPPORTED.  The ring-unrolled
+ * (nt_last_kernel_path() 2, 4, 6 or 7 after the trace) can be traced: otherwise NT_ERR_UNSUPPORTED.  The ring-unrolled
  * variant of the 256 x 256 kernel and its persistent form (one workgroup walking several programs) have the same per-lane
  * offsets and slice stepping as the kernel traced here.
  * A product of at most 32 rows may run on a kernel that loads its fragments through registers; what is traced then is the
@@ -398,7 +399,12 @@ nt_status nt_trace_tile(int32_t kind, const nt_tensor_desc *d0, const nt_tensor_
  * image's positions; operand A is still the input.
  * Paths 6 and 7 sum over the reduction index in another order than the arrangement lists it: their slice s, index kk is channel
  * c = 32 (s % (C / 32)) + kk of filter tap t = s / (C / 32), i.e. the arrangement's k = c * R * S + t.
+ * NT_TRACE_CONV_RESIDENT (NT_ERR_UNSUPPORTED if the call would not run on such a kernel; nt_last_conv_plan() afterwards gives its
+ * tiles): slice s, index kk is channel c = 32 (s / (R * S)) + kk of tap t = s % (R * S).  Programs are tile of positions * tiles of
+ * filters + tile of filters, tile rows of two heights as above.  The kernel for few positions numbers them n P Q + p Q + q, the
+ * one for many likewise with an image's P Q rounded up to a multiple of 8 (the surplus ones repeat the image's last).
  */
+#define NT_TRACE_CONV_RESIDENT 3
 nt_status nt_trace_loader_slice(int32_t kind, const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                                 const nt_tensor_desc *dC, int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w,
                                 nt_dtype in_dtype, nt_dtype out_dtype, nt_tile_cfg cfg, int32_t operand, int64_t program_id, int64_t slice,

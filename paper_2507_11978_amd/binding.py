@@ -500,10 +500,10 @@ def conv2d_implicit(x, w, y, stride=(1, 1), pad=(0, 0), tile=None, stream=None):
 def trace_loader_slice(kind, a, b, c, operand, program_id, slice_index, tile=None, stride=(1, 1), pad=(0, 0), stream=None):
     """What the matrix-instruction kernel's own loader leaves in LDS for one operand (0 = A, 1 = B) of program `program_id` and
     32-k slice `slice_index`: a numpy uint16 array [256, 32] of 16-bit patterns, row r = row of the operand's tile, 0xFFFF in
-    the rows past the tile's.  a, b: device tensors (read); c: a tensor of the output's shape and dtype (not written)."""
+    the rows past the tile's.  kind "conv2d_resident": of the kernels that keep a convolution's input rows in LDS.  a, b: device tensors (read); c: a tensor of the output's shape and dtype (not written)."""
     import numpy as np
     import torch
-    kinds = {"gemm": 0, "bmm": 1, "conv2d": 2}
+    kinds = {"gemm": 0, "bmm": 1, "conv2d": 2, "conv2d_resident": 3}
     _require_cuda(a, b, c)
     out = torch.full((256 * 32,), -1, dtype=torch.int16, device="cuda")
     _check(load().nt_trace_loader_slice(kinds[kind], a.data_ptr(), _ref(a), b.data_ptr(), _ref(b),

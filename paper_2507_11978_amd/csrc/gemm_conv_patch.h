@@ -31,12 +31,17 @@ struct ConvPatchArgs {
     float inv_inner, inv_pq, inv_q, inv_w, inv_units;       // reciprocals
     int32_t tap[kPatchMaxTaps];    // byte offset of each tap in a plane
     int out_dtype;
+    // loader trace (nullptr otherwise): 32 k of one tap of one block of channels, as the matrix instructions read them
+    uint16_t *trace_out;
+    int32_t trace_program, trace_slice, trace_operand;
 };
 
 struct ConvPatchPlan { int tile, waves; };     // wavefronts per program: the parts of the reduction
 // geometry, tile and estimated time (us) for a convolution; false: not built for it
 bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *p, double *cost);
 nt_conv_plan conv_patch_describe(const ConvPatchArgs &a, const ConvPatchPlan &p);
+// (trace: one workgroup, one slice of one operand to a.trace_out)
+nt_status launch_conv_patch_trace(const ConvPatchArgs &a, const ConvPatchPlan &p, hipStream_t s);
 nt_status launch_conv_patch(const ConvPatchArgs &a, const ConvPatchPlan &p, bool bf16, hipStream_t s);
 
 }  // namespace nt

@@ -39,8 +39,9 @@ __device__ __forceinline__ float4p mfma16p(u32x4 a, u32x4 b, float4p c)
 __device__ __forceinline__ int32_t quotient(int32_t x, float r) { return (int32_t)(((float)x + 0.5f) * r); }
 __device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// UMAX: runs per lane and block; MAXW: wavefronts per workgroup
-template <int RS, int MF, int NP, int UMAX, int MAXW, bool BF16>
+// UMAX: runs per lane and block; MAXW: wavefronts per workgroup.  TRACE: not a convolution; the wavefront that takes the traced slice's block of
+// channels brings it in and writes out the fragments of its tap (program = tile of positions * filter tiles + tile of filters).
+template <int RS, int MF, int NP, int UMAX, int MAXW, bool BF16, bool TRACE = false>
 __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchArgs g)
 {
     constexpr int FT = 16 * MF, PT = 16 * NP;
@@ -57,6 +58,13 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
         const int32_t outer = uniform(quotient(seq, g.inv_inner)), in = seq - outer * g.inner;
         fi = g.f_major ? outer : in;
         pi = g.f_major ? in : outer;
+    }
+    int32_t first = wave;                                                          // this wavefront's first block of channels
+    if constexpr (TRACE) {
+        fi = g.trace_program % g.ft;
+        pi = g.trace_program / g.ft;
+        first = g.trace_slice / RS;
+        if (wave != first % waves) return;
     }
     const int32_t f0 = fi * FT, m0 = pi * PT;
     char *const mine = smem + wave * g.region;
@@ -78,7 +86,7 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
 #pragma unroll
             for (int i = 0; i < RS; ++i) dma16(p + i * 64, woff[mf], raw0 + (uint32_t)((mf * RS + i) * 1024));
     };
-    request_filter(wave);
+    request_filter(first);
 
     // ---- geometry of the patch
     const int32_t m1 = (m0 + PT < g.M ? m0 + PT : g.M) - 1;
@@ -139,7 +147,7 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
                 for (int j = 0; j < 8; ++j) __builtin_memcpy(&X[k][j], p + (int64_t)j * xs1 * 2 + goff[k], 8);
             }
     };
-    request_input(wave);
+    request_input(first);
     for (uint32_t a = lane * 16; a < 4 * g.plane; a += 1024) lds_write16(planes, a, u32x4{0, 0, 0, 0});
 
     float4p acc[MF][NP];
@@ -148,7 +156,7 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
 #pragma unroll
         for (int np = 0; np < NP; ++np) acc[mf][np] = float4p{0.f, 0.f, 0.f, 0.f};
 
-    for (int32_t b = wave; b < g.blocks; b += waves) {
+    for (int32_t b = first; b < g.blocks; b += waves) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                           // the block has arrived
         // ---- filter fragments: lane (row l16, channels 8 grp ..) of every tap.  Chunk c of a row lies in kilobyte c / 4.
         u32x4 A[MF][RS];
@@ -181,6 +189,24 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
                     lds_write16(planes, slot[k][t], v);
                 }
             }
+        if constexpr (TRACE) {
+            const int32_t tap = g.trace_slice - first * RS;
+            uint16_t *out = g.trace_out + l16 * 32 + grp * 8;
+            if (g.trace_operand == 0) {
+#pragma unroll
+                for (int np = 0; np < NP; ++np) {
+                    const u32x4 v = lds_read16(planes, pos[np] + (uint32_t)g.tap[tap]);
+                    __builtin_memcpy(out + np * 512, &v, 16);
+                }
+            } else {
+#pragma unroll
+                for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+                    for (int t = 0; t < RS; ++t)
+                        if (t == tap) __builtin_memcpy(out + mf * 512, &A[mf][t], 16);
+            }
+            return;
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                         // (the raw filter has been read: the next block may land on it)
         if (b + waves < g.blocks) {
             request_filter(b + waves);
@@ -360,17 +386,17 @@ nt_conv_plan conv_patch_describe(const ConvPatchArgs &a, const ConvPatchPlan &p)
     return nt_conv_plan{1, {16 * t.np, 16 * t.np}, 16 * t.mf, {a.pt, 0}, p.waves, t.umax};
 }
 
-template <int RS, int MF, int NP, int UMAX, int MAXW, bool BF16>
+template <int RS, int MF, int NP, int UMAX, int MAXW, bool BF16, bool TRACE = false>
 static nt_status launch_conv_patch_t(const ConvPatchArgs &a, int waves, hipStream_t s)
 {
-    auto kern = conv_patch_kernel<RS, MF, NP, UMAX, MAXW, BF16>;
+    auto kern = conv_patch_kernel<RS, MF, NP, UMAX, MAXW, BF16, TRACE>;
     static DeviceOnce configured;
     if (!configured.done()) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
         if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
         configured.set();
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.ft * a.pt)), dim3((unsigned)(64 * waves)), (size_t)a.region * waves, s, a);
+    hipLaunchKernelGGL(kern, dim3(TRACE ? 1u : (unsigned)(a.ft * a.pt)), dim3((unsigned)(64 * waves)), (size_t)a.region * waves, s, a);
     return check_launch("conv_patch_kernel");
 }
 
@@ -381,6 +407,15 @@ nt_status launch_conv_patch(const ConvPatchArgs &a, const ConvPatchPlan &p, bool
     static const Launcher table[][2] = {NT_PATCH_TILES(NT_PATCH_ENTRY)};
 #undef NT_PATCH_ENTRY
     return table[p.tile][bf16 ? 1 : 0](a, p.waves, s);
+}
+
+nt_status launch_conv_patch_trace(const ConvPatchArgs &a, const ConvPatchPlan &p, hipStream_t s)
+{
+    typedef nt_status (*Launcher)(const ConvPatchArgs &, int, hipStream_t);
+#define NT_PATCH_ENTRY(RS, MF, NP, U, W) launch_conv_patch_t<RS, MF, NP, U, W, false, true>,
+    static const Launcher table[] = {NT_PATCH_TILES(NT_PATCH_ENTRY)};
+#undef NT_PATCH_ENTRY
+    return table[p.tile](a, p.waves, s);
 }
 
 }  // namespace nt

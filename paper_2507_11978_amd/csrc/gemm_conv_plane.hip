@@ -37,11 +37,6 @@ nt_status launch_conv_plane_filter(const uint16_t *w, int64_t ldb, uint16_t *out
     return check_launch("conv_plane_filter_kernel");
 }
 
-// the kernels that are built: heights of the tile in 32 positions, width in 32 filters, runs per lane and block, taps (0: any)
-#define NT_PLANE_TILES(X) \
-    X(8, 7, 8, 2, 9) X(7, 6, 8, 2, 9) X(6, 5, 8, 2, 9) X(5, 4, 8, 2, 9) X(4, 3, 8, 2, 9) X(4, 3, 8, 3, 9) \
-    X(8, 7, 4, 2, 9) X(7, 6, 4, 2, 9) X(6, 5, 4, 2, 9) X(5, 4, 4, 2, 9) X(4, 3, 4, 2, 9) X(4, 3, 4, 3, 9) \
-    X(6, 5, 8, 2, 0) X(4, 3, 8, 2, 0) X(8, 7, 8, 3, 0) X(6, 5, 8, 3, 0) X(4, 3, 8, 3, 0) X(8, 7, 4, 2, 0) X(4, 3, 4, 2, 0) X(8, 7, 4, 3, 0)
 template <int TMA, int TMB, int TN, int U, int TAPS> nt_status launch_conv_plane_t(const ConvPlaneArgs &a, bool bf16, hipStream_t s);
 #define NT_PLANE_ENTRY(TMA, TMB, TN, U, TAPS) extern template nt_status launch_conv_plane_t<TMA, TMB, TN, U, TAPS>(const ConvPlaneArgs &, bool, hipStream_t);
 NT_PLANE_TILES(NT_PLANE_ENTRY)

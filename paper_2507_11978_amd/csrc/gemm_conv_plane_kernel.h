@@ -30,7 +30,8 @@ constexpr int kPlaneRing = 3;      // slices of the filter
 // U: runs of four elements per lane and block.  U = 2 (at most 64 runs of eight elements under a tile): two sets of planes; U = 3 (96): one, filled in a block's last trip
 constexpr int plane_sets(int u) { return u == 2 ? 2 : 1; }
 // TAPS: 9 (a block is nine trips of straight code), 0: any number from 6 on
-template <bool BF16, int TM, int TN, int U, int TAPS>
+// TRACE: not a convolution; the program sets itself up at the traced slice's block of channels and writes out the fragments of its tap
+template <bool BF16, int TM, int TN, int U, int TAPS, bool TRACE>
 __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char *smem, int32_t m0, int32_t f0)
 {
     constexpr int BM = 32 * TM, BN = 32 * TN, kRing = kPlaneRing, NX = 4 * U, SETS = plane_sets(U);
@@ -84,7 +85,8 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
         xoff[i] = ((uint32_t)(n0 + img) * g.xs0 + (uint32_t)e + (i == 0 ? 0u : (uint32_t)(lane >> 5) * (uint32_t)g.xs1)) * 2u;
     }
     const int64_t xs2 = g.xs1 * 2;
-    const char *const x0 = reinterpret_cast<const char *>(g.x) + (int64_t)(wave * 8) * xs2;      // (eight channels each)
+    const int32_t RS = g.R * g.S, first_slice = TRACE ? g.c.trace_slice : 0;
+    const char *const x0 = reinterpret_cast<const char *>(g.x) + (int64_t)((TRACE ? first_slice / RS * 32 : 0) + wave * 8) * xs2;      // (eight channels each)
     auto request_input = [&](const char *p, int i) {           // load i of the block whose rows of this wavefront's channels start at p
         constexpr int PER2 = U == 3 ? 3 : 2;                   // loads per two channels
         const int c = i / PER2 * 2 + (i % PER2 == PER2 - 1 ? 1 : 0);
@@ -98,13 +100,13 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
     TileB tb;
     tb.init(wave, lane, g.ldb, wave_n * (BN / 2), 0);
     const u32x4 rsrc = make_rsrc(g.w + (int64_t)f0 * g.ldb, (int64_t)(g.c.N - f0) * g.ldb * 2);
-    const int32_t RS = g.R * g.S, n_slices = g.blocks * RS;
+    const int32_t n_slices = g.blocks * RS;
     constexpr int ND = TileB::PER;
     // (slices past the last, requested by the last trips: whatever lies there, or zeros, never multiplied)
 #pragma unroll
     for (int s = 0; s < kRing; ++s)
 #pragma unroll
-        for (int d = 0; d < ND; ++d) tb.issue_one_buf(d, rsrc, (uint32_t)s * (kSliceK * 2), lds0 + s * SLICE, wave);
+        for (int d = 0; d < ND; ++d) tb.issue_one_buf(d, rsrc, (uint32_t)(first_slice + s) * (kSliceK * 2), lds0 + s * SLICE, wave);
 
     // ---- this lane's runs of four elements (half a run of eight) on their way into the planes: where they lie in the staging
     // area, and each element's chunk.  Lane l writes its elements in the order t ^ ((l / 4) % 4): 16 lanes then write 16 different
@@ -194,6 +196,21 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
     move_rows(0);
     NT_WAIT_VMCNT((kRing - 1) * ND);
     __syncthreads();
+    if constexpr (TRACE) {
+        NT_WAIT_VMCNT(0);
+        rd_off = (uint32_t)__builtin_amdgcn_readlane(tap_table, first_slice % RS);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) lds_read(r, 0, 0);
+        uint16_t *out = g.c.trace_out + l16 * 32 + grp * 8;
+        if (g.c.trace_operand == 0 && wave_n == 0) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t) __builtin_memcpy(out + (wave_m * (BM / 2) + t * 16) * 32, &fa[0][t], 16);
+        } else if (g.c.trace_operand == 1 && wave_m == 0) {
+#pragma unroll
+            for (int t = 0; t < TN; ++t) __builtin_memcpy(out + (wave_n * (BN / 2) + t * 16) * 32, &fb[0][t], 16);
+        }
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < NR; ++r) lds_read(r, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -328,33 +345,41 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
 
 // The grid: c.mt_a tiles of 32 TMA positions, then c.mt - c.mt_a of 32 TMB, each kind times c.nt filter tiles: whole rounds of
 // programs (one per compute unit) cost their length, and two heights leave the last round little to wait for.
-template <bool BF16, int TMA, int TMB, int TN, int U, int TAPS>
+template <bool BF16, int TMA, int TMB, int TN, int U, int TAPS, bool TRACE = false>
 __global__ __launch_bounds__(kThreads, 1) void conv_plane_kernel(const ConvPlaneArgs g)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const uint32_t nt32 = (uint32_t)g.c.nt, mta = (uint32_t)g.c.mt_a, mtb = (uint32_t)g.c.mt - mta, n_a = mta * nt32;
-    const bool first = blockIdx.x < n_a;                       // (uniform)
-    const uint32_t pid = first ? program_of_workgroup_t<uint32_t>(blockIdx.x, mta, nt32) : program_of_workgroup_t<uint32_t>(blockIdx.x - n_a, mtb, nt32);
+    const uint32_t w = TRACE ? (uint32_t)g.c.trace_program : blockIdx.x;
+    const bool first = w < n_a;                                // (uniform)
+    // (the trace numbers programs tile of positions by tile of positions over both kinds)
+    const uint32_t pid = TRACE ? (first ? w : w - n_a) : first ? program_of_workgroup_t<uint32_t>(w, mta, nt32) : program_of_workgroup_t<uint32_t>(w - n_a, mtb, nt32);
     const uint32_t ti = pid / nt32;
     const int32_t f0 = __builtin_amdgcn_readfirstlane((int)(pid - ti * nt32)) * 32 * TN, i = __builtin_amdgcn_readfirstlane((int)ti);
-    if (first) conv_plane_program<BF16, TMA, TN, U, TAPS>(g, smem, i * 32 * TMA, f0);
-    else conv_plane_program<BF16, TMB, TN, U, TAPS>(g, smem, (int32_t)mta * 32 * TMA + i * 32 * TMB, f0);
+    if (first) conv_plane_program<BF16, TMA, TN, U, TAPS, TRACE>(g, smem, i * 32 * TMA, f0);
+    else conv_plane_program<BF16, TMB, TN, U, TAPS, TRACE>(g, smem, (int32_t)mta * 32 * TMA + i * 32 * TMB, f0);
+}
+
+template <bool BF16, int TMA, int TMB, int TN, int U, int TAPS, bool TRACE = false>
+nt_status launch_conv_plane_inst(const ConvPlaneArgs &a, hipStream_t s)
+{
+    auto kern = conv_plane_kernel<BF16, TMA, TMB, TN, U, TAPS, TRACE>;
+    static DeviceOnce configured;
+    if (!configured.done()) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+        if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
+        configured.set();
+    }
+    // (the output tile goes through the same LDS: 64 KB per 128 filters)
+    const size_t lds = std::max<size_t>((size_t)kPlaneRing * 32 * TN * 64 + (size_t)U * 16 * 1024 + (size_t)plane_sets(U) * 4 * a.plane, (size_t)2 * 32 * TN * 256);
+    hipLaunchKernelGGL(kern, dim3(TRACE ? 1u : (unsigned)(a.c.mt * a.c.nt)), dim3(kThreads), lds, s, a);
+    return check_launch("conv_plane_kernel");
 }
 
 template <int TMA, int TMB, int TN, int U, int TAPS>
 nt_status launch_conv_plane_t(const ConvPlaneArgs &a, bool bf16, hipStream_t s)
 {
-    auto kern = bf16 ? conv_plane_kernel<true, TMA, TMB, TN, U, TAPS> : conv_plane_kernel<false, TMA, TMB, TN, U, TAPS>;
-    static DeviceOnce configured[2];
-    if (!configured[bf16 ? 1 : 0].done()) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
-        if (e != hipSuccess) return fail(NT_ERR_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
-        configured[bf16 ? 1 : 0].set();
-    }
-    // (the output tile goes through the same LDS: 64 KB per 128 filters)
-    const size_t lds = std::max<size_t>((size_t)kPlaneRing * 32 * TN * 64 + (size_t)U * 16 * 1024 + (size_t)plane_sets(U) * 4 * a.plane, (size_t)2 * 32 * TN * 256);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.c.mt * a.c.nt)), dim3(kThreads), lds, s, a);
-    return check_launch("conv_plane_kernel");
+    return bf16 ? launch_conv_plane_inst<true, TMA, TMB, TN, U, TAPS>(a, s) : launch_conv_plane_inst<false, TMA, TMB, TN, U, TAPS>(a, s);
 }
 
 }  // namespace nt

@@ -1074,11 +1074,21 @@ static bool conv_below_uses_workspace(const GemmLaunch &g)
 //   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
 //     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
 //     workspace otherwise: those keep to the patch or the channels-last copy.
+// (programs below `first` have the first height of the plan)
+static nt_status trace_fits(const LoaderTrace &t, const nt_conv_plan &p, int64_t first, int64_t programs, int64_t slices)
+{
+    if (t.program < 0 || t.program >= programs) return fail(NT_ERR_INVALID_ARG, "program_id outside the grid");
+    if (t.slice < 0 || t.slice >= slices) return fail(NT_ERR_INVALID_ARG, "slice outside the reduction");
+    const int64_t rows = t.operand != 0 ? p.filters : p.positions[t.program < first ? 0 : 1];
+    if ((size_t)rows * 32 > t.capacity) return fail(NT_ERR_BUFFER_TOO_SMALL, "trace buffer smaller than the slice");
+    return NT_OK;
+}
+
 static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
     const ConvHint &h = g.conv;
-    if (!conv_is_bare(g) || g.trace.out || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
+    if (!conv_is_bare(g) || (g.trace.out && !g.trace.resident) || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
     const int64_t RS = h.R * h.S, K = h.C * RS, HW = h.H * h.W, lim = 1 << 20;
     if (RS < 6 || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
     if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K) return NT_OK;
@@ -1128,6 +1138,12 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
             a.c.Y = g.C; a.c.out_dtype = g.out_dtype;
             if (path_out) *path_out = unit ? PATH_CONV_TAP : PATH_CONV_CL;
             t_conv_plan = conv_plane_describe(k.plane_plan);
+            if (g.trace.out) {
+                const nt_status st = trace_fits(g.trace, t_conv_plan, k.plane_plan.mt_a * a.c.nt, a.c.mt * a.c.nt, (int64_t)a.blocks * RS);
+                if (st != NT_OK) return st;
+                a.c.trace_out = g.trace.out; a.c.trace_program = g.trace.program; a.c.trace_slice = g.trace.slice; a.c.trace_operand = g.trace.operand;
+                return launch_conv_plane_trace(a, k.plane_plan, s);
+            }
             return launch_conv_plane(a, k.plane_plan, bf16, s);
         }
     }
@@ -1139,6 +1155,13 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
         if (path_out) *path_out = PATH_CONV_CL;
         t_k_split = k.patch_plan.waves;
         t_conv_plan = conv_patch_describe(k.patch, k.patch_plan);
+        if (g.trace.out) {
+            const int64_t programs = (int64_t)a.ft * a.pt;
+            const nt_status st = trace_fits(g.trace, t_conv_plan, programs, programs, (int64_t)a.blocks * RS);
+            if (st != NT_OK) return st;
+            a.trace_out = g.trace.out; a.trace_program = (int32_t)g.trace.program; a.trace_slice = g.trace.slice; a.trace_operand = g.trace.operand;
+            return launch_conv_patch_trace(a, k.patch_plan, s);
+        }
         return launch_conv_patch(a, k.patch_plan, bf16, s);
     }
     return NT_OK;
@@ -1318,7 +1341,7 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     }
     FastArgs a{};
     int alay = KCONTIG, blay = MNCONTIG;
-    if (lower_plain(g, &a, &alay, &blay)) return route_matrix(g, a, alay, blay, path_out);
+    if (!g.trace.resident && lower_plain(g, &a, &alay, &blay)) return route_matrix(g, a, alay, blay, path_out);
     // (the library's own 64 x 64 tile is built for the direct kernel only: what that does not take, an addmm input without unit
     // stride along n say, runs as before on 128 x 128)
     if (!g.user_tile && g.tile.bm == 64 && !g.conv.valid) {
@@ -1331,6 +1354,7 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     bool taken = false;
     nt_status st = route_conv_resident(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
+    if (g.trace.resident) return fail(NT_ERR_UNSUPPORTED, "this convolution does not run on the kernels that keep the input rows in LDS");
     st = route_conv_channels_last(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     ConvArgs c{};

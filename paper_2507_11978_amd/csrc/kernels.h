@@ -29,6 +29,7 @@ struct LoaderTrace {
     size_t capacity;
     int64_t program;
     int32_t slice, operand;
+    bool resident;                    // of the convolution kernels that keep the input rows in LDS, where the call runs on one (else: of the others)
 };
 
 struct GemmLaunch {

@@ -637,10 +637,12 @@ nt_status nt_trace_loader_slice(int32_t kind, const void *A, const nt_tensor_des
                                 nt_dtype in_dtype, nt_dtype out_dtype, nt_tile_cfg cfg, int32_t operand, int64_t program_id, int64_t slice,
                                 uint16_t *values_out, size_t capacity, void *hip_stream)
 {
-    if (kind < KIND_GEMM || kind > KIND_CONV) return fail(NT_ERR_INVALID_ARG, "kind must be 0 (gemm), 1 (bmm) or 2 (conv2d)");
+    if (kind < KIND_GEMM || kind > NT_TRACE_CONV_RESIDENT) return fail(NT_ERR_INVALID_ARG, "kind must be 0 (gemm), 1 (bmm), 2 (conv2d) or 3 (conv2d, resident input rows)");
+    const bool resident = kind == NT_TRACE_CONV_RESIDENT;
+    if (resident) kind = KIND_CONV;
     if (operand != NT_OPERAND_A && operand != NT_OPERAND_B) return fail(NT_ERR_INVALID_ARG, "operand must be 0 (A) or 1 (B)");
     if (!values_out) return fail(NT_ERR_INVALID_ARG, "null output pointer");
-    const nt::LoaderTrace tr{values_out, capacity, program_id, (int32_t)slice, operand};
+    const nt::LoaderTrace tr{values_out, capacity, program_id, (int32_t)slice, operand, resident};
     if (slice < 0 || slice > 0x7fffffff) return fail(NT_ERR_INVALID_ARG, "slice outside the reduction");
     // (the output pointer only has to be non-null: a trace stores nothing through it)
     return run(kind, A, dA, B, dB, values_out, dC, stride_h, stride_w, pad_h, pad_w, in_dtype, out_dtype, cfg, hip_stream,

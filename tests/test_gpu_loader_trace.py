@@ -266,11 +266,81 @@ def test_convolution_on_the_channels_last_copy(Nn, C, H, W, F, R, S, stride, pad
             assert off[r, k] == (((n * C + c) * H + hh) * W + ww if 0 <= hh < H and 0 <= ww < W else -1)
 
 
+@pytest.mark.parametrize("kernel,shape,stride,pad", [
+    (nt.CONV_FEW_POSITIONS, (3, 96, 21, 21, 300, 3, 3), (1, 1), (1, 1)),      # tiles of 64 filters x 32 positions, odd planes
+    (nt.CONV_FEW_POSITIONS, (4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # 16 x 48, four blocks of channels a wavefront
+    (nt.CONV_FEW_POSITIONS, (11, 96, 28, 28, 300, 3, 3), (2, 2), (1, 1)),     # 32 x 96, strided
+    (nt.CONV_FEW_POSITIONS, (9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # several images in a tile
+    (nt.CONV_FEW_POSITIONS, (3, 160, 11, 7, 30, 3, 3), (3, 3), (2, 2)),       # padding that no tap's neighbour shares
+    (nt.CONV_FEW_POSITIONS, (7, 96, 28, 28, 40, 5, 5), (1, 1), (2, 2)),       # 25 taps, 16 x 96
+    (nt.CONV_FEW_POSITIONS, (3, 64, 10, 9, 24, 9, 1), (1, 1), (4, 0)),        # nine taps in a column
+    (nt.CONV_MANY_POSITIONS, (36, 32, 58, 58, 130, 3, 3), (1, 1), (1, 1)),    # 256 and 224 positions x 256 filters
+    (nt.CONV_MANY_POSITIONS, (51, 64, 64, 64, 160, 3, 3), (2, 2), (1, 1)),    # 128 and 96, one set of planes
+    (nt.CONV_MANY_POSITIONS, (50, 32, 48, 49, 40, 3, 5), (1, 1), (1, 2)),     # 256 and 224 x 128, taps in a loop
+    (nt.CONV_MANY_POSITIONS, (51, 96, 64, 64, 100, 3, 2), (2, 2), (1, 1)),    # 128 and 96 x 256, taps in a loop, one set of planes
+    (nt.CONV_MANY_POSITIONS, (150, 64, 9, 9, 136, 3, 3), (1, 1), (1, 1)),     # several images in a tile, surplus positions
+])
+def test_convolution_with_its_input_rows_in_lds(kernel, shape, stride, pad):
+    """The kernels that keep the input rows under a tile in LDS: the reduction in blocks of 32 channels, tap by tap; zeros in the
+    place of the padding; tile rows of two heights."""
+    dt = "f16"
+    Nn, C, H, W, F, R, S = shape
+    P, Q = (H + 2 * pad[0] - R) // stride[0] + 1, (W + 2 * pad[1] - S) // stride[1] + 1
+    RS, PQ = R * S, P * Q
+    image = PQ if kernel == nt.CONV_FEW_POSITIONS else -(-PQ // 8) * 8                # positions of an image as the kernel numbers them
+    shx, shw, shy = (Nn, C, H, W), (F, C, R, S), (Nn, F, P, Q)
+
+    def trace(operand, pid, sl):
+        return loader_offsets("conv2d_resident", shx, contiguous(shx), shw, contiguous(shw), shy, dt, operand, pid, sl, stride=stride, pad=pad)
+    trace(0, 0, 0)
+    plan = nt.last_conv_plan()
+    assert plan.kernel == kernel
+    heights = [plan.positions[0]] * plan.tiles[0] + [plan.positions[1]] * plan.tiles[1]
+    starts = np.concatenate([[0], np.cumsum(heights)])
+    assert starts[-2] < Nn * image <= starts[-1]
+    ft, n_slices = -(-F // plan.filters), C // 32 * RS
+    for bad in ((len(heights) * ft, 0), (-1, 0), (0, n_slices)):
+        with pytest.raises(nt.NtError) as e:
+            trace(0, *bad)
+        assert e.value.name == "NT_ERR_INVALID_ARG"
+
+    def want(n, p, q, sl):
+        """Input offsets of slice sl at output position (n, p, q), -1 in the padding."""
+        c, t = 32 * (sl // RS) + np.arange(32), sl % RS
+        h, w = p * stride[0] - pad[0] + t // S, q * stride[1] - pad[1] + t % S
+        return ((n * C + c) * H + h) * W + w if 0 <= h < H and 0 <= w < W else np.full(32, -1)
+    tiles = sorted({0, len(heights) // 3, max(plan.tiles[0] - 1, 0), min(plan.tiles[0], len(heights) - 1), len(heights) - 1})
+    for i, tile in enumerate(tiles):
+        j = (0, ft - 1)[i % 2]
+        for sl in sorted({0, RS // 2, (n_slices // 2 + i) % n_slices, n_slices - 1}):
+            got_x, got_w = trace(0, tile * ft + j, sl), trace(1, tile * ft + j, sl)
+            assert (got_x[heights[tile]:] == -2).all() and (got_w[plan.filters:] == -2).all()
+            for r in range(heights[tile]):
+                m = int(starts[tile]) + r
+                n, pq = m // image, m % image
+                if n < Nn and pq < PQ:
+                    assert np.array_equal(got_x[r], want(n, pq // Q, pq % Q, sl)), ("x", tile, j, sl, r)
+            ks = (32 * (sl // RS) + np.arange(32)) * RS + sl % RS
+            for r in range(min(plan.filters, F - j * plan.filters)):
+                assert np.array_equal(got_w[r], (j * plan.filters + r) * C * RS + ks), ("w", tile, j, sl, r)
+    # (the closed form above is the arrangement's: one tile of it, element by element)
+    a_arr, _, _ = arr.conv2d_arrangement(arr.Tensor(shx), arr.Tensor(shw), arr.Tensor(shy), 64, 64, 64, stride, pad)
+    off, _, shp = arr.tile_index_set(a_arr, 0, (0,))
+    off = off.reshape(shp)
+    for r in range(min(64, Nn * PQ)):
+        for k in range(min(64, C * RS)):
+            assert off[r, k] == want(r // PQ, r % PQ // Q, r % Q, k // RS // 32 * RS + k % RS)[k // RS % 32]
+
+
 def test_refusals():
     dt = "f16"
     a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((64, 128), (64, 64), (64, 64)))
     with pytest.raises(nt.NtError) as e:                     # rows with a step between their elements: the operand-map kernel
         nt.trace_loader_slice("gemm", a[:, ::2], b, c, 0, 0, 0, tile=(64, 64, 32))
+    assert e.value.name == "NT_ERR_UNSUPPORTED"
+    x, w, y = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((2, 16, 14, 14), (64, 16, 3, 3), (2, 64, 12, 12)))
+    with pytest.raises(nt.NtError) as e:                     # half a block of channels: no resident rows
+        nt.trace_loader_slice("conv2d_resident", x, w, y, 0, 0, 0)
     assert e.value.name == "NT_ERR_UNSUPPORTED"
     a, b, c = (torch.zeros(s, dtype=torch.float16, device="cuda") for s in ((256, 64), (64, 256), (256, 256)))
     for bad in ((0, 4, 0), (0, 0, 2), (2, 0, 0)):
