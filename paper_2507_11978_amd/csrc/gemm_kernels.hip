@@ -9,6 +9,7 @@
 #include "gemm_direct.h"
 #include "gemm_direct16.h"
 #include "gemm_skinny.h"
+#include "kept.h"
 
 namespace nt {
 
@@ -792,13 +793,6 @@ static bool conv_unfold_ok(const GemmLaunch &g)
            h.xs[0] >= 0 && h.xs[2] >= 0 && h.xs[3] >= 0 && h.P * h.Q >= 8 && K >= 8 && K <= 65535 && Mp < (1 << 22) && (size_t)K * Mp * 2 <= kSplitWsMax;
 }
 
-static bool same_conv(const ConvHint &a, const ConvHint &b)
-{
-    auto same = [](const int64_t (&x)[4], const int64_t (&y)[4]) { return x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3]; };
-    return a.N == b.N && a.C == b.C && a.H == b.H && a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.P == b.P && a.Q == b.Q && a.sh == b.sh && a.sw == b.sw &&
-           a.ph == b.ph && a.pw == b.pw && a.dh == b.dh && a.dw == b.dw && same(a.xs, b.xs) && same(a.ws, b.ws) && same(a.ys, b.ys);
-}
-
 // Estimated time (us) of a convolution on the routes that copy its input or fetch the unfolded one: unit stride with many
 // positions by conv_cost (0.9 of it: (32,512,14,14)*(512,512,3,3) 72 for 66, (32,256,56,56)*(256,256,3,3) 143 for 124,
 // (7,448,56,56)*(114,448,3,3) 63 for 58); the others are fits to 179 drawn convolutions (unit stride within 19 %, strided 11 %).
@@ -1084,6 +1078,16 @@ static nt_status trace_fits(const LoaderTrace &t, const nt_conv_plan &p, int64_t
     return NT_OK;
 }
 
+// all that the choice and the plans depend on
+struct ResidentKey { int64_t hint[27]; int32_t tile[4]; };      // (bm, bn, bk; filter rows aligned to 16 bytes)
+struct ResidentPlan {
+    ConvPatchArgs patch{};
+    ConvPatchPlan patch_plan{};
+    ConvPlaneArgs plane{};
+    ConvPlanePlan plane_plan{};
+    bool patch_ahead = false, plane_ahead = false, plane_alone = false;      // plane_alone: the routes below need no workspace
+};
+
 static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
@@ -1099,31 +1103,22 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     const bool aligned = h.ws[0] % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
     const bool patch_ok = (RS == 9 || RS == 25) && aligned && !(unit && (h.C < 64 || (h.K > 128 && !small)));
     const bool plane_ok = K <= 32768 && !(unit && small);
-    // (the estimates cost the host more than the rest of the call: the last few answers are kept, by value)
-    struct Known {
-        ConvHint h{};
-        nt_tile_cfg tile{};
-        ConvPatchArgs patch{};
-        ConvPatchPlan patch_plan{};
-        ConvPlaneArgs plane{};
-        ConvPlanePlan plane_plan{};
-        bool set = false, aligned = false, patch_ahead = false, plane_ahead = false, plane_alone = false;
-    };
-    static thread_local Known known[64];
-    Known &k = known[(uint64_t)(h.N * 31 + h.C * 7 + h.H * 5 + h.K * 3 + h.R + h.sh) % 61];
-    if (!k.set || k.aligned != aligned || k.tile.bm != g.tile.bm || k.tile.bn != g.tile.bn || k.tile.bk != g.tile.bk || !same_conv(k.h, h)) {
-        k = Known{};
-        k.h = h;
-        k.tile = g.tile;
-        k.aligned = aligned;
+    // (the estimates cost the host more than the rest of the call: the last 64 answers of a thread are kept, by value; 60 KB)
+    static thread_local Kept<ResidentKey, ResidentPlan> plans;
+    const ResidentKey key{{h.N, h.C, h.H, h.W, h.K, h.R, h.S, h.P, h.Q, h.sh, h.sw, h.ph, h.pw, h.dh, h.dw, h.xs[0], h.xs[1], h.xs[2], h.xs[3],
+                           h.ws[0], h.ws[1], h.ws[2], h.ws[3], h.ys[0], h.ys[1], h.ys[2], h.ys[3]}, {g.tile.bm, g.tile.bn, g.tile.bk, aligned ? 1 : 0}};
+    const ResidentPlan *kept = plans.find(key);
+    if (!kept) {
+        ResidentPlan k;
         double cost = conv_copied_cost(h), c = 0;
         if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.patch_ahead = true; cost = c; }
         if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) {
             k.plane_ahead = true;
             k.plane_alone = !conv_below_uses_workspace(g);
         }
-        k.set = true;
+        kept = &plans.put(key, k);
     }
+    const ResidentPlan &k = *kept;
     hipStream_t s = (hipStream_t)g.stream;
     const bool bf16 = g.in_dtype == NT_BF16;
     // (a captured call that needs no workspace otherwise stays independent of it, as its replays take no lease)

@@ -4,6 +4,7 @@
 #include <string>
 
 #include "arrange.h"
+#include "kept.h"
 #include "kernels.h"
 
 namespace nt {
@@ -244,42 +245,37 @@ nt_status arrange_query(int kind, const nt_tensor_desc *d0, const nt_tensor_desc
 // What a convolution's three descriptors and parameters come to: grid and operand maps.  Building the Section 4.3 views and lowering
 // them is 20 meta-operations on hierarchical tensors and three passes over their nodes with a dozen allocations each; it was half
 // of what a small convolution's call cost the host.  The results of the last calls are kept per thread, by value (sizes, strides,
-// stride, padding, tile: all that they depend on).
+// stride, padding, tile: all that they depend on; 64 of them, 70 KB, until the thread ends).
 struct ConvPlan {
-    int64_t key[24] = {0};
-    int32_t par[4] = {0, 0, 0, 0};
-    nt_tile_cfg cfg{};
-    bool set = false;
-    nt::OperandMap ma, mb, mc;
+    struct Key {
+        int64_t desc[24];                  // sizes and strides of input, filter, output
+        int32_t par[8];                    // stride, padding, tile
+    };
+    OperandMap ma, mb, mc;
     int64_t batch, sa, sb, sc, M, N, K, mt, nt, kt;
     nt_tile_cfg tile;
-
-    // the slot of these parameters (nullptr: no descriptors of a convolution), its key written or compared
-    static ConvPlan *find(const nt_tensor_desc *const (&d)[3], const int32_t (&par)[4], nt_tile_cfg cfg, bool *known)
-    {
-        static thread_local ConvPlan plans[64];
-        *known = false;
-        int64_t key[24];
-        uint64_t h = 0;
-        for (int t = 0; t < 3; ++t) {
-            if (!d[t] || d[t]->ndim != 4) return nullptr;
-            for (int i = 0; i < 4; ++i) {
-                key[8 * t + i] = d[t]->size[i];
-                key[8 * t + 4 + i] = d[t]->stride[i];
-                h = (h ^ (uint64_t)d[t]->size[i]) * 0x9E3779B97F4A7C15ull;
-            }
-        }
-        ConvPlan &p = plans[(h ^ (uint64_t)(par[0] * 5 + par[2])) >> 7 & 63];
-        *known = p.set && !memcmp(p.key, key, sizeof(key)) && !memcmp(p.par, par, sizeof(par)) && p.cfg.bm == cfg.bm && p.cfg.bn == cfg.bn && p.cfg.bk == cfg.bk;
-        if (!*known) {
-            p.set = false;
-            memcpy(p.key, key, sizeof(key));
-            memcpy(p.par, par, sizeof(par));
-            p.cfg = cfg;
-        }
-        return &p;
-    }
 };
+
+nt::Kept<ConvPlan::Key, ConvPlan> &conv_plans()
+{
+    static thread_local nt::Kept<ConvPlan::Key, ConvPlan> plans;
+    return plans;
+}
+
+// false: not the descriptors of a convolution
+bool conv_plan_key(const nt_tensor_desc *const (&d)[3], const int32_t (&par)[4], nt_tile_cfg cfg, ConvPlan::Key *key)
+{
+    for (int t = 0; t < 3; ++t) {
+        if (!d[t] || d[t]->ndim != 4) return false;
+        for (int i = 0; i < 4; ++i) {
+            key->desc[8 * t + i] = d[t]->size[i];
+            key->desc[8 * t + 4 + i] = d[t]->stride[i];
+        }
+    }
+    const int32_t all[8] = {par[0], par[1], par[2], par[3], cfg.bm, cfg.bn, cfg.bk, 0};
+    memcpy(key->par, all, sizeof(all));
+    return true;
+}
 
 // D / dD / alpha / beta: the addmm epilogue C = beta * D + alpha * (A . B); dD == nullptr: plain product
 thread_local int t_last_path = -1;
@@ -298,9 +294,10 @@ nt_status run(int kind, const void *A, const nt_tensor_desc *dA, const void *B, 
     Problem p;
     nt::GemmLaunch g{};
     int64_t nb;
-    bool known = false;
-    ConvPlan *plan = kind == KIND_CONV ? ConvPlan::find({dA, dB, dC}, {sh, sw, ph, pw}, cfg, &known) : nullptr;
-    if (known) {
+    ConvPlan::Key key;
+    const bool keep = kind == KIND_CONV && conv_plan_key({dA, dB, dC}, {sh, sw, ph, pw}, cfg, &key);
+    const ConvPlan *plan = keep ? conv_plans().find(key) : nullptr;
+    if (plan) {
         p.batch = plan->batch; p.M = plan->M; p.N = plan->N; p.K = plan->K;
         p.mm.mt = plan->mt; p.mm.nt = plan->nt; p.mm.kt = plan->kt;
         p.tile = plan->tile;
@@ -309,21 +306,14 @@ nt_status run(int kind, const void *A, const nt_tensor_desc *dA, const void *B, 
     }
     if (p.batch == 0 || p.M == 0 || p.N == 0) return NT_OK;
     if (!C || (p.K > 0 && (!A || !B))) return fail(NT_ERR_INVALID_ARG, "null device pointer");
-    if (known) {
+    if (plan) {
         g.ma = plan->ma; g.mb = plan->mb; g.mc = plan->mc;
         g.sa_batch = plan->sa; g.sb_batch = plan->sb; g.sc_batch = plan->sc;
     } else {
         NT_TRY(p.va.lower_matrix_view(&g.ma, &nb, &g.sa_batch));
         NT_TRY(p.vb.lower_matrix_view(&g.mb, &nb, &g.sb_batch));
         NT_TRY(p.vc.lower_matrix_view(&g.mc, &nb, &g.sc_batch));
-        if (plan) {
-            plan->ma = g.ma; plan->mb = g.mb; plan->mc = g.mc;
-            plan->sa = g.sa_batch; plan->sb = g.sb_batch; plan->sc = g.sc_batch;
-            plan->batch = p.batch; plan->M = p.M; plan->N = p.N; plan->K = p.K;
-            plan->mt = p.mm.mt; plan->nt = p.mm.nt; plan->kt = p.mm.kt;
-            plan->tile = p.tile;
-            plan->set = true;
-        }
+        if (keep) conv_plans().put(key, {g.ma, g.mb, g.mc, p.batch, g.sa_batch, g.sb_batch, g.sc_batch, p.M, p.N, p.K, p.mm.mt, p.mm.nt, p.mm.kt, p.tile});
     }
     g.alpha = alpha;
     g.beta = beta;
