@@ -26,6 +26,14 @@ namespace nt {
 // x / d, r = 1 / d rounded: exact while x < 2^21 ((x + 1/2) / d lies at least 1 / (2 d) from a whole number)
 __device__ __forceinline__ int32_t plane_quotient(int32_t x, float r) { return (int32_t)(((float)x + 0.5f) * r); }
 
+// mfma16 on an accumulator among the vector registers
+template <bool BF16>
+__device__ __forceinline__ void mfma16v(float4v &acc, const u32x4 &a, const u32x4 &b)
+{
+    if constexpr (BF16) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+
 constexpr int kPlaneRing = 3;      // slices of the filter
 // U: runs of four elements per lane and block.  U = 2 (at most 64 runs of eight elements under a tile): two sets of planes; U = 3 (96): one, filled in a block's last trip
 constexpr int plane_sets(int u) { return u == 2 ? 2 : 1; }
@@ -176,6 +184,29 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
 
+    // The matrix instructions are inline assembly: the compiler does not know when their results arrive, nor that an accumulator must not be
+    // written right ahead of one, and so must find no cause to move an accumulator between them.
+    //   settle: wait states, and every accumulator pinned to where the instructions left it until these are over.  (Without the pins the
+    //   256 x 256 tile's epilogue had one block moved three instructions behind its last matrix instruction after an odd number
+    //   of blocks of channels: 256 wrong outputs per wavefront.)
+    //   Of the 64 accumulator blocks of that tile, which fill the accumulator half of the file to the last register, eight live in the other
+    //   half, which has room (full, one block was parked at the top of the loop and put back right ahead of its first use).
+    constexpr int TMA = TM * TN == 64 ? TM - 1 : TM;           // rows of blocks in the accumulator half
+    auto multiply = [&](int tm, int tn, const u32x4 &a, const u32x4 &b) {
+        if (tm < TMA) mfma16<BF16>(acc[tm][tn], a, b);
+        else mfma16v<BF16>(acc[tm][tn], a, b);
+    };
+    auto settle = [&] {
+        asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                if (a < TMA) asm volatile("" : "+a"(acc[a][b]));
+                else asm volatile("" : "+v"(acc[a][b]));
+            }
+    };
+
     // lane t: byte offset of tap t in a plane (at most 64 taps)
     const int32_t tr = plane_quotient(lane, 1.f / (float)g.S);
     const int32_t tap_table = tr * (int32_t)g.tap_row + (lane - tr * g.S) * (int32_t)g.tap_col;
@@ -246,7 +277,7 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
 #pragma unroll
                 for (int idx = 0; idx < NM; ++idx) {
                     const int tm = idx / TN, tn = idx % TN;
-                    mfma16<BF16>(acc[tm][tn], fa[set_r][tm], fb[set_r][tn]);      // a lane holds one filter and 4 positions (see conv_store_rows16)
+                    multiply(tm, tn, fa[set_r][tm], fb[set_r][tn]);               // a lane holds one filter and 4 positions (see conv_store_rows16)
                     if (idx < LR)
 #pragma unroll
                         for (int r = idx * NR / LR; r < (idx + 1) * NR / LR; ++r) lds_read(r, set_r ^ 1, (uint32_t)((t + 1) % 3) * SLICE);
@@ -277,7 +308,7 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
         for (; b + 1 < g.blocks; b += 2) {
             block(integral_constant<int, 0>{}, b);
             block(integral_constant<int, 1>{}, b + 1);
-            asm volatile("s_nop 7" ::: "memory");          // (wait states ahead of anything the compiler may do to an accumulator)
+            settle();
         }
         if (b < g.blocks) block(integral_constant<int, 0>{}, b);
     } else {
@@ -298,7 +329,7 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
 #pragma unroll
             for (int idx = 0; idx < NM; ++idx) {
                 const int tm = idx / TN, tn = idx % TN;
-                mfma16<BF16>(acc[tm][tn], fa[SET][tm], fb[SET][tn]);
+                multiply(tm, tn, fa[SET][tm], fb[SET][tn]);
                 if (idx < LR)
 #pragma unroll
                     for (int r = idx * NR / LR; r < (idx + 1) * NR / LR; ++r) lds_read(r, SET ^ 1, next);
@@ -328,11 +359,11 @@ __device__ __forceinline__ void conv_plane_program(const ConvPlaneArgs &g, char 
         for (int32_t s = 0; s + 1 < n_slices; s += 2) {
             step(integral_constant<int, 0>{});
             step(integral_constant<int, 1>{});
-            asm volatile("s_nop 7" ::: "memory");
+            settle();
         }
         if (n_slices & 1) step(integral_constant<int, 0>{});
     }
-    asm volatile("s_nop 15" ::: "memory");
+    settle();
     NT_WAIT_VMCNT(0);
     __syncthreads();
     asm volatile("s_nop 15" ::: "memory");

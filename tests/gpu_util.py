@@ -17,6 +17,14 @@ def to_gpu(bits: np.ndarray, dtype: str) -> torch.Tensor:
     return t.view(TORCH_DT[dtype]).cuda()
 
 
+def inside(t, lead):
+    """the tensor in the middle of a larger buffer of NaNs, `lead` elements from its start"""
+    buf = torch.full((t.numel() + lead + 64,), float("nan"), dtype=t.dtype, device=t.device)
+    v = buf[lead:lead + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
 def to_f64(t: torch.Tensor) -> np.ndarray:
     return t.detach().to(torch.float64).cpu().numpy()
 
