@@ -8,32 +8,24 @@ import torch
 import paper_2507_11978_amd as nt
 import synthetic_inputs as si
 from oracle import numeric as onum
-from gpu_util import TORCH_DT, to_gpu
+from gpu_util import TORCH_DT, inside, to_gpu
 
 pytestmark = pytest.mark.gpu
 
 
-def inside(t, lead):
-    """the tensor in the middle of a larger buffer of NaNs, `lead` elements from its start"""
-    buf = torch.full((t.numel() + lead + 64,), float("nan"), dtype=t.dtype, device=t.device)
-    v = buf[lead:lead + t.numel()].view(t.shape)
-    v.copy_(t)
-    return v
-
-
-@pytest.mark.parametrize("shape,stride,pad", [
-    # one shape for each kernel that is built (filters x positions per tile)
-    ((1, 64, 6, 6, 40, 3, 3), (2, 2), (1, 1)),         # 16 x 32
-    ((7, 128, 25, 25, 100, 3, 3), (2, 2), (1, 1)),     # 16 x 48
-    ((13, 96, 28, 28, 40, 3, 3), (1, 1), (1, 1)),      # 16 x 96
-    ((10, 128, 21, 21, 100, 3, 3), (2, 2), (1, 1)),    # 32 x 32
-    ((12, 64, 25, 25, 72, 3, 3), (1, 1), (1, 1)),      # 32 x 48
-    ((13, 64, 21, 21, 130, 3, 3), (1, 1), (1, 1)),     # 32 x 64
-    ((11, 96, 28, 28, 300, 3, 3), (2, 2), (1, 1)),     # 32 x 96
-    ((3, 96, 21, 21, 300, 3, 3), (1, 1), (1, 1)),      # 64 x 32
-    ((1, 64, 6, 6, 40, 5, 5), (2, 2), (2, 2)),         # 25 taps: 16 x 32
-    ((7, 64, 21, 21, 40, 5, 5), (1, 1), (2, 2)),       # 16 x 64
-    ((7, 96, 28, 28, 40, 5, 5), (1, 1), (2, 2)),       # 16 x 96
+@pytest.mark.parametrize("shape,stride,pad,tile", [(*c, None) if len(c) == 3 else c for c in [
+    # one shape for each kernel that is built: filters and positions per tile, wavefronts that share the reduction
+    ((1, 64, 6, 6, 40, 3, 3), (2, 2), (1, 1), (16, 32, 2)),
+    ((7, 128, 25, 25, 100, 3, 3), (2, 2), (1, 1), (16, 48, 4)),
+    ((13, 96, 28, 28, 40, 3, 3), (1, 1), (1, 1), (16, 96, 3)),
+    ((10, 128, 21, 21, 100, 3, 3), (2, 2), (1, 1), (32, 32, 4)),
+    ((12, 64, 25, 25, 72, 3, 3), (1, 1), (1, 1), (32, 48, 2)),
+    ((13, 64, 21, 21, 130, 3, 3), (1, 1), (1, 1), (32, 64, 2)),
+    ((11, 96, 28, 28, 300, 3, 3), (2, 2), (1, 1), (32, 96, 3)),
+    ((3, 96, 21, 21, 300, 3, 3), (1, 1), (1, 1), (64, 32, 3)),
+    ((1, 64, 6, 6, 40, 5, 5), (2, 2), (2, 2), (16, 32, 2)),         # 25 taps
+    ((7, 64, 21, 21, 40, 5, 5), (1, 1), (2, 2), (16, 64, 2)),
+    ((7, 96, 28, 28, 40, 5, 5), (1, 1), (2, 2), (16, 96, 3)),
     # edges of the patch
     ((4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # no padding, rows of 12: a tile's rows end at other places than the input's
     ((9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # 25 positions per image, odd planes: several images in a tile, 2-byte aligned runs
@@ -45,8 +37,8 @@ def inside(t, lead):
     ((3, 160, 11, 7, 30, 3, 3), (3, 3), (2, 2)),       # stride as long as the filter, wide padding
     ((5, 64, 9, 8, 40, 3, 3), (4, 5), (0, 0)),         # rows and columns between the positions that no tap reads
     ((2, 64, 4, 6, 40, 5, 5), (1, 1), (4, 4)),         # more padding than image under some taps
-])
-def test_conv_patch(shape, stride, pad):
+]])
+def test_conv_patch(shape, stride, pad, tile):
     N, C, H, W, F, R, S = shape
     for dt, out, lead in (("f16", "f32", 32), ("bf16", "bf16", 33), ("f16", "f16", 47)):
         X, Wt = si.conv_inputs(N, C, H, W, F, R, S, dt, seed=91, dist="int")
@@ -59,6 +51,7 @@ def test_conv_patch(shape, stride, pad):
         torch.cuda.synchronize()
         plan = nt.last_conv_plan()
         assert plan.kernel == nt.CONV_FEW_POSITIONS and nt.last_kernel_path() == nt.PATH_CONV_CL and nt.last_k_split() == plan.wavefronts
+        assert tile in (None, (plan.filters, plan.positions[0], plan.wavefronts))
         assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
         assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
 

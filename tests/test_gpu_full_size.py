@@ -156,8 +156,8 @@ def test_conv_tile_and_split_chosen_together(shape, want_split):
 
 
 def test_full_size_conv_of_the_papers_kernel_list():
-    """(4, 512, 14, 14) * (512, 512, 3, 3) in the launch configuration bench.py times (on the channels-last copy, its reduction
-    split) and on the implicit kernel (the tile named; 18 programs per output tile): every output against the oracle, and a
+    """(4, 512, 14, 14) * (512, 512, 3, 3) in the launch configuration bench.py times (one launch straight from the tensors, its reduction
+    split over a program's wavefronts) and on the implicit kernel (the tile named; 18 programs per output tile): every output against the oracle, and a
     second call gives the same bits."""
     cfg = si.CONFIGS["c6_f16_conv_paper"]
     N, Cc, H, W, K, R, S = (cfg[k] for k in ("N", "C", "H", "W", "K", "R", "S"))
@@ -171,7 +171,7 @@ def test_full_size_conv_of_the_papers_kernel_list():
         nt.conv2d_implicit(x, w, Y, (1, 1), (0, 0), tile=tile)
         nt.conv2d_implicit(x, w, Y2, (1, 1), (0, 0), tile=tile)
         torch.cuda.synchronize()
-        assert nt.last_kernel_path() == path and (nt.last_k_split() == 18 if tile else nt.last_k_split() > 1)
+        assert nt.last_kernel_path() == path and nt.last_conv_plan().kernel == (0 if tile else nt.CONV_FEW_POSITIONS) and (nt.last_k_split() == 18 if tile else nt.last_k_split() > 1)
         assert torch.equal(Y, Y2)
         check_samples(to_f64(Y).ravel(), ref.ravel(), "f16")
 

@@ -210,7 +210,7 @@ def test_convolution(Nn, C, H, W, F, R, S, pad, layout):
     (2, 96, 9, 8, 72, 1, 1, (1, 1), (0, 0), "kcrs"),          # one tap over dense images: a product per image
 ])
 def test_convolution_on_the_channels_last_copy(Nn, C, H, W, F, R, S, stride, pad, layout):
-    """The library's own choice for channels in whole blocks of 32: tiles of 64 or 128 positions and filters, the reduction tap by
+    """What channels in whole blocks of 32 run on where the input rows do not stay in LDS: tiles of 64 or 128 positions and filters, the reduction tap by
     tap, what the copy put in place of the padding."""
     dt = "f16"
     P, Q = (H + 2 * pad[0] - R) // stride[0] + 1, (W + 2 * pad[1] - S) // stride[1] + 1

@@ -9,7 +9,7 @@ import paper_2507_11978_amd as nt
 import synthetic_inputs as si
 from oracle import arrangement as arr
 from oracle import numeric as onum
-from gpu_util import TORCH_DT, assert_gates, to_f64, to_gpu
+from gpu_util import TORCH_DT, assert_gates, inside, to_f64, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -345,8 +345,8 @@ def test_conv2d_small(shape, stride, pad, tile):
     ((1, 8, 8, 18, 128, 3, 3), (1, 0), (256, 128, 64)),       # padding along h only
     ((2, 64, 8, 8, 128, 1, 1), (0, 0), (256, 128, 64)),       # 1x1 filter
     ((2, 4, 9, 8, 256, 5, 3), (2, 1), (256, 256, 64)),        # 5x3 filter
-    ((5, 64, 24, 16, 256, 3, 3), (1, 1), None),               # library default tile: few positions, on the channels-last copy
-    ((12, 64, 32, 32, 256, 3, 3), (1, 1), None),              # ... enough of them for this kernel
+    ((5, 64, 24, 16, 256, 3, 3), (1, 1), None),               # library default tile: few positions, straight from the caller's tensors
+    ((12, 64, 32, 32, 256, 3, 3), (1, 1), None),              # ... many: the other kernel whose input rows stay in LDS
 ])
 def test_conv2d_dense_unit_stride(shape, pad, tile, dt, out):
     """Shapes the dedicated implicit-GEMM kernel takes: contiguous NCHW, stride 1 (here with Q % 8 == 0)."""
@@ -561,15 +561,9 @@ def test_split_along_k_with_a_shorter_last_part(M, N, K, dt, out):
     ref = onum.gemm(A, B, dt)
     want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
 
-    def inside(t):
-        buf = torch.full((t.numel() + 66,), float("nan"), dtype=t.dtype, device="cuda")
-        v = buf[33:33 + t.numel()].view(t.shape)
-        v.copy_(t)
-        return v
-
     a, b = to_gpu(A, dt), to_gpu(B, dt)
-    at, bt = inside(a.t().contiguous()).t(), inside(b.t().contiguous()).t()
-    a, b = inside(a), inside(b)
+    at, bt = inside(a.t().contiguous(), 33).t(), inside(b.t().contiguous(), 33).t()
+    a, b = inside(a, 33), inside(b, 33)
     split = 1
     for aa, bb in [(a, b), (a, bt), (at, b), (at, bt)]:
         buf = torch.full((M + 2, N + 8), float("nan"), dtype=TORCH_DT[out], device="cuda")
@@ -711,6 +705,7 @@ def test_conv2d_dense_rows_that_are_no_multiple_of_eight(shape, pad):
     ((3, 256, 8, 8, 130, 3, 3), (0, 0)),       # 36 k tiles, Q = 6
     ((2, 512, 7, 7, 256, 1, 1), (0, 0)),       # 1 x 1 filter, 8 k tiles
     ((1, 128, 7, 7, 256, 3, 3), (1, 1)),       # 49 output positions: one tile of 256 rows, 18 k tiles in four parts
+    ((4, 256, 14, 14, 96, 2, 2), (0, 0)),      # four taps: the library's own choice is the channels-last copy, its reduction split over programs
 ])
 def test_conv2d_dense_split_along_k(shape, pad):
     """Few output tiles and a long reduction: the k tiles are dealt to several programs per output tile, whose fp32
@@ -723,7 +718,7 @@ def test_conv2d_dense_split_along_k(shape, pad):
         ref = onum.conv2d(X, Wt, dt, (1, 1), pad)
         # the sums are integers below 2^24: exact in fp32, then rounded once (to nearest even) to the output format
         want = torch.from_numpy(ref).to(torch.float32).to(TORCH_DT[out])
-        for tile in ((256, 128, 64), (256, 256, 64), None):  # (named: on these kernels; the library's own choice: on the channels-last copy)
+        for tile in ((256, 128, 64), (256, 256, 64), None):  # (named: on these kernels; the library's own choice: see below)
             big = torch.full((N, K + 3, ref.shape[2], ref.shape[3]), float("nan"), dtype=TORCH_DT[out], device="cuda")
             Y = big[:, 2:K + 2]
             nt.conv2d_implicit(to_gpu(X, dt), to_gpu(Wt, dt), Y, (1, 1), pad, tile=tile)
@@ -732,8 +727,9 @@ def test_conv2d_dense_split_along_k(shape, pad):
                 assert nt.last_kernel_path() == nt.PATH_CONV
             elif tile:
                 assert nt.last_kernel_path() == (nt.PATH_CONV_TAP if tile[1] == 256 and K > 128 else nt.PATH_CONV_DIRECT)
-            elif R * S > 1:
+            elif R * S > 1:                                  # (nine taps: straight from the tensors, split over a program's wavefronts)
                 assert nt.last_kernel_path() == nt.PATH_CONV_CL
+                assert nt.last_conv_plan().kernel == (nt.CONV_FEW_POSITIONS if R * S == 9 else 0)
             assert nt.last_k_split() > 1
             assert torch.equal(Y.cpu(), want), f"conv split {shape} {pad} {dt} {out} {tile}"
             assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
@@ -769,7 +765,7 @@ def test_conv2d_dense_split_along_k_is_reproducible():
 ])
 def test_conv2d_through_the_workspace(shape, stride, pad):
     """Convolutions the implicit kernels do not take as they are.  Channels in whole blocks of 32 and more than one tap: on the
-    channels-last copy.  Other strided ones: the unfolded input is written once into the workspace and the product runs per
+    channels-last copy (an NCHW input perhaps straight from its rows).  Other strided ones: the unfolded input is written once into the workspace and the product runs per
     image on the matrix kernels.  Other unit-stride ones (wide padding, channels-last input): a dense zero-padded copy of the
     input is made and the implicit kernels run on it without padding.  Small
     integers: exact; NCHW and channels-last views; what lies around the output (a channel slice of a larger tensor)
@@ -786,7 +782,7 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
             nt.conv2d_implicit(x, to_gpu(Wt, dt), Y, stride, pad)
             torch.cuda.synchronize()
             if Cc % 32 == 0 and R * S > 1:
-                assert nt.last_kernel_path() == nt.PATH_CONV_CL
+                assert nt.last_kernel_path() == nt.PATH_CONV_CL and not (channels_last and nt.last_conv_plan().kernel)
             elif stride == (1, 1):
                 assert nt.last_kernel_path() == (nt.PATH_CONV_DIRECT if (Cc * R * S) % 32 == 0 else nt.PATH_CONV)
             else:
@@ -810,7 +806,7 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
 def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
     """Channels in whole blocks of 32, strided or with few positions: the edges of the copy's tiles, of the product's tiles in
     filters and positions, odd and single slices, output chunks that end inside an image, splits.  Small integers: exact;
-    NCHW and channels-last inputs and filters; what lies around the output (a channel slice) stays untouched."""
+    channels-last inputs and filters (all on the copy) and NCHW ones (where the kernels with resident rows leave them); what lies around the output (a channel slice) stays untouched."""
     N, Cc, H, W, K, R, S = shape
     for dt, out in (("f16", "f32"), ("bf16", "bf16"), ("f16", "f16")):
         X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, seed=33, dist="int")
@@ -828,6 +824,7 @@ def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
             torch.cuda.synchronize()
             # (one tap over dense images: the input is the matrix already)
             assert nt.last_kernel_path() == (nt.PATH_DIRECT if R * S == 1 and not last else nt.PATH_CONV_CL)
+            assert nt.last_conv_plan().kernel == 0 or not last and R * S == 9
             assert torch.equal(Y.cpu(), want), f"conv {shape} {stride} {pad} {dt} {out} channels_last={last}"
             assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, K + 2:]).all()
 

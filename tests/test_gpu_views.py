@@ -41,14 +41,16 @@ def test_convolution_written_as_an_arrangement_by_the_caller(shape, stride, pad,
     assert np.array_equal(to_f64(Y), ref)
 
 
-@pytest.mark.parametrize("shape,stride,pad,want", [
-    ((2, 32, 20, 24, 64, 3, 3), (1, 1), (1, 1), "direct"),        # dense, unit stride: the convolution kernel that streams into LDS
-    ((32, 128, 20, 24, 256, 3, 3), (1, 1), (1, 1), "tap"),         # ... and the one that walks the reduction tap by tap
-    ((2, 16, 21, 21, 64, 3, 3), (2, 2), (1, 1), "unfold"),        # strided: the unfolded input + the matrix kernels
-    ((2, 8, 20, 20, 32, 5, 5), (1, 1), (2, 2), "padded"),         # two columns of padding: the zero-padded copy
-    ((2, 64, 21, 19, 70, 3, 3), (2, 2), (1, 1), "last"),          # channels in whole blocks of 32: the channels-last copy
+@pytest.mark.parametrize("shape,stride,pad,want,kernel", [
+    ((2, 32, 20, 24, 64, 3, 3), (1, 1), (1, 1), "direct", 0),        # dense, unit stride: the convolution kernel that streams into LDS
+    ((32, 128, 20, 24, 256, 3, 3), (1, 1), (1, 1), "tap", nt.CONV_MANY_POSITIONS),         # ... many positions: with the input rows in LDS
+    ((32, 256, 20, 24, 256, 2, 2), (1, 1), (0, 0), "tap", 0),         # ... and the kernel that walks the reduction tap by tap
+    ((2, 16, 21, 21, 64, 3, 3), (2, 2), (1, 1), "unfold", 0),        # strided: the unfolded input + the matrix kernels
+    ((2, 8, 20, 20, 32, 5, 5), (1, 1), (2, 2), "padded", 0),         # two columns of padding: the zero-padded copy
+    ((2, 64, 21, 19, 70, 3, 3), (2, 2), (1, 1), "last", nt.CONV_FEW_POSITIONS),          # channels in whole blocks of 32: straight from the tensors
+    ((2, 64, 21, 19, 70, 2, 2), (2, 2), (1, 1), "last", 0),          # ... four taps: the channels-last copy
 ])
-def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride, pad, want):
+def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride, pad, want, kernel):
     """Views that address their tensors exactly like the Section 4.3 arrangement are recognised from their lowered index maps
     and run where nt_conv2d_implicit runs: same kernels, bit-identical output."""
     dt = "f16"
@@ -62,13 +64,14 @@ def test_a_callers_convolution_views_reach_the_convolution_kernels(shape, stride
     Y = torch.full((N, K, P, Q), float("nan"), dtype=torch.float32, device="cuda")
     nt.matmul_views(x, px, w, pw, Y, py)
     torch.cuda.synchronize()
-    path = nt.last_kernel_path()
+    path, plan = nt.last_kernel_path(), bytes(nt.last_conv_plan())
+    assert nt.last_conv_plan().kernel == kernel
     assert path == {"direct": nt.PATH_CONV_DIRECT, "tap": nt.PATH_CONV_TAP, "unfold": nt.PATH_CONV_UNFOLD, "padded": nt.PATH_CONV, "last": nt.PATH_CONV_CL}[want]
     assert np.array_equal(to_f64(Y), ref)
     Y2 = torch.full((N, K, P, Q), float("nan"), dtype=torch.float32, device="cuda")
     nt.conv2d_implicit(x, w, Y2, stride, pad)
     torch.cuda.synchronize()
-    assert nt.last_kernel_path() == path and torch.equal(Y, Y2)
+    assert nt.last_kernel_path() == path and bytes(nt.last_conv_plan()) == plan and torch.equal(Y, Y2)
 
 
 @pytest.mark.parametrize("shape,stride,pad,dilation", [((2, 16, 20, 22, 64, 3, 3), (1, 1), (2, 2), (2, 2)), ((1, 8, 17, 19, 40, 3, 2), (2, 1), (1, 3), (1, 3)),
@@ -92,7 +95,7 @@ def test_dilated_convolution_views(shape, stride, pad, dilation):
 
 
 @pytest.mark.parametrize("G,Cg,Kg,hw,stride,pad,dilation,want", [
-    (2, 32, 64, 24, (1, 1), (1, 1), (1, 1), "last"),        # two groups (images of theirs are not dense), each on the channels-last copy
+    (2, 32, 64, 24, (1, 1), (1, 1), (1, 1), "last"),        # two groups (images of theirs are not dense), each straight from its channels
     (2, 16, 64, 24, (1, 1), (1, 1), (1, 1), "padded"),      # ... each on the zero-padded copy
     (2, 8, 64, 24, (1, 1), (2, 1), (1, 1), "direct"),       # ... with whole 32-k slices
     (4, 8, 8, 15, (2, 2), (1, 1), (1, 1), "unfold"),        # strided groups

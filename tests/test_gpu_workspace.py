@@ -15,12 +15,18 @@ from gpu_util import TORCH_DT, to_f64, to_gpu
 pytestmark = pytest.mark.gpu
 
 
+def last(t):
+    """the same tensor stored channels-last"""
+    return t.contiguous(memory_format=torch.channels_last)
+
+
 def test_two_streams_share_the_workspace_without_racing():
     """Two streams issue different k-split convolutions and skinny products at the same time, several rounds, no host
     synchronisation in between: each partial-tile region is handed from one call to the next through the library's
     event, so every result must be the exact integer result of its own problem."""
     dt = "f16"
-    # (a) convolution, 12 programs x 72 k tiles -> split; (b) another one with other sizes; (c), (d) skinny products
+    # (a) convolution, 12 programs x 72 k tiles -> split; (b) another one with other sizes (channels-last inputs: on the copy in the
+    # workspace); (c), (d) skinny products
     Xa, Wa = si.conv_inputs(4, 512, 14, 14, 512, 3, 3, dt, seed=41, dist="int")
     Xb, Wb = si.conv_inputs(2, 256, 10, 10, 192, 3, 3, dt, seed=42, dist="int")
     Ac, Bc = si.gemm_inputs(16, 1024, 4096, dt, seed=43, dist="int")
@@ -28,7 +34,7 @@ def test_two_streams_share_the_workspace_without_racing():
     ref_a = onum.conv2d(Xa, Wa, dt, (1, 1), (0, 0), nthreads=16)
     ref_b = onum.conv2d(Xb, Wb, dt, (1, 1), (1, 1), nthreads=16)
     ref_c, ref_d = onum.gemm(Ac, Bc, dt), onum.gemm(Ad, Bd, dt)
-    xa, wa, xb, wb = to_gpu(Xa, dt), to_gpu(Wa, dt), to_gpu(Xb, dt), to_gpu(Wb, dt)
+    xa, wa, xb, wb = last(to_gpu(Xa, dt)), to_gpu(Wa, dt), last(to_gpu(Xb, dt)), to_gpu(Wb, dt)
     ac, bc, ad, bd = to_gpu(Ac, dt), to_gpu(Bc, dt), to_gpu(Ad, dt), to_gpu(Bd, dt)
     rounds = 6
     ya = [torch.full(ref_a.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(rounds)]
@@ -39,11 +45,11 @@ def test_two_streams_share_the_workspace_without_racing():
     torch.cuda.synchronize()
     for r in range(rounds):
         nt.conv2d_implicit(xa, wa, ya[r], (1, 1), (0, 0), stream=s1)
-        assert nt.last_k_split() > 1
+        assert nt.last_k_split() > 1 and nt.last_conv_plan().kernel == 0
         nt.gemm(ac, bc, yc[r], stream=s2)
         assert nt.last_k_split() > 1
         nt.conv2d_implicit(xb, wb, yb[r], (1, 1), (1, 1), stream=s2)
-        assert nt.last_k_split() > 1
+        assert nt.last_k_split() > 1 and nt.last_conv_plan().kernel == 0
         nt.gemm(ad, bd, yd[r], stream=s1)
         assert nt.last_k_split() > 1
     torch.cuda.synchronize()
@@ -64,7 +70,7 @@ def test_two_streams_padded_copy_unfolded_and_channels_last_routes():
         X, Wt = si.conv_inputs(*shape, dt, seed=seed, dist="int")
         ref = onum.conv2d(X, Wt, dt, stride, pad, nthreads=16)
         ys = [torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(2 * rounds)]
-        cases.append((to_gpu(X, dt), to_gpu(Wt, dt), stride, pad, path, ref, ys))
+        cases.append((last(to_gpu(X, dt)) if path == nt.PATH_CONV_CL else to_gpu(X, dt), to_gpu(Wt, dt), stride, pad, path, ref, ys))
     streams = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
     for r in range(rounds):
@@ -72,7 +78,7 @@ def test_two_streams_padded_copy_unfolded_and_channels_last_routes():
             for s in range(2):                                            # stream 0 at case i, stream 1 at the one after it
                 x, w, stride, pad, path, _, ys = cases[(i + s) % len(cases)]
                 nt.conv2d_implicit(x, w, ys[2 * r + s], stride, pad, stream=streams[s])
-                assert nt.last_kernel_path() == path
+                assert nt.last_kernel_path() == path and nt.last_conv_plan().kernel == 0
     torch.cuda.synchronize()
     for _, _, stride, pad, path, ref, ys in cases:
         for r, y in enumerate(ys):
@@ -89,7 +95,7 @@ def test_more_streams_than_parts_of_the_workspace():
         N, Cc, hw, K, stride = [(4, 256, 14, 256, 1), (2, 64, 30, 96, 2), (3, 128, 9, 70, 1), (1, 32, 57, 40, 2)][i]
         X, Wt = si.conv_inputs(N, Cc, hw, hw, K, 3, 3, dt, seed=60 + i, dist="int")
         ref = onum.conv2d(X, Wt, dt, (stride, stride), (1, 1), nthreads=16)
-        x, w = to_gpu(X, dt), to_gpu(Wt, dt)
+        x, w = last(to_gpu(X, dt)), to_gpu(Wt, dt)
         jobs.append((ref, lambda y, s, x=x, w=w, st=stride: nt.conv2d_implicit(x, w, y, (st, st), (1, 1), stream=s)))
     A, B = si.gemm_inputs(48, 640, 4096, dt, seed=65, dist="int")
     a, b = to_gpu(A, dt), to_gpu(B, dt)
@@ -125,7 +131,7 @@ def test_calls_captured_into_a_graph(warm):
     for i, (N, Cc, hw, K, stride) in enumerate([(2, 64, 30, 96, 2), (4, 256, 14, 256, 1), (8, 32, 28, 256, 1), (2, 48, 21, 40, 2)]):
         X, Wt = si.conv_inputs(N, Cc, hw, hw, K, 3, 3, dt, seed=70 + i, dist="int")
         ref = onum.conv2d(X, Wt, dt, (stride, stride), (1, 1), nthreads=16)
-        jobs.append((ref, to_gpu(X, dt), lambda x, y, s, w=to_gpu(Wt, dt), st=stride: nt.conv2d_implicit(x, w, y, (st, st), (1, 1), stream=s)))
+        jobs.append((ref, last(to_gpu(X, dt)) if i < 2 else to_gpu(X, dt), lambda x, y, s, w=to_gpu(Wt, dt), st=stride: nt.conv2d_implicit(x, w, y, (st, st), (1, 1), stream=s)))
     A, B = si.gemm_inputs(48, 640, 4096, dt, seed=75, dist="int")
     jobs.append((onum.gemm(A, B, dt), to_gpu(A, dt), lambda x, y, s, b=to_gpu(B, dt): nt.gemm(x, b, y, stream=s)))
     eager, main, side = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
