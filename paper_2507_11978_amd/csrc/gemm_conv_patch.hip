@@ -321,8 +321,8 @@ static bool patch_sizes(const ConvHint &h, const PatchTile &t, PatchSizes *z)
 // Estimated time (us) of the launch on that tile with `waves` wavefronts per program: programs run in rounds of as many as a
 // unit's LDS and registers hold; a program costs a fixed part, its blocks of channels -- each the latency of a wavefront's own
 // work, or the unit's throughput for all that are resident, whichever is longer -- and the sum of its wavefronts' parts.
-// A fit to 3907 launches of 179 drawn convolutions (64 to 512 channels and filters, images of 7 to 56, both strides, 3 x 3 and
-// 5 x 5; spread 8.4 %); the tile it names is 2.0 % behind the best one in the mean.
+// A fit to launches on every tile (64 to 512 channels and filters, images of 7 to 56, both strides, 3 x 3 and 5 x 5).  70 drawn convolutions that
+// it sends here take 1.13 times its figure in the mean, with a spread of 10 % (four sets of operands in turn, graph replays).
 static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t programs, int64_t waves)
 {
     // (LDS is dealt out in pieces of 1280 bytes: five programs of 32 KB do not fit)

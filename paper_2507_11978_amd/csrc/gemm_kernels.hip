@@ -795,7 +795,7 @@ static bool conv_unfold_ok(const GemmLaunch &g)
 
 // Estimated time (us) of a convolution on the routes that copy its input or fetch the unfolded one: unit stride with many
 // positions by conv_cost (0.9 of it: (32,512,14,14)*(512,512,3,3) 72 for 66, (32,256,56,56)*(256,256,3,3) 143 for 124,
-// (7,448,56,56)*(114,448,3,3) 63 for 58); the others are fits to 179 drawn convolutions (unit stride within 19 %, strided 11 %).
+// (7,448,56,56)*(114,448,3,3) 63 for 58); the others are fits (unit stride within a fifth, strided a tenth).
 static double conv_copied_cost(const ConvHint &h)
 {
     const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
@@ -1242,8 +1242,8 @@ static nt_status route_matrix(const GemmLaunch &g, FastArgs a, int alay, int bla
     };
     const bool direct = plain_direct || (out_ok && (alay == KCONTIG || g.K * a.lda < (1LL << 30)) && (blay == KCONTIG || g.K * a.ldb < (1LL << 30)));
     // k split: `ksplit` parts of K as the entries of a batched product into fp32 slices of the workspace.  Equal parts of whole k tiles;
-    // K no multiple of 64 (range-checked loads): whole k tiles but for a shorter last part.  One launch / so (us over rotating
-    // operands, in graph replays): weights stored [K, N] 10 x 3008 x 5408 25.2 / 11.8, 31 x 3094 x 3768 19.2 / 11.2, 1 x 7779 x 7368
+    // K no multiple of 64 (range-checked loads): whole k tiles but for a shorter last part.  One launch / so (us on the device, over
+    // rotating operands): weights stored [K, N] 10 x 3008 x 5408 25.2 / 11.8, 31 x 3094 x 3768 19.2 / 11.2, 1 x 7779 x 7368
     // 40.6 / 30.0; [N, K] 47 x 3176 x 4264 21.5 / 12.1, 25 x 1888 x 2083 11.3 / 8.8; square ones 446 x 448 x 6712 37.1 / 15.3,
     // 448 x 234 x 2021 14.9 / 10.1.  Not those that the kernel for few rows takes, which needs no second launch.
     double split_cost = 0;

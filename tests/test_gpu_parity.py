@@ -765,10 +765,9 @@ def test_conv2d_dense_split_along_k_is_reproducible():
 ])
 def test_conv2d_through_the_workspace(shape, stride, pad):
     """Convolutions the implicit kernels do not take as they are.  Channels in whole blocks of 32 and more than one tap: on the
-    channels-last copy (an NCHW input perhaps straight from its rows).  Other strided ones: the unfolded input is written once into the workspace and the product runs per
-    image on the matrix kernels.  Other unit-stride ones (wide padding, channels-last input): a dense zero-padded copy of the
-    input is made and the implicit kernels run on it without padding.  Small
-    integers: exact; NCHW and channels-last views; what lies around the output (a channel slice of a larger tensor)
+    channels-last copy (an NCHW input perhaps straight from its rows).  Other strided ones: the unfolded input is written once into
+    the workspace and the product runs per image on the matrix kernels.  Other unit-stride ones (wide padding, channels-last input): a
+    dense zero-padded copy of the input is made and the implicit kernels run on it without padding.  Small integers: exact; NCHW and channels-last views; what lies around the output (a channel slice of a larger tensor)
     stays untouched."""
     N, Cc, H, W, K, R, S = shape
     for dt, out in (("f16", "f32"), ("bf16", "bf16")):
@@ -806,7 +805,8 @@ def test_conv2d_through_the_workspace(shape, stride, pad):
 def test_conv2d_on_the_channels_last_copy(shape, stride, pad):
     """Channels in whole blocks of 32, strided or with few positions: the edges of the copy's tiles, of the product's tiles in
     filters and positions, odd and single slices, output chunks that end inside an image, splits.  Small integers: exact;
-    channels-last inputs and filters (all on the copy) and NCHW ones (where the kernels with resident rows leave them); what lies around the output (a channel slice) stays untouched."""
+    channels-last inputs and filters (all on the copy) and NCHW ones (where the kernels with resident rows leave them); what lies
+    around the output (a channel slice) stays untouched."""
     N, Cc, H, W, K, R, S = shape
     for dt, out in (("f16", "f32"), ("bf16", "bf16"), ("f16", "f16")):
         X, Wt = si.conv_inputs(N, Cc, H, W, K, R, S, dt, seed=33, dist="int")
