@@ -213,8 +213,8 @@ nt_status nt_gemm(const void *A, const nt_tensor_desc *dA, const void *B, const 
  * more (parts x M x N x 4 bytes) is refused with NT_ERR_UNSUPPORTED and a message that names both sizes; nothing is
  * launched then.  Every call on a GPU shares that GPU's array and nothing orders them: calls that overlap on one
  * GPU (different streams or host threads, both splitting) race on it -- keep them on one stream.  The array needs no
- * clearing between calls: every part writes its whole slice before the sum reads it.  (K no multiple of 64: as nt_gemm, not split while
- * the stream is captured.) */
+ * clearing between calls: every part writes its whole slice before the sum reads it.  (A K that is no multiple of 64 is split alike, but
+ * in no more parts than the array holds, by nt_gemm as well, and not while the stream is captured.) */
 #define NT_NOALLOC_SCRATCH_BYTES (32u << 20)
 nt_status nt_gemm_noalloc(const void *A, const nt_tensor_desc *dA, const void *B, const nt_tensor_desc *dB,
                           void *C, const nt_tensor_desc *dC, nt_dtype in_dtype, nt_dtype out_dtype,
