@@ -26,9 +26,11 @@
 // ahead and V one: rings of three and two blocks, 40 KB, and 117 registers let four workgroups share a compute unit, which
 // overlaps the exponentials of one with the MFMAs of another.  (Through registers, one block ahead, two blocks of each, three
 // workgroups: 69.8 us against 63.8 at 4 x 48 heads x 1024 fp16, 90.5 / 81.2 at 4 x 16 x 2048; the next half block's scores
-// computed between this one's exponentials measured no gain.)  What bounds it: the matrix and vector work of co-resident
-// wavefronts overlap only in part -- a loop of just this mix, 16 MFMAs and 96 vector instructions per 64 keys, takes 442 ns
-// per wavefront and SIMD against 252 for the MFMAs alone on constant data -- and the clock falls by a third on real data.
+// computed between this one's exponentials measured no gain.)  What bounds it: per 64 keys and wavefront 16 MFMAs (512 cycles) and 80
+// vector instructions (450 cycles), which run behind another wavefront's MFMAs (670 cycles for both, in a loop of just these, four
+// wavefronts per SIMD) as long as there are four, and the clock, 1.65 GHz on real data: without the loads into LDS the same cycles
+// take 53 us for 63, without LDS reads 46 (4 x 48 heads x 1024).  Blocks of 64 queries per wavefront with the MFMAs of one half behind the
+// exponentials of the other measured the same 62 us at half the LDS reads.
 #include "gemm_direct.h"
 #include <type_traits>
 
@@ -54,6 +56,7 @@ typedef short short4v_a __attribute__((ext_vector_type(4)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
 
 // two fp32 values -> one register of two 16-bit values, round to nearest even (v_cvt_pk_{f16,bf16}_f32)
 template <bool BF16>
@@ -71,14 +74,22 @@ __device__ __forceinline__ float add_pair(uint32_t w, float acc)
     else return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, w), __builtin_bit_cast(half2v, 0x3c003c00u), acc, false);
 }
 
+template <bool BF16>
+__device__ __forceinline__ float4v mfma16s(u32x4 a, u32x4 b, float4v c)
+{
+    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bhalf8, a), __builtin_bit_cast(bhalf8, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+}
+
 // SPLIT: the key blocks are dealt out to SPLIT groups of four wavefronts (group i: blocks i, i + SPLIT, ...), each with rings, a
 // row reference, sums and an accumulator of its own; group 0 merges them at the end.
 // AHEAD: rows that the range-checked loads do not take, one group: K and V through registers, one block ahead (loaded and
 // written to LDS at the top of a block instead, bf16, rows of pitch 63: 4 x 48 heads x 1024 78 us against 68, 8 x 64 heads,
 // 128 x 2048, 66 against 56; 2.1 M packed keys x 8 heads 32.0 ms in four groups, 29.1 so).
-// NW: wavefronts per group, 32 queries each (4; 1 or 2 where 128 queries a workgroup leave units empty).
-template <bool BF16, bool DMA, int SPLIT, int NW>
-__global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 : 2) void sdpa_kernel(const SdpaArgs g)
+// NW: wavefronts per group, 32 queries each (4; 1 or 2 where 128 queries a workgroup leave units empty; 8 where 256 fill them).
+// LONG (groups with some blocks to walk): how the wait for Q and the row sums are arranged, see below.
+template <bool BF16, bool DMA, int SPLIT, int NW, bool LONG>
+__global__ __launch_bounds__(64 * NW * SPLIT, NW >= 4 && (DMA || SPLIT > 1) ? 4 : 2) void sdpa_kernel(const SdpaArgs g)
 {
     constexpr bool AHEAD = !DMA && SPLIT == 1;
     static_assert(NW == 4 || !AHEAD, "one group ahead of its arithmetic: four wavefronts");
@@ -146,6 +157,15 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
     auto request_k = [&](int kb, uint32_t slot) { request(kb, slot, Kp, g.k_ss, k_ch, k_rsrc, k_off); };
     auto request_v = [&](int kb, uint32_t slot) { request(kb, 3 * BLK + slot, Vp, g.v_ss, v_ch, v_rsrc, v_off); };
 
+    // Row sums.  v_dot2c holds up the matrix pipe (a loop of 16 matrix instructions of 32 cycles, 2 dot2 behind each: 830 cycles, without
+    // 515; the exponentials, fma and packs of a block run behind matrix instructions of other wavefronts, the dots only between
+    // them), so LONG takes the sums on the matrix pipe: four 16 x 16 x 32 instructions a block against an operand of ones and zeros.
+    // With few blocks to walk their chain is the longer one.  Lane l of a 16 x 16 x 32 matrix instruction supplies row l % 16 and
+    // k 8 (l / 16) .. + 7 of it; of the weights (B operand) lanes c and c + 32 hold query c, lanes c + 16 and c + 48 query c + 16.
+    // Rows 4 i .. 4 i + 3 with i even take the former, the others the latter: lane l then receives the sum of query l % 32.
+    const uint32_t one_pair = ((lane >> 4) & 1) == ((lane >> 2) & 1) ? (BF16 ? 0x3f803f80u : 0x3c003c00u) : 0u;
+    const u32x4 ones{one_pair, one_pair, one_pair, one_pair};
+
     // ---- per-lane LDS read addresses
     // K fragment (A operand, row = key l32 of a 32-key half, chunk 2 ks + hi, swizzled like the write)
     // Key row 32 + l32 has the swizzle of row l32 with bit 2 flipped, so its chunk for k step ks sits where row
@@ -177,6 +197,13 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
     if constexpr (!AHEAD) {
         request_k(group, 0);
         request_v(group, 0);
+        // LONG: Q is waited for here, with the first blocks.  Its loads are ordinary ones; left to the compiler, the last two are waited for
+        // at their first use inside the loop, by a wait for everything outstanding, the blocks just requested among it: 192 heads,
+        // 1024 x 1024 66.6 us for 64.3.  With few blocks to walk, the start is what counts, and this costs 0.1 us.
+        if constexpr (LONG) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(qf[ks]));
+        }
         request_k(group + SPLIT, BLK);
     }
     // one key block: K in the slot at LDS offset `slot`, V in the slot at `vslot` behind the K ring
@@ -203,11 +230,10 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
                 for (int v = 0; v < 16; ++v)
                     if (key_base + jb * 32 + 8 * (v / 4) + 4 * hi + (v % 4) >= g.Sk) st[jb][v] = out;
         }
-        // ---- P^T = 2^(c S^T - M), packed to 16 bits, and its row sum (this lane's keys only; the halves are added at the end)
+        // ---- P^T = 2^(c S^T - M), packed to 16 bits, and its row sum (LONG: over all 64 keys; else this lane's, the halves are added at the end)
         float rs;
         u32x4 pk[2][2];
         auto exponentials = [&](const float m) {
-            rs = 0.f;
 #pragma unroll
             for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
@@ -216,14 +242,32 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
                     for (int j = 0; j < 4; ++j) {
                         const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[jb][8 * s2 + 2 * j], g.scale_log2e, -m));
                         const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[jb][8 * s2 + 2 * j + 1], g.scale_log2e, -m));
-                        const uint32_t w = pack2<BF16>(p0, p1);
-                        pk[jb][s2][j] = w;
-                        rs = add_pair<BF16>(w, rs);
+                        pk[jb][s2][j] = pack2<BF16>(p0, p1);
                     }
+        };
+        auto own_sum = [&] {                                             // of this lane's keys
+            float t = 0.f;
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t = add_pair<BF16>(pk[jb][s2][j], t);
+            return t;
         };
         bool accept = false;
         if (!pending) {
             exponentials(m_ref);
+            if constexpr (LONG) {
+                float4v sum{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2) sum = mfma16s<BF16>(ones, pk[jb][s2], sum);
+                rs = sum[0];
+            } else {
+                rs = own_sum();
+            }
             accept = __all(rs < 32768.f);                                // no weight beyond 2^15: the reference is close enough
         }
         if (!accept) {                                                   // wavefront-uniform: a row without reference, or a score far above M
@@ -237,6 +281,8 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
             const float m_use = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_ref - m_use);
             exponentials(m_use);
+            rs = own_sum();                                              // (not by matrix instructions: a row's NaN stays its own)
+            if constexpr (LONG) rs += __shfl_xor(rs, 32, 64);
             l_run *= alpha;
 #pragma unroll
             for (int db = 0; db < 2; ++db)
@@ -350,7 +396,7 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW == 4 && (DMA || SPLIT > 1) ? 4 
 
     // ---- O = O^T / l, stored along d: after the half-wavefronts trade register groups a lane owns
     // d = 32 db + 16 hi .. + 15 of its query row
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = LONG ? l_run : l_run + __shfl_xor(l_run, 32, 64);
     const float inv = 1.0f / l_tot;
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
@@ -527,10 +573,10 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void sdpa_decode_kernel(const Sd
     }
 }
 
-template <bool BF16, bool DMA, int SPLIT, int NW>
+template <bool BF16, bool DMA, int SPLIT, int NW, bool LONG>
 static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream_t s)
 {
-    auto kern = sdpa_kernel<BF16, DMA, SPLIT, NW>;
+    auto kern = sdpa_kernel<BF16, DMA, SPLIT, NW, LONG>;
     static DeviceOnce configured;
     if (!configured.done()) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(SPLIT * kSdpaLds));
@@ -541,19 +587,32 @@ static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream
     return check_launch("sdpa_kernel");
 }
 
+template <bool BF16, bool DMA, int SPLIT, int NW>
+static nt_status launch_sdpa_length(const SdpaArgs &k, int64_t programs, hipStream_t s)
+{
+    // Blocks per group from which on LONG is ahead (us, without / with): one wavefront a group 5 (17 blocks in four groups 11.0 / 10.2,
+    // 16 8.5 / 8.7, 7 6.3 / 6.5), else 3 (12 blocks in four groups 9.4 / 8.9, 10 in two 8.8 / 8.2, 3 in one 9.0 / 8.5, 2 in one 6.4 / 6.8;
+    // 2 with more programs than are resident from the start 12.8 / 12.3).
+    // (rows through registers go by the same rule, and give the same bits)
+    if (((k.Sk + kKeyBlock - 1) / kKeyBlock + SPLIT - 1) / SPLIT >= (NW == 1 ? 5 : programs > 1024 ? 2 : 3)) return launch_sdpa_inst<BF16, DMA, SPLIT, NW, true>(k, programs, s);
+    return launch_sdpa_inst<BF16, DMA, SPLIT, NW, false>(k, programs, s);
+}
+
 template <bool BF16, bool DMA, int NW>
 static nt_status launch_sdpa_groups(const SdpaArgs &k, int64_t programs, int split, hipStream_t s)
 {
-    if (split == 4) return launch_sdpa_inst<BF16, DMA, 4, NW>(k, programs, s);
+    if (split == 4) return launch_sdpa_length<BF16, DMA, 4, NW>(k, programs, s);
     if constexpr (DMA || NW < 4)
-        if (split == 2) return launch_sdpa_inst<BF16, DMA, 2, NW>(k, programs, s);
-    if constexpr (DMA || NW == 4) return launch_sdpa_inst<BF16, DMA, 1, NW>(k, programs, s);
+        if (split == 2) return launch_sdpa_length<BF16, DMA, 2, NW>(k, programs, s);
+    if constexpr (DMA || NW == 4) return launch_sdpa_length<BF16, DMA, 1, NW>(k, programs, s);
     return fail(NT_ERR_UNSUPPORTED, "no attention kernel for this split");
 }
 
 template <bool BF16, bool DMA>
 static nt_status launch_sdpa_split(const SdpaArgs &k, int64_t programs, int split, int nw, hipStream_t s)
 {
+    if constexpr (DMA)
+        if (nw == 8) return launch_sdpa_inst<BF16, true, 1, 8, true>(k, programs, s);
     if (nw == 1) return launch_sdpa_groups<BF16, DMA, 1>(k, programs, split, s);
     if (nw == 2) return launch_sdpa_groups<BF16, DMA, 2>(k, programs, split, s);
     return launch_sdpa_groups<BF16, DMA, 4>(k, programs, split, s);
@@ -633,6 +692,10 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
         // programs x 64 blocks 57 / 44, 160 x 24 24.2 / 22.0, 256 x 32 32 / 35), two do not (512 x 32 51 / 56).
         split = nblk >= 12 && programs <= 160 ? 4 : 1;
     }
+    // Blocks of 256 queries where that costs no more rounds of the units: the keys travel from L2 to LDS half as often.  Measured (us, 128 /
+    // 256 queries): 192 heads, 1024 x 1024 64.2 / 61.7, 93 heads, 1280 x 581 28.5 / 26.7, 80 heads, 408 x 397 12.5 / 12.0; with a round
+    // more they lose: 100 heads, 1815 x 227 22.0 / 25.0, 72 heads, 2040 x 736 39.2 / 42.2.
+    if (dma && split == 1 && nw == 4 && nblk >= 3 && 2 * ((blocks_of(2 * kQBlock) + 255) / 256) <= (programs + 255) / 256) nw = 8;
     k.nqb = (int32_t)(((int64_t)a.Sq + 32 * nw - 1) / (32 * nw));
     hipStream_t s = (hipStream_t)stream;
     const int64_t grid = bh * k.nqb;

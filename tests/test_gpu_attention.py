@@ -292,3 +292,28 @@ def test_blocks_of_queries_of_every_width(dt, B, H, Sq, Sk):
         nt.sdpa(gq, gk.contiguous(), gv.contiguous(), want)
         torch.cuda.synchronize()
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,Sq,Sk", [
+    # groups with enough blocks to walk take their row sums on the matrix pipe: the first such number of blocks and the one before,
+    # one wavefront a group, two, four, and blocks of 256 queries with a last one of one query and of all but one
+    (1, 3, 64, 1024), (1, 3, 64, 1025), (1, 64, 256, 640), (1, 64, 256, 641), (1, 130, 400, 128), (1, 130, 400, 129), (1, 64, 1024, 129), (1, 96, 1025, 150),
+    (3, 43, 511, 193), (5, 52, 512, 128)])
+def test_row_sums_of_walks_of_every_length(dt, B, H, Sq, Sk):
+    """Against the definition, with scores that raise the reference late; a query of NaN stays the only one."""
+    q, k, v = (si.normal_bits((B, H, n, 64), dt, 160 + i, 1.0) for i, n in enumerate([Sq, Sk, Sk]))
+    kd = onum.decode(k, dt).astype(np.float32)
+    kd[:, :, -40:] *= 6.0
+    k = si.round_to_bits(kd, dt)
+    got = run(q, k, v, dt)
+    heads = slice(0, 3)
+    assert_gates(got[:, heads], oat.sdpa(q[:, heads], k[:, heads], v[:, heads], dt), dt, f"sdpa {dt} {B}x{H}x{Sq}x{Sk}")
+    assert np.isfinite(got).all()
+    holes = np.arange(5, Sq, 37)
+    q[:, :, holes, 9] = 0x7e00 if dt == "f16" else 0x7fc0
+    with_nan = run(q, k, v, dt)
+    assert np.isnan(with_nan[:, :, holes]).all()
+    rest = np.delete(np.arange(Sq), holes)
+    # (a wavefront that holds a NaN sets its reference anew for every block: the others' results move by their weights' rounding, within the gates)
+    assert_gates(with_nan[:, heads][:, :, rest], got[:, heads][:, :, rest], dt, "sdpa beside NaN")
