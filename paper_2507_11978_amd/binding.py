@@ -1,4 +1,5 @@
-"""ctypes binding of include/nt.h -- argument marshalling only."""
+"""ctypes binding of include/nt.h -- argument marshalling only.  The calls that a program makes on torch tensors again and again
+go through an extension module (csrc/python/calls.cpp) that takes the tensors apart natively; what it declines is marshalled here."""
 from __future__ import annotations
 
 import ctypes as C
@@ -9,6 +10,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libnt.so")
+_CALLS_PATH = os.path.join(_HERE, "_nt_calls.so")
 MAX_DIMS, MAX_LEVELS = 8, 8
 
 OP_TILE, OP_EXPAND, OP_SQUEEZE, OP_PERMUTE, OP_FLATTEN, OP_RAVEL, OP_DESCEND, OP_ASCEND = range(8)
@@ -142,6 +144,27 @@ def load():
 def _check(st: int):
     if st != 0:
         raise NtError(st, load().nt_last_error().decode())
+
+
+_calls = None
+
+
+def _load_calls():
+    """The extension module, bound to the library's functions.  Called on behalf of a caller who holds torch tensors."""
+    global _calls
+    if not os.path.exists(_CALLS_PATH):
+        raise RuntimeError(f"{_CALLS_PATH} is missing: run `python -m paper_2507_11978_amd.build` (or __graft_entry__.build()) first")
+    import importlib.util
+
+    import torch  # noqa: F401  (its libraries hold what the module refers to)
+    spec = importlib.util.spec_from_file_location("_nt_calls", _CALLS_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    lib = load()
+    module.bind(*(C.cast(getattr(lib, name), C.c_void_p).value
+                  for name in ("nt_gemm", "nt_bmm", "nt_addmm", "nt_addmm_act", "nt_conv2d_implicit", "nt_sdpa", "nt_softmax", "nt_rms_norm", "nt_add", "nt_silu")))
+    _calls = module
+    return module
 
 
 def version() -> str:
@@ -341,6 +364,12 @@ def _require_cuda(*ts):
 
 def gemm(A, B, Cout, tile=None, stream=None):
     """Cout[M,N] = A[M,K] @ B[K,N] on the GPU; tensors may be any strided views."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).gemm(A, B, Cout, tile, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return Cout
     _require_cuda(A, B, Cout)
     _check(load().nt_gemm(A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
                           Cout.data_ptr(), _ref(Cout), _code(A),
@@ -396,6 +425,12 @@ def addmm(inp, A, B, Cout, alpha=1.0, beta=1.0, tile=None, stream=None, act=None
     """Cout[M,N] = act(beta * inp + alpha * (A[M,K] @ B[K,N])); inp has Cout's dtype and is handed over as
     an [M, N] view (stride 0 along broadcast axes).  act: None, "relu", "silu" or "gelu_tanh" (fused into the
     epilogue); inp may be None when beta is 0."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).addmm(inp, A, B, Cout, alpha, beta, ACTIVATIONS.get(act), tile, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return Cout
     if act is not None or inp is None:
         if act not in ACTIVATIONS:
             raise ValueError(f"unknown activation {act!r}")
@@ -430,6 +465,12 @@ def addmm(inp, A, B, Cout, alpha=1.0, beta=1.0, tile=None, stream=None, act=None
 
 def add(x, y, out, block_size=0, stream=None):
     """out = x + y over 1-D tensors (16-bit floating point, any stride)."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).add(x, y, out, block_size, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return out
     _require_cuda(x, y, out)
     _check(load().nt_add(x.data_ptr(), _ref(x), y.data_ptr(), _ref(y), out.data_ptr(),
                          _ref(out), _code(x), int(block_size), _stream_ptr(stream)))
@@ -437,6 +478,12 @@ def add(x, y, out, block_size=0, stream=None):
 
 
 def silu(x, out, block_size=0, stream=None):
+    if _recorder is None:
+        st = (_calls or _load_calls()).silu(x, out, block_size, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return out
     _require_cuda(x, out)
     _check(load().nt_silu(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
                           _code(x), int(block_size), _stream_ptr(stream)))
@@ -445,6 +492,12 @@ def silu(x, out, block_size=0, stream=None):
 
 def softmax(x, out, stream=None):
     """Row-wise softmax of a 2-D tensor."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).softmax(x, out, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return out
     _require_cuda(x, out)
     _check(load().nt_softmax(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
                              _code(x), _stream_ptr(stream)))
@@ -453,6 +506,12 @@ def softmax(x, out, stream=None):
 
 def rms_norm(x, out, eps=1e-6, stream=None):
     """Row-wise x / sqrt(mean(x^2) + eps) of a 2-D tensor (no weight)."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).rms_norm(x, out, eps, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return out
     _require_cuda(x, out)
     _check(load().nt_rms_norm(x.data_ptr(), _ref(x), out.data_ptr(), _ref(out),
                               float(eps), _code(x), _stream_ptr(stream)))
@@ -474,6 +533,12 @@ def matmul_views(A, ops_a, B, ops_b, Cout, ops_c, tile=None, stream=None):
 
 def sdpa(q, k, v, out, scale=0.0, stream=None):
     """out = softmax(scale * q @ k^T) @ v per (batch, head); tensors [batch, heads, seq, 64]; scale 0 = 1/sqrt(64)."""
+    if _recorder is None:
+        st = (_calls or _load_calls()).sdpa(q, k, v, out, scale, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return out
     _require_cuda(q, k, v, out)
     _check(load().nt_sdpa(q.data_ptr(), _ref(q), k.data_ptr(), _ref(k), v.data_ptr(), _ref(v),
                           out.data_ptr(), _ref(out), float(scale), _code(q), _stream_ptr(stream)))
@@ -481,6 +546,12 @@ def sdpa(q, k, v, out, scale=0.0, stream=None):
 
 
 def bmm(A, B, Cout, tile=None, stream=None):
+    if _recorder is None:
+        st = (_calls or _load_calls()).bmm(A, B, Cout, tile, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return Cout
     _require_cuda(A, B, Cout)
     _check(load().nt_bmm(A.data_ptr(), _ref(A), B.data_ptr(), _ref(B),
                          Cout.data_ptr(), _ref(Cout), _code(A),
@@ -489,6 +560,12 @@ def bmm(A, B, Cout, tile=None, stream=None):
 
 
 def conv2d_implicit(x, w, y, stride=(1, 1), pad=(0, 0), tile=None, stream=None):
+    if _recorder is None:
+        st = (_calls or _load_calls()).conv2d(x, w, y, stride, pad, tile, stream)
+        if st is not None:
+            if st:
+                _check(st)
+            return y
     _require_cuda(x, w, y)
     _check(load().nt_conv2d_implicit(x.data_ptr(), _ref(x), w.data_ptr(), _ref(w),
                                      y.data_ptr(), _ref(y), int(stride[0]), int(stride[1]),

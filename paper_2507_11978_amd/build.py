@@ -1,19 +1,23 @@
-"""Build libnt.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Build libnt.so (HIP kernels + C ABI) for gfx950 with hipcc and _nt_calls.so (the binding's native marshalling), in-tree.
 
 Each source is compiled to an object file in parallel (the kernel instantiations are
 spread over several translation units for that purpose), then linked."""
 from __future__ import annotations
 
 import glob
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnt.so")
+CALLS = os.path.join(HERE, "_nt_calls.so")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the epilogues unroll 256 accumulator elements with address arithmetic, masks and format switches per
@@ -50,12 +54,30 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_calls(force: bool) -> None:
+    """The extension module that takes the launching calls' torch tensors apart (host code; the torch that is installed)."""
+    src = os.path.join(CSRC, "python", "calls.cpp")
+    newest = max(os.path.getmtime(p) for p in (src, os.path.join(HERE, "..", "include", "nt.h")))
+    if not force and os.path.exists(CALLS) and os.path.getmtime(CALLS) >= newest:
+        return
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"), os.path.join(ROCM, "include"),
+               sysconfig.get_paths()["include"]]
+    # (the macros select HIP's headers for the AMD compiler and torch's for ROCm, as torch's own extension builder does)
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"] + ["-isystem" + i for i in include] +
+                         [src, "-o", CALLS, "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on {src}:\n" + res.stdout + res.stderr)
+
+
 def build(force: bool = True, jobs: int = 8) -> str:
-    """Compile every HIP/C++ source into paper_2507_11978_amd/libnt.so.
+    """Compile every HIP/C++ source into paper_2507_11978_amd/libnt.so, and the binding's extension module beside it.
     force=False recompiles only what is older than its source or a header."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        calls = pool.submit(_build_calls, force)
         objs = list(pool.map(lambda s: _compile(s, force), sources()))
+        calls.result()
     res = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs,
                          capture_output=True, text=True)
     if res.returncode != 0:

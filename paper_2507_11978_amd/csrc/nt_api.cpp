@@ -184,11 +184,30 @@ nt_status build_problem(int kind, const nt_tensor_desc *d0, const nt_tensor_desc
         const int want = kind == KIND_BMM ? 3 : 2;
         if (d0->ndim != want || d1->ndim != want || d2->ndim != want)
             return fail(NT_ERR_SHAPE_MISMATCH, kind == KIND_BMM ? "bmm tensors must be 3-D" : "gemm tensors must be 2-D");
-        NT_TRY(p->va.init(d0));
-        NT_TRY(p->vb.init(d1));
-        NT_TRY(p->vc.init(d2));
+        if (grid_only) {
+            // A plain product's views are its tensors: nothing of an arrangement is needed but what init() checks (the three
+            // hierarchical tensors and their shapes cost a small product's call a dozen allocations, 0.6 us).
+            for (const nt_tensor_desc *d : {d0, d1, d2})
+                for (int i = 0; i < want; ++i)
+                    if (d->size[i] < 0) return fail(NT_ERR_INVALID_ARG, "negative size");
+        } else {
+            NT_TRY(p->va.init(d0));
+            NT_TRY(p->vb.init(d1));
+            NT_TRY(p->vc.init(d2));
+        }
     }
-    const std::vector<int64_t> sa = p->va.level_shape(0), sb = p->vb.level_shape(0), sc = p->vc.level_shape(0);
+    struct Shape { size_t n; int64_t v[NT_MAX_DIMS]; int64_t operator[](size_t i) const { return v[i]; } size_t size() const { return n; } };
+    auto shape_of = [&](const nt_tensor_desc *d, const Arrangement &v) {
+        Shape s{};
+        if (grid_only && (kind == KIND_GEMM || kind == KIND_BMM)) {
+            s.n = (size_t)d->ndim;
+            for (int i = 0; i < d->ndim; ++i) s.v[i] = d->size[i];
+        } else {
+            for (const int64_t x : v.level_shape(0)) s.v[s.n++] = x;
+        }
+        return s;
+    };
+    const Shape sa = shape_of(d0, p->va), sb = shape_of(d1, p->vb), sc = shape_of(d2, p->vc);
     const size_t o = sa.size() == 3 ? 1 : 0;
     if (o == 1) {
         if (sa[0] != sb[0] || sa[0] != sc[0]) return fail(NT_ERR_SHAPE_MISMATCH, "batch sizes differ");
@@ -277,6 +296,21 @@ bool conv_plan_key(const nt_tensor_desc *const (&d)[3], const int32_t (&par)[4],
     return true;
 }
 
+// What an un-arranged [rows, cols] or [batch, rows, cols] tensor's view is lowered to (as Arrangement::lower_matrix_view
+// gives it): one digit per axis, no bounds beyond the tensor's own.
+OperandMap plain_matrix(const nt_tensor_desc *d, int64_t *batch_stride)
+{
+    const int r = d->ndim - 2, c = d->ndim - 1;
+    OperandMap m{};
+    m.rows = m.rrad[0] = d->size[r];
+    m.cols = m.crad[0] = d->size[c];
+    m.nrd = m.ncd = 1;
+    m.roff[0] = d->stride[r];
+    m.coff[0] = d->stride[c];
+    *batch_stride = d->ndim == 3 ? d->stride[0] : 0;
+    return m;
+}
+
 // D / dD / alpha / beta: the addmm epilogue C = beta * D + alpha * (A . B); dD == nullptr: plain product
 thread_local int t_last_path = -1;
 
@@ -309,6 +343,10 @@ nt_status run(int kind, const void *A, const nt_tensor_desc *dA, const void *B, 
     if (plan) {
         g.ma = plan->ma; g.mb = plan->mb; g.mc = plan->mc;
         g.sa_batch = plan->sa; g.sb_batch = plan->sb; g.sc_batch = plan->sc;
+    } else if (kind == KIND_GEMM || kind == KIND_BMM) {
+        g.ma = plain_matrix(dA, &g.sa_batch);
+        g.mb = plain_matrix(dB, &g.sb_batch);
+        g.mc = plain_matrix(dC, &g.sc_batch);
     } else {
         NT_TRY(p.va.lower_matrix_view(&g.ma, &nb, &g.sa_batch));
         NT_TRY(p.vb.lower_matrix_view(&g.mb, &nb, &g.sb_batch));
@@ -321,11 +359,11 @@ nt_status run(int kind, const void *A, const nt_tensor_desc *dA, const void *B, 
     g.has_d = dD != nullptr && beta != 0.f;
     if (g.has_d) {
         if (!D) return fail(NT_ERR_INVALID_ARG, "null input pointer with beta != 0");
-        nt::Arrangement vd;
-        NT_TRY(vd.init(dD));
-        const std::vector<int64_t> sd = vd.level_shape(0);
-        if (sd.size() != 2 || sd[0] != p.M || sd[1] != p.N) return fail(NT_ERR_SHAPE_MISMATCH, "input shape differs from [M, N]");
-        NT_TRY(vd.lower_matrix_view(&g.md, &nb, &g.sd_batch));
+        if (dD->ndim < 1 || dD->ndim > NT_MAX_DIMS) return fail(NT_ERR_INVALID_ARG, "ndim must be 1..6");
+        for (int i = 0; i < dD->ndim; ++i)
+            if (dD->size[i] < 0) return fail(NT_ERR_INVALID_ARG, "negative size");
+        if (dD->ndim != 2 || dD->size[0] != p.M || dD->size[1] != p.N) return fail(NT_ERR_SHAPE_MISMATCH, "input shape differs from [M, N]");
+        g.md = plain_matrix(dD, &g.sd_batch);
         g.D = D;
     }
     if (p.K == 0) {
