@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64 * NW * SPLIT, NW >= 4 && (DMA || SPLIT > 1) ? 4 
 
 // ---- few query rows (a decoding step: one query per head against a cache of keys)
 // Bound by reading K and V once; of the 128 query rows of sdpa_kernel's block all but a few would be padding, and its one
-// workgroup per head walks the keys in turn.  Here one workgroup of 16 wavefronts (4: short sequences, or heads
+// workgroup per head walks the keys in turn.  Here one workgroup of 16 wavefronts (4 or 8: short sequences, or heads
 // enough to fill the chip) per (head, query) deals the keys out to its
 // wavefronts, 32 at a time: eight lanes hold one key's 64 elements (a load instruction covers 8 keys, 1 KB), four keys per lane
 // group in flight and the next four behind them.  Scores, weights and sums stay in fp32 (a lane group keeps a maximum and a
@@ -645,15 +645,16 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
         k.BH = (int32_t)(batch * a.H);
         k.nqb = a.Sq;
         const int64_t programs = batch * a.H * a.Sq;
-        const int waves = programs >= 768 || a.Sk <= 128 ? 4 : 16;
+        // A workgroup of 16 wavefronts has a unit to itself (122 registers): beyond 256 programs they queue up for the units, and with few
+        // keys most of its wavefronts have none.  4 / 8 / 16 wavefronts (us, f16, in graph replays): 560 heads x 130 keys 7.1 / 8.3 / 11.3,
+        // x 488 15.6 / 14.6 / 18.0, 310 x 310 8.2 / 8.3 / 9.8, x 2047 35.6 / 36.5 / 38.0; 252 x 310 6.6 / 6.8 / 6.7, x 1338 15.7 / 15.9 / 15.9;
+        // 54 x 225 4.1 / 4.1 / 4.5, x 600 6.2 / 5.6 / 5.9, x 902 8.4 / 7.8 / 7.1, x 4096 24.3 / 20.1 / 19.1.
+        const int waves = programs > 256 ? (programs > 512 && a.Sk > 384 ? 8 : 4) : a.Sk <= (programs > 160 ? 640 : 256) ? 4 : a.Sk <= 640 ? 8 : 16;
         const dim3 grid((unsigned)programs), block(64 * waves);
-        if (waves == 4) {
-            if (bf16) hipLaunchKernelGGL((sdpa_decode_kernel<true, 4>), grid, block, 0, (hipStream_t)stream, k);
-            else hipLaunchKernelGGL((sdpa_decode_kernel<false, 4>), grid, block, 0, (hipStream_t)stream, k);
-        } else {
-            if (bf16) hipLaunchKernelGGL((sdpa_decode_kernel<true, 16>), grid, block, 0, (hipStream_t)stream, k);
-            else hipLaunchKernelGGL((sdpa_decode_kernel<false, 16>), grid, block, 0, (hipStream_t)stream, k);
-        }
+        auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, (hipStream_t)stream, k); };
+        if (waves == 4) bf16 ? launch(sdpa_decode_kernel<true, 4>) : launch(sdpa_decode_kernel<false, 4>);
+        else if (waves == 8) bf16 ? launch(sdpa_decode_kernel<true, 8>) : launch(sdpa_decode_kernel<false, 8>);
+        else bf16 ? launch(sdpa_decode_kernel<true, 16>) : launch(sdpa_decode_kernel<false, 16>);
         return check_launch("sdpa_decode_kernel");
     }
     const int64_t bh = batch * a.H;

@@ -317,3 +317,10 @@ def test_row_sums_of_walks_of_every_length(dt, B, H, Sq, Sk):
     rest = np.delete(np.arange(Sq), holes)
     # (a wavefront that holds a NaN sets its reference anew for every block: the others' results move by their weights' rounding, within the gates)
     assert_gates(with_nan[:, heads][:, :, rest], got[:, heads][:, :, rest], dt, "sdpa beside NaN")
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("H,Sk", [(160, 256), (160, 257), (160, 640), (161, 640), (160, 641), (256, 641), (257, 641), (512, 385), (513, 384), (513, 385)])
+def test_one_query_on_every_number_of_wavefronts(dt, H, Sk):
+    q, k, v = (si.normal_bits((1, H, n, 64), dt, 170 + i, 1.5) for i, n in enumerate([1, Sk, Sk]))
+    assert_gates(run(q, k, v, dt), oat.sdpa(q, k, v, dt), dt, f"sdpa {dt} {H} heads x {Sk}")
