@@ -288,7 +288,8 @@ __global__ __launch_bounds__(MAXW * 64) void conv_patch_kernel(const ConvPatchAr
 // the kernels that are built: taps, blocks of 16 filters and positions per tile, runs per lane and block, wavefronts at most
 #define NT_PATCH_TILES(X) \
     X(9, 1, 2, 5, 8) X(9, 1, 3, 5, 8) X(9, 1, 6, 5, 8) X(9, 2, 2, 4, 8) X(9, 2, 3, 4, 8) X(9, 2, 4, 4, 8) X(9, 2, 6, 8, 4) X(9, 4, 2, 8, 4) \
-    X(25, 1, 2, 7, 4) X(25, 1, 4, 7, 4) X(25, 1, 6, 8, 4)
+    X(25, 1, 2, 7, 4) X(25, 1, 4, 7, 4) X(25, 1, 6, 8, 4) \
+    X(1, 1, 2, 5, 8) X(1, 2, 2, 5, 8) X(1, 2, 4, 8, 8) X(1, 4, 2, 5, 8) X(1, 4, 4, 8, 8)
 struct PatchTile { int taps, mf, np, umax, maxw; };
 #define NT_PATCH_ENTRY(RS, MF, NP, U, W) {RS, MF, NP, U, W},
 static const PatchTile kPatchTiles[] = {NT_PATCH_TILES(NT_PATCH_ENTRY)};

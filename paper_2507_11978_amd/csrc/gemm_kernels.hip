@@ -851,6 +851,27 @@ static ConvClSizes conv_cl_sizes(const ConvHint &h, bool natural, int parts)
     return z;
 }
 
+// ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
+// workspace, whatever the number of positions (us a call, the kernels of route 1 / here): (2,192,28,28)*(200,192,1,1) 14.2 / 9.7,
+// (7,352,7,7)*(384,352,1,1) 19.5 / 10.0, (2,480,7,7)*(103,480,1,1) 18.4 / 5.7, (22,480,13,13)*(448,480,1,1) 27.8 / 9.6,
+// (26,192,28,28)*(192,192,1,1) 15.2 / 8.4, (2,512,56,56)*(383,512,1,1) 16.2 / 9.8, (23,192,56,56)*(448,192,1,1) 34.4 / 33.0.
+static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *taken)
+{
+    *taken = false;
+    const ConvHint &h = g.conv;
+    if (!conv_is_bare(g) || g.trace.resident || h.R != 1 || h.S != 1 || h.sh != 1 || h.sw != 1 || h.ph != 0 || h.pw != 0 || h.C % 32 != 0) return NT_OK;
+    if (h.xs[3] != 1 || h.xs[2] != h.W || h.xs[0] < 0 || h.ys[3] != 1 || h.ys[2] != h.Q || h.ws[1] != 1 || h.ws[0] < h.C || h.P * h.Q < 8) return NT_OK;
+    if (h.N * h.P * h.Q >= (1LL << 30) || h.K >= (1LL << 22) || h.C > 32768) return NT_OK;
+    GemmLaunch u = per_image_product(g, g.A, h.C, h.xs[1], h.xs[0]);
+    u.trace = g.trace;
+    u.trace.operand = 1 - g.trace.operand;                   // (the product's A is the filter)
+    FastArgs fa{};
+    int alay, blay;
+    if (!lower_plain(u, &fa, &alay, &blay)) return NT_OK;
+    *taken = true;
+    return launch_gemm(u, path_out);                         // (more images than one launch holds go out in several)
+}
+
 // ---- route 0: on a channels-last copy of the input (gemm_conv_cl.hip), the filter's tap-major copy beside it: convolutions
 // with channels in whole blocks of 32 that are
 //   strided or dilated, with more than one tap (the unfolded input, route 3, is then several times the copy: 62.0 -> 39.2 us
@@ -879,21 +900,7 @@ static nt_status route_conv_channels_last(const GemmLaunch &g, int *path_out, bo
         int32_t kt_per = 0;
         parts = conv_ksplit(M8, F, (K + 63) / 64, g.tile.bn, &kt_per);
         per = 2 * (int64_t)kt_per;
-        // One tap, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, small tiles:
-        // (2,192,28,28)*(200,192,1,1) 14.2 -> 9.7 us a call, (7,352,7,7)*(384,352,1,1) 19.5 -> 10.0.  (With a split route 1 keeps it:
-        // a copy buys nothing there.)
-        if (RS == 1 && parts > 1) return NT_OK;
-        if (RS == 1 && h.ph == 0 && h.pw == 0 && natural && h.xs[3] == 1 && h.xs[2] == h.W && h.xs[0] >= 0 && PQ >= 8) {
-            GemmLaunch u = per_image_product(g, g.A, h.C, h.xs[1], h.xs[0]);
-            u.trace = g.trace;
-            u.trace.operand = 1 - g.trace.operand;           // (the product's A is the filter)
-            FastArgs fa{};
-            int alay, blay;
-            if (lower_plain(u, &fa, &alay, &blay)) {
-                *taken = true;
-                return route_matrix(u, fa, alay, blay, path_out);
-            }
-        }
+        if (RS == 1 && parts > 1) return NT_OK;              // (a copy buys nothing there)
         // Without a split route 1 needs no workspace.  Up to 128 filters it is no slower by enough to give that up ((1,32,56,56) *
         // (32,32,3,3) 12.2 / 11.5 us, (2,32,64,64) * (128,32,3,3) 15.7 / 12.8, but 6.5 / 9.8 and 9.4 / 16 on two streams; (8,32,28,28) *
         // (256,32,3,3) 19.4 / 12.5, 10.5 / 10.5); a captured call stays independent of it, as its replays take no lease.
@@ -1064,7 +1071,10 @@ static bool conv_below_uses_workspace(const GemmLaunch &g)
 // kernels that do this is estimated to be ahead of the routes below:
 //   gemm_conv_patch.hip, 9 or 25 taps: one launch straight from the caller's tensors.  Of unit stride only what does not run on
 //     tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one block gives a program's
-//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters;
+//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters.  Strided with one tap (a
+//     down-sampling shortcut), up to an estimate of 10.3 us: two launches and the workspace cost a call through the unfolded input 11
+//     to 13 us, however small.  Unfolded / here, us a call: (3,64,14,14)*(104,64,1,1) 11.8 / 5.3, (2,512,14,14)*(128,512,1,1) 12.4 /
+//     7.7, (14,224,56,56)*(136,224,1,1) 15.5 / 15.5; beyond, its rows that no tap reads tell: (13,288,56,56)*(327,288,1,1) 19.7 / 39.8;
 //   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
 //     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
 //     workspace otherwise: those keep to the patch or the channels-last copy.
@@ -1094,15 +1104,18 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     const ConvHint &h = g.conv;
     if (!conv_is_bare(g) || (g.trace.out && !g.trace.resident) || h.C % 32 != 0 || h.P <= 0 || h.Q <= 0 || h.ph < 0 || h.pw < 0) return NT_OK;
     const int64_t RS = h.R * h.S, K = h.C * RS, HW = h.H * h.W, lim = 1 << 20;
-    if (RS < 6 || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
+    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1, small = conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K);
+    if ((RS < 6 && RS != 1) || RS > 64 || h.xs[3] != 1 || h.xs[2] != h.W || h.ys[3] != 1 || h.ys[2] != h.Q || h.xs[0] < 0 || h.xs[1] < 0) return NT_OK;
     if (h.ws[3] != 1 || h.ws[2] != h.S || h.ws[1] != RS || h.ws[0] < K) return NT_OK;
     // (32-bit byte offsets; divisions through fp32 reciprocals, exact below 2^21)
     if (HW < 8 || HW >= lim || (h.H + 2 * h.ph) * (h.W + 2 * h.pw) >= lim || h.N * (h.P * h.Q + 8) >= lim || h.K >= lim || h.K * h.ws[0] >= (1LL << 30) ||
         (h.N - 1) * h.xs[0] + (h.C - 1) * h.xs[1] + HW >= (1LL << 30)) return NT_OK;
-    const bool unit = h.sh == 1 && h.sw == 1 && h.dh == 1 && h.dw == 1, small = conv_small(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K);
     const bool aligned = h.ws[0] % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
-    const bool patch_ok = (RS == 9 || RS == 25) && aligned && !(unit && (h.C < 64 || (h.K > 128 && !small)));
-    const bool plane_ok = K <= 32768 && !(unit && small);
+    // (one tap of unit stride: the product per image, route 0b, unless a long reduction leaves units without a program)
+    int32_t kt_per = 0;
+    if (RS == 1 && unit && !(small && conv_ksplit(h.N * h.P * ((h.Q + 7) / 8 * 8), h.K, (K + 63) / 64, g.tile.bn, &kt_per) > 1)) return NT_OK;
+    const bool patch_ok = (RS == 9 || RS == 25 || RS == 1) && aligned && !(unit && (h.C < 64 || (h.K > 128 && !small)));
+    const bool plane_ok = RS >= 6 && K <= 32768 && !(unit && small);
     // (the estimates cost the host more than the rest of the call: the last 64 answers of a thread are kept, by value; 60 KB)
     static thread_local Kept<ResidentKey, ResidentPlan> plans;
     const ResidentKey key{{h.N, h.C, h.H, h.W, h.K, h.R, h.S, h.P, h.Q, h.sh, h.sw, h.ph, h.pw, h.dh, h.dw, h.xs[0], h.xs[1], h.xs[2], h.xs[3],
@@ -1110,7 +1123,7 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     const ResidentPlan *kept = plans.find(key);
     if (!kept) {
         ResidentPlan k;
-        double cost = conv_copied_cost(h), c = 0;
+        double cost = RS == 1 ? 10.3 : conv_copied_cost(h), c = 0;
         if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.patch_ahead = true; cost = c; }
         if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) {
             k.plane_ahead = true;
@@ -1147,7 +1160,7 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
         a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
         a.out_dtype = g.out_dtype;
         *taken = true;
-        if (path_out) *path_out = PATH_CONV_CL;
+        if (path_out) *path_out = RS > 1 ? PATH_CONV_CL : unit ? PATH_CONV_DIRECT : PATH_CONV_UNFOLD;
         t_k_split = k.patch_plan.waves;
         t_conv_plan = conv_patch_describe(k.patch, k.patch_plan);
         if (g.trace.out) {
@@ -1350,6 +1363,8 @@ nt_status launch_gemm(const GemmLaunch &g, int *path_out)
     nt_status st = route_conv_resident(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     if (g.trace.resident) return fail(NT_ERR_UNSUPPORTED, "this convolution does not run on the kernels that keep the input rows in LDS");
+    st = route_conv_pointwise(g, path_out, &taken);
+    if (taken || st != NT_OK) return st;
     st = route_conv_channels_last(g, path_out, &taken);
     if (taken || st != NT_OK) return st;
     ConvArgs c{};

@@ -61,7 +61,8 @@ struct GemmLaunch {
 };
 
 // Which code path a launch would take (reported for tests and the benchmark).  The two kernels with resident input rows go by
-// PATH_CONV_TAP (many positions, unit stride) or PATH_CONV_CL, the routes that took such calls before; last_conv_plan() tells.
+// PATH_CONV_TAP (many positions, unit stride), PATH_CONV_CL or (one tap) PATH_CONV_DIRECT and PATH_CONV_UNFOLD, the routes that took such
+// calls before; last_conv_plan() tells.
 enum KernelPath { PATH_GENERIC = 0, PATH_FAST = 1, PATH_DIRECT = 2, PATH_CONV = 3, PATH_CONV_DIRECT = 4, PATH_CONV_UNFOLD = 5, PATH_CONV_TAP = 6, PATH_CONV_CL = 7 };
 
 bool tile_is_built(nt_tile_cfg cfg);

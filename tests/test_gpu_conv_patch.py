@@ -1,5 +1,5 @@
-"""Convolutions that run in one launch straight from the caller's tensors (gemm_conv_patch.hip): 9 or 25 taps, dense planes,
-channels in whole blocks of 32, few positions or filters.  Small integers: every sum is exact, so the result must be the
+"""Convolutions that run in one launch straight from the caller's tensors (gemm_conv_patch.hip): 9 or 25 taps, or one and a stride, dense
+planes, channels in whole blocks of 32, few positions or filters.  Small integers: every sum is exact, so the result must be the
 oracle's bit for bit whatever the tile, the number of wavefronts that share the reduction and the patch's geometry."""
 import numpy as np
 import pytest
@@ -26,6 +26,11 @@ pytestmark = pytest.mark.gpu
     ((1, 64, 6, 6, 40, 5, 5), (2, 2), (2, 2), (16, 32, 2)),         # 25 taps
     ((7, 64, 21, 21, 40, 5, 5), (1, 1), (2, 2), (16, 64, 2)),
     ((7, 96, 28, 28, 40, 5, 5), (1, 1), (2, 2), (16, 96, 3)),
+    ((1, 64, 14, 14, 40, 1, 1), (2, 2), (0, 0), (16, 32, 2)),       # one tap
+    ((4, 352, 27, 27, 300, 1, 1), (2, 2), (0, 0), (32, 32, 6)),
+    ((20, 64, 28, 28, 70, 1, 1), (2, 2), (0, 0)), ((9, 96, 56, 56, 130, 1, 1), (2, 2), (0, 0)), ((16, 96, 27, 25, 66, 1, 1), (2, 2), (0, 0)),
+    ((2, 64, 9, 13, 24, 1, 1), (3, 1), (0, 0)), ((3, 64, 8, 9, 17, 1, 1), (1, 2), (2, 3)),
+    ((2, 480, 7, 7, 103, 1, 1), (1, 1), (0, 0)), ((5, 512, 8, 9, 256, 1, 1), (1, 1), (0, 0)),      # ... unit stride, a reduction worth sharing
     # edges of the patch
     ((4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # no padding, rows of 12: a tile's rows end at other places than the input's
     ((9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # 25 positions per image, odd planes: several images in a tile, 2-byte aligned runs
@@ -50,7 +55,8 @@ def test_conv_patch(shape, stride, pad, tile):
         nt.conv2d_implicit(x, w, Y, stride, pad)
         torch.cuda.synchronize()
         plan = nt.last_conv_plan()
-        assert plan.kernel == nt.CONV_FEW_POSITIONS and nt.last_kernel_path() == nt.PATH_CONV_CL and nt.last_k_split() == plan.wavefronts
+        path = nt.PATH_CONV_CL if R * S > 1 else nt.PATH_CONV_UNFOLD if max(stride) > 1 else nt.PATH_CONV_DIRECT
+        assert plan.kernel == nt.CONV_FEW_POSITIONS and nt.last_kernel_path() == path and nt.last_k_split() == plan.wavefronts
         assert tile in (None, (plan.filters, plan.positions[0], plan.wavefronts))
         assert torch.equal(Y.cpu(), want), (shape, stride, pad, dt, out)
         assert torch.isnan(big[:, :2]).all() and torch.isnan(big[:, F + 2:]).all()
@@ -66,4 +72,19 @@ def test_conv_patch_of_a_channel_slice():
     nt.conv2d_implicit(to_gpu(X, dt)[:, 32:32 + C], to_gpu(Wt, dt)[:, 32:32 + C], Y, (1, 1), (1, 1))
     torch.cuda.synchronize()
     assert nt.last_conv_plan().kernel == nt.CONV_FEW_POSITIONS
+    assert np.array_equal(Y.double().cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("shape", [(22, 448, 13, 13, 448), (2, 416, 7, 7, 103), (7, 128, 28, 28, 272), (2, 64, 56, 56, 383), (1, 32, 2, 4, 8), (300, 32, 3, 3, 40)])
+def test_one_tap_of_unit_stride_is_a_product_per_image(shape):
+    """However many positions, filters and images, of a slice of the channels."""
+    N, C, H, W, F = shape
+    dt = "f16"
+    X, Wt = si.conv_inputs(N, C + 32, H, W, F, 1, 1, dt, seed=93, dist="int")
+    ref = onum.conv2d(np.ascontiguousarray(X[:, 32:]), np.ascontiguousarray(Wt[:, 32:]), dt, (1, 1), (0, 0), nthreads=16)
+    x, w = to_gpu(X, dt)[:, 32:], to_gpu(Wt, dt)[:, 32:]
+    Y = torch.full(ref.shape, float("nan"), dtype=torch.float32, device="cuda")
+    nt.conv2d_implicit(x, w, Y)
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_DIRECT and nt.last_k_split() == 1 and nt.last_conv_plan().kernel == 0
     assert np.array_equal(Y.double().cpu().numpy(), ref)
