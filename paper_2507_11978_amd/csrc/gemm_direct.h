@@ -23,6 +23,9 @@ constexpr int kSliceK = 32;      // k extent of one LDS slice
 // loads: eight slices (64 KB), so that a reduction of up to 256 is requested whole before the first slice is waited for
 // (256 x 256 x 256 on 16 programs: 43.4 us through the operand-map kernel, which waits for every k tile, 3.9 us here).
 constexpr int ring_of(int bm, int bn) { return bm + bn == 128 ? 8 : bm + bn == 384 || bm + bn == 320 ? 3 : 4; }   // (320: the convolution kernel's 256 x 64, 60 KB)
+// Slices per trip of the loop, between two barriers: the 64 x 64 tile's four matrix instructions per slice and wavefront are too few to hide
+// a barrier and the LDS reads behind it (1344 x 704 x 2888 16.5 -> 14.0 us, 704 x 656 x 590 6.6 -> 6.0).
+constexpr int slices_per_trip(int bm, int bn) { return bm + bn == 128 ? 2 : 1; }
 constexpr int residency_of(int bm, int bn) { return bm + bn == 512 ? 1 : 2; }
 
 // s_waitcnt that waits until at most n vector-memory operations are outstanding and leaves

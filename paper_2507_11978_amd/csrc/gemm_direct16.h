@@ -395,7 +395,7 @@ template <int BM, int BN, bool BF16, int ALAY, int BLAY, bool EDGE, bool TRACE =
 __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_kernel(const FastArgs g)
 {
     constexpr int TM = BM / 32, TN = BN / 32;
-    constexpr int kRing = ring_of(BM, BN);
+    constexpr int kRing = ring_of(BM, BN), KS = slices_per_trip(BM, BN), kGroups = kRing / KS;      // (ring positions: groups of KS slices)
     using TileA = DirectTile16<BM, ALAY>;
     using TileB = DirectTile16<BN, BLAY>;
     constexpr uint32_t A_BYTES = TileA::BYTES, B_BYTES = TileB::BYTES, B_BASE = kRing * A_BYTES;
@@ -444,15 +444,17 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
 
-    // operand fragments of one slice, two sets: [set][fragment]
-    u32x4 fa[2][TM], fb[2][TN];
+    // operand fragments of one group of slices, two sets: [set][slice][fragment]
+    u32x4 fa[2][KS][TM], fb[2][KS][TN];
     constexpr int NRA = TM * TileA::RPF, NRB = TN * TileB::RPF, NR = NRA + NRB;   // LDS reads per slice
     // LDS read r of a slice, in the order the next trip's matrix instructions need the data:
     // A fragment 0, every B fragment, then the remaining A fragments
-    auto lds_read = [&](int r, int set, uint32_t ring) {
-        if (r < TileA::RPF) ta.read(fa[set], smem, r, ring * A_BYTES);
-        else if (r < TileA::RPF + NRB) tb.read(fb[set], smem, r - TileA::RPF, ring * B_BYTES);
-        else ta.read(fa[set], smem, r - NRB, ring * A_BYTES);
+    auto lds_read = [&](int rr, int set, uint32_t group) {
+        const int h = rr / NR, r = rr % NR;
+        const uint32_t ring = group * KS + h;
+        if (r < TileA::RPF) ta.read(fa[set][h], smem, r, ring * A_BYTES);
+        else if (r < TileA::RPF + NRB) tb.read(fb[set][h], smem, r - TileA::RPF, ring * B_BYTES);
+        else ta.read(fa[set][h], smem, r - NRB, ring * A_BYTES);
     };
     constexpr int NM = TM * TN, ND = TileA::PER + TileB::PER;
     u32x4 rsrc_a{0, 0, 0, 0}, rsrc_b{0, 0, 0, 0};
@@ -469,26 +471,34 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
             else tb.issue_one_buf(d - TileA::PER, rsrc_b, (uint32_t)(pb - gB), lds0 + B_BASE + ring * B_BYTES, wave);
         }
     };
-    // One trip: the TM x TN matrix instructions on fragment set `set`; between them, spread evenly so that neither
+    const int64_t last = n_slices - 1;
+    // Slices past the last one are requested all the same (the loop has one shape).  Full tiles: the last slice again, never
+    // multiplied.  EDGE: an offset beyond any buffer (2^31; the lanes' own offsets stay below 2^31), so that zeros arrive:
+    // an odd number of slices is rounded up to whole passes of the loop below by trips that multiply zeros.
+    auto slice_a = [&](int64_t s) { return gA + (s <= last ? s * a_step : (EDGE ? (int64_t)0x80000000LL : last * a_step)); };
+    auto slice_b = [&](int64_t s) { return gB + (s <= last ? s * b_step : (EDGE ? (int64_t)0x80000000LL : last * b_step)); };
+    // One trip: the KS x TM x TN matrix instructions on fragment set `set`; between them, spread evenly so that neither
     // the LDS queue nor the memory queue holds the in-order wavefront back while the matrix pipe runs dry, the LDS
-    // reads of the next slice (ring position rring) into the other set and the ND global -> LDS loads of the slice
-    // at (pa, pb) into ring position dring.
-    auto trip = [&](int set, uint32_t rring, const char *pa, const char *pb, uint32_t dring) {
-        constexpr int RS = NM * 3 / 4;                      // the reads go out during the first three quarters: all have returned by the next barrier
+    // reads of the next group of slices (ring position rring) into the other set and the KS x ND global -> LDS loads of the
+    // group that begins with slice `s` into ring position dring.
+    auto trip = [&](int set, uint32_t rring, int64_t s, uint32_t dring) {
+        constexpr int RS = KS * NM * 3 / 4;                 // the reads go out during the first three quarters: all have returned by the next barrier
+        const char *pa[KS], *pb[KS];
 #pragma unroll
-        for (int idx = 0; idx < NM; ++idx) {
-            const int tm = idx / TN, tn = idx % TN;
-            mfma16<BF16>(acc[tm][tn], fb[set][tn], fa[set][tm]);      // transposed block (see store_tile16_rows)
+        for (int h = 0; h < KS; ++h) { pa[h] = slice_a(s + h); pb[h] = slice_b(s + h); }
+#pragma unroll
+        for (int idx = 0; idx < KS * NM; ++idx) {
+            const int h = idx / NM, tm = idx % NM / TN, tn = idx % TN;
+            mfma16<BF16>(acc[tm][tn], fb[set][h][tn], fa[set][h][tm]);      // transposed block (see store_tile16_rows)
             if (idx < RS)
 #pragma unroll
-                for (int r = idx * NR / RS; r < (idx + 1) * NR / RS; ++r) lds_read(r, set ^ 1, rring);
+                for (int r = idx * KS * NR / RS; r < (idx + 1) * KS * NR / RS; ++r) lds_read(r, set ^ 1, rring);
 #pragma unroll
-            for (int d = idx * ND / NM; d < (idx + 1) * ND / NM; ++d) dma(d, pa, pb, dring);
+            for (int d = idx * ND / NM; d < (idx + 1) * ND / NM; ++d) dma(d % ND, pa[d / ND], pb[d / ND], dring * KS + d / ND);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    const int64_t last = n_slices - 1;
     // The range check of a buffer load works on the load's 4-byte words: with an odd pitch or extent the word that holds an
     // operand's very last element can end 2 bytes past the operand, and then arrives as zero.  The wavefront whose load
     // brings that word in fetches the element by itself (a 2-byte load inside the operand) and puts it in its place once
@@ -520,12 +530,6 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
             }
         }
     };
-    // Slices past the last one are requested all the same (the loop has one shape).  Full tiles: the last slice again, never
-    // multiplied.  EDGE: an offset beyond any buffer (2^31; the lanes' own offsets stay below 2^31), so that zeros arrive:
-    // an odd number of slices is rounded up to whole passes of the loop below by one trip that multiplies zeros.
-    auto slice_a = [&](int64_t s) { return gA + (s <= last ? s * a_step : (EDGE ? (int64_t)0x80000000LL : last * a_step)); };
-    auto slice_b = [&](int64_t s) { return gB + (s <= last ? s * b_step : (EDGE ? (int64_t)0x80000000LL : last * b_step)); };
-
     if constexpr (TRACE) {
         const int64_t s = g.trace_slice;
 #pragma unroll
@@ -545,32 +549,40 @@ __global__ __launch_bounds__(kThreads, residency_of(BM, BN)) void gemm_direct16_
     for (int s = 0; s < kRing; ++s)
 #pragma unroll
         for (int d = 0; d < ND; ++d) dma(d, slice_a(s), slice_b(s), s);
-    NT_WAIT_VMCNT((kRing - 1) * ND);
-    settle(0, 0);
+    NT_WAIT_VMCNT((kRing - KS) * ND);
+#pragma unroll
+    for (int h = 0; h < KS; ++h) settle(h, h);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NR; ++r) lds_read(r, 0, 0);
+    for (int r = 0; r < KS * NR; ++r) lds_read(r, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
 
-    // Slice s sits at ring position s % kRing.  At the top of trip s this wavefront's part of slice s+1 must have
-    // landed (the loads of the younger slices may still be in flight); the barrier then says that slice s+1 is
-    // complete and that every wavefront holds its fragments of slice s in registers, so the position of slice s can
-    // be overwritten by slice s+kRing.  Two trips per pass (the fragment sets alternate).
+    // Group p (slices KS p ..) sits at ring position p % kGroups.  At the top of trip p this wavefront's part of group p+1 must have
+    // landed (the loads of the younger groups may still be in flight); the barrier then says that group p+1 is
+    // complete and that every wavefront holds its fragments of group p in registers, so the position of group p can
+    // be overwritten by group p+kGroups.  Two trips per pass (the fragment sets alternate).
     uint32_t ring = 0;
-    for (int64_t sl = 0; sl < n_slices; sl += 2) {
-        uint32_t nxt = ring + 1 == kRing ? 0 : ring + 1;
-        NT_WAIT_VMCNT((kRing - 2) * ND);
-        settle(sl + 1, nxt);
-        __syncthreads();
-        trip(0, nxt, slice_a(sl + kRing), slice_b(sl + kRing), ring);
-        ring = nxt;
-        nxt = ring + 1 == kRing ? 0 : ring + 1;
-        NT_WAIT_VMCNT((kRing - 2) * ND);
-        settle(sl + 2, nxt);
-        __syncthreads();
-        trip(1, nxt, slice_a(sl + 1 + kRing), slice_b(sl + 1 + kRing), ring);
-        ring = nxt;
+    const int64_t groups = (n_slices + KS - 1) / KS;
+#define NT_TRIP(SET, P)                                                                     \
+    do {                                                                                    \
+        const uint32_t nxt = ring + 1 == kGroups ? 0 : ring + 1;                            \
+        NT_WAIT_VMCNT((kGroups - 2) * KS * ND);                                             \
+        _Pragma("unroll") for (int h = 0; h < KS; ++h) settle(((P) + 1) * KS + h, nxt * KS + h); \
+        __syncthreads();                                                                    \
+        trip(SET, nxt, ((P) + kGroups) * KS, ring);                                         \
+        ring = nxt;                                                                         \
+    } while (0)
+    // (an odd number of groups: rounded up by a trip on zeros where a trip is one slice -- full tiles have an even number of them --, a
+    // pass of one trip where it is two)
+    const int64_t whole = KS == 1 ? groups + (groups & 1) : groups & ~(int64_t)1;
+    for (int64_t p = 0; p < whole; p += 2) {
+        NT_TRIP(0, p);
+        NT_TRIP(1, p + 1);
     }
+    if constexpr (KS > 1) {
+        if (groups & 1) NT_TRIP(0, whole);
+    }
+#undef NT_TRIP
     NT_WAIT_VMCNT(0);                                      // drain the surplus prefetches ...
     __syncthreads();                                       // ... of every wavefront: the epilogue reuses the LDS
     // The accumulators are read by ordinary instructions from here on, and the compiler does not know that the inline
