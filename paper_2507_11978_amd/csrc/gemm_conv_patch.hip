@@ -329,7 +329,11 @@ static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t progra
     // (LDS is dealt out in pieces of 1280 bytes: five programs of 32 KB do not fit)
     const double slots = t.maxw == 8 ? 8 : 4, units = 256;
     const double resident = std::max(1.0, std::min((double)(128 / ((z.region * waves + 1279) / 1280)), std::floor(slots / (double)waves)));
-    const double mine = programs > units ? std::min(resident, (double)programs / units) : 1.0;
+    // (programs to a unit: between one and two, units that have two set the pace more than the mean says, in long walks.  By the
+    // mean alone (4,512,14,14)*(512,512,3,3) ran on 384 programs, 13.7 us, for 192 of twice the filters, 12.2;
+    // (8,416,13,13)*(88,416,3,3) on 11.3 us for 9.0.  Of less than 12 blocks programs leave their unit to the next before they get in its way:
+    // there this loses, 288 channels 14.0 / 15.4, 128 6.6 / 7.9, for some that gain, 128 channels 8.0 / 7.0)
+    const double share = (double)programs / units, mine = programs > units ? std::min(resident, share < 2 && z.blocks >= 12 ? 0.5 * (share + 2) : share) : 1.0;
     double rounds = std::max(1.0, (double)programs / (units * resident));
     rounds = rounds < 4 ? std::ceil(rounds) : rounds + 0.3;
     const double runs = (double)((z.runs + 15) / 16), mm = t.taps * t.mf * t.np, reads = t.taps * (t.mf + t.np);

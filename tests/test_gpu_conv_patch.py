@@ -31,6 +31,7 @@ pytestmark = pytest.mark.gpu
     ((20, 64, 28, 28, 70, 1, 1), (2, 2), (0, 0)), ((9, 96, 56, 56, 130, 1, 1), (2, 2), (0, 0)), ((16, 96, 27, 25, 66, 1, 1), (2, 2), (0, 0)),
     ((2, 64, 9, 13, 24, 1, 1), (3, 1), (0, 0)), ((3, 64, 8, 9, 17, 1, 1), (1, 2), (2, 3)),
     ((2, 480, 7, 7, 103, 1, 1), (1, 1), (0, 0)), ((5, 512, 8, 9, 256, 1, 1), (1, 1), (0, 0)),      # ... unit stride, a reduction worth sharing
+    ((8, 416, 13, 13, 88, 3, 3), (1, 1), (1, 1)), ((1, 480, 28, 28, 208, 5, 5), (1, 1), (2, 2)),   # long walks, one to two programs to a unit
     # edges of the patch
     ((4, 512, 14, 14, 512, 3, 3), (1, 1), (0, 0)),     # no padding, rows of 12: a tile's rows end at other places than the input's
     ((9, 96, 5, 5, 33, 3, 3), (1, 1), (1, 1)),         # 25 positions per image, odd planes: several images in a tile, 2-byte aligned runs
