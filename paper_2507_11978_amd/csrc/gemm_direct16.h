@@ -13,8 +13,8 @@
 // 1.60 PFLOP/s for v_mfma_f32_32x32x16 (both reach 2.4 with all-zero operands): the chip is power managed, the narrower
 // instruction moves fewer accumulator bits per flop, and the difference is clock.
 //
-// One trip of the loop = one slice.  A trip multiplies the fragments of slice s (all in registers, read during the
-// trip before) while it reads the fragments of slice s+1 into the other register set and requests slice s+ring
+// One trip of the loop = one slice (two on the 64 x 64 tile: slices_per_trip in gemm_direct.h).  A trip multiplies the
+// fragments of slice s (all in registers, read during the trip before) while it reads the fragments of slice s+1 into the other register set and requests slice s+ring
 // into the ring position that slice s has just left; one barrier per trip, at its top, says that slice s+1 has
 // landed in LDS and that nobody reads slice s there any more.
 //
