@@ -851,10 +851,57 @@ static ConvClSizes conv_cl_sizes(const ConvHint &h, bool natural, int parts)
     return z;
 }
 
+// Rows of positions: whole multiples of 8 (16 bytes), even, odd.
+static int row_class(int64_t n) { return n % 8 == 0 ? 0 : n % 2 == 0 ? 1 : 2; }
+
+// How many programs' time a unit spends: between their mean number per unit and the most (`one`: of which a unit holds one at a time).
+static double unit_programs(int64_t programs, bool one)
+{
+    const double most = (double)((programs + 255) / 256);
+    return one ? most : std::max(1.0, 0.5 * (most + (double)programs / 256));
+}
+
+// Estimated time (us) of a call of one tap as a product per image: a start, a program's fixed part and its k tiles (64 x 64: more where
+// rows are no multiple of 16 bytes) for the programs of a unit, MB of input -- once more for every further strip of filters -- and MB of
+// output by the class of an image's positions.  Fits to 1560 calls (1 to 512 images of 3 x 3 to 56 x 56, 32 to 16384 channels, 16 to
+// 2048 filters), spread 4 to 9 % by tile.
+static double one_tap_product_cost(const GemmLaunch &u)
+{
+    struct Fit { int bm, bn; double start, program, tile, unaligned, in, again, out[3]; };
+    static const Fit fits[] = {{64, 64, 3.0, 0.70, 0.20, 0.05, 0.017, 0.025, {0.0, 0.02, 0.36}}, {128, 128, 3.7, 0.98, 0.49, 0.0, 0.027, 0.010, {0.11, 0.28, 0.43}},
+                               {256, 128, 3.9, 1.66, 0.71, 0.0, 0.098, 0.050, {0.12, 0.23, 0.34}}, {128, 256, 3.8, 1.70, 0.74, 0.0, 0.080, 0.017, {0.10, 0.23, 0.29}},
+                               {256, 256, 0.0, 10.95, 1.03, 0.0, 0.109, 0.014, {0.0, 0.34, 0.46}}};
+    const int rows = row_class(u.N);
+    const double share = unit_programs(u.batch * u.mt * u.nt, u.tile.bm + u.tile.bn == 512), mb = 2e-6 * (double)u.batch * (double)u.N;
+    for (const Fit &f : fits)
+        if (f.bm == u.tile.bm && f.bn == u.tile.bn)
+            return f.start + share * (f.program + (f.tile + (rows && u.N > 64 ? f.unaligned : 0.0)) * (double)u.K / 64) +
+                   mb * ((f.in + f.again * (double)(u.mt - 1)) * (double)u.K + f.out[rows] * (double)u.M);
+    return 0;
+}
+
+// The same on the kernels of route 1 without a split, by their tile (128 filters, 64, 256) and the class of an output row.  Fits to 850
+// calls, spread 5 to 9 %.
+static double one_tap_implicit_cost(const GemmLaunch &g)
+{
+    const ConvHint &h = g.conv;
+    const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
+    struct Fit { double start, program, tile, in, out; };
+    static const Fit fits[3][3] = {{{5.3, 2.2, 0.97, 0.067, 0.071}, {7.3, 2.95, 1.25, 0.014, 0.176}, {8.5, 1.56, 1.20, 0.070, 0.715}},
+                                   {{4.0, 1.7, 0.77, 0.067, 0.080}, {4.8, 2.1, 0.90, 0.052, 0.185}, {6.6, 0.0, 0.99, 0.079, 0.758}},
+                                   {{7.0, 0.0, 1.40, 0.036, 0.380}, {8.4, 5.0, 1.33, 0.045, 0.657}, {5.9, 7.6, 1.45, 0.029, 0.877}}};
+    const Fit &f = fits[g.tile.bn == 256 ? 2 : h.K <= 64 ? 1 : 0][row_class(h.Q)];
+    const double share = unit_programs(((M8 + 255) / 256) * ((h.K + g.tile.bn - 1) / g.tile.bn), g.tile.bn == 256), mb = 2e-6 * (double)h.N * (double)(h.P * h.Q);
+    return f.start + share * (f.program + f.tile * (double)h.C / 64) + mb * (f.in * (double)h.C + f.out * (double)h.K);
+}
+
 // ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
-// workspace, whatever the number of positions (us a call, the kernels of route 1 / here): (2,192,28,28)*(200,192,1,1) 14.2 / 9.7,
+// workspace (us a call, the kernels of route 1 / here): (2,192,28,28)*(200,192,1,1) 14.2 / 9.7,
 // (7,352,7,7)*(384,352,1,1) 19.5 / 10.0, (2,480,7,7)*(103,480,1,1) 18.4 / 5.7, (22,480,13,13)*(448,480,1,1) 27.8 / 9.6,
 // (26,192,28,28)*(192,192,1,1) 15.2 / 8.4, (2,512,56,56)*(383,512,1,1) 16.2 / 9.8, (23,192,56,56)*(448,192,1,1) 34.4 / 33.0.
+// Each image's positions are rounded up to a tile, though, which many small images pay for, and route 1's tiles of 64 filters suit a
+// handful of them: (286,96,8,8)*(438,96,1,1) 12.5 / 15.3, (256,1024,7,7)*(2048,1024,1,1) 107 / 128, (184,64,56,56)*(18,64,1,1) 30.1 /
+// 33.8.  Those of many positions whose reduction route 1 would not split stay there where its estimate is 2 % ahead.
 static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
@@ -868,6 +915,11 @@ static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *
     FastArgs fa{};
     int alay, blay;
     if (!lower_plain(u, &fa, &alay, &blay)) return NT_OK;
+    const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
+    int32_t kt_per = 0;
+    ConvArgs c{};
+    if (!conv_small(M8, h.K) && conv_ksplit(M8, h.K, (h.C + 63) / 64, g.tile.bn, &kt_per) == 1 && 1.02 * one_tap_implicit_cost(g) < one_tap_product_cost(u) && match_conv(g, &c))
+        return NT_OK;
     *taken = true;
     return launch_gemm(u, path_out);                         // (more images than one launch holds go out in several)
 }
