@@ -296,7 +296,7 @@ static const PatchTile kPatchTiles[] = {NT_PATCH_TILES(NT_PATCH_ENTRY)};
 #undef NT_PATCH_ENTRY
 
 // sizes of a patch that the estimate needs
-struct PatchSizes { int64_t rows, row, span, image, last_h, units, runs, plane, region, blocks, most; };
+struct PatchSizes { int64_t rows, row, span, image, images, last_h, units, runs, plane, region, blocks, most; };
 
 static bool patch_sizes(const ConvHint &h, const PatchTile &t, PatchSizes *z)
 {
@@ -306,7 +306,7 @@ static bool patch_sizes(const ConvHint &h, const PatchTile &t, PatchSizes *z)
     z->row = (h.Q - 1) * h.sw + (h.S - 1) * h.dw + 1;
     // the most output rows and images that PT positions touch, the most input rows under them (more images: span rows for sh)
     const int64_t out_rows = std::min<int64_t>((PT + h.Q - 2) / h.Q + 1, h.N * h.P);
-    const int64_t images = std::min<int64_t>(std::min<int64_t>((PT + PQ - 2) / PQ + 1, h.N), out_rows);
+    const int64_t images = z->images = std::min<int64_t>(std::min<int64_t>((PT + PQ - 2) / PQ + 1, h.N), out_rows);
     z->rows = std::max((out_rows - 1) * h.sh + z->span, (out_rows - images) * h.sh + images * z->span);
     z->last_h = std::min<int64_t>(h.H - 1, (h.P - 1) * h.sh + z->span - 1 - h.ph);
     z->units = z->last_h >= 0 ? ((z->last_h + 1) * h.W + 3) / 4 : 1;
@@ -341,6 +341,23 @@ static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t progra
     return 2.33 + rounds * (1.30 + 0.572e-3 * (double)z.plane + (double)((z.blocks + waves - 1) / waves) * std::max(latency, unit) + 0.0324 * (double)((waves - 1) * t.mf * t.np));
 }
 
+// The same for one tap on the tile that patch_cost has picked: with two to eight matrix instructions per block the loads are all there is
+// to it, and patch_cost, a fit to nine and 25 taps, is short by 10 % (stride 2) to 75 % (planes of 3 x 3).  A block costs a wavefront
+// its instructions and runs, and the unit the runs of all wavefronts, more for every image whose planes are no multiple of 16 bytes apart
+// (`aligned`: they are); what the launch moves comes on top, the input once more, from the caches, for every further tile of filters.
+// A fit to 745 drawn launches (32 to 3400 channels, 16 to 2048 filters, planes of 3 to 56, both strides), spread 10 %.
+static double patch_cost_one_tap(const ConvHint &h, const PatchTile &t, const PatchSizes &z, int64_t programs, int64_t waves, bool aligned)
+{
+    const double resident = std::max(1.0, std::min((double)(128 / ((z.region * waves + 1279) / 1280)), std::floor((t.maxw == 8 ? 8.0 : 4.0) / (double)waves)));
+    const double share = (double)programs / 256, mine = std::max(1.0, std::min(resident, share));
+    double rounds = std::max(1.0, share / resident);
+    rounds = rounds < 4 ? std::ceil(rounds) : rounds + 0.3;
+    const double mm = t.mf * t.np, runs = (double)((z.runs + 15) / 16);
+    const double block = 0.028 * mm + 0.358 * runs + (0.0074 * runs + (aligned ? 0.0 : 0.021 * (double)z.images)) * mine * (double)waves;
+    const double in = 2e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W), out = 2e-6 * (double)h.N * (double)h.K * (double)(h.P * h.Q);
+    return 3.4 + rounds * ((double)((z.blocks + waves - 1) / waves) * block + 0.04 * (double)(waves - 1) * mm) + (0.07 + 0.006 * (double)((h.K - 1) / (16 * t.mf))) * in + 0.57 * out;
+}
+
 bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best, double *cost_out)
 {
     const int64_t M = h.N * h.P * h.Q;
@@ -364,9 +381,12 @@ bool conv_patch_plan(const ConvHint &h, ConvPatchArgs *a, ConvPatchPlan *best, d
         }
     }
     if (best->waves == 0) return false;
-    *cost_out = best_cost;
     const PatchTile &t = kPatchTiles[best->tile];
     const int64_t PT = 16 * t.np, FT = 16 * t.mf, PQ = h.P * h.Q;
+    const int64_t programs = ((h.K + FT - 1) / FT) * ((M + PT - 1) / PT);
+    // (one tap beyond 10.3 of patch_cost: longer walks than the fit has seen, and slower by far than it says: (2,9120,14,14)*(35,9120,1,1) 46.7 us
+    // for 17.5 on the implicit kernels, strided (17,8192,14,14)*(23,8192,1,1) 74.6 for 53.8 unfolded)
+    *cost_out = t.taps > 1 ? best_cost : best_cost < 10.3 ? patch_cost_one_tap(h, t, z, programs, best->waves, h.xs[0] % 8 == 0 && h.xs[1] % 8 == 0) : 1e30;
     a->xs1 = h.xs[1]; a->syn = h.ys[0]; a->syf = h.ys[1];
     a->xs0 = (uint32_t)h.xs[0]; a->ldb = (uint32_t)h.ws[0];
     a->F = (int32_t)h.K; a->M = (int32_t)M; a->blocks = (int32_t)z.blocks;

@@ -895,6 +895,18 @@ static double one_tap_implicit_cost(const GemmLaunch &g)
     return f.start + share * (f.program + f.tile * (double)h.C / 64) + mb * (f.in * (double)h.C + f.out * (double)h.K);
 }
 
+// What a call of one tap costs (us) on the routes that do without gemm_conv_patch.hip.  Unit stride: the product (a tenth more, on a tie the
+// reduction is shared).  Strided: the unfolded input -- a launch, the image it reads, a line per channel -- and the product on it; 700
+// calls, spread 6 %.  Where that is not open either, the operand-map kernel is all there is.
+static double one_tap_without_patch(const GemmLaunch &g)
+{
+    const ConvHint &h = g.conv;
+    const bool unit = h.sh == 1 && h.sw == 1;
+    if (unit ? h.ph != 0 || h.pw != 0 : !conv_unfold_ok(g)) return 1e30;
+    const double product = one_tap_product_cost(per_image_product(g, g.A, h.C, h.P * h.Q, h.C * h.P * h.Q));
+    return unit ? 1.1 * product : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
+}
+
 // ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
 // workspace (us a call, the kernels of route 1 / here): (2,192,28,28)*(200,192,1,1) 14.2 / 9.7,
 // (7,352,7,7)*(384,352,1,1) 19.5 / 10.0, (2,480,7,7)*(103,480,1,1) 18.4 / 5.7, (22,480,13,13)*(448,480,1,1) 27.8 / 9.6,
@@ -1123,10 +1135,11 @@ static bool conv_below_uses_workspace(const GemmLaunch &g)
 // kernels that do this is estimated to be ahead of the routes below:
 //   gemm_conv_patch.hip, 9 or 25 taps: one launch straight from the caller's tensors.  Of unit stride only what does not run on
 //     tiles of 256 filters (few positions, or at most 128 filters), from two blocks of channels on: one block gives a program's
-//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters.  Strided with one tap (a
-//     down-sampling shortcut), up to an estimate of 10.3 us: two launches and the workspace cost a call through the unfolded input 11
-//     to 13 us, however small.  Unfolded / here, us a call: (3,64,14,14)*(104,64,1,1) 11.8 / 5.3, (2,512,14,14)*(128,512,1,1) 12.4 /
-//     7.7, (14,224,56,56)*(136,224,1,1) 15.5 / 15.5; beyond, its rows that no tap reads tell: (13,288,56,56)*(327,288,1,1) 19.7 / 39.8;
+//     wavefronts nothing to share, and the kernels of route 1 need no copy for up to 128 filters.  Strided with one tap too (a
+//     down-sampling shortcut): two launches and the workspace cost a call through the unfolded input 11 us and more, however small.
+//     Unfolded / here, us a call: (3,64,14,14)*(104,64,1,1) 11.8 / 5.3, (2,512,14,14)*(128,512,1,1) 12.4 / 7.7,
+//     (14,224,56,56)*(136,224,1,1) 15.5 / 15.5; but (4,384,27,27)*(1000,384,1,1) 11.1 / 13.0, (6,608,28,28)*(271,608,1,1) 12.6 / 15.3, and
+//     rows that no tap reads tell, (13,288,56,56)*(327,288,1,1) 19.7 / 39.8;
 //   gemm_conv_plane.hip, six taps or more: tiles of up to 256 x 256, the filter's copy in the workspace (estimate + 20 %: what it
 //     is short by on rows that are far off 16 bytes).  Not the small unit-stride ones whose reduction is split, or that need no
 //     workspace otherwise: those keep to the patch or the channels-last copy.
@@ -1175,7 +1188,7 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     const ResidentPlan *kept = plans.find(key);
     if (!kept) {
         ResidentPlan k;
-        double cost = RS == 1 ? 10.3 : conv_copied_cost(h), c = 0;
+        double cost = RS == 1 ? one_tap_without_patch(g) : conv_copied_cost(h), c = 0;
         if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.patch_ahead = true; cost = c; }
         if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) {
             k.plane_ahead = true;

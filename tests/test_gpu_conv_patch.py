@@ -103,3 +103,18 @@ def test_one_tap_of_many_small_images_keeps_the_implicit_product(shape):
     assert nt.last_kernel_path() == nt.PATH_CONV_DIRECT and nt.last_k_split() == 1 and nt.last_conv_plan().kernel == 0
     # (sums of small integers: exact in fp32 whatever their order)
     assert torch.equal(Y, torch.matmul(w.float().reshape(F, C), x.float().reshape(N, C, H * W)).reshape(Y.shape))
+
+
+@pytest.mark.parametrize("shape", [(4, 384, 27, 27, 1000), (6, 608, 28, 28, 271)])
+def test_one_strided_tap_is_unfolded_where_that_is_ahead(shape):
+    """11.1 us for 13.0 straight from the caller's tensors, 12.6 for 15.3."""
+    N, C, H, W, F = shape
+    X, Wt = si.conv_inputs(N, C, H, W, F, 1, 1, "f16", seed=95, dist="int")
+    x, w = to_gpu(X, "f16"), to_gpu(Wt, "f16")
+    P, Q = (H + 1) // 2, (W + 1) // 2
+    Y = torch.full((N, F, P, Q), float("nan"), dtype=torch.float32, device="cuda")
+    nt.conv2d_implicit(x, w, Y, (2, 2))
+    torch.cuda.synchronize()
+    assert nt.last_kernel_path() == nt.PATH_CONV_UNFOLD and nt.last_conv_plan().kernel == 0
+    sub = x.float()[:, :, ::2, ::2].reshape(N, C, P * Q)
+    assert torch.equal(Y, torch.matmul(w.float().reshape(F, C), sub).reshape(Y.shape))
