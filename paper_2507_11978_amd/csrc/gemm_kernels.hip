@@ -895,7 +895,7 @@ static double one_tap_implicit_cost(const GemmLaunch &g)
     return f.start + share * (f.program + f.tile * (double)h.C / 64) + mb * (f.in * (double)h.C + f.out * (double)h.K);
 }
 
-// What a call of one tap costs (us) on the routes that do without gemm_conv_patch.hip.  Unit stride: the product (a tenth more, on a tie the
+// What a call of one tap costs (us) on the routes that do without gemm_conv_patch.hip.  Unit stride: the product (a fifth more: near a tie the
 // reduction is shared).  Strided: the unfolded input -- a launch, the image it reads, a line per channel -- and the product on it; 700
 // calls, spread 6 %.  Where that is not open either, the operand-map kernel is all there is.
 static double one_tap_without_patch(const GemmLaunch &g)
@@ -904,7 +904,7 @@ static double one_tap_without_patch(const GemmLaunch &g)
     const bool unit = h.sh == 1 && h.sw == 1;
     if (unit ? h.ph != 0 || h.pw != 0 : !conv_unfold_ok(g)) return 1e30;
     const double product = one_tap_product_cost(per_image_product(g, g.A, h.C, h.P * h.Q, h.C * h.P * h.Q));
-    return unit ? 1.1 * product : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
+    return unit ? 1.2 * product : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
 }
 
 // ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
