@@ -895,16 +895,37 @@ static double one_tap_implicit_cost(const GemmLaunch &g)
     return f.start + share * (f.program + f.tile * (double)h.C / 64) + mb * (f.in * (double)h.C + f.out * (double)h.K);
 }
 
+// ... and of few positions with the reduction split over `parts` programs of `per` k tiles, the sums through the workspace.  A fit to 613 calls
+// (up to 16384 channels), spread 10 to 12 %.
+static double one_tap_split_cost(const ConvHint &h, int parts, int64_t per)
+{
+    const double sums = 8e-6 * (double)parts * (double)(h.N * h.P * h.Q) * (double)h.K;
+    return h.Q % 2 ? 10.9 + 1.55 * (double)per + 0.38 * sums : 11.8 + 1.2 * (double)per + (h.Q % 8 ? 0.3 : 0.2) * sums;
+}
+
+// The same call on the kernels of route 1, if they take it and -- few positions with a split, many without -- have an estimate; else 1e30.
+static double one_tap_route_1(const GemmLaunch &g)
+{
+    const ConvHint &h = g.conv;
+    const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
+    int32_t per = 0;
+    ConvArgs c{};
+    const bool small = conv_small(M8, h.K);
+    const int parts = conv_ksplit(M8, h.K, (h.C + 63) / 64, g.tile.bn, &per);
+    if (small != (parts > 1) || !match_conv(g, &c)) return 1e30;
+    return parts > 1 ? one_tap_split_cost(h, parts, per) : one_tap_implicit_cost(g);
+}
+
 // What a call of one tap costs (us) on the routes that do without gemm_conv_patch.hip.  Unit stride: the product (a fifth more: near a tie the
-// reduction is shared).  Strided: the unfolded input -- a launch, the image it reads, a line per channel -- and the product on it; 700
-// calls, spread 6 %.  Where that is not open either, the operand-map kernel is all there is.
+// reduction is shared) or the kernels of route 1.  Strided: the unfolded input -- a launch, the image it reads, a line per channel -- and the
+// product on it; 700 calls, spread 6 %.  Where that is not open either, the operand-map kernel is all there is.
 static double one_tap_without_patch(const GemmLaunch &g)
 {
     const ConvHint &h = g.conv;
     const bool unit = h.sh == 1 && h.sw == 1;
-    if (unit ? h.ph != 0 || h.pw != 0 : !conv_unfold_ok(g)) return 1e30;
-    const double product = one_tap_product_cost(per_image_product(g, g.A, h.C, h.P * h.Q, h.C * h.P * h.Q));
-    return unit ? 1.2 * product : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
+    if (!unit && !conv_unfold_ok(g)) return 1e30;
+    const double product = unit && (h.ph != 0 || h.pw != 0) ? 1e30 : one_tap_product_cost(per_image_product(g, g.A, h.C, h.P * h.Q, h.C * h.P * h.Q));
+    return unit ? std::min(1.2 * product, one_tap_route_1(g)) : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
 }
 
 // ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
@@ -913,7 +934,8 @@ static double one_tap_without_patch(const GemmLaunch &g)
 // (26,192,28,28)*(192,192,1,1) 15.2 / 8.4, (2,512,56,56)*(383,512,1,1) 16.2 / 9.8, (23,192,56,56)*(448,192,1,1) 34.4 / 33.0.
 // Each image's positions are rounded up to a tile, though, which many small images pay for, and route 1's tiles of 64 filters suit a
 // handful of them: (286,96,8,8)*(438,96,1,1) 12.5 / 15.3, (256,1024,7,7)*(2048,1024,1,1) 107 / 128, (184,64,56,56)*(18,64,1,1) 30.1 /
-// 33.8.  Those of many positions whose reduction route 1 would not split stay there where its estimate is 2 % ahead.
+// 33.8; and its reduction is never split: (1,8192,7,7)*(64,8192,1,1) 16.2 / 30.0, (1,8192,14,14)*(128,8192,1,1) 21.0 / 38.5.  Calls stay there
+// where its estimate is 2 % ahead.
 static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
@@ -927,11 +949,7 @@ static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *
     FastArgs fa{};
     int alay, blay;
     if (!lower_plain(u, &fa, &alay, &blay)) return NT_OK;
-    const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
-    int32_t kt_per = 0;
-    ConvArgs c{};
-    if (!conv_small(M8, h.K) && conv_ksplit(M8, h.K, (h.C + 63) / 64, g.tile.bn, &kt_per) == 1 && 1.02 * one_tap_implicit_cost(g) < one_tap_product_cost(u) && match_conv(g, &c))
-        return NT_OK;
+    if (1.02 * one_tap_route_1(g) < one_tap_product_cost(u)) return NT_OK;
     *taken = true;
     return launch_gemm(u, path_out);                         // (more images than one launch holds go out in several)
 }
