@@ -57,7 +57,7 @@ def _compile(src: str, force: bool) -> str:
 def _build_calls(force: bool) -> None:
     """The extension module that takes the launching calls' torch tensors apart (host code; the torch that is installed)."""
     src = os.path.join(CSRC, "python", "calls.cpp")
-    newest = max(os.path.getmtime(p) for p in (src, os.path.join(HERE, "..", "include", "nt.h")))
+    newest = max(os.path.getmtime(p) for p in (src, os.path.join(CSRC, "python", "without_lock.h"), os.path.join(HERE, "..", "include", "nt.h")))
     if not force and os.path.exists(CALLS) and os.path.getmtime(CALLS) >= newest:
         return
     torch = importlib.util.find_spec("torch").submodule_search_locations[0]

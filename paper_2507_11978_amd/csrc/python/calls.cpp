@@ -12,6 +12,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../../include/nt.h"
+#include "without_lock.h"
 
 namespace {
 
@@ -106,24 +107,14 @@ bool modes_active() { return at::impl::torch_function_mode_enabled(); }
 
 PyObject *declined() { Py_RETURN_NONE; }
 
-// (the interpreter lock is given up for the call, as ctypes does)
-template <typename F>
-PyObject *call(F f)
-{
-    nt_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return PyLong_FromLong((long)st);
-}
-
-// C++ exceptions must not cross into the interpreter: the general path repeats the call and reports what it finds
+// C++ exceptions must not cross into the interpreter.  One from taking the arguments apart: the general path repeats the call and reports
+// what it finds.  (Not a catch-all, see without_lock.h.)
 template <typename F>
 PyObject *guarded(F f)
 {
     try {
         return modes_active() ? declined() : f();
-    } catch (...) {
+    } catch (const std::exception &) {
         return declined();
     }
 }
@@ -135,7 +126,7 @@ PyObject *product(decltype(p_gemm) fn, PyObject *const *a, Py_ssize_t n)
         nt_tile_cfg cfg;
         void *s;
         if (!fn || n != 5 || !take(a[0], &A) || !take(a[1], &B) || !take(a[2], &C) || !tile_of(a[3], &cfg) || !stream_of(a[4], &s)) return declined();
-        return call([&] { return fn(A.p, &A.d, B.p, &B.d, C.p, &C.d, A.dtype, C.dtype, cfg, s); });
+        return without_lock([&] { return fn(A.p, &A.d, B.p, &B.d, C.p, &C.d, A.dtype, C.dtype, cfg, s); });
     });
 }
 PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n) { return product(p_gemm, a, n); }
@@ -160,8 +151,8 @@ PyObject *addmm(PyObject *, PyObject *const *a, Py_ssize_t n)
         } else if (D.d.ndim != 2 || D.d.size[0] != C.d.size[0] || D.d.size[1] != C.d.size[1]) {
             return declined();
         }
-        if (act) return call([&] { return p_addmm_act(D.p, &D.d, A.p, &A.d, B.p, &B.d, C.p, &C.d, alpha, beta, (nt_activation)act, A.dtype, C.dtype, cfg, s); });
-        return call([&] { return p_addmm(D.p, &D.d, A.p, &A.d, B.p, &B.d, C.p, &C.d, alpha, beta, A.dtype, C.dtype, cfg, s); });
+        if (act) return without_lock([&] { return p_addmm_act(D.p, &D.d, A.p, &A.d, B.p, &B.d, C.p, &C.d, alpha, beta, (nt_activation)act, A.dtype, C.dtype, cfg, s); });
+        return without_lock([&] { return p_addmm(D.p, &D.d, A.p, &A.d, B.p, &B.d, C.p, &C.d, alpha, beta, A.dtype, C.dtype, cfg, s); });
     });
 }
 
@@ -176,7 +167,7 @@ PyObject *conv2d(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!p_conv || n != 7 || !take(a[0], &x) || !take(a[1], &w) || !take(a[2], &y) || !integers(a[3], 2, stride) || !integers(a[4], 2, pad) ||
             !tile_of(a[5], &cfg) || !stream_of(a[6], &s))
             return declined();
-        return call([&] { return p_conv(x.p, &x.d, w.p, &w.d, y.p, &y.d, stride[0], stride[1], pad[0], pad[1], x.dtype, y.dtype, cfg, s); });
+        return without_lock([&] { return p_conv(x.p, &x.d, w.p, &w.d, y.p, &y.d, stride[0], stride[1], pad[0], pad[1], x.dtype, y.dtype, cfg, s); });
     });
 }
 
@@ -187,7 +178,7 @@ PyObject *sdpa(PyObject *, PyObject *const *a, Py_ssize_t n)
         float scale;
         void *s;
         if (!p_sdpa || n != 6 || !take(a[0], &q) || !take(a[1], &k) || !take(a[2], &v) || !take(a[3], &o) || !real(a[4], &scale) || !stream_of(a[5], &s)) return declined();
-        return call([&] { return p_sdpa(q.p, &q.d, k.p, &k.d, v.p, &v.d, o.p, &o.d, scale, q.dtype, s); });
+        return without_lock([&] { return p_sdpa(q.p, &q.d, k.p, &k.d, v.p, &v.d, o.p, &o.d, scale, q.dtype, s); });
     });
 }
 
@@ -197,7 +188,7 @@ PyObject *softmax(PyObject *, PyObject *const *a, Py_ssize_t n)
         Operand x, o;
         void *s;
         if (!p_softmax || n != 3 || !take(a[0], &x) || !take(a[1], &o) || !stream_of(a[2], &s)) return declined();
-        return call([&] { return p_softmax(x.p, &x.d, o.p, &o.d, x.dtype, s); });
+        return without_lock([&] { return p_softmax(x.p, &x.d, o.p, &o.d, x.dtype, s); });
     });
 }
 
@@ -208,7 +199,7 @@ PyObject *rms_norm(PyObject *, PyObject *const *a, Py_ssize_t n)
         float eps;
         void *s;
         if (!p_rms_norm || n != 4 || !take(a[0], &x) || !take(a[1], &o) || !real(a[2], &eps) || !stream_of(a[3], &s)) return declined();
-        return call([&] { return p_rms_norm(x.p, &x.d, o.p, &o.d, eps, x.dtype, s); });
+        return without_lock([&] { return p_rms_norm(x.p, &x.d, o.p, &o.d, eps, x.dtype, s); });
     });
 }
 
@@ -219,7 +210,7 @@ PyObject *add(PyObject *, PyObject *const *a, Py_ssize_t n)
         int32_t block;
         void *s;
         if (!p_add || n != 5 || !take(a[0], &x) || !take(a[1], &y) || !take(a[2], &o) || !integer(a[3], &block) || !stream_of(a[4], &s)) return declined();
-        return call([&] { return p_add(x.p, &x.d, y.p, &y.d, o.p, &o.d, x.dtype, block, s); });
+        return without_lock([&] { return p_add(x.p, &x.d, y.p, &y.d, o.p, &o.d, x.dtype, block, s); });
     });
 }
 
@@ -230,7 +221,7 @@ PyObject *silu(PyObject *, PyObject *const *a, Py_ssize_t n)
         int32_t block;
         void *s;
         if (!p_silu || n != 4 || !take(a[0], &x) || !take(a[1], &o) || !integer(a[2], &block) || !stream_of(a[3], &s)) return declined();
-        return call([&] { return p_silu(x.p, &x.d, o.p, &o.d, x.dtype, block, s); });
+        return without_lock([&] { return p_silu(x.p, &x.d, o.p, &o.d, x.dtype, block, s); });
     });
 }
 
