@@ -146,23 +146,34 @@ def _check(st: int):
         raise NtError(st, load().nt_last_error().decode())
 
 
+class _Declining:
+    """Stands in for the extension module where there is none: every call is marshalled below."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 _calls = None
 
 
 def _load_calls():
-    """The extension module, bound to the library's functions.  Called on behalf of a caller who holds torch tensors."""
+    """The extension module, bound to the library's functions, or what stands in for it.  Called on behalf of a caller who holds torch tensors."""
     global _calls
-    if not os.path.exists(_CALLS_PATH):
-        raise RuntimeError(f"{_CALLS_PATH} is missing: run `python -m paper_2507_11978_amd.build` (or __graft_entry__.build()) first")
     import importlib.util
+    import warnings
 
     import torch  # noqa: F401  (its libraries hold what the module refers to)
-    spec = importlib.util.spec_from_file_location("_nt_calls", _CALLS_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
     lib = load()
-    module.bind(*(C.cast(getattr(lib, name), C.c_void_p).value
-                  for name in ("nt_gemm", "nt_bmm", "nt_addmm", "nt_addmm_act", "nt_conv2d_implicit", "nt_sdpa", "nt_softmax", "nt_rms_norm", "nt_add", "nt_silu")))
+    try:
+        spec = importlib.util.spec_from_file_location("_nt_calls", _CALLS_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(*(C.cast(getattr(lib, name), C.c_void_p).value
+                      for name in ("nt_gemm", "nt_bmm", "nt_addmm", "nt_addmm_act", "nt_conv2d_implicit", "nt_sdpa", "nt_softmax", "nt_rms_norm", "nt_add", "nt_silu")))
+    except (ImportError, OSError) as e:                     # not built, or built for another torch
+        warnings.warn(f"{_CALLS_PATH} cannot be loaded ({e}): calls are marshalled through ctypes, some 2 us slower each; "
+                      "python -m paper_2507_11978_amd.build builds it", RuntimeWarning, stacklevel=3)
+        module = _Declining()
     _calls = module
     return module
 
