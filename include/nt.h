@@ -159,7 +159,8 @@ nt_status nt_program_order(int64_t batch, int64_t mt, int64_t nt, int64_t *pid_o
  * LDS), 5 unfolded input written to the workspace + the matrix kernels, 6 convolution kernel that streams into LDS and walks
  * the reduction filter tap by filter tap (256 filters per program, channels in whole blocks of 32; reads a tap-major copy of
  * the filter that it puts in the workspace), 7 convolution on a channels-last copy of its input in the workspace, or, for both 6
- * (many positions, unit stride) and 7 (any other), a kernel that keeps the input rows in LDS (nt_last_conv_plan tells them apart),
+ * (many positions, unit stride) and 7 (any other), a kernel that keeps the input rows in LDS; one of these reports 4 (unit stride) or 5
+ * for a single filter tap, with nothing unfolded (nt_last_conv_plan tells them apart),
  * -1 none (nothing launched yet, an error, or an empty problem).  For tests and diagnostics. */
 int32_t nt_last_kernel_path(void);
 
@@ -175,7 +176,17 @@ typedef struct {
 } nt_conv_plan;
 nt_status nt_last_conv_plan(nt_conv_plan *out);
 
-/* Into how many parts the reduction of that call was split -- over programs (see "Memory" at nt_gemm and nt_conv2d_implicit), or over the
+/* How the calling thread's last nt_sdpa call (its last launch) was laid out; zeros if nothing was launched.  For tests and diagnostics. */
+typedef struct {
+    int32_t queries;         /* per workgroup: 32, 64, 128 or 256; 1: the kernel for few queries */
+    int32_t groups;          /* of wavefronts that the blocks of keys are dealt out to */
+    int32_t wavefronts;      /* per workgroup */
+    int32_t matrix_sums;     /* 1: row sums on the matrix pipe */
+    int32_t streamed;        /* 1: keys and values straight into LDS, 0: through registers */
+} nt_sdpa_plan;
+nt_status nt_last_sdpa_plan(nt_sdpa_plan *out);
+
+/* Into how many parts the reduction of the last product or convolution was split -- over programs (see "Memory" at nt_gemm and nt_conv2d_implicit), or over the
  * wavefronts of a program (products of few rows; convolutions of few positions straight from the caller's tensors); 1: not split.
  * For tests and diagnostics. */
 int32_t nt_last_k_split(void);

@@ -45,6 +45,11 @@ class ConvPlan(C.Structure):
                 ("runs", C.c_int32)]
 
 
+class SdpaPlan(C.Structure):
+    """How the last attention call was laid out (see nt_sdpa_plan)."""
+    _fields_ = [("queries", C.c_int32), ("groups", C.c_int32), ("wavefronts", C.c_int32), ("matrix_sums", C.c_int32), ("streamed", C.c_int32)]
+
+
 _lib = None
 
 
@@ -135,6 +140,8 @@ def load():
     L.nt_last_k_split.restype = i32
     L.nt_last_conv_plan.argtypes = [C.POINTER(ConvPlan)]
     L.nt_last_conv_plan.restype = i32
+    L.nt_last_sdpa_plan.argtypes = [C.POINTER(SdpaPlan)]
+    L.nt_last_sdpa_plan.restype = i32
     L.nt_last_error.restype = C.c_char_p
     L.nt_version.restype = C.c_char_p
     _lib = L
@@ -426,6 +433,13 @@ def last_conv_plan() -> ConvPlan:
     """How this thread's last conv2d_implicit / matmul_views call ran on a kernel with resident input rows (kernel 0: it did not)."""
     plan = ConvPlan()
     _check(load().nt_last_conv_plan(C.byref(plan)))
+    return plan
+
+
+def last_sdpa_plan() -> SdpaPlan:
+    """How the calling thread's last sdpa() was laid out."""
+    plan = SdpaPlan()
+    _check(load().nt_last_sdpa_plan(C.byref(plan)))
     return plan
 
 

@@ -573,6 +573,9 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void sdpa_decode_kernel(const Sd
     }
 }
 
+static thread_local nt_sdpa_plan t_plan;
+const nt_sdpa_plan &last_sdpa_plan() { return t_plan; }
+
 template <bool BF16, bool DMA, int SPLIT, int NW, bool LONG>
 static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream_t s)
 {
@@ -584,6 +587,7 @@ static nt_status launch_sdpa_inst(const SdpaArgs &k, int64_t programs, hipStream
         configured.set();
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)programs), dim3(64 * NW * SPLIT), SPLIT * kSdpaLds, s, k);
+    t_plan = nt_sdpa_plan{32 * NW, SPLIT, NW * SPLIT, LONG ? 1 : 0, DMA ? 1 : 0};
     return check_launch("sdpa_kernel");
 }
 
@@ -594,8 +598,17 @@ static nt_status launch_sdpa_length(const SdpaArgs &k, int64_t programs, hipStre
     // 16 8.5 / 8.7, 7 6.3 / 6.5), else 3 (12 blocks in four groups 9.4 / 8.9, 10 in two 8.8 / 8.2, 3 in one 9.0 / 8.5, 2 in one 6.4 / 6.8;
     // 2 with more programs than are resident from the start 12.8 / 12.3).
     // (rows through registers go by the same rule, and give the same bits)
-    if (((k.Sk + kKeyBlock - 1) / kKeyBlock + SPLIT - 1) / SPLIT >= (NW == 1 ? 5 : programs > 1024 ? 2 : 3)) return launch_sdpa_inst<BF16, DMA, SPLIT, NW, true>(k, programs, s);
-    return launch_sdpa_inst<BF16, DMA, SPLIT, NW, false>(k, programs, s);
+    // By the rules of launch_sdpa some kernels only ever walk more blocks than that, or fewer: four groups of more than one wavefront have twelve to share
+    // at least, two of four seven; two groups of one wavefront have six at most, one group of one or two wavefronts a single one.
+    if constexpr ((SPLIT == 4 && NW > 1) || (SPLIT == 2 && NW == 4)) {
+        return launch_sdpa_inst<BF16, DMA, SPLIT, NW, true>(k, programs, s);
+    } else if constexpr ((SPLIT == 2 && NW == 1) || (SPLIT == 1 && NW < 4)) {
+        return launch_sdpa_inst<BF16, DMA, SPLIT, NW, false>(k, programs, s);
+    } else {
+        const int64_t blocks = (((int64_t)k.Sk + kKeyBlock - 1) / kKeyBlock + SPLIT - 1) / SPLIT;
+        if (blocks >= (NW == 1 ? 5 : programs > 1024 ? 2 : 3)) return launch_sdpa_inst<BF16, DMA, SPLIT, NW, true>(k, programs, s);
+        return launch_sdpa_inst<BF16, DMA, SPLIT, NW, false>(k, programs, s);
+    }
 }
 
 template <bool BF16, bool DMA, int NW>
@@ -655,6 +668,7 @@ nt_status launch_sdpa(const SdpaArgs &a, int64_t batch, bool bf16, void *stream)
         if (waves == 4) bf16 ? launch(sdpa_decode_kernel<true, 4>) : launch(sdpa_decode_kernel<false, 4>);
         else if (waves == 8) bf16 ? launch(sdpa_decode_kernel<true, 8>) : launch(sdpa_decode_kernel<false, 8>);
         else bf16 ? launch(sdpa_decode_kernel<true, 16>) : launch(sdpa_decode_kernel<false, 16>);
+        t_plan = nt_sdpa_plan{1, 1, waves, 0, 0};
         return check_launch("sdpa_decode_kernel");
     }
     const int64_t bh = batch * a.H;
@@ -708,6 +722,7 @@ nt_status launch_sdpa_desc(const void *q, const nt_tensor_desc *dq, const void *
                            const void *v, const nt_tensor_desc *dv, void *o, const nt_tensor_desc *dout,
                            float scale, int dtype, void *stream)
 {
+    t_plan = nt_sdpa_plan{};
     const nt_tensor_desc *d[4] = {dq, dk, dv, dout};
     for (const nt_tensor_desc *t : d) {
         if (!t) return fail(NT_ERR_INVALID_ARG, "null tensor descriptor");

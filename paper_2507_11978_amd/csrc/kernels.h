@@ -70,6 +70,7 @@ bool tile_is_built(nt_tile_cfg cfg);
 int last_k_split();
 // how it ran on the convolution kernels that keep the input rows in LDS (kernel 0: it did not)
 const nt_conv_plan &last_conv_plan();
+const nt_sdpa_plan &last_sdpa_plan();
 // the tile the MFMA kernels run a plain (batched) product of this size fastest with, by a cost model fitted to measurements
 // (narrow: the 64 x 64 tile may be taken -- operands and output have the unit strides of the direct kernel)
 nt_tile_cfg pick_gemm_tile(int64_t batch, int64_t M, int64_t N, int64_t K, bool narrow);

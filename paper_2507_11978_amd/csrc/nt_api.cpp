@@ -506,6 +506,13 @@ nt_status nt_last_conv_plan(nt_conv_plan *out)
     return NT_OK;
 }
 
+nt_status nt_last_sdpa_plan(nt_sdpa_plan *out)
+{
+    if (!out) return fail(NT_ERR_INVALID_ARG, "null output pointer");
+    *out = nt::last_sdpa_plan();
+    return NT_OK;
+}
+
 nt_status nt_matmul_views(const void *A, const nt_tensor_desc *dA, const nt_meta_op *opsA, int32_t nA,
                           const void *B, const nt_tensor_desc *dB, const nt_meta_op *opsB, int32_t nB,
                           void *C, const nt_tensor_desc *dC, const nt_meta_op *opsC, int32_t nC,
