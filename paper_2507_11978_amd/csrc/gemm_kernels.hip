@@ -904,7 +904,8 @@ static double one_tap_split_cost(const ConvHint &h, int parts, int64_t per)
 }
 
 // The same call on the kernels of route 1, if they take it and -- few positions with a split, many without -- have an estimate; else 1e30.
-static double one_tap_route_1(const GemmLaunch &g)
+// *workspace: whether they go through it.
+static double one_tap_route_1(const GemmLaunch &g, bool *workspace)
 {
     const ConvHint &h = g.conv;
     const int64_t M8 = h.N * h.P * ((h.Q + 7) / 8 * 8);
@@ -913,6 +914,7 @@ static double one_tap_route_1(const GemmLaunch &g)
     const bool small = conv_small(M8, h.K);
     const int parts = conv_ksplit(M8, h.K, (h.C + 63) / 64, g.tile.bn, &per);
     if (small != (parts > 1) || !match_conv(g, &c)) return 1e30;
+    *workspace = conv_scratch_need(g, c) > 0;
     return parts > 1 ? one_tap_split_cost(h, parts, per) : one_tap_implicit_cost(g);
 }
 
@@ -925,7 +927,8 @@ static double one_tap_without_patch(const GemmLaunch &g)
     const bool unit = h.sh == 1 && h.sw == 1;
     if (!unit && !conv_unfold_ok(g)) return 1e30;
     const double product = unit && (h.ph != 0 || h.pw != 0) ? 1e30 : one_tap_product_cost(per_image_product(g, g.A, h.C, h.P * h.Q, h.C * h.P * h.Q));
-    return unit ? std::min(1.2 * product, one_tap_route_1(g)) : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
+    bool workspace = false;
+    return unit ? std::min(1.2 * product, one_tap_route_1(g, &workspace)) : 4.5 + 1.08 * product + 0.45e-6 * (double)h.N * (double)h.C * (double)(h.H * h.W) + 0.82e-3 * (double)h.C;
 }
 
 // ---- route 0b: one tap, unit stride, no padding, dense images: the input is the matrix already.  No copy, no rows rounded up, no
@@ -935,7 +938,7 @@ static double one_tap_without_patch(const GemmLaunch &g)
 // Each image's positions are rounded up to a tile, though, which many small images pay for, and route 1's tiles of 64 filters suit a
 // handful of them: (286,96,8,8)*(438,96,1,1) 12.5 / 15.3, (256,1024,7,7)*(2048,1024,1,1) 107 / 128, (184,64,56,56)*(18,64,1,1) 30.1 /
 // 33.8; and its reduction is never split: (1,8192,7,7)*(64,8192,1,1) 16.2 / 30.0, (1,8192,14,14)*(128,8192,1,1) 21.0 / 38.5.  Calls stay there
-// where its estimate is 2 % ahead.
+// where its estimate is 2 % ahead, but for captured ones that would need the workspace: they can do without, and their replays take no lease.
 static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *taken)
 {
     *taken = false;
@@ -949,7 +952,8 @@ static nt_status route_conv_pointwise(const GemmLaunch &g, int *path_out, bool *
     FastArgs fa{};
     int alay, blay;
     if (!lower_plain(u, &fa, &alay, &blay)) return NT_OK;
-    if (1.02 * one_tap_route_1(g) < one_tap_product_cost(u)) return NT_OK;
+    bool workspace = false;
+    if (1.02 * one_tap_route_1(g, &workspace) < one_tap_product_cost(u) && !(workspace && capture_of((hipStream_t)g.stream) != 0)) return NT_OK;
     *taken = true;
     return launch_gemm(u, path_out);                         // (more images than one launch holds go out in several)
 }
@@ -1179,6 +1183,7 @@ struct ResidentPlan {
     ConvPlaneArgs plane{};
     ConvPlanePlan plane_plan{};
     bool patch_ahead = false, plane_ahead = false, plane_alone = false;      // plane_alone: the routes below need no workspace
+    bool patch_open = false;                                                 // (one tap) the patch can be had, if not ahead
 };
 
 static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *taken)
@@ -1207,7 +1212,10 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
     if (!kept) {
         ResidentPlan k;
         double cost = RS == 1 ? one_tap_without_patch(g) : conv_copied_cost(h), c = 0;
-        if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c) && c < cost) { k.patch_ahead = true; cost = c; }
+        if (patch_ok && conv_patch_plan(h, &k.patch, &k.patch_plan, &c)) {
+            k.patch_open = RS == 1 && c < 1e30;
+            if (c < cost) { k.patch_ahead = true; cost = c; }
+        }
         if (plane_ok && conv_plane_plan(h, &k.plane, &k.plane_plan, &c) && 1.2 * c < cost) {
             k.plane_ahead = true;
             k.plane_alone = !conv_below_uses_workspace(g);
@@ -1238,7 +1246,8 @@ static nt_status route_conv_resident(const GemmLaunch &g, int *path_out, bool *t
             return launch_conv_plane(a, k.plane_plan, bf16, s);
         }
     }
-    if (k.patch_ahead) {
+    // (one tap, captured: what is ahead of the patch may need the workspace)
+    if (k.patch_ahead || (k.patch_open && capture_of(s) != 0)) {
         ConvPatchArgs a = k.patch;
         a.x = (const uint16_t *)g.A; a.w = (const uint16_t *)g.B; a.Y = g.C;
         a.out_dtype = g.out_dtype;

@@ -206,6 +206,25 @@ def test_overlapping_replays_of_convolutions_that_need_no_workspace(shape):
     replay_two_at_once(lambda x, w, y, s: nt.conv2d_implicit(x, w, y, (1, 1), pad, stream=s), problems, lambda: nt.last_kernel_path() != nt.PATH_CONV_TAP)
 
 
+@pytest.mark.parametrize("shape,stride,path", [((1, 8192, 7, 7, 64, 1, 1), 1, "PATH_DIRECT"), ((1, 2080, 13, 13, 300, 1, 1), 1, "PATH_CONV_DIRECT"),
+                                               ((4, 384, 27, 27, 1000, 1, 1), 2, "PATH_CONV_UNFOLD")])
+def test_overlapping_replays_of_convolutions_of_one_tap(shape, stride, path):
+    """A very long reduction, one that a program's wavefronts share, a strided one: eager, the first and the last go through the workspace (a
+    split, the unfolded input); captured, none does."""
+    dt, problems = "f16", []
+    for seed in (84, 85):
+        X, Wt = si.conv_inputs(*shape, dt, seed=seed, dist="int")
+        x, w = to_gpu(X, dt), to_gpu(Wt, dt)
+        sub = x.float()[:, :, ::stride, ::stride]
+        want = torch.matmul(w.float().reshape(shape[4], shape[1]), sub.reshape(shape[0], shape[1], -1)).reshape(shape[0], shape[4], *sub.shape[2:])
+        problems.append(((x, w), want.double().cpu().numpy()))
+    uses_it = lambda: nt.last_kernel_path() == nt.PATH_CONV_UNFOLD and nt.last_conv_plan().kernel == 0 or nt.last_kernel_path() == nt.PATH_CONV_DIRECT and nt.last_conv_plan().kernel == 0
+    nt.conv2d_implicit(*problems[0][0], torch.empty(problems[0][1].shape, dtype=torch.float32, device="cuda"), (stride, stride))
+    assert uses_it() == (shape[1] != 2080)
+    replay_two_at_once(lambda x, w, y, s: nt.conv2d_implicit(x, w, y, (stride, stride), stream=s), problems,
+                       lambda: nt.last_kernel_path() == getattr(nt, path) and not uses_it())
+
+
 @pytest.mark.parametrize("product", [nt.gemm, nt.gemm_noalloc])
 def test_overlapping_replays_of_products_with_a_ragged_k(product):
     """K no multiple of 64: split through scratch memory in an eager call, which captured ones -- two graphs replayed at once -- must
