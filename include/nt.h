@@ -339,7 +339,9 @@ nt_status nt_bmm(const void *A, const nt_tensor_desc *dA, const void *B, const n
  * Calls with dense planes, channels in whole blocks of 32 and at least six filter taps keep the input rows under an output tile in LDS
  * where that is estimated to be ahead of the ways below: with few positions or filters and 9 or 25 taps straight from the
  * caller's tensors, without workspace; with many positions the filter is copied (only) into the workspace -- where the call is captured
- * in a graph, only if the ways below would go through the workspace too.
+ * in a graph, only if the ways below would go through the workspace too.  With one tap, dense planes and channels in whole blocks of 32
+ * the call goes the way that is estimated to be ahead: straight from the caller's tensors, as a product per image (unit stride), or
+ * a way below; captured in a graph, not through the workspace where one of the former two may be had.
  * Strided calls with channels in whole blocks of 32 and more than one filter tap, and unit-stride calls with such channels and
  * few output positions, run on a zero-padded channels-last copy of their input, made in the workspace beside the filter's
  * tap-major copy (unit-stride calls that need no k split keep to the kernels below with at most 128 filters, and where they

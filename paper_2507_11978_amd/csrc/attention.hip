@@ -1,8 +1,8 @@
 // Scaled dot-product attention, forward (Section 5.1: the paper's sdpa kernels implement the
 // FlashAttention-2 algorithm): O = softmax(scale * Q K^T) V per (batch, head), head size 64.
 //
-// Arrangement: Q and O are tiled into blocks of 128 query rows (32 or 64 in launches that leave units empty), one program per (batch, head,
-// block); K and V are tiled into blocks of 64 keys, all of which every program visits in turn.
+// Arrangement: Q and O are tiled into blocks of 128 query rows (32 or 64 in launches that leave units empty, 256 where that costs no more
+// rounds of them), one program per (batch, head, block); K and V are tiled into blocks of 64 keys, all of which every program visits in turn.
 // Application (per program): a row reference M (close to the running row maximum), row sum l,
 // accumulator O; per key block
 //   S = Q K_j^T;  P = 2^(c S - M)  (c = scale * log2 e);  l += rowsum P;  O += P V_j;   finally O / l.
@@ -23,12 +23,12 @@
 // delivers, for a lane's d, four consecutive keys at any position.  O^T again has the query on
 // the lane axis, so rescaling by 2^(M - M') is a per-lane scalar.  Q fragments stay in registers.
 // K_j and V_j travel straight into LDS (range-checked loads; through registers where strides do not allow it), K two blocks
-// ahead and V one: rings of three and two blocks, 40 KB, and 117 registers let four workgroups share a compute unit, which
+// ahead and V one: rings of three and two blocks, 40 KB, and 126 registers (256 queries: 124) let sixteen wavefronts share a compute unit, which
 // overlaps the exponentials of one with the MFMAs of another.  (Through registers, one block ahead, two blocks of each, three
 // workgroups: 69.8 us against 63.8 at 4 x 48 heads x 1024 fp16, 90.5 / 81.2 at 4 x 16 x 2048; the next half block's scores
 // computed between this one's exponentials measured no gain.)  What bounds it: per 64 keys and wavefront 16 MFMAs (512 cycles) and 80
-// vector instructions (450 cycles), which run behind another wavefront's MFMAs (670 cycles for both, in a loop of just these, four
-// wavefronts per SIMD) as long as there are four, and the clock, 1.65 GHz on real data: without the loads into LDS the same cycles
+// vector instructions (32 fma, 32 exponentials, 16 packs: 400 cycles), which run behind another wavefront's MFMAs (670 cycles for both, in a loop of just these, four
+// wavefronts per SIMD) as long as there are four, and the clock, 1.65 to 1.75 GHz on real data: without the loads into LDS the same cycles
 // take 53 us for 63, without LDS reads 46 (4 x 48 heads x 1024).  Blocks of 64 queries per wavefront with the MFMAs of one half behind the
 // exponentials of the other measured the same 62 us at half the LDS reads.
 #include "gemm_direct.h"

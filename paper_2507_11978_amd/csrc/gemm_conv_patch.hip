@@ -322,8 +322,9 @@ static bool patch_sizes(const ConvHint &h, const PatchTile &t, PatchSizes *z)
 // Estimated time (us) of the launch on that tile with `waves` wavefronts per program: programs run in rounds of as many as a
 // unit's LDS and registers hold; a program costs a fixed part, its blocks of channels -- each the latency of a wavefront's own
 // work, or the unit's throughput for all that are resident, whichever is longer -- and the sum of its wavefronts' parts.
-// A fit to launches on every tile (64 to 512 channels and filters, images of 7 to 56, both strides, 3 x 3 and 5 x 5).  70 drawn convolutions that
-// it sends here take 1.13 times its figure in the mean, with a spread of 10 % (four sets of operands in turn, graph replays).
+// A fit to launches on every tile for nine and 25 taps (64 to 512 channels and filters, images of 7 to 56, both strides).  190 drawn convolutions
+// that it sends here take 1.09 times its figure in the mean, with a spread of 12 % (four sets of operands in turn, graph replays).  One tap: it picks
+// the tile only, see patch_cost_one_tap.
 static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t programs, int64_t waves)
 {
     // (LDS is dealt out in pieces of 1280 bytes: five programs of 32 KB do not fit)
@@ -332,7 +333,8 @@ static double patch_cost(const PatchTile &t, const PatchSizes &z, int64_t progra
     // (programs to a unit: between one and two, units that have two set the pace more than the mean says, in long walks.  By the
     // mean alone (4,512,14,14)*(512,512,3,3) ran on 384 programs, 13.7 us, for 192 of twice the filters, 12.2;
     // (8,416,13,13)*(88,416,3,3) on 11.3 us for 9.0.  Of less than 12 blocks programs leave their unit to the next before they get in its way:
-    // there this loses, 288 channels 14.0 / 15.4, 128 6.6 / 7.9, for some that gain, 128 channels 8.0 / 7.0)
+    // there this loses, 288 channels 14.0 / 15.4, 128 6.6 / 7.9, for some that gain, 128 channels 8.0 / 7.0.  Twelve is where the drawn ones that it picks another
+    // tile for stop losing: 310 of 64 to 512 channels, geometric mean 0.998, none slower)
     const double share = (double)programs / units, mine = programs > units ? std::min(resident, share < 2 && z.blocks >= 12 ? 0.5 * (share + 2) : share) : 1.0;
     double rounds = std::max(1.0, (double)programs / (units * resident));
     rounds = rounds < 4 ? std::ceil(rounds) : rounds + 0.3;
