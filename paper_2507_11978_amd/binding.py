@@ -178,9 +178,9 @@ def _load_calls():
         module.bind(*(C.cast(getattr(lib, name), C.c_void_p).value
                       for name in ("nt_gemm", "nt_bmm", "nt_addmm", "nt_addmm_act", "nt_conv2d_implicit", "nt_sdpa", "nt_softmax", "nt_rms_norm", "nt_add", "nt_silu")))
     except (ImportError, OSError) as e:                     # not built, or built for another torch
+        module = _calls = _Declining()
         warnings.warn(f"{_CALLS_PATH} cannot be loaded ({e}): calls are marshalled through ctypes, some 2 us slower each; "
                       "python -m paper_2507_11978_amd.build builds it", RuntimeWarning, stacklevel=3)
-        module = _Declining()
     _calls = module
     return module
 
